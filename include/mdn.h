@@ -28,9 +28,9 @@
  *     intermediate the library stores: MDN_DTYPE_BF16 (bf16 MFMA operands, fp32 accumulation
  *     and fp32 states) or MDN_DTYPE_F32 (fp32 MFMA throughout).
  *   - All pointers must be 16-byte aligned.  dk, dv in {64, 128}; C in {16, 32, 64} (Algorithm 1's chunk sizes);
- *     any T >= 1: when T is not a multiple of C the last chunk is partial (Algorithm 1 pads it; here the padding
- *     tokens are exact identity steps, k = v = q = 0, alpha = mu = 1, beta = 0, on copies inside the workspace, so
- *     outputs, final states and gradients are those of the T tokens given).  C = 64 is the tuned path: the kernels
+ *     any T >= 1: when T is not a multiple of C the last chunk is partial (Algorithm 1 pads it; here the kernels fill
+ *     the chunk up with exact identity steps, k = v = q = 0, alpha = mu = 1, beta = 0, on chip, so outputs, final states
+ *     and gradients are those of the T tokens given).  C = 64 is the tuned path: the kernels
  *     work on 64-token tiles, and a chunk of 16 or 32 tokens runs as one such tile filled up with identity steps
  *     (the exact algorithm at that chunk size, at 64 / C times the work and workspace; results do not depend on C
  *     beyond rounding).  The packed variable-length calls take C = 64 only.
@@ -85,8 +85,7 @@ typedef struct mdn_shape {
 int mdn_workspace_bytes(const mdn_shape *shape, int which, size_t *bytes_out);
 
 /* Bytes of the optional `states_saved` buffer: the states S, M at the start of every chunk in the storage
- * dtype, 2 dk dv elements per (batch, head, chunk), ceil(T/C) chunks.  Only mdn_chunk_bwd reads it (the blocks
- * of the full chunks come first, [B, H, T/C, 2, dk, dv], then one block per (batch, head) for a partial chunk). */
+ * dtype, 2 dk dv elements per (batch, head, chunk), ceil(T/C) chunks.  Only mdn_chunk_bwd reads it. */
 int mdn_saved_states_bytes(const mdn_shape *shape, size_t *bytes_out);
 
 /* Bytes of the optional `operands_saved` buffer: the chunk-local operands of the reverse pass
@@ -161,20 +160,11 @@ int mdn_chunk_bwd(const mdn_shape *shape, const void *q, const void *k, const vo
  * sequences lie one after another along T of [1, T, H, *] tensors, sequence i being the tokens
  * [cu_seqlens[i], cu_seqlens[i+1]); cu_seqlens is a HOST array of n_seq + 1 increasing offsets with cu_seqlens[0] = 0
  * and cu_seqlens[n_seq] = shape.T; shape.B must be 1.  States are [n_seq, H, dk, dv].  Any lengths >= 1.
- * A call that neither gives nor asks for per-sequence states (forward: S0, M0, S_final, M_final all NULL; backward:
- * S0, M0, dS_final, dM_final, dS0, dM0 all NULL) runs the whole batch as ONE stream of shape.T tokens, with alpha and
- * mu set to zero (in copies of its own) at the first token of every sequence but the first: by Eq. Mt.recurrent /
- * St.recurrent such a token neither sees the states before it nor passes an adjoint back to them, which is what a
- * sequence that starts from zero states computes; the gradients of those zeroed gates are zero.  One set of
- * launches however many the sequences.  A forward with zero initial states that wants the final states (S0, M0 NULL,
- * S_final and M_final given: prefill of a batch of prompts) runs the same stream, keeps its chunk-start states in the
- * workspace and then runs, as one batch, the last chunk of every sequence once more from its start state up to the
- * sequence's end (with 16-bit storage the start states are kept as value + rounding remainder, so the final states
- * start from fp32-accurate states as in mdn_chunk_fwd).  Any other call runs each
- * sequence by itself through the same kernels as
- * mdn_chunk_fwd / mdn_chunk_bwd, one after the other on the stream (exact, but a batch of many short sequences does
- * not fill the GPU).  The backward reconstructs the states and recomputes the operands (no states_saved /
- * operands_saved here).  workspace: mdn_workspace_bytes_varlen.
+ * One set of launches however many the sequences and whatever states are given or asked for: every kernel looks its
+ * sequence up in two small tables that the call builds in the workspace from cu_seqlens (which is read before the call
+ * returns), and the scans of all sequences run beside each other, the longest first.  The backward reconstructs the
+ * states and recomputes the operands (no states_saved / operands_saved here).  workspace: mdn_workspace_bytes_varlen
+ * (MDN_WS_FWD or MDN_WS_BWD; the latter is enough for calls with adjoints of the final states as well).
  * Errors as for the fixed-length calls; MDN_ERR_SHAPE also for inconsistent cu_seqlens.
  */
 int mdn_workspace_bytes_varlen(const mdn_shape *shape, const int32_t *cu_seqlens, int32_t n_seq, int which, size_t *bytes_out);

@@ -503,8 +503,7 @@ def _varlen_workspace(shape, cu, n, which, device):
 def mdn_chunk_fwd_varlen(q, k, v, beta, alpha, mu, cu_seqlens, eta=None, S0=None, M0=None, scale=None, save_vt=False,
                          want_states=True):
     """Packed variable-length forward: q, k, v [1, T, H, d], gates [1, T, H], cu_seqlens a host sequence of n + 1
-    offsets; states [n, H, dk, dv].  Returns dict(o, S, M, vt); S, M are None with want_states=False (without initial
-    states either, the library then runs the batch as one stream of tokens)."""
+    offsets; states [n, H, dk, dv].  Returns dict(o, S, M, vt); S, M are None with want_states=False."""
     if q.dim() != 4 or q.shape[0] != 1:
         raise MdnError(f"packed batches are [1, T, H, d]; got q {tuple(q.shape)}")
     cu, n = _cu(cu_seqlens, q.shape[1])
@@ -525,8 +524,7 @@ def mdn_chunk_fwd_varlen(q, k, v, beta, alpha, mu, cu_seqlens, eta=None, S0=None
 def mdn_chunk_bwd_varlen(q, k, v, beta, alpha, mu, vt, dO, cu_seqlens, eta=None, S0=None, M0=None, dS_final=None,
                          dM_final=None, scale=None, want_deta=False, want_state_grads=True):
     """Packed variable-length backward.  Returns dict(dq, dk, dv, dbeta, dalpha, dmu, deta, dS0, dM0); dS0, dM0 are
-    None with want_state_grads=False (with no initial states and no adjoints of the final states either, the
-    library then runs the batch as one stream of tokens)."""
+    None with want_state_grads=False."""
     if q.dim() != 4 or q.shape[0] != 1:
         raise MdnError(f"packed batches are [1, T, H, d]; got q {tuple(q.shape)}")
     cu, n = _cu(cu_seqlens, q.shape[1])

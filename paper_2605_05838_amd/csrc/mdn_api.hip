@@ -5,9 +5,9 @@
 
 #include <hip/hip_runtime.h>
 #include <string.h>
+#include <algorithm>
 #include <atomic>
 #include <mutex>
-#include <type_traits>
 #include <vector>
 
 using namespace mdn;
@@ -26,11 +26,15 @@ int check_shape(const mdn_shape *s, bool chunked, Dims *d) {
     // (chunks of 16 or 32 tokens run as 64-token tiles: up to 4 rows per token)
     const long long tile = chunked ? 64 / s->C : 1;
     if ((long long)s->B * s->H > (1 << 24) || ((long long)s->B * s->T + 64) * s->H * tile > (1LL << 31) - 1) return MDN_ERR_SHAPE;
-    d->B = s->B; d->T = s->T; d->H = s->H; d->N = s->T / 64; d->BH = s->B * s->H; // N: the FULL chunks
-    d->n0 = 0; d->n1 = d->N;
+    *d = Dims{};
+    d->B = s->B; d->T = s->T; d->H = s->H; d->N = (int)(((long long)s->T + 63) / 64); d->BH = s->B * s->H;
+    d->n0 = 0; d->n1 = d->N; d->nchunks = (int)((long long)s->B * d->N);
     d->dk = s->dk; d->dv = s->dv; d->dtype = s->dtype; d->scale = s->scale;
     return MDN_OK;
 }
+
+// chunk blocks of a call: one per chunk and head
+size_t chunk_blocks(const Dims &d) { return (size_t)d.nchunks * d.H; }
 
 bool misaligned(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) != 0; }
 
@@ -49,7 +53,7 @@ struct Carver {
 struct FwdWs { float *coef; void *KT, *Tm, *Bm; float *carryS, *carryM; size_t total; };
 
 FwdWs carve_fwd(const Dims &d, void *ws) {
-    const size_t es = d.dtype == MDN_DTYPE_F32 ? 4 : 2, nb = (size_t)d.BH * d.N;
+    const size_t es = d.dtype == MDN_DTYPE_F32 ? 4 : 2, nb = chunk_blocks(d);
     Carver c(ws);
     FwdWs w;
     w.coef = static_cast<float *>(c.take(nb * (size_t)(64 * kCoefBlockCols * sizeof(float))));
@@ -68,7 +72,7 @@ FwdWs carve_fwd(const Dims &d, void *ws) {
 struct RevOps { float *coef; void *KT, *QT, *BmT, *TmT; size_t total; };
 
 RevOps carve_rev(const Dims &d, void *p) {
-    const size_t es = d.dtype == MDN_DTYPE_F32 ? 4 : 2, nb = (size_t)d.BH * d.N;
+    const size_t es = d.dtype == MDN_DTYPE_F32 ? 4 : 2, nb = chunk_blocks(d);
     Carver c(p);
     RevOps w;
     w.coef = static_cast<float *>(c.take(nb * (size_t)(64 * kCoefBlockCols * sizeof(float))));
@@ -85,7 +89,7 @@ struct BwdWs { RevOps ops; void *dstates, *states, *dstates_lo, *states_lo; floa
 // `precise`: room for the rounding remainders of the two state tensors as well (16-bit storage, calls that bring
 // adjoints of the final states in; see precise_call)
 BwdWs carve_bwd(const Dims &d, void *ws, bool precise) {
-    const size_t es = d.dtype == MDN_DTYPE_F32 ? 4 : 2, nb = (size_t)d.BH * d.N;
+    const size_t es = d.dtype == MDN_DTYPE_F32 ? 4 : 2, nb = chunk_blocks(d);
     BwdWs w;
     w.ops = carve_rev(d, ws);
     Carver c(ws);
@@ -100,73 +104,8 @@ BwdWs carve_bwd(const Dims &d, void *ws, bool precise) {
     return w;
 }
 
-// ---- a sequence length that is not a multiple of 64: the full chunks run on the caller's tensors (d.N counts
-// them, d.T stays the row stride between sequences), the partial last chunk on padded copies (see mdn_tail.hip)
-Dims tail_dims(const Dims &d) {
-    Dims t = d;
-    t.T = 64; t.N = 1; t.n0 = 0; t.n1 = 1;
-    return t;
-}
-
 size_t elem_size(const Dims &d) { return d.dtype == MDN_DTYPE_F32 ? 4 : 2; }
-size_t saved_states_part(const Dims &d) { return (size_t)d.BH * d.N * 2 * d.dk * d.dv * elem_size(d); }
-
-// padded [B,64,H,*] copies of the partial chunk's tensors, and the states handed between the two parts
-struct TailBufs {
-    void *q, *k, *v, *o, *vt, *dO, *dq, *dk, *dv;
-    float *beta, *alpha, *mu, *eta, *dbeta, *dalpha, *dmu, *deta;
-    float *S_mid, *M_mid, *dS_mid, *dM_mid;
-    size_t total;
-};
-
-TailBufs carve_tail(const Dims &d, bool backward, void *p) {
-    const size_t es = elem_size(d), rows = (size_t)d.B * 64 * d.H, st = (size_t)d.BH * d.dk * d.dv * sizeof(float);
-    Carver c(p);
-    TailBufs t = {};
-    t.q = c.take(rows * d.dk * es);
-    t.k = c.take(rows * d.dk * es);
-    t.v = c.take(rows * d.dv * es);
-    t.vt = c.take(rows * d.dv * es);
-    t.beta = static_cast<float *>(c.take(rows * 4));
-    t.alpha = static_cast<float *>(c.take(rows * 4));
-    t.mu = static_cast<float *>(c.take(rows * 4));
-    t.eta = static_cast<float *>(c.take(rows * 4));
-    t.S_mid = static_cast<float *>(c.take(st));
-    t.M_mid = static_cast<float *>(c.take(st));
-    if (!backward) {
-        t.o = c.take(rows * d.dv * es);
-    } else {
-        t.dO = c.take(rows * d.dv * es);
-        t.dq = c.take(rows * d.dk * es);
-        t.dk = c.take(rows * d.dk * es);
-        t.dv = c.take(rows * d.dv * es);
-        t.dbeta = static_cast<float *>(c.take(rows * 4));
-        t.dalpha = static_cast<float *>(c.take(rows * 4));
-        t.dmu = static_cast<float *>(c.take(rows * 4));
-        t.deta = static_cast<float *>(c.take(rows * 4));
-        t.dS_mid = static_cast<float *>(c.take(st));
-        t.dM_mid = static_cast<float *>(c.take(st));
-    }
-    t.total = c.off;
-    return t;
-}
-
-void *offset(void *p, size_t bytes) { return p ? static_cast<char *>(p) + bytes : nullptr; }
-const void *offset(const void *p, size_t bytes) { return p ? static_cast<const char *>(p) + bytes : nullptr; }
-
-struct TailList {
-    TailCopy c;
-    TailList(const Dims &d, int r) {
-        c = {};
-        c.B = d.B; c.T = d.T; c.H = d.H; c.t0 = d.N * 64; c.r = r;
-    }
-    void add(const void *full, void *padded, size_t row_bytes, float pad = 0.f) {
-        if (!full || !padded) return;
-        TailTensor &t = c.t[c.n++];
-        t.full = full; t.padded = padded; t.row_bytes = (int)row_bytes;
-        memcpy(&t.pad_word, &pad, 4); // (0.f and 1.f are also right for the 16-bit rows: only 0 is used there)
-    }
-};
+size_t saved_states_total(const Dims &d) { return chunk_blocks(d) * 2 * d.dk * d.dv * elem_size(d); }
 
 int launch_status(hipError_t e) { return e == hipSuccess ? MDN_OK : MDN_ERR_LAUNCH; }
 
@@ -206,15 +145,13 @@ template <typename F> int timed(int id, hipStream_t s, F &&launch) {
 // the scan's workgroups leave the other CUs to it.  States cross a segment boundary through two small fp32
 // buffers in the workspace.
 std::atomic<int> g_segments{0}; // 0: automatic
-// this thread is inside a pair of calls that run beside each other on the two streams: no segments inside them
-thread_local bool t_side_stream_taken = false;
 
 // the serial scans of a call would occupy at most half of the CUs
 bool few_scan_workgroups(const Dims &d) { return 2 * scan_workgroups(d) <= num_cus(); }
 
 int segments(const Dims &d) {
     int k;
-    if (t_side_stream_taken || t_no_alloc) return 1;
+    if (t_no_alloc || d.seqs) return 1; // (packed batches: the scans of the sequences run beside each other)
     const int forced = g_segments.load(std::memory_order_relaxed);
     if (forced > 0) {
         k = forced;
@@ -232,7 +169,7 @@ int segments(const Dims &d) {
 struct Side {
     hipStream_t stream = nullptr;
     std::vector<hipEvent_t> ev;
-    std::recursive_mutex mutex; // (recursive: two calls beside each other take it, then each call inside may again)
+    std::mutex mutex;
 };
 
 // the second stream and n events on the current device (created once, default priority); call with the lock held
@@ -262,14 +199,13 @@ Dims segment(const Dims &d, int i, int k) {
     return r;
 }
 
-// ---- the forward over the chunks [0, d.N) of the tensors in `c`
+// ---- the forward over all chunks of the tensors in `c`
 struct FwdCall {
     const void *q, *k, *v;
     const float *beta, *alpha, *mu, *eta, *S0, *M0;
     void *o;
     float *S_final, *M_final;
     void *vt_saved, *states_saved, *operands_saved;
-    void *states_lo; // rounding remainders of states_saved (16-bit storage), or null; see packed_final_states
 };
 
 int run_fwd(const Dims &d, const FwdCall &c, const FwdWs &w, hipStream_t s) {
@@ -285,7 +221,6 @@ int run_fwd(const Dims &d, const FwdCall &c, const FwdWs &w, hipStream_t s) {
     ScanFwdArgs sa = {};
     sa.q = c.q; sa.k = c.k; sa.v = c.v; sa.coef = ia.coef; sa.KT = ia.KT; sa.Tm = w.Tm; sa.Bm = w.Bm;
     sa.S0 = c.S0; sa.M0 = c.M0; sa.o = c.o; sa.vt_saved = c.vt_saved; sa.states_saved = c.states_saved;
-    sa.states_lo = c.states_lo;
     sa.S_final = c.S_final; sa.M_final = c.M_final;
     // K^T for this forward alone: not written if its scan forms K^T out of the k rows itself
     if (!c.operands_saved && !scan_fwd_reads_KT(d)) ia.KT = nullptr, sa.KT = nullptr;
@@ -299,7 +234,7 @@ int run_fwd(const Dims &d, const FwdCall &c, const FwdWs &w, hipStream_t s) {
     // segments: precompute of segment i+1 on the second stream beside the scan of segment i on the caller's
     Side *sdev = side_device();
     if (!sdev) return MDN_ERR_LAUNCH;
-    std::lock_guard<std::recursive_mutex> lock(sdev->mutex);
+    std::lock_guard<std::mutex> lock(sdev->mutex);
     Side *sd = side(nseg + 1);
     if (!sd) return MDN_ERR_LAUNCH;
     if (hipEventRecord(sd->ev[nseg], s) != hipSuccess || hipStreamWaitEvent(sd->stream, sd->ev[nseg], 0) != hipSuccess)
@@ -323,8 +258,8 @@ int run_fwd(const Dims &d, const FwdCall &c, const FwdWs &w, hipStream_t s) {
     return MDN_OK;
 }
 
-// ---- the backward over the chunks [0, d.N) of the tensors in `c`, in two steps: what does not depend on the
-// adjoints coming in from the right (the reverse pass's operands, the chunk-start states), then the rest
+// ---- the backward over all chunks of the tensors in `c`, in two steps: what does not depend on the adjoints coming in
+// from the right (the reverse pass's operands, the chunk-start states), then the rest
 struct BwdCall {
     const void *q, *k, *v;
     const float *beta, *alpha, *mu, *eta, *S0, *M0;
@@ -346,9 +281,7 @@ bool precise_call(const Dims &d, const BwdCall &c) {
     return d.dtype == MDN_DTYPE_BF16 && (c.dS_final || c.dM_final);
 }
 
-// S_after, M_after (or null): the states after the last chunk, which the reconstruction can hand on
-int bwd_prepare(const Dims &d, const BwdCall &c, const BwdWs &w, float *S_after, float *M_after, hipStream_t s,
-                Prepared *out, bool precise) {
+int bwd_prepare(const Dims &d, const BwdCall &c, const BwdWs &w, hipStream_t s, Prepared *out, bool precise) {
     int rc;
     // chunk-local operands in the layouts of the reverse pass: kept by the forward, or recomputed
     out->ro = w.ops;
@@ -366,7 +299,7 @@ int bwd_prepare(const Dims &d, const BwdCall &c, const BwdWs &w, float *S_after,
     if (!out->states) {
         RebuildArgs ra = {};
         ra.coef = out->ro.coef; ra.k = c.k; ra.KT = out->ro.KT; ra.vt_saved = c.vt_saved; ra.S0 = c.S0; ra.M0 = c.M0;
-        ra.states = w.states; ra.states_lo = precise ? w.states_lo : nullptr; ra.S_final = S_after; ra.M_final = M_after;
+        ra.states = w.states; ra.states_lo = precise ? w.states_lo : nullptr;
         rc = timed(MDN_KERNEL_REBUILD, s, [&] { return launch_rebuild(d, ra, s); });
         if (rc) return rc;
         out->states = w.states;
@@ -397,7 +330,7 @@ int bwd_run(const Dims &d, const BwdCall &c, const BwdWs &w, const Prepared &p, 
     // of segment i-1 on the caller's; the caller's stream then waits for the last gradient launch
     Side *sdev = side_device();
     if (!sdev) return MDN_ERR_LAUNCH;
-    std::lock_guard<std::recursive_mutex> lock(sdev->mutex);
+    std::lock_guard<std::mutex> lock(sdev->mutex);
     Side *sd = side(nseg + 1);
     if (!sd) return MDN_ERR_LAUNCH;
     rc = MDN_OK;
@@ -421,130 +354,24 @@ int bwd_run(const Dims &d, const BwdCall &c, const BwdWs &w, const Prepared &p, 
     return rc;
 }
 
-size_t fwd_ws_total(const Dims &d, int r) {
-    if (r == 0) return carve_fwd(d, nullptr).total;
-    return carve_fwd(d, nullptr).total + carve_fwd(tail_dims(d), nullptr).total + carve_tail(d, false, nullptr).total;
-}
-size_t bwd_ws_total(const Dims &d, int r, bool precise) {
-    if (r == 0) return carve_bwd(d, nullptr, precise).total;
-    return carve_bwd(d, nullptr, precise).total + carve_bwd(tail_dims(d), nullptr, precise).total +
-           carve_tail(d, true, nullptr).total;
-}
-
-// The forward over a sequence of any length: d.N full chunks and r = T % 64 tokens of a partial one.
-int fwd_any(const Dims &d, int r, FwdCall c, void *workspace, hipStream_t s) {
-    int rc;
-    const FwdWs w = carve_fwd(d, workspace);
-    if (r == 0) return run_fwd(d, c, w, s);
-
-    // full chunks on the caller's tensors, then the partial chunk on padded copies
-    const Dims dt = tail_dims(d);
-    const FwdWs wt = carve_fwd(dt, offset(workspace, w.total));
-    const TailBufs tb = carve_tail(d, false, offset(workspace, w.total + wt.total));
-    const size_t es = elem_size(d);
-    float *S_final = c.S_final, *M_final = c.M_final;
-    void *o = c.o;
-    if (d.N > 0) {
-        c.S_final = tb.S_mid;
-        c.M_final = tb.M_mid;
-        rc = run_fwd(d, c, w, s);
-        if (rc) return rc;
-    }
-    TailList in(d, r);
-    in.add(c.q, tb.q, d.dk * es);
-    in.add(c.k, tb.k, d.dk * es);
-    in.add(c.v, tb.v, d.dv * es);
-    in.add(c.beta, tb.beta, 4, 0.f);
-    in.add(c.alpha, tb.alpha, 4, 1.f);
-    in.add(c.mu, tb.mu, 4, 1.f);
-    in.add(c.eta, tb.eta, 4, 1.f);
-    rc = launch_status(launch_tail_copy(in.c, true, s));
-    if (rc) return rc;
-    FwdCall ct = {tb.q, tb.k, tb.v, tb.beta, tb.alpha, tb.mu, c.eta ? tb.eta : nullptr,
-                  d.N > 0 ? tb.S_mid : c.S0, d.N > 0 ? tb.M_mid : c.M0, tb.o, S_final, M_final,
-                  c.vt_saved ? tb.vt : nullptr, offset(c.states_saved, saved_states_part(d)),
-                  offset(c.operands_saved, carve_rev(d, nullptr).total), offset(c.states_lo, saved_states_part(d))};
-    rc = run_fwd(dt, ct, wt, s);
-    if (rc) return rc;
-    TailList out(d, r);
-    out.add(o, tb.o, d.dv * es);
-    out.add(c.vt_saved, tb.vt, d.dv * es);
-    return launch_status(launch_tail_copy(out.c, false, s));
-}
-
-// The backward over a sequence of any length (see fwd_any).
-int bwd_any(const Dims &d, int r, BwdCall c, void *workspace, hipStream_t s) {
-    int rc;
-    const BwdCall u = c; // the caller's pointers (c is redirected for the full chunks below)
-    const bool precise = precise_call(d, u);
+int bwd_all(const Dims &d, const BwdCall &c, void *workspace, hipStream_t s) {
+    const bool precise = precise_call(d, c);
     const BwdWs w = carve_bwd(d, workspace, precise);
-    Prepared pm;
-    if (r == 0) {
-        rc = bwd_prepare(d, c, w, nullptr, nullptr, s, &pm, precise);
-        return rc ? rc : bwd_run(d, c, w, pm, s, precise);
-    }
-
-    // the partial chunk comes last in the sequence, so first in the reverse pass; what it needs from the full
-    // chunks (the states they leave) is ready after their preparation step
-    const Dims dt = tail_dims(d);
-    const BwdWs wt = carve_bwd(dt, offset(workspace, w.total), precise);
-    const TailBufs tb = carve_tail(d, true, offset(workspace, w.total + wt.total));
-    const size_t es = elem_size(d);
-    if (d.N > 0) {
-        rc = bwd_prepare(d, c, w, tb.S_mid, tb.M_mid, s, &pm, precise);
-        if (rc) return rc;
-    }
-    TailList in(d, r);
-    in.add(u.q, tb.q, d.dk * es);
-    in.add(u.k, tb.k, d.dk * es);
-    in.add(u.v, tb.v, d.dv * es);
-    in.add(u.vt_saved, tb.vt, d.dv * es);
-    in.add(u.dO, tb.dO, d.dv * es);
-    in.add(u.beta, tb.beta, 4, 0.f);
-    in.add(u.alpha, tb.alpha, 4, 1.f);
-    in.add(u.mu, tb.mu, 4, 1.f);
-    in.add(u.eta, tb.eta, 4, 1.f);
-    rc = launch_status(launch_tail_copy(in.c, true, s));
-    if (rc) return rc;
-    // (with states kept by the forward the partial chunk's start states are in their own part of that buffer;
-    //  otherwise they are reconstructed from what the full chunks leave)
-    BwdCall ct = {tb.q, tb.k, tb.v, tb.beta, tb.alpha, tb.mu, u.eta ? tb.eta : nullptr,
-                  d.N > 0 ? tb.S_mid : u.S0, d.N > 0 ? tb.M_mid : u.M0, tb.vt,
-                  offset(u.states_saved, saved_states_part(d)), offset(u.operands_saved, carve_rev(d, nullptr).total), tb.dO,
-                  u.dS_final, u.dM_final, tb.dq, tb.dk, tb.dv, tb.dbeta, tb.dalpha, tb.dmu, u.deta ? tb.deta : nullptr,
-                  d.N > 0 ? tb.dS_mid : u.dS0, d.N > 0 ? tb.dM_mid : u.dM0};
-    Prepared pt;
-    rc = bwd_prepare(dt, ct, wt, nullptr, nullptr, s, &pt, precise);
-    if (rc) return rc;
-    rc = bwd_run(dt, ct, wt, pt, s, precise);
-    if (rc) return rc;
-    if (d.N > 0) {
-        c.dS_final = tb.dS_mid;
-        c.dM_final = tb.dM_mid;
-        rc = bwd_run(d, c, w, pm, s, precise);
-        if (rc) return rc;
-    }
-    TailList out(d, r);
-    out.add(u.dq, tb.dq, d.dk * es);
-    out.add(u.dk, tb.dk, d.dk * es);
-    out.add(u.dv, tb.dv, d.dv * es);
-    out.add(u.dbeta, tb.dbeta, 4);
-    out.add(u.dalpha, tb.dalpha, 4);
-    out.add(u.dmu, tb.dmu, 4);
-    out.add(u.deta, tb.deta, 4);
-    return launch_status(launch_tail_copy(out.c, false, s));
+    Prepared p;
+    const int rc = bwd_prepare(d, c, w, s, &p, precise);
+    return rc ? rc : bwd_run(d, c, w, p, s, precise);
 }
 
 // ---- chunk sizes below 64 (Algorithm 1 lists C in {16, 32, 64}).  The kernels are built around 64-token tiles (four
 // waves of 16 tokens, 64-lane coefficient scans), so a chunk of C < 64 tokens runs as one such tile whose rows from C on
 // are identity steps of the recurrence (k = v = q = 0, alpha = mu = 1, beta = 0, dO = 0: they change no state and pass
-// every adjoint through, see the partial last chunk above): the chunk-local coefficients, the triangular solve and the
+// every adjoint through): the chunk-local coefficients, the triangular solve and the
 // state hand-over are exactly those of Algorithm 1 at chunk size C, at 64 / C times the work of the C = 64 path.
 // The tokens are expanded into padded copies in the workspace and the results collected from them.
 Dims expanded_dims(const Dims &d, int C) {
     Dims e = d;
     const int NC = (d.T + C - 1) / C;
-    e.T = NC * 64; e.N = NC; e.n0 = 0; e.n1 = NC;
+    e.T = NC * 64; e.N = NC; e.n0 = 0; e.n1 = NC; e.nchunks = e.B * NC;
     return e;
 }
 
@@ -569,7 +396,7 @@ ExpBufs carve_exp(const Dims &e, bool backward, bool precise, void *p) {
     x.eta = static_cast<float *>(c.take(rows * 4));
     if (!backward) {
         x.o = c.take(rows * e.dv * es);
-        x.rest = c.take(fwd_ws_total(e, 0));
+        x.rest = c.take(carve_fwd(e, nullptr).total);
     } else {
         x.dO = c.take(rows * e.dv * es);
         x.dq = c.take(rows * e.dk * es);
@@ -579,7 +406,7 @@ ExpBufs carve_exp(const Dims &e, bool backward, bool precise, void *p) {
         x.dalpha = static_cast<float *>(c.take(rows * 4));
         x.dmu = static_cast<float *>(c.take(rows * 4));
         x.deta = static_cast<float *>(c.take(rows * 4));
-        x.rest = c.take(bwd_ws_total(e, 0, precise));
+        x.rest = c.take(carve_bwd(e, nullptr, precise).total);
     }
     x.total = c.off;
     return x;
@@ -593,7 +420,7 @@ struct ChunkList {
     }
     void add(const void *full, void *padded, size_t row_bytes, float pad = 0.f) {
         if (!full || !padded) return;
-        TailTensor &t = c.t[c.n++];
+        TileTensor &t = c.t[c.n++];
         t.full = full; t.padded = padded; t.row_bytes = (int)row_bytes;
         memcpy(&t.pad_word, &pad, 4);
     }
@@ -643,11 +470,7 @@ int bwd_small_chunks(const Dims &d, int C, const BwdCall &c, void *workspace, hi
     const BwdCall ce = {x.q, x.k, x.v, x.beta, x.alpha, x.mu, c.eta ? x.eta : nullptr, c.S0, c.M0, x.vt, c.states_saved,
                         c.operands_saved, x.dO, c.dS_final, c.dM_final, x.dq, x.dk, x.dv, x.dbeta, x.dalpha, x.dmu,
                         c.deta ? x.deta : nullptr, c.dS0, c.dM0};
-    const BwdWs w = carve_bwd(e, x.rest, precise);
-    Prepared pm;
-    rc = bwd_prepare(e, ce, w, nullptr, nullptr, s, &pm, precise);
-    if (rc) return rc;
-    rc = bwd_run(e, ce, w, pm, s, precise);
+    rc = bwd_all(e, ce, x.rest, s);
     if (rc) return rc;
     ChunkList out(d, C);
     out.add(c.dq, x.dq, d.dk * es);
@@ -662,221 +485,71 @@ int bwd_small_chunks(const Dims &d, int C, const BwdCall &c, void *workspace, hi
 
 // workspace, kept states and kept operands of a call, whatever its chunk size
 size_t fwd_ws_call(const Dims &d, const mdn_shape *shape) {
-    if (shape->C == 64) return fwd_ws_total(d, shape->T % 64);
+    if (shape->C == 64) return carve_fwd(d, nullptr).total;
     return carve_exp(expanded_dims(d, shape->C), false, false, nullptr).total;
 }
 size_t bwd_ws_call(const Dims &d, const mdn_shape *shape, bool precise) {
-    if (shape->C == 64) return bwd_ws_total(d, shape->T % 64, precise);
+    if (shape->C == 64) return carve_bwd(d, nullptr, precise).total;
     return carve_exp(expanded_dims(d, shape->C), true, precise, nullptr).total;
 }
 
-// ---- packed variable-length batches: the sequences lie one after another along T of a [1, T, H, *] tensor;
-// sequence i is tokens [cu[i], cu[i+1]).  Each sequence runs as a batch of one through the any-length path
-// (stream order makes the shared workspace safe).
+// ---- packed variable-length batches: the sequences lie one after another along T of a [1, T, H, *] tensor; sequence i
+// is tokens [cu[i], cu[i+1]).  Every kernel finds its sequence in two small device tables (mdn_kernels.h), so the batch
+// is one set of launches: the chunk-parallel kernels over the chunks of all sequences, the scans with one workgroup
+// per (sequence, head, dv-block), longest sequences first so that the last workgroups to start are the shortest.
 int check_varlen(const mdn_shape *shape, const int32_t *cu, int32_t n_seq, Dims *d) {
     const int rc = check_shape(shape, true, d);
     if (rc) return rc;
     if (shape->C != 64) return MDN_ERR_SHAPE; // (packed batches: chunk size 64 only)
     if (!cu) return MDN_ERR_NULL;
     if (shape->B != 1 || n_seq < 1 || cu[0] != 0 || cu[n_seq] != shape->T) return MDN_ERR_SHAPE;
-    for (int i = 0; i < n_seq; ++i)
+    long long chunks = 0, longest = 0;
+    for (int i = 0; i < n_seq; ++i) {
         if (cu[i + 1] <= cu[i]) return MDN_ERR_SHAPE;
+        const long long N = ((long long)cu[i + 1] - cu[i] + 63) / 64;
+        chunks += N;
+        longest = N > longest ? N : longest;
+    }
+    if (n_seq == 1) return MDN_OK; // an ordinary batch of one
+    if ((long long)n_seq * d->H > (1 << 24) || chunks * d->H > (1LL << 31) - 1) return MDN_ERR_SHAPE;
+    d->B = n_seq; d->BH = n_seq * d->H; d->N = d->n1 = (int)longest; d->nchunks = (int)chunks;
     return MDN_OK;
 }
 
-Dims seq_dims(const Dims &all, int len) {
-    Dims d = all;
-    d.B = 1; d.T = len; d.N = len / 64; d.BH = all.H; d.n0 = 0; d.n1 = d.N;
-    return d;
-}
-
-// ---- the same batch as ONE stream of tokens.  By Eq. Mt.recurrent / St.recurrent a token with alpha = mu = 0
-// sees nothing of the states before it (e = v, M = -eta k e^T, S = -beta M: what a sequence that starts from zero
-// states computes at its first token, whose own alpha and mu multiply those zeros and do not matter), and passes no
-// adjoint back to them.  So with alpha and mu set to zero at the first token of every sequence but the first, the
-// whole batch is one sequence of shape->T tokens: one set of launches, however many and however short the sequences,
-// and no partial chunk but the last.  Open to calls that neither give nor ask for per-sequence states; the
-// gradients of the zeroed gates are zero (they multiply zero states) and are set so.
-// When the stream's scans would leave half of the CUs idle (few heads), it is cut in two at the sequence start nearest
-// to its middle and the halves run beside each other, one on the caller's stream and one on the library's second
-// stream: nothing passes between them, the state is cut there anyway.
-struct PackedWs { float *alpha, *mu; void *rest, *rest2; int cut; size_t total; };
-
-// index m (0 < m < n_seq) of the sequence that starts the second half, or 0: no cut
-int packed_cut(const Dims &d, const int32_t *cu, int n_seq) {
-    if (n_seq < 2 || !few_scan_workgroups(d) || d.T < 2048) return 0;
-    int best = 1;
-    for (int i = 1; i < n_seq; ++i)
-        if (llabs(2LL * cu[i] - d.T) < llabs(2LL * cu[best] - d.T)) best = i;
-    // (a lopsided cut would only take the overlap of the chunk-parallel kernels with the scans away from the long half)
-    const int small = cu[best] < d.T - cu[best] ? cu[best] : d.T - cu[best];
-    return small >= d.T / 4 ? best : 0;
-}
-
-PackedWs carve_packed(const Dims &d, const int32_t *cu, int n_seq, bool backward, void *ws) {
+// the tables at the start of the workspace (none for a single sequence), the rest behind them
+struct PackedWs { SeqEntry *seqs; ChunkEntry *chunks; void *rest; size_t head; };
+PackedWs carve_packed(const Dims &d, int32_t n_seq, void *ws) {
     Carver c(ws);
     PackedWs w = {};
-    w.alpha = static_cast<float *>(c.take((size_t)d.T * d.H * sizeof(float)));
-    w.mu = static_cast<float *>(c.take((size_t)d.T * d.H * sizeof(float)));
-    w.cut = packed_cut(d, cu, n_seq);
-    auto need = [&](int len) {
-        const Dims p = seq_dims(d, len);
-        return backward ? bwd_ws_total(p, len % 64, false) : fwd_ws_total(p, len % 64);
-    };
-    if (w.cut) {
-        w.rest = c.take(need(cu[w.cut]));
-        w.rest2 = c.take(need(d.T - cu[w.cut]));
-    } else {
-        w.rest = c.take(need(d.T));
+    if (n_seq > 1) {
+        w.seqs = static_cast<SeqEntry *>(c.take((size_t)n_seq * sizeof(SeqEntry)));
+        w.chunks = static_cast<ChunkEntry *>(c.take((size_t)d.nchunks * sizeof(ChunkEntry)));
     }
-    w.total = c.off;
+    w.head = c.off;
+    w.rest = ws ? static_cast<char *>(ws) + c.off : nullptr;
     return w;
 }
 
-// the two halves beside each other: first(stream), second(stream) are the two calls
-template <typename F1, typename F2> int run_beside(hipStream_t s, F1 &&first, F2 &&second) {
-    constexpr int E0 = 30, E1 = 31; // (the events below these belong to the segments of a single call)
-    Side *sdev = side_device();
-    if (!sdev) return MDN_ERR_LAUNCH;
-    std::lock_guard<std::recursive_mutex> lock(sdev->mutex);
-    Side *sd = side(E1 + 1);
-    if (!sd) return MDN_ERR_LAUNCH;
-    if (hipEventRecord(sd->ev[E0], s) != hipSuccess || hipStreamWaitEvent(sd->stream, sd->ev[E0], 0) != hipSuccess)
-        return MDN_ERR_LAUNCH; // whatever the caller's stream holds so far comes first
-    t_side_stream_taken = true;
-    int rc = first(s);
-    if (!rc) rc = second(sd->stream);
-    t_side_stream_taken = false;
-    if (hipEventRecord(sd->ev[E1], sd->stream) != hipSuccess || hipStreamWaitEvent(s, sd->ev[E1], 0) != hipSuccess)
-        return MDN_ERR_LAUNCH;
-    return rc;
-}
-
-// value at the first tokens of sequences 1 .. n_seq-1 of a (and b)
-int set_at_sequence_starts(const Dims &d, const int32_t *cu, int n_seq, float *a, float *b, float value, hipStream_t s) {
-    SeqStarts st;
-    st.H = d.H;
-    for (int i = 1; i < n_seq;) {
-        st.n = 0;
-        while (i < n_seq && st.n < kSeqStartsPerLaunch) st.t[st.n++] = cu[i++];
-        if (launch_set_at_tokens(a, b, value, st, s) != hipSuccess) return MDN_ERR_LAUNCH;
+// builds the tables on the stream and points d at them
+int packed_tables(Dims *d, const int32_t *cu, int32_t n_seq, const PackedWs &w, hipStream_t s) {
+    if (n_seq == 1) return MDN_OK;
+    std::vector<SeqEntry> e(n_seq);
+    int cb = 0;
+    for (int i = 0; i < n_seq; ++i) {
+        e[i] = SeqEntry{cu[i], cu[i + 1] - cu[i], cb, i};
+        cb += (e[i].len + 63) / 64;
     }
+    std::stable_sort(e.begin(), e.end(), [](const SeqEntry &a, const SeqEntry &b) { return a.len > b.len; });
+    SeqList l;
+    l.H = d->H;
+    for (l.first = 0; l.first < n_seq; l.first += l.n) {
+        l.n = n_seq - l.first < kSeqsPerLaunch ? n_seq - l.first : kSeqsPerLaunch;
+        memcpy(l.e, e.data() + l.first, (size_t)l.n * sizeof(SeqEntry));
+        if (launch_seq_tables(l, w.seqs, w.chunks, s) != hipSuccess) return MDN_ERR_LAUNCH;
+    }
+    d->seqs = w.seqs;
+    d->chunks = w.chunks;
     return MDN_OK;
-}
-
-// copies of alpha, mu with the sequence starts zeroed
-int packed_gates(const Dims &d, const int32_t *cu, int n_seq, const float *alpha, const float *mu, const PackedWs &w,
-                 hipStream_t s) {
-    const size_t bytes = (size_t)d.T * d.H * sizeof(float);
-    if (hipMemcpyAsync(w.alpha, alpha, bytes, hipMemcpyDeviceToDevice, s) != hipSuccess ||
-        hipMemcpyAsync(w.mu, mu, bytes, hipMemcpyDeviceToDevice, s) != hipSuccess)
-        return MDN_ERR_LAUNCH;
-    return set_at_sequence_starts(d, cu, n_seq, w.alpha, w.mu, 0.f, s);
-}
-
-// ---- the stream form with per-sequence FINAL states (zero initial states): the stream keeps its chunk-start
-// states; the state after a sequence's last token is that of the chunk holding the token, run once more from its
-// start state over the tokens up to the sequence's end, the rest of the chunk padded with tokens that change no state
-// (as for a partial last chunk).  All sequences' last chunks form one batch of n_seq rows of 64 tokens.
-Dims rows_dims(const Dims &d, int n_seq) {
-    Dims t = tail_dims(d);
-    t.B = n_seq; t.BH = n_seq * d.H;
-    return t;
-}
-
-// one half of the stream (or all of it): sequences [seq0, seq1), tokens [t0, t0 + len)
-struct StreamPiece {
-    int seq0, seq1, t0, len;
-    void *states; // its chunk-start states (full chunks, then the partial chunk's block)
-    void *states_lo; // 16-bit storage: what the rounding of `states` dropped (the final states start from hi + lo)
-    void *rest;   // its forward workspace
-};
-
-struct PackedFinalWs {
-    PackedWs g;       // gate copies
-    int npieces;
-    StreamPiece piece[2];
-    void *k, *v, *o;  // padded rows [n_seq, 64, H, *]
-    float *beta, *alpha, *mu, *eta, *S0, *M0;
-    void *rest_rows;
-    size_t total;
-};
-
-PackedFinalWs carve_packed_final(const Dims &d, const int32_t *cu, int n_seq, void *ws) {
-    const size_t es = elem_size(d), rows = (size_t)n_seq * 64 * d.H, st = (size_t)n_seq * d.H * d.dk * d.dv * sizeof(float);
-    const Dims dr = rows_dims(d, n_seq);
-    Carver c(ws);
-    PackedFinalWs w = {};
-    w.g.alpha = static_cast<float *>(c.take((size_t)d.T * d.H * sizeof(float)));
-    w.g.mu = static_cast<float *>(c.take((size_t)d.T * d.H * sizeof(float)));
-    const int cut = packed_cut(d, cu, n_seq);
-    w.npieces = cut ? 2 : 1;
-    w.piece[0] = {0, cut ? cut : n_seq, 0, cut ? cu[cut] : d.T, nullptr, nullptr, nullptr};
-    w.piece[1] = {cut, n_seq, cut ? cu[cut] : 0, cut ? d.T - cu[cut] : 0, nullptr, nullptr, nullptr};
-    for (int p = 0; p < w.npieces; ++p) {
-        const Dims dp = seq_dims(d, w.piece[p].len);
-        const size_t sb = saved_states_part(dp) + (dp.T % 64 ? saved_states_part(tail_dims(dp)) : 0);
-        w.piece[p].states = c.take(sb);
-        w.piece[p].states_lo = d.dtype == MDN_DTYPE_BF16 ? c.take(sb) : nullptr;
-        w.piece[p].rest = c.take(fwd_ws_total(dp, dp.T % 64));
-    }
-    w.k = c.take(rows * d.dk * es);
-    w.v = c.take(rows * d.dv * es);
-    w.o = c.take(rows * d.dv * es);
-    w.beta = static_cast<float *>(c.take(rows * 4));
-    w.alpha = static_cast<float *>(c.take(rows * 4));
-    w.mu = static_cast<float *>(c.take(rows * 4));
-    w.eta = static_cast<float *>(c.take(rows * 4));
-    w.S0 = static_cast<float *>(c.take(st));
-    w.M0 = static_cast<float *>(c.take(st));
-    w.rest_rows = c.take(fwd_ws_total(dr, 0));
-    w.total = c.off;
-    return w;
-}
-
-int packed_final_states(const Dims &d, const int32_t *cu, int n_seq, const FwdCall &stream, const PackedFinalWs &w,
-                        float *S_final, float *M_final, hipStream_t s) {
-    const size_t es = elem_size(d), st = (size_t)d.H * d.dk * d.dv;
-    for (int p = 0; p < w.npieces; ++p) {
-        const StreamPiece &pc = w.piece[p];
-        const Dims dp = seq_dims(d, pc.len); // (the piece's chunks count from its own first token)
-        for (int i0 = pc.seq0; i0 < pc.seq1; i0 += kSeqRowsPerLaunch) {
-            const int n = pc.seq1 - i0 < kSeqRowsPerLaunch ? pc.seq1 - i0 : kSeqRowsPerLaunch;
-            const size_t rows0 = (size_t)i0 * 64 * d.H;
-            SeqRows g = {};
-            SeqChunks sc = {};
-            g.n = sc.n = n; g.H = sc.H = d.H;
-            sc.N = dp.N; sc.dk = d.dk; sc.dv = d.dv; sc.dtype = d.dtype;
-            for (int e = 0; e < n; ++e) {
-                const int end = cu[i0 + e + 1] - pc.t0, chunk = (end - 1) / 64;
-                sc.chunk[e] = chunk;
-                g.t0[e] = pc.t0 + chunk * 64;
-                g.r[e] = end - chunk * 64;
-            }
-            auto add = [&](const void *full, void *padded, size_t row_bytes, float pad) {
-                if (!full) return;
-                TailTensor &t = g.t[g.ntens++];
-                t.full = full; t.padded = static_cast<char *>(padded) + rows0 * row_bytes; t.row_bytes = (int)row_bytes;
-                memcpy(&t.pad_word, &pad, 4);
-            };
-            add(stream.k, w.k, d.dk * es, 0.f);
-            add(stream.v, w.v, d.dv * es, 0.f);
-            add(stream.beta, w.beta, 4, 0.f);
-            add(stream.alpha, w.alpha, 4, 1.f);
-            add(stream.mu, w.mu, 4, 1.f);
-            add(stream.eta, w.eta, 4, 1.f);
-            if (launch_gather_seq_rows(g, s) != hipSuccess) return MDN_ERR_LAUNCH;
-            if (launch_states_to_f32(pc.states, offset(pc.states, saved_states_part(dp)), pc.states_lo,
-                                     offset(pc.states_lo, saved_states_part(dp)), sc, w.S0 + (size_t)i0 * st,
-                                     w.M0 + (size_t)i0 * st, s) != hipSuccess)
-                return MDN_ERR_LAUNCH;
-        }
-    }
-    // (the rows' outputs o are of no use: q is given the k rows, o a scratch tensor)
-    const Dims dr = rows_dims(d, n_seq);
-    FwdCall c = {w.k, w.k, w.v, w.beta, w.alpha, w.mu, stream.eta ? w.eta : nullptr, w.S0, w.M0, w.o, S_final, M_final,
-                 nullptr, nullptr, nullptr};
-    return run_fwd(dr, c, carve_fwd(dr, w.rest_rows), s);
 }
 
 // ---- the forward's workspace as a fixed array in device memory, for callers that cannot allocate.  Every GPU the
@@ -898,12 +571,6 @@ int scratch_address(void **out) {
     }
     *out = per_device[dev];
     return MDN_OK;
-}
-
-template <typename P> P *at_token(P *base, size_t token, size_t bytes_per_token) {
-    return base ? reinterpret_cast<P *>(reinterpret_cast<char *>(const_cast<typename std::remove_const<P>::type *>(base)) +
-                                        token * bytes_per_token)
-                : nullptr;
 }
 
 } // namespace
@@ -983,9 +650,7 @@ int mdn_saved_states_bytes(const mdn_shape *shape, size_t *bytes_out) {
     if (!bytes_out) return MDN_ERR_NULL;
     int rc = check_shape(shape, true, &d);
     if (rc) return rc;
-    // the full chunks' blocks first, then (T % 64 != 0) one block per (batch, head) for the partial chunk
-    if (shape->C != 64) *bytes_out = saved_states_part(expanded_dims(d, shape->C));
-    else *bytes_out = saved_states_part(d) + (shape->T % 64 ? saved_states_part(tail_dims(d)) : 0);
+    *bytes_out = saved_states_total(shape->C == 64 ? d : expanded_dims(d, shape->C));
     return MDN_OK;
 }
 
@@ -994,8 +659,7 @@ int mdn_saved_operands_bytes(const mdn_shape *shape, size_t *bytes_out) {
     if (!bytes_out) return MDN_ERR_NULL;
     int rc = check_shape(shape, true, &d);
     if (rc) return rc;
-    if (shape->C != 64) *bytes_out = carve_rev(expanded_dims(d, shape->C), nullptr).total;
-    else *bytes_out = carve_rev(d, nullptr).total + (shape->T % 64 ? carve_rev(tail_dims(d), nullptr).total : 0);
+    *bytes_out = carve_rev(shape->C == 64 ? d : expanded_dims(d, shape->C), nullptr).total;
     return MDN_OK;
 }
 
@@ -1011,12 +675,11 @@ int mdn_chunk_fwd(const mdn_shape *shape, const void *q, const void *k, const vo
                           operands_saved, workspace};
     for (const void *p : ptrs)
         if (p && misaligned(p)) return MDN_ERR_ALIGN;
-    const int r = shape->T % 64;
     if (workspace_bytes < fwd_ws_call(d, shape)) return MDN_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
     FwdCall c = {q, k, v, beta, alpha, mu, eta, S0, M0, o, S_final, M_final, vt_saved, states_saved, operands_saved};
     if (shape->C != 64) return fwd_small_chunks(d, shape->C, c, workspace, s);
-    return fwd_any(d, r, c, workspace, s);
+    return run_fwd(d, c, carve_fwd(d, workspace), s);
 }
 
 int mdn_chunk_fwd_noalloc(const mdn_shape *shape, const void *q, const void *k, const void *v, const float *beta,
@@ -1029,17 +692,16 @@ int mdn_chunk_fwd_noalloc(const mdn_shape *shape, const void *q, const void *k, 
     const void *ptrs[] = {q, k, v, beta, alpha, mu, eta, S0, M0, o, S_final, M_final, vt_saved};
     for (const void *p : ptrs)
         if (p && misaligned(p)) return MDN_ERR_ALIGN;
-    const int r = shape->T % 64;
     if (fwd_ws_call(d, shape) > (size_t)MDN_NOALLOC_SCRATCH_BYTES) return MDN_ERR_WORKSPACE;
     void *ws = nullptr;
     rc = scratch_address(&ws);
     if (rc) return rc;
     // Nothing in the forward's workspace has to start from zero: the chunk-local operands are written in full by the
-    // chunk-parallel kernel before the scan reads them, the padded copies of a partial chunk by the gather kernel.
+    // chunk-parallel kernel before the scan reads them, the padded copies of chunks below 64 tokens by the copy kernel.
     FwdCall c = {q, k, v, beta, alpha, mu, eta, S0, M0, o, S_final, M_final, vt_saved, nullptr, nullptr};
     t_no_alloc = true; // one stream, no timing events: nothing below creates a stream, an event or memory
     rc = shape->C != 64 ? fwd_small_chunks(d, shape->C, c, ws, static_cast<hipStream_t>(stream))
-                        : fwd_any(d, r, c, ws, static_cast<hipStream_t>(stream));
+                        : run_fwd(d, c, carve_fwd(d, ws), static_cast<hipStream_t>(stream));
     t_no_alloc = false;
     return rc;
 }
@@ -1061,13 +723,12 @@ int mdn_chunk_bwd(const mdn_shape *shape, const void *q, const void *k, const vo
                           dq, dk, dv, dbeta, dalpha, dmu, deta, dS0, dM0, workspace};
     for (const void *p : ptrs)
         if (p && misaligned(p)) return MDN_ERR_ALIGN;
-    const int r = shape->T % 64;
     BwdCall c = {q, k, v, beta, alpha, mu, eta, S0, M0, vt_saved, states_saved, operands_saved, dO, dS_final, dM_final,
                  dq, dk, dv, dbeta, dalpha, dmu, deta, dS0, dM0};
     if (workspace_bytes < bwd_ws_call(d, shape, precise_call(d, c))) return MDN_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (shape->C != 64) return bwd_small_chunks(d, shape->C, c, workspace, s);
-    return bwd_any(d, r, c, workspace, s);
+    return bwd_all(d, c, workspace, s);
 }
 
 int mdn_workspace_bytes_varlen(const mdn_shape *shape, const int32_t *cu_seqlens, int32_t n_seq, int which, size_t *bytes_out) {
@@ -1076,21 +737,9 @@ int mdn_workspace_bytes_varlen(const mdn_shape *shape, const int32_t *cu_seqlens
     const int rc = check_varlen(shape, cu_seqlens, n_seq, &d);
     if (rc) return rc;
     if (which != MDN_WS_FWD && which != MDN_WS_BWD) return MDN_ERR_SHAPE;
-    size_t need = 0;
-    for (int i = 0; i < n_seq; ++i) {
-        const int len = cu_seqlens[i + 1] - cu_seqlens[i];
-        const Dims ds = seq_dims(d, len);
-        // (a sequence run by itself may bring adjoints of its final states in)
-        const size_t b = which == MDN_WS_FWD ? fwd_ws_total(ds, len % 64) : bwd_ws_total(ds, len % 64, ds.dtype == MDN_DTYPE_BF16);
-        need = b > need ? b : need;
-    }
-    // (either way of running the batch may be taken: see mdn_chunk_fwd_varlen)
-    size_t packed = carve_packed(d, cu_seqlens, n_seq, which == MDN_WS_BWD, nullptr).total;
-    if (which == MDN_WS_FWD) {
-        const size_t pf = carve_packed_final(d, cu_seqlens, n_seq, nullptr).total;
-        packed = pf > packed ? pf : packed;
-    }
-    *bytes_out = packed > need ? packed : need;
+    // (a backward call may bring adjoints of the final states in: room for the rounding remainders as well)
+    *bytes_out = carve_packed(d, n_seq, nullptr).head +
+                 (which == MDN_WS_FWD ? carve_fwd(d, nullptr).total : carve_bwd(d, nullptr, d.dtype == MDN_DTYPE_BF16).total);
     return MDN_OK;
 }
 
@@ -1110,57 +759,11 @@ int mdn_chunk_fwd_varlen(const mdn_shape *shape, const int32_t *cu_seqlens, int3
     if (rc) return rc;
     if (workspace_bytes < need) return MDN_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (!S0 && !M0 && !S_final && !M_final) {
-        // no per-sequence states in or out: the batch as one stream of tokens
-        const PackedWs w = carve_packed(d, cu_seqlens, n_seq, false, workspace);
-        rc = packed_gates(d, cu_seqlens, n_seq, alpha, mu, w, s);
-        if (rc) return rc;
-        const size_t es = elem_size(d), rk = (size_t)d.H * d.dk * es, rv = (size_t)d.H * d.dv * es, rg = (size_t)d.H * 4;
-        auto part = [&](size_t t0, int len, void *ws, hipStream_t st) {
-            FwdCall c = {at_token(q, t0, rk), at_token(k, t0, rk), at_token(v, t0, rv), at_token(beta, t0, rg),
-                         at_token(w.alpha, t0, rg), at_token(w.mu, t0, rg), at_token(eta, t0, rg), nullptr, nullptr,
-                         at_token(o, t0, rv), nullptr, nullptr, at_token(vt_saved, t0, rv), nullptr, nullptr};
-            return fwd_any(seq_dims(d, len), len % 64, c, ws, st);
-        };
-        if (!w.cut) return part(0, d.T, w.rest, s);
-        const int t1 = cu_seqlens[w.cut];
-        return run_beside(s, [&](hipStream_t st) { return part(0, t1, w.rest, st); },
-                          [&](hipStream_t st) { return part((size_t)t1, d.T - t1, w.rest2, st); });
-    }
-    if (!S0 && !M0 && S_final && M_final) {
-        // zero initial states, final states of every sequence wanted: the stream, then the sequences' last chunks
-        const PackedFinalWs w = carve_packed_final(d, cu_seqlens, n_seq, workspace);
-        rc = packed_gates(d, cu_seqlens, n_seq, alpha, mu, w.g, s);
-        if (rc) return rc;
-        const size_t es = elem_size(d), rk = (size_t)d.H * d.dk * es, rv = (size_t)d.H * d.dv * es, rg = (size_t)d.H * 4;
-        auto part = [&](const StreamPiece &pc, hipStream_t st) {
-            const size_t t0 = (size_t)pc.t0;
-            FwdCall c = {at_token(q, t0, rk), at_token(k, t0, rk), at_token(v, t0, rv), at_token(beta, t0, rg),
-                         at_token(w.g.alpha, t0, rg), at_token(w.g.mu, t0, rg), at_token(eta, t0, rg), nullptr, nullptr,
-                         at_token(o, t0, rv), nullptr, nullptr, at_token(vt_saved, t0, rv), pc.states, nullptr, pc.states_lo};
-            return fwd_any(seq_dims(d, pc.len), pc.len % 64, c, pc.rest, st);
-        };
-        rc = w.npieces == 1 ? part(w.piece[0], s)
-                            : run_beside(s, [&](hipStream_t st) { return part(w.piece[0], st); },
-                                         [&](hipStream_t st) { return part(w.piece[1], st); });
-        if (rc) return rc;
-        const FwdCall whole = {q, k, v, beta, w.g.alpha, w.g.mu, eta, nullptr, nullptr, o, nullptr, nullptr, vt_saved, nullptr,
-                               nullptr};
-        return packed_final_states(d, cu_seqlens, n_seq, whole, w, S_final, M_final, s);
-    }
-    const size_t es = elem_size(d), rk = (size_t)d.H * d.dk * es, rv = (size_t)d.H * d.dv * es, rg = (size_t)d.H * 4;
-    const size_t st = (size_t)d.H * d.dk * d.dv * sizeof(float);
-    for (int i = 0; i < n_seq; ++i) {
-        const size_t t0 = (size_t)cu_seqlens[i];
-        const int len = cu_seqlens[i + 1] - cu_seqlens[i];
-        FwdCall c = {at_token(q, t0, rk), at_token(k, t0, rk), at_token(v, t0, rv), at_token(beta, t0, rg),
-                     at_token(alpha, t0, rg), at_token(mu, t0, rg), at_token(eta, t0, rg), at_token(S0, i, st),
-                     at_token(M0, i, st), at_token(o, t0, rv), at_token(S_final, i, st), at_token(M_final, i, st),
-                     at_token(vt_saved, t0, rv), nullptr, nullptr};
-        rc = fwd_any(seq_dims(d, len), len % 64, c, workspace, s);
-        if (rc) return rc;
-    }
-    return MDN_OK;
+    const PackedWs w = carve_packed(d, n_seq, workspace);
+    rc = packed_tables(&d, cu_seqlens, n_seq, w, s);
+    if (rc) return rc;
+    const FwdCall c = {q, k, v, beta, alpha, mu, eta, S0, M0, o, S_final, M_final, vt_saved, nullptr, nullptr};
+    return run_fwd(d, c, carve_fwd(d, w.rest), s);
 }
 
 int mdn_chunk_bwd_varlen(const mdn_shape *shape, const int32_t *cu_seqlens, int32_t n_seq, const void *q, const void *k,
@@ -1183,45 +786,12 @@ int mdn_chunk_bwd_varlen(const mdn_shape *shape, const int32_t *cu_seqlens, int3
     if (rc) return rc;
     if (workspace_bytes < need) return MDN_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (!S0 && !M0 && !dS_final && !dM_final && !dS0 && !dM0) {
-        // no per-sequence states or state adjoints in or out: the batch as one stream of tokens
-        const PackedWs w = carve_packed(d, cu_seqlens, n_seq, true, workspace);
-        rc = packed_gates(d, cu_seqlens, n_seq, alpha, mu, w, s);
-        if (rc) return rc;
-        const size_t es = elem_size(d), rk = (size_t)d.H * d.dk * es, rv = (size_t)d.H * d.dv * es, rg = (size_t)d.H * 4;
-        auto part = [&](size_t t0, int len, void *ws, hipStream_t st) {
-            BwdCall c = {at_token(q, t0, rk), at_token(k, t0, rk), at_token(v, t0, rv), at_token(beta, t0, rg),
-                         at_token(w.alpha, t0, rg), at_token(w.mu, t0, rg), at_token(eta, t0, rg), nullptr, nullptr,
-                         at_token(vt_saved, t0, rv), nullptr, nullptr, at_token(dO, t0, rv), nullptr, nullptr,
-                         at_token(dq, t0, rk), at_token(dk, t0, rk), at_token(dv, t0, rv), at_token(dbeta, t0, rg),
-                         at_token(dalpha, t0, rg), at_token(dmu, t0, rg), at_token(deta, t0, rg), nullptr, nullptr};
-            return bwd_any(seq_dims(d, len), len % 64, c, ws, st);
-        };
-        if (!w.cut) {
-            rc = part(0, d.T, w.rest, s);
-        } else {
-            const int t1 = cu_seqlens[w.cut];
-            rc = run_beside(s, [&](hipStream_t st) { return part(0, t1, w.rest, st); },
-                            [&](hipStream_t st) { return part((size_t)t1, d.T - t1, w.rest2, st); });
-        }
-        if (rc) return rc;
-        return set_at_sequence_starts(d, cu_seqlens, n_seq, dalpha, dmu, 0.f, s);
-    }
-    const size_t es = elem_size(d), rk = (size_t)d.H * d.dk * es, rv = (size_t)d.H * d.dv * es, rg = (size_t)d.H * 4;
-    const size_t st = (size_t)d.H * d.dk * d.dv * sizeof(float);
-    for (int i = 0; i < n_seq; ++i) {
-        const size_t t0 = (size_t)cu_seqlens[i];
-        const int len = cu_seqlens[i + 1] - cu_seqlens[i];
-        BwdCall c = {at_token(q, t0, rk), at_token(k, t0, rk), at_token(v, t0, rv), at_token(beta, t0, rg),
-                     at_token(alpha, t0, rg), at_token(mu, t0, rg), at_token(eta, t0, rg), at_token(S0, i, st),
-                     at_token(M0, i, st), at_token(vt_saved, t0, rv), nullptr, nullptr, at_token(dO, t0, rv),
-                     at_token(dS_final, i, st), at_token(dM_final, i, st), at_token(dq, t0, rk), at_token(dk, t0, rk),
-                     at_token(dv, t0, rv), at_token(dbeta, t0, rg), at_token(dalpha, t0, rg), at_token(dmu, t0, rg),
-                     at_token(deta, t0, rg), at_token(dS0, i, st), at_token(dM0, i, st)};
-        rc = bwd_any(seq_dims(d, len), len % 64, c, workspace, s);
-        if (rc) return rc;
-    }
-    return MDN_OK;
+    const PackedWs w = carve_packed(d, n_seq, workspace);
+    rc = packed_tables(&d, cu_seqlens, n_seq, w, s);
+    if (rc) return rc;
+    const BwdCall c = {q, k, v, beta, alpha, mu, eta, S0, M0, vt_saved, nullptr, nullptr, dO, dS_final, dM_final,
+                       dq, dk, dv, dbeta, dalpha, dmu, deta, dS0, dM0};
+    return bwd_all(d, c, w.rest, s);
 }
 
 int mdn_recurrent_step(const mdn_shape *shape, const void *q, const void *k, const void *v, const float *beta,

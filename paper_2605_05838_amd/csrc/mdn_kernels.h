@@ -6,17 +6,38 @@
 
 namespace mdn {
 
+// One sequence of a packed batch, and one 64-token chunk of it: device tables that packed calls build in their
+// workspace (fixed-length batches need none: the same values follow from B, T, H).
+struct SeqEntry {
+    int t0, len; // first token (row of the [T_total, H, *] tensors), tokens
+    int cb;      // chunks of the sequences before it in memory order
+    int idx;     // its index in the caller's order (states are [n_seq, H, dk, dv] in that order)
+};
+struct ChunkEntry {
+    int t0, rows; // first token, tokens (1..64)
+    int blk, N;   // chunk block of head 0, and what each further head adds (the sequence's chunks)
+};
+
 struct Dims {
-    int B, T, H, N, BH; // N = T / 64 chunks, BH = B * H
+    int B, T, H, N, BH; // B sequences of T tokens, N = ceil(T / 64) chunks each, BH = B * H.  Packed batches: B
+                        // sequences of their own lengths, N = the longest one's chunks, T = all tokens
     int n0, n1;         // chunks [n0, n1) handled by this launch (0, N unless the call is split into segments)
     int dk, dv;
     int dtype; // MDN_DTYPE_*
     float scale;
+    int nchunks;              // chunks of all sequences together (B * N unless packed)
+    const SeqEntry *seqs;     // packed batches: [B], longest first (the scans' order of dispatch); otherwise null
+    const ChunkEntry *chunks; // packed batches: [nchunks], memory order; otherwise null
 };
 
 // Chunk-parallel precompute ("intra") kernel arguments.  Workspace tensors are chunk-blocked,
-// [BH][N][tile], in the storage dtype unless noted; inside a tile, an MFMA operand [rows][k] is in
-// the kblk layout and a [rows][dv] tensor in the vblk layout of mdn_device.h.
+// [sequence][H][chunk of the sequence][tile] (written [BH][N] below: what it is for a fixed-length batch), in the storage
+// dtype unless noted; inside a tile, an MFMA operand [rows][k] is in the kblk layout and a [rows][dv] tensor in
+// the vblk layout of mdn_device.h.
+// A chunk of fewer than 64 tokens (the last one of a sequence) is filled up with identity steps of the recurrence:
+// k = q = eta = 0, alpha = mu = 1, beta = 0.  The intra kernel writes its operands that way (rows of K^T, Q^T, Bm zero,
+// rows of T those of the unit matrix, Gamma_C = Rho_C = 0), after which whatever finite values the scans read for V, k,
+// dO in those rows meet zeros; the scans read the last real token's row there and store only real rows.
 constexpr int kCoefBlockCols = 8; // floats per token in the coefficient block
 
 struct IntraArgs {
@@ -42,8 +63,8 @@ struct ScanFwdArgs {
     void *o;                                // [B,T,H,dv]
     void *vt_saved;                         // [B,T,H,dv] or null
     void *states_saved;                     // [BH][N][2] x vblk [dk][dv], or null
-    void *states_lo;                        // same layout, or null: what the 16-bit rounding of states_saved dropped
-                                            // (see GradArgs, and the packed prefill in mdn_api.hip)
+    void *states_lo;                        // reconstruction, same layout, or null: what the 16-bit rounding of
+                                            // states_saved dropped (see GradArgs)
     float *S_final, *M_final;               // or null
 };
 
@@ -116,58 +137,30 @@ hipError_t launch_scan_bwd(const Dims &d, const ScanBwdArgs &a, hipStream_t s);
 hipError_t launch_grad(const Dims &d, const GradArgs &a, hipStream_t s);
 hipError_t launch_recurrent(const Dims &d, const RecurrentArgs &a, hipStream_t s);
 
-// Rows of a partial last chunk: tokens t0 .. t0+r-1 of every sequence of a [B,T,H,row] tensor <-> rows 0 .. r-1 of
-// a padded [B,64,H,row] copy (gather fills the rows from r on with pad_word).
-struct TailTensor {
-    const void *full; // the caller's tensor (written by scatter)
-    void *padded;     // the padded copy (written by gather)
+// One tensor of a copy between the caller's layout and padded 64-token tiles.
+struct TileTensor {
+    const void *full; // the caller's tensor
+    void *padded;     // the padded copy
     int row_bytes;    // a multiple of 4
     uint32_t pad_word;
 };
-struct TailCopy {
-    int B, T, H, t0, r, n; // n tensors
-    TailTensor t[12];
-};
-hipError_t launch_tail_copy(const TailCopy &c, bool gather, hipStream_t s);
 
 // Chunk sizes below 64 (Algorithm 1 lists C in {16, 32, 64}): every chunk of C tokens becomes one 64-token tile whose
-// rows from C on are padding (TailTensor::pad_word).  expand: [B,T,H,row] -> [B, ceil(T/C) * 64, H, row];
+// rows from C on are padding (TileTensor::pad_word).  expand: [B,T,H,row] -> [B, ceil(T/C) * 64, H, row];
 // collect: the real rows back.
 struct ChunkCopy {
     int B, T, H, C, NC, n; // NC = ceil(T / C) chunks, n tensors
-    TailTensor t[12];
+    TileTensor t[12];
 };
 hipError_t launch_chunk_copy(const ChunkCopy &c, bool expand, hipStream_t s);
 
-// Packed variable-length batches run as one stream of tokens whose state is cut at the first token of every
-// sequence but the first: x[t, h] = value for the listed tokens t of up to two [T, H] fp32 tensors (a, b; b may be
-// null).  The token list travels in the kernel arguments, kSeqStartsPerLaunch at a time.
-constexpr int kSeqStartsPerLaunch = 240;
-struct SeqStarts {
-    int n, H;
-    int t[kSeqStartsPerLaunch];
+// Packed variable-length batches: writes the device tables of Dims from the entries, which travel in the kernel
+// arguments, kSeqsPerLaunch at a time (seqs[first + i] = e[i], and the chunk entries of that sequence).
+constexpr int kSeqsPerLaunch = 224;
+struct SeqList {
+    int n, first, H;
+    SeqEntry e[kSeqsPerLaunch];
 };
-hipError_t launch_set_at_tokens(float *a, float *b, float value, const SeqStarts &st, hipStream_t s);
-
-// The last (possibly partial) chunk of each listed sequence of a token stream [T, H, *], as a batch of padded
-// 64-token rows [n, 64, H, *]: entry i takes tokens [t0[i], t0[i] + r[i]) (1 <= r <= 64) and pads like TailCopy.
-constexpr int kSeqRowsPerLaunch = 200;
-struct SeqRows {
-    int n, H, ntens;
-    int t0[kSeqRowsPerLaunch], r[kSeqRowsPerLaunch];
-    TailTensor t[8];
-};
-hipError_t launch_gather_seq_rows(const SeqRows &g, hipStream_t s);
-
-// Chunk-start states out of the saved-states buffer of a single-batch call (blocks [H][N][2] in the vblk layout and
-// the storage type, then one block pair per head for the partial chunk) as fp32 [n, H, dk, dv]: entry i takes chunk
-// chunk[i] (== N: the partial chunk's block).
-struct SeqChunks {
-    int n, H, N, dk, dv, dtype;
-    int chunk[kSeqRowsPerLaunch];
-};
-// (lo_full, lo_tail: the rounding remainders of the same blocks, or null)
-hipError_t launch_states_to_f32(const void *states_full, const void *states_tail, const void *lo_full, const void *lo_tail,
-                                const SeqChunks &c, float *S, float *M, hipStream_t s);
+hipError_t launch_seq_tables(const SeqList &l, SeqEntry *seqs, ChunkEntry *chunks, hipStream_t s);
 
 } // namespace mdn

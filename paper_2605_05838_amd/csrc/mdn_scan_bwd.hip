@@ -21,8 +21,7 @@
 // The chunk-end adjoint states are written for the chunk-parallel gradient kernel.
 #include "mdn_device.h"
 #include "mdn_kernels.h"
-
-#include <stdlib.h>
+#include "mdn_seq.h"
 
 namespace mdn {
 
@@ -44,17 +43,17 @@ template <typename T, int DK, int MV> struct RevOps {
 // The operands of one chunk are requested in five portions (P = 0..4) spread over the work on the previous chunk: a
 // wave that issues them all at once sits at the issue until the memory pipeline has taken them (the time
 // to move a chunk's operands into the CU), with its matrix work waiting behind.
+// itok: this lane's token of a chunk, in token rows (i * H; in a partial chunk no further than the last real token).
 template <typename T, int DK, int DV, int DVB, int P>
-__device__ __forceinline__ void fetch_part(RevOps<T, DK, DVB / 16> &c, const Dims &d, const ScanBwdArgs &a, int bh, int b,
-                                           int h, int n, int dv0) {
+__device__ __forceinline__ void fetch_part(RevOps<T, DK, DVB / 16> &c, const Dims &d, const ScanBwdArgs &a, const ScanSeq &sq,
+                                           int n, int dv0, unsigned itok) {
     typedef Op<T> O;
     typedef RevOps<T, DK, DVB / 16> CO;
     const int lane = lane_id(), w = wave_id(), r = lane & 15, kg = lane >> 4, i = w * 16 + r;
     // every address is a wave-uniform 64-bit base (chunk, batch, head: scalar arithmetic) plus a 32-bit lane offset that
     // does not change from chunk to chunk (at32: one address register per access, no vector 64-bit adds)
-    const size_t blk = (size_t)bh * d.N + n;
-    const size_t tok0 = ((size_t)b * d.T + (size_t)n * 64) * d.H + h; // the chunk's first token of this head
-    const unsigned itok = (unsigned)(i * d.H);                        // this lane's token, in token rows
+    const size_t blk = sq.blk + n;
+    const size_t tok0 = sq.tok + (size_t)n * 64 * d.H; // the chunk's first token of this head
     if (P == 0) {
         // (through the vector path on purpose: a scalar load would share its wait counter with the LDS reads and
         //  make the first of those wait for memory)
@@ -92,13 +91,13 @@ __device__ __forceinline__ void fetch_part(RevOps<T, DK, DVB / 16> &c, const Dim
 }
 
 template <typename T, int DK, int DV, int DVB>
-__device__ __forceinline__ void fetch_chunk(RevOps<T, DK, DVB / 16> &c, const Dims &d, const ScanBwdArgs &a, int bh,
-                                            int b, int h, int n, int dv0) {
-    fetch_part<T, DK, DV, DVB, 0>(c, d, a, bh, b, h, n, dv0);
-    fetch_part<T, DK, DV, DVB, 1>(c, d, a, bh, b, h, n, dv0);
-    fetch_part<T, DK, DV, DVB, 2>(c, d, a, bh, b, h, n, dv0);
-    fetch_part<T, DK, DV, DVB, 3>(c, d, a, bh, b, h, n, dv0);
-    fetch_part<T, DK, DV, DVB, 4>(c, d, a, bh, b, h, n, dv0);
+__device__ __forceinline__ void fetch_chunk(RevOps<T, DK, DVB / 16> &c, const Dims &d, const ScanBwdArgs &a,
+                                            const ScanSeq &sq, int n, int dv0, unsigned itok) {
+    fetch_part<T, DK, DV, DVB, 0>(c, d, a, sq, n, dv0, itok);
+    fetch_part<T, DK, DV, DVB, 1>(c, d, a, sq, n, dv0, itok);
+    fetch_part<T, DK, DV, DVB, 2>(c, d, a, sq, n, dv0, itok);
+    fetch_part<T, DK, DV, DVB, 3>(c, d, a, sq, n, dv0, itok);
+    fetch_part<T, DK, DV, DVB, 4>(c, d, a, sq, n, dv0, itok);
 }
 
 template <typename T, int DK, int DV, int DVB>
@@ -120,8 +119,12 @@ __global__ __launch_bounds__(kThreads) void scan_bwd_kernel(Dims d, ScanBwdArgs 
     int bh, blkv;
     xcd_map(blockIdx.x, G, bh, blkv);
     if (bh >= d.BH) return;
-    const int b = bh / d.H, h = bh % d.H, dv0 = blkv * DVB;
+    const ScanSeq sq = scan_seq(d, bh);
+    const int dv0 = blkv * DVB;
     const int lane = lane_id(), w = wave_id(), r = lane & 15, kg = lane >> 4, i = w * 16 + r;
+    // a partial last chunk (the first one here): its loads stop at the last real token
+    const int ragged = sq.len & 63 ? sq.len >> 6 : -1, last = (sq.len & 63) - 1; // that chunk (or none), its last row
+    const unsigned iH = (unsigned)(i * d.H), itok = sq.n1 - 1 == ragged ? (unsigned)(min(i, last) * d.H) : iH;
 
     // element x of tile (mv, nd): dS[dk = (w*ND + nd)*16 + r][dv = mv*16 + kg*4 + x]
     f32x4 accS[MV][ND], accM[MV][ND];
@@ -129,16 +132,17 @@ __global__ __launch_bounds__(kThreads) void scan_bwd_kernel(Dims d, ScanBwdArgs 
     for (int mv = 0; mv < MV; ++mv)
 #pragma unroll
         for (int nd = 0; nd < ND; ++nd) {
-            const size_t g = ((size_t)bh * DK + (w * ND + nd) * 16 + r) * DV + dv0 + kg * (4 * MV) + mv * 4;
+            const size_t g = (sq.state * DK + (w * ND + nd) * 16 + r) * DV + dv0 + kg * (4 * MV) + mv * 4;
             accS[mv][nd] = a.dS_final ? *reinterpret_cast<const f32x4 *>(a.dS_final + g) : f32x4{0.f, 0.f, 0.f, 0.f};
             accM[mv][nd] = a.dM_final ? *reinterpret_cast<const f32x4 *>(a.dM_final + g) : f32x4{0.f, 0.f, 0.f, 0.f};
         }
 
     // one chunk: the operands of chunk n are in `cur`; those of chunk n-1 go on their way into `nxt`
     auto step = [&](int n, const CO &cur, CO &nxt) {
-        const size_t blk = (size_t)bh * d.N + n;
-        const int nn = n > d.n0 ? n - 1 : d.n0;
-        fetch_part<T, DK, DV, DVB, 0>(nxt, d, a, bh, b, h, nn, dv0);
+        const size_t blk = sq.blk + n;
+        const int nn = n > sq.n0 ? n - 1 : sq.n0;
+        const unsigned itn = nn == ragged ? itok : iH;
+        fetch_part<T, DK, DV, DVB, 0>(nxt, d, a, sq, nn, dv0, itn);
 
         // adjoints of this chunk's END states: operand copy to LDS, storage copy to HBM.  (The stores cost this
         // kernel ~45 us whoever issues them and whenever: in one burst here, 208 us; spread over the step in 8
@@ -181,7 +185,7 @@ __global__ __launch_bounds__(kThreads) void scan_bwd_kernel(Dims d, ScanBwdArgs 
                 }
             }
         }
-        fetch_part<T, DK, DV, DVB, 1>(nxt, d, a, bh, b, h, nn, dv0);
+        fetch_part<T, DK, DV, DVB, 1>(nxt, d, a, sq, nn, dv0, itn);
         // dO^T slice of this chunk in three scalings
 #pragma unroll
         for (int mv = 0; mv < MV; ++mv) {
@@ -204,7 +208,7 @@ __global__ __launch_bounds__(kThreads) void scan_bwd_kernel(Dims d, ScanBwdArgs 
 #pragma unroll
                 for (int mv = 0; mv < MV; ++mv)
                     accD[mv] = O::mma(TV::frag(sO0, mv, s * O::KSTEP, r, kg), cur.bmT[s], accD[mv]);
-            fetch_part<T, DK, DV, DVB, 2>(nxt, d, a, bh, b, h, nn, dv0);
+            fetch_part<T, DK, DV, DVB, 2>(nxt, d, a, sq, nn, dv0, itn);
 #pragma unroll
             for (int s = 0; s < CO::KS; ++s)
 #pragma unroll
@@ -212,7 +216,7 @@ __global__ __launch_bounds__(kThreads) void scan_bwd_kernel(Dims d, ScanBwdArgs 
                     x1[mv] = O::mma(TD::frag(sD, mv, s * O::KSTEP, r, kg), cur.k[s], x1[mv]);
                     x2[mv] = O::mma(TD::frag(sD, mv, DK + s * O::KSTEP, r, kg), cur.k[s], x2[mv]);
                 }
-            fetch_part<T, DK, DV, DVB, 3>(nxt, d, a, bh, b, h, nn, dv0);
+            fetch_part<T, DK, DV, DVB, 3>(nxt, d, a, sq, nn, dv0, itn);
 #pragma unroll
             for (int mv = 0; mv < MV; ++mv) TV::put4(sDV, mv * 16 + kg * 4, i, accD[mv] + cur.c1[COEF_GC - 4] * x1[mv] - cur.c1[COEF_RC - 4] * x2[mv]);
         }
@@ -228,9 +232,10 @@ __global__ __launch_bounds__(kThreads) void scan_bwd_kernel(Dims d, ScanBwdArgs 
 #pragma unroll
                 for (int mv = 0; mv < MV; ++mv)
                     dR[mv] = O::mma(TV::frag(sDV, mv, s * O::KSTEP, r, kg), cur.tT[s], dR[mv]);
-            fetch_part<T, DK, DV, DVB, 4>(nxt, d, a, bh, b, h, nn, dv0);
-            const size_t tok0 = ((size_t)b * d.T + (size_t)n * 64) * d.H + h;
-            store_cols<T, MV>(at32(static_cast<T *>(a.dv) + tok0 * DV + dv0, (unsigned)(i * d.H) * DV + kg * (4 * MV)), dR);
+            fetch_part<T, DK, DV, DVB, 4>(nxt, d, a, sq, nn, dv0, itn);
+            const size_t tok0 = sq.tok + (size_t)n * 64 * d.H;
+            RowStore(static_cast<T *>(a.dv) + tok0 * DV + dv0, n == ragged ? last + 1 : 64, d.H * DV, DVB)
+                .template put_narrowed<T, MV>(iH * DV + kg * (4 * MV), dR);
 #pragma unroll
             for (int mv = 0; mv < MV; ++mv) {
                 TV::put4(sRa, mv * 16 + kg * 4, i, -cur.c0[COEF_A] * dR[mv]);
@@ -273,20 +278,20 @@ __global__ __launch_bounds__(kThreads) void scan_bwd_kernel(Dims d, ScanBwdArgs 
     // every register of the set that was just requested, i.e. wait for all of its loads
     {
         CO opsA, opsB;
-        fetch_chunk<T, DK, DV, DVB>(opsA, d, a, bh, b, h, d.n1 - 1, dv0);
-        int n = d.n1 - 1;
-        for (; n >= d.n0 + 1; n -= 2) {
+        fetch_chunk<T, DK, DV, DVB>(opsA, d, a, sq, sq.n1 - 1, dv0, itok);
+        int n = sq.n1 - 1;
+        for (; n >= sq.n0 + 1; n -= 2) {
             step(n, opsA, opsB);
             step(n - 1, opsB, opsA);
         }
-        if (n == d.n0) step(n, opsA, opsB);
+        if (n == sq.n0) step(n, opsA, opsB);
     }
 
 #pragma unroll
     for (int mv = 0; mv < MV; ++mv)
 #pragma unroll
         for (int nd = 0; nd < ND; ++nd) {
-            const size_t g = ((size_t)bh * DK + (w * ND + nd) * 16 + r) * DV + dv0 + kg * (4 * MV) + mv * 4;
+            const size_t g = (sq.state * DK + (w * ND + nd) * 16 + r) * DV + dv0 + kg * (4 * MV) + mv * 4;
             if (a.dS0) *reinterpret_cast<f32x4 *>(a.dS0 + g) = accS[mv][nd];
             if (a.dM0) *reinterpret_cast<f32x4 *>(a.dM0 + g) = accM[mv][nd];
         }

@@ -29,8 +29,7 @@
 // only waits on LDS and MFMA latency.
 #include "mdn_device.h"
 #include "mdn_kernels.h"
-
-#include <stdlib.h>
+#include "mdn_seq.h"
 
 namespace mdn {
 
@@ -56,17 +55,17 @@ template <typename T, int DK, int MV> struct ChunkOps {
 // The operands of one chunk are requested in portions (P = 0..4) spread over the work on the previous
 // chunk: a wave that issues them all at once sits at the issue until the memory pipeline has taken them
 // (the time to move a chunk's operands into the CU), with its matrix work waiting behind.
+// itok: this lane's token of a chunk, in token rows (i * H; in a partial chunk no further than the last real token).
 template <typename T, int DK, int DV, int DVB, bool REBUILD, int P, bool KTILE>
-__device__ __forceinline__ void fetch_part(ChunkOps<T, DK, DVB / 16> &c, const Dims &d, const ScanFwdArgs &a, int bh,
-                                           int b, int h, int n, int dv0) {
+__device__ __forceinline__ void fetch_part(ChunkOps<T, DK, DVB / 16> &c, const Dims &d, const ScanFwdArgs &a, const ScanSeq &sq,
+                                           int n, int dv0, unsigned itok) {
     typedef Op<T> O;
     typedef ChunkOps<T, DK, DVB / 16> CO;
     const int lane = lane_id(), w = wave_id() & 3, r = lane & 15, kg = lane >> 4, i = w * 16 + r;
     // every address is a wave-uniform 64-bit base (chunk, batch, head: scalar arithmetic) plus a 32-bit lane offset that
     // does not change from chunk to chunk (at32: one address register per access, no vector 64-bit adds)
-    const size_t blk = (size_t)bh * d.N + n;
-    const size_t tok0 = ((size_t)b * d.T + (size_t)n * 64) * d.H + h; // the chunk's first token of this head
-    const unsigned itok = (unsigned)(i * d.H);                        // this lane's token, in token rows
+    const size_t blk = sq.blk + n;
+    const size_t tok0 = sq.tok + (size_t)n * 64 * d.H; // the chunk's first token of this head
     if (P == 0) {
         // (through the vector path on purpose: a scalar load would share its wait counter with the LDS reads and
         //  make the first of those wait for memory)
@@ -108,12 +107,12 @@ __device__ __forceinline__ void fetch_part(ChunkOps<T, DK, DVB / 16> &c, const D
 
 template <typename T, int DK, int DV, int DVB, bool REBUILD, bool KTILE>
 __device__ __forceinline__ void fetch_chunk(ChunkOps<T, DK, DVB / 16> &c, const Dims &d, const ScanFwdArgs &a,
-                                            int bh, int b, int h, int n, int dv0) {
-    fetch_part<T, DK, DV, DVB, REBUILD, 0, KTILE>(c, d, a, bh, b, h, n, dv0);
-    fetch_part<T, DK, DV, DVB, REBUILD, 4, KTILE>(c, d, a, bh, b, h, n, dv0);
-    fetch_part<T, DK, DV, DVB, REBUILD, 1, KTILE>(c, d, a, bh, b, h, n, dv0);
-    fetch_part<T, DK, DV, DVB, REBUILD, 3, KTILE>(c, d, a, bh, b, h, n, dv0);
-    fetch_part<T, DK, DV, DVB, REBUILD, 2, KTILE>(c, d, a, bh, b, h, n, dv0);
+                                            const ScanSeq &sq, int n, int dv0, unsigned itok) {
+    fetch_part<T, DK, DV, DVB, REBUILD, 0, KTILE>(c, d, a, sq, n, dv0, itok);
+    fetch_part<T, DK, DV, DVB, REBUILD, 4, KTILE>(c, d, a, sq, n, dv0, itok);
+    fetch_part<T, DK, DV, DVB, REBUILD, 1, KTILE>(c, d, a, sq, n, dv0, itok);
+    fetch_part<T, DK, DV, DVB, REBUILD, 3, KTILE>(c, d, a, sq, n, dv0, itok);
+    fetch_part<T, DK, DV, DVB, REBUILD, 2, KTILE>(c, d, a, sq, n, dv0, itok);
 }
 
 // accumulator element x of tile (mv, nd) of wave w is S[dk = (w*ND + nd)*16 + r][dv = mv*16 + kg*4 + x]
@@ -157,25 +156,35 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(Dims d, ScanFwdArgs 
     int bh, blkv;
     xcd_map(blockIdx.x, G, bh, blkv);
     if (bh >= d.BH) return;
-    const int b = bh / d.H, h = bh % d.H, dv0 = blkv * DVB;
+    const ScanSeq sq = scan_seq(d, bh);
+    const int dv0 = blkv * DVB;
     const int lane = lane_id(), w = wave_id(), r = lane & 15, kg = lane >> 4, i = w * 16 + r;
+    // a partial last chunk: its loads stop at the last real token
+    const int ragged = sq.len & 63 ? sq.len >> 6 : -1, last = (sq.len & 63) - 1; // that chunk (or none), its last row
+    const unsigned iH = (unsigned)(i * d.H);
+    unsigned itok = iH;
 
     // k rows of chunk n into ring slot `slot`
     auto request_k = [&](int n, int slot) {
         if constexpr (KTILE) {
-            const T *kg0 = static_cast<const T *>(a.k) + (((size_t)b * d.T + (size_t)n * 64) * d.H + h) * DK;
-            dma_token_tile<T, DK, 4>(sKr + slot * (64 * DK), kg0, (unsigned)(d.H * DK), __builtin_amdgcn_readfirstlane(w), lane);
+            const T *kg0 = static_cast<const T *>(a.k) + (sq.tok + (size_t)n * 64 * d.H) * DK;
+            T *dst = sKr + slot * (64 * DK);
+            const unsigned rs = (unsigned)(d.H * DK);
+            const int ws = __builtin_amdgcn_readfirstlane(w);
+            if (n == ragged) dma_token_tile<T, DK, 4>(dst, kg0, rs, ws, lane, last);
+            else dma_token_tile<T, DK, 4>(dst, kg0, rs, ws, lane);
         }
     };
-    request_k(d.n0, 0);
-    request_k(d.n0 + 1 < d.n1 ? d.n0 + 1 : d.n0, 1);
+    request_k(sq.n0, 0);
+    request_k(sq.n0 + 1 < sq.n1 ? sq.n0 + 1 : sq.n0, 1);
+    if (sq.n0 == ragged) itok = (unsigned)(min(i, last) * d.H);
 
     f32x4 accS[MV][ND], accM[MV][ND];
 #pragma unroll
     for (int mv = 0; mv < MV; ++mv)
 #pragma unroll
         for (int nd = 0; nd < ND; ++nd) {
-            const size_t g = ((size_t)bh * DK + (w * ND + nd) * 16 + r) * DV + dv0 + kg * (4 * MV) + mv * 4;
+            const size_t g = (sq.state * DK + (w * ND + nd) * 16 + r) * DV + dv0 + kg * (4 * MV) + mv * 4;
             accS[mv][nd] = a.S0 ? *reinterpret_cast<const f32x4 *>(a.S0 + g) : f32x4{0.f, 0.f, 0.f, 0.f};
             accM[mv][nd] = a.M0 ? *reinterpret_cast<const f32x4 *>(a.M0 + g) : f32x4{0.f, 0.f, 0.f, 0.f};
         }
@@ -188,12 +197,11 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(Dims d, ScanFwdArgs 
     // kernel ~75 us whichever wave issues them and whenever).  Reconstruction, which does little else than store:
     // in 8 portions spread over the step (109 against 127 us in one burst).
     constexpr int NS = 2 * ND; // vector stores per lane: S and M, ND rows, MV * 4 consecutive columns each
-    constexpr bool LO = sizeof(T) == 2;
+    constexpr bool LO = sizeof(T) == 2 && REBUILD;
     typename Raw4<T>::type sv[NS][MV];
     typename Raw4<T>::type sl[LO ? NS : 1][MV];
     // sv: the states in storage form; sl: what that rounding dropped, rounded again (16-bit storage, on request: the
-    // reconstruction of a backward call that brings state adjoints in, and the forward of a packed batch of prompts,
-    // whose sequences' final states start from these chunk-start states)
+    // reconstruction of a backward call that brings state adjoints in)
     auto narrow_states = [&]() {
 #pragma unroll
         for (int nd = 0; nd < ND; ++nd)
@@ -241,20 +249,21 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(Dims d, ScanFwdArgs 
     if constexpr (!REBUILD) {
         if (a.states_saved) { // the start states of the first chunk: what came in
             narrow_states();
-            sblk = (size_t)bh * d.N + d.n0;
+            sblk = sq.blk + sq.n0;
             emit_states(std::integral_constant<int, 0>{});
         }
     }
     int slot = 0;
     auto step = [&](int n, const CO &cur, CO &nxt) {
-        const size_t blk = (size_t)bh * d.N + n;
-        const size_t tok0 = ((size_t)b * d.T + (size_t)n * 64) * d.H + h; // (uniform base + 32-bit lane offset, as in fetch_part)
-        const unsigned itok = (unsigned)(i * d.H);
-        const int nn = (n + 1 < d.n1) ? n + 1 : n;
+        const size_t blk = sq.blk + n;
+        const size_t tok0 = sq.tok + (size_t)n * 64 * d.H; // (uniform base + 32-bit lane offset, as in fetch_part)
+        const int nn = (n + 1 < sq.n1) ? n + 1 : n;
+        const int rows = n == ragged ? last + 1 : 64; // tokens of this chunk: their outputs are stored
+        if (nn == ragged) itok = (unsigned)(min(i, last) * d.H); // (the chunk requested from here on is the partial one)
         const T *kc = sKr + slot * (64 * DK);
-        if (n + 2 < d.n1) request_k(n + 2, slot >= 1 ? slot - 1 : 2);
+        if (n + 2 < sq.n1) request_k(n + 2, slot >= 1 ? slot - 1 : 2);
         slot = slot == 2 ? 0 : slot + 1;
-        fetch_part<T, DK, DV, DVB, REBUILD, 0, KTILE>(nxt, d, a, bh, b, h, nn, dv0);
+        fetch_part<T, DK, DV, DVB, REBUILD, 0, KTILE>(nxt, d, a, sq, nn, dv0, itok);
 
         sblk = blk;
         auto emit_in_step = [&](auto PORTION) {
@@ -265,7 +274,7 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(Dims d, ScanFwdArgs 
         }
         emit_in_step(std::integral_constant<int, 0>{});
 
-        fetch_part<T, DK, DV, DVB, REBUILD, 4, KTILE>(nxt, d, a, bh, b, h, nn, dv0);
+        fetch_part<T, DK, DV, DVB, REBUILD, 4, KTILE>(nxt, d, a, sq, nn, dv0, itok);
         emit_in_step(std::integral_constant<int, 1>{});
         // ---------------- stage 1: R^T = (V - a.(K S) + pb.(K M))^T and the inter-chunk read-outs for token i,
         //                  then V~^T = R^T T^T over all 64 tokens
@@ -292,7 +301,7 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(Dims d, ScanFwdArgs 
                     accOM[mv] = O::mma(fm, cur.q[s], accOM[mv]);
                 }
             }
-            fetch_part<T, DK, DV, DVB, REBUILD, 1, KTILE>(nxt, d, a, bh, b, h, nn, dv0);
+            fetch_part<T, DK, DV, DVB, REBUILD, 1, KTILE>(nxt, d, a, sq, nn, dv0, itok);
 #pragma unroll
             for (int mv = 0; mv < MV; ++mv) {
                 accO[mv] = d.scale * (cur.c0[COEF_A] * accOS[mv] - cur.c0[COEF_B] * accOM[mv]);
@@ -323,7 +332,7 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(Dims d, ScanFwdArgs 
                 vt[mv] = widen4_packed(vb[mv]);
             }
             if (a.vt_saved) {
-                store_cols_raw<MV>(at32(static_cast<T *>(a.vt_saved) + tok0 * DV + dv0, itok * DV + kg * (4 * MV)), vb);
+                RowStore(static_cast<T *>(a.vt_saved) + tok0 * DV + dv0, rows, d.H * DV, DVB).template put_cols<T, MV>(iH * DV + kg * (4 * MV), vb);
             }
         } else {
 #pragma unroll
@@ -344,7 +353,7 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(Dims d, ScanFwdArgs 
         __syncthreads();
 
         // ---------------- stage 2: intra-chunk output and the state update
-        fetch_part<T, DK, DV, DVB, REBUILD, 2, KTILE>(nxt, d, a, bh, b, h, nn, dv0);
+        fetch_part<T, DK, DV, DVB, REBUILD, 2, KTILE>(nxt, d, a, sq, nn, dv0, itok);
         emit_in_step(std::integral_constant<int, 4>{});
         const float aC = cur.c0[COEF_AC], bC = cur.c1[COEF_BC - 4], mC = cur.c1[COEF_MC - 4];
 #pragma unroll
@@ -377,7 +386,7 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(Dims d, ScanFwdArgs 
             }
         }
         emit_in_step(std::integral_constant<int, 5>{});
-        fetch_part<T, DK, DV, DVB, REBUILD, 3, KTILE>(nxt, d, a, bh, b, h, nn, dv0);
+        fetch_part<T, DK, DV, DVB, REBUILD, 3, KTILE>(nxt, d, a, sq, nn, dv0, itok);
         emit_in_step(std::integral_constant<int, 6>{});
         if constexpr (!REBUILD) {
             // the states after this chunk, narrowed once: the LDS copy for the next chunk's stage 1 and, in HBM, that
@@ -391,11 +400,11 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(Dims d, ScanFwdArgs 
                     TS::put4_raw(sSt, mv * 16 + kg * 4, dk, sv[2 * nd][mv]);
                     TS::put4_raw(sSt, mv * 16 + kg * 4, DK + dk, sv[2 * nd + 1][mv]);
                 }
-            if (n + 1 < d.n1) {
+            if (n + 1 < sq.n1) {
                 sblk = blk + 1;
                 emit_states(std::integral_constant<int, 0>{});
             }
-            store_cols<T, MV>(at32(static_cast<T *>(a.o) + tok0 * DV + dv0, itok * DV + kg * (4 * MV)), accO);
+            RowStore(static_cast<T *>(a.o) + tok0 * DV + dv0, rows, d.H * DV, DVB).template put_narrowed<T, MV>(iH * DV + kg * (4 * MV), accO);
         }
         emit_in_step(std::integral_constant<int, 7>{});
         __syncthreads();
@@ -404,20 +413,20 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(Dims d, ScanFwdArgs 
     // register of the set that was just requested, i.e. wait for all of its loads
     {
         CO opsA, opsB;
-        fetch_chunk<T, DK, DV, DVB, REBUILD, KTILE>(opsA, d, a, bh, b, h, d.n0, dv0);
-        int n = d.n0;
-        for (; n + 1 < d.n1; n += 2) {
+        fetch_chunk<T, DK, DV, DVB, REBUILD, KTILE>(opsA, d, a, sq, sq.n0, dv0, itok);
+        int n = sq.n0;
+        for (; n + 1 < sq.n1; n += 2) {
             step(n, opsA, opsB);
             step(n + 1, opsB, opsA);
         }
-        if (n < d.n1) step(n, opsA, opsB);
+        if (n < sq.n1) step(n, opsA, opsB);
     }
 
 #pragma unroll
     for (int mv = 0; mv < MV; ++mv)
 #pragma unroll
         for (int nd = 0; nd < ND; ++nd) {
-            const size_t g = ((size_t)bh * DK + (w * ND + nd) * 16 + r) * DV + dv0 + kg * (4 * MV) + mv * 4;
+            const size_t g = (sq.state * DK + (w * ND + nd) * 16 + r) * DV + dv0 + kg * (4 * MV) + mv * 4;
             if (a.S_final) *reinterpret_cast<f32x4 *>(a.S_final + g) = accS[mv][nd];
             if (a.M_final) *reinterpret_cast<f32x4 *>(a.M_final + g) = accM[mv][nd];
         }

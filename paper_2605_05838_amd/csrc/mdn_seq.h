@@ -1,0 +1,65 @@
+// Where a workgroup's sequence or chunk lies: from the device tables of a packed batch, or by arithmetic for a
+// fixed-length one.  Everything here is wave-uniform.
+#pragma once
+#include "mdn_kernels.h"
+
+namespace mdn {
+
+// one (sequence, head) pair of a scan
+struct ScanSeq {
+    size_t tok;   // its first token, as a row of the [tokens, H] tensors
+    size_t blk;   // its first chunk block
+    size_t state; // its index in the [sequences, H] state tensors
+    int len;      // tokens
+    int n0, n1;   // chunks of this launch
+};
+__device__ __forceinline__ ScanSeq scan_seq(const Dims &d, int bh) {
+    const int b = bh / d.H, h = bh % d.H;
+    ScanSeq q;
+    if (d.seqs) {
+        const SeqEntry e = d.seqs[b];
+        const int N = (e.len + 63) >> 6;
+        q.tok = (size_t)e.t0 * d.H + h;
+        q.blk = (size_t)e.cb * d.H + (size_t)h * N;
+        q.state = (size_t)e.idx * d.H + h;
+        q.len = e.len;
+        q.n0 = 0;
+        q.n1 = N;
+    } else {
+        q.tok = (size_t)b * d.T * d.H + h;
+        q.blk = (size_t)bh * d.N;
+        q.state = bh;
+        q.len = d.T;
+        q.n0 = d.n0;
+        q.n1 = d.n1;
+    }
+    return q;
+}
+
+// one chunk of a chunk-parallel kernel.  x runs over the chunks of a launch (those of all sequences for a packed
+// batch, [n0, n1) of one (batch, head) pair otherwise), y over the heads or over the (batch, head) pairs.
+struct ChunkPos {
+    size_t tok; // its first token of this head, as a row of the [tokens, H] tensors
+    size_t blk; // its chunk block
+    int rows;   // tokens, 1..64
+};
+__device__ __forceinline__ ChunkPos chunk_pos(const Dims &d, int x, int y) {
+    ChunkPos p;
+    if (d.chunks) {
+        const ChunkEntry e = d.chunks[x];
+        p.tok = (size_t)e.t0 * d.H + y;
+        p.blk = (size_t)e.blk + (size_t)y * e.N;
+        p.rows = e.rows;
+    } else {
+        const int n = d.n0 + x, b = y / d.H, h = y % d.H, left = d.T - n * 64;
+        p.tok = ((size_t)b * d.T + (size_t)n * 64) * d.H + h;
+        p.blk = (size_t)y * d.N + n;
+        p.rows = left < 64 ? left : 64;
+    }
+    return p;
+}
+// the grid of such a launch
+inline int chunk_grid_x(const Dims &d) { return d.chunks ? d.nchunks : d.n1 - d.n0; }
+inline int chunk_grid_y(const Dims &d) { return d.chunks ? d.H : d.BH; }
+
+} // namespace mdn

@@ -1,0 +1,61 @@
+// How sequences are laid out in 64-token chunks: the device tables of packed variable-length batches, and the padded
+// copies of chunk sizes below 64.  A padding token of such a copy has k = v = q = 0, alpha = mu = 1, beta = 0: by
+// Eq. Mt.recurrent / St.recurrent it changes neither S nor M, and with dO = 0 on the padding rows the reverse pass is
+// exact as well.
+#include "mdn_device.h"
+#include "mdn_kernels.h"
+
+namespace mdn {
+
+namespace {
+
+// blockIdx.x = sequence of the list
+__global__ __launch_bounds__(64) void seq_tables_kernel(SeqList l, SeqEntry *seqs, ChunkEntry *chunks) {
+    const SeqEntry e = l.e[blockIdx.x];
+    if (threadIdx.x == 0) seqs[l.first + blockIdx.x] = e;
+    const int N = (e.len + 63) / 64;
+    for (int n = threadIdx.x; n < N; n += 64)
+        chunks[e.cb + n] = ChunkEntry{e.t0 + n * 64, min(64, e.len - n * 64), e.cb * l.H + n, N};
+}
+
+// chunks of C < 64 tokens as 64-token tiles: blockIdx.y = tensor, blockIdx.x = (b, chunk, i, h) row of the padded tensor
+template <bool EXPAND> __global__ __launch_bounds__(64) void chunk_copy_kernel(ChunkCopy c) {
+    const TileTensor t = c.t[blockIdx.y];
+    const int row = blockIdx.x, h = row % c.H, i = (row / c.H) % 64, nc = (row / (c.H * 64)) % c.NC, b = row / (c.H * 64 * c.NC);
+    const int words = t.row_bytes / 4, tok = nc * c.C + i;
+    const bool real = i < c.C && tok < c.T;
+    uint32_t *pad = reinterpret_cast<uint32_t *>(static_cast<char *>(t.padded) + (size_t)row * t.row_bytes);
+    uint32_t *full = reinterpret_cast<uint32_t *>(static_cast<char *>(const_cast<void *>(t.full)) +
+                                                  (((size_t)b * c.T + (real ? tok : 0)) * c.H + h) * t.row_bytes);
+    if (EXPAND) {
+        for (int x = threadIdx.x; x < words; x += 64) pad[x] = real ? full[x] : t.pad_word;
+    } else if (real) {
+        for (int x = threadIdx.x; x < words; x += 64) full[x] = pad[x];
+    }
+}
+
+} // namespace
+
+hipError_t launch_seq_tables(const SeqList &l, SeqEntry *seqs, ChunkEntry *chunks, hipStream_t s) {
+    if (l.n < 1) return hipSuccess;
+    if (l.n > kSeqsPerLaunch || l.first < 0 || l.H < 1 || !seqs || !chunks) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(seq_tables_kernel, dim3(l.n), dim3(64), 0, s, l, seqs, chunks);
+    return hipGetLastError();
+}
+
+hipError_t launch_chunk_copy(const ChunkCopy &c, bool expand, hipStream_t s) {
+    if (c.n < 1) return hipSuccess;
+    if (c.n > 12 || c.B < 1 || c.H < 1 || c.T < 1 || (c.C != 16 && c.C != 32) || c.NC != (c.T + c.C - 1) / c.C) return hipErrorInvalidValue;
+    for (int k = 0; k < c.n; ++k)
+        if (!c.t[k].full || !c.t[k].padded || c.t[k].row_bytes < 4 || c.t[k].row_bytes % 4) return hipErrorInvalidValue;
+    const long long rows = (long long)c.B * c.NC * 64 * c.H;
+    if (rows > 0x7fffffffLL) return hipErrorInvalidValue;
+    dim3 grid((unsigned)rows, c.n), block(64);
+    if (expand)
+        hipLaunchKernelGGL(chunk_copy_kernel<true>, grid, block, 0, s, c);
+    else
+        hipLaunchKernelGGL(chunk_copy_kernel<false>, grid, block, 0, s, c);
+    return hipGetLastError();
+}
+
+} // namespace mdn

@@ -111,3 +111,36 @@ def test_packed_prompts_with_final_states_of_every_sequence(dtype, d, lens):
         assert worst_err(host(f["o"])[:, sl], rf["o"]) <= tol, (i, "o")
         assert worst_err(host(f["S"])[i:i + 1], rf["S"]) <= tol, (i, "S")
         assert worst_err(host(f["M"])[i:i + 1], rf["M"]) <= tol, (i, "M")
+
+
+@pytest.mark.parametrize("dtype,n", [("f32", 229), ("bf16", 3)])
+def test_packed_states_in_and_out_of_many_short_and_of_uneven_sequences(dtype, n):
+    """More sequences than one launch's list of entries holds (lengths 1 to 4), and three sequences whose order of
+    dispatch (longest first) is not the caller's: states and their adjoints have to come back in the caller's order."""
+    d, H = 64, 1
+    lens = [1 + i % 4 for i in range(n)] if n > 3 else [65, 1, 130]
+    T = sum(lens)
+    w = synth.custom(B=1, T=T, H=H, dk=d, dv=d, dtype=dtype, seed=74, with_eta=True, backward=True)
+    t = to_dev(w)
+    cu = np.concatenate([[0], np.cumsum(lens)]).tolist()
+    rng = np.random.default_rng(4)
+    S0, M0, dSf = ((rng.standard_normal((n, H, d, d)) * 0.2).astype(np.float32) for _ in range(3))
+    dev = lambda a: torch.from_numpy(a).cuda()
+    x = tuple(t[k] for k in ("q", "k", "v", "beta", "alpha", "mu"))
+    f = binding.mdn_chunk_fwd_varlen(*x, cu, eta=t["eta"], S0=dev(S0), M0=dev(M0), scale=w.scale, save_vt=True)
+    g = binding.mdn_chunk_bwd_varlen(*x, f["vt"], t["dO"], cu, eta=t["eta"], S0=dev(S0), M0=dev(M0), dS_final=dev(dSf),
+                                     scale=w.scale, want_deta=True)
+    torch.cuda.synchronize()
+    a = {k: (None if v is None else v.astype(np.float64)) for k, v in w.arrays.items()}
+    ref = {k: [] for k in ("o", "S", "M", "dq", "dk", "dv", "dalpha", "dbeta", "dmu", "deta", "dS0", "dM0")}
+    for i in range(n):
+        q = [a[k][:, cu[i]:cu[i + 1]] for k in ("q", "k", "v", "alpha", "beta", "mu")]
+        kw = dict(eta=a["eta"][:, cu[i]:cu[i + 1]], S0=S0[i:i + 1].astype(np.float64), M0=M0[i:i + 1].astype(np.float64),
+                  scale=w.scale)
+        rf = orc.forward(*q, **kw)
+        rb = orc.backward(*q, a["dO"][:, cu[i]:cu[i + 1]], dS_T=dSf[i:i + 1].astype(np.float64), **kw)
+        for k in ref:
+            ref[k].append((rf if k in rf else rb)[k])
+    for k, parts in ref.items():
+        x = np.concatenate(parts, axis=0 if k in ("S", "M", "dS0", "dM0") else 1)
+        assert worst_err(host((f if k in f else g)[k]), x) <= TOL[dtype], k
