@@ -30,8 +30,9 @@ struct GateArgs {
 };
 
 __global__ __launch_bounds__(GT) void gates_fwd_kernel(GateArgs g, float *alpha, float *beta, float *mu, float *eta) {
-    for (long long i = (long long)blockIdx.x * GT + threadIdx.x; i < g.n; i += (long long)gridDim.x * GT) {
-        const int h = (int)(i % g.H);
+    const int dh = (int)((unsigned)(gridDim.x * GT) % (unsigned)g.H);
+    int h = (int)((blockIdx.x * GT + threadIdx.x) % (unsigned)g.H); // (carried along: a 64-bit remainder per element costs more than the rest)
+    for (long long i = (long long)blockIdx.x * GT + threadIdx.x; i < g.n; i += (long long)gridDim.x * GT, h += dh, h -= h >= g.H ? g.H : 0) {
         const float e = tanhf(g.xe[i] / g.tau) + 1.f, u = e * g.s, den = 1.f + u * u;
         eta[i] = e;
         alpha[i] = __expf(-g.a_alpha[h] * softplus_f(g.xa[i] + g.b_alpha[h])) / den;
@@ -41,15 +42,26 @@ __global__ __launch_bounds__(GT) void gates_fwd_kernel(GateArgs g, float *alpha,
 }
 
 // dpar: [4][H] = da_alpha, db_alpha, da_mu, db_mu (accumulated: the caller's launch sequence zeroes it first)
-__global__ __launch_bounds__(GT) void gates_bwd_kernel(GateArgs g, const float *dalpha, const float *dbeta, const float *dmu,
-                                                        const float *deta, float *dxa, float *dxm, float *dxb, float *dxe,
-                                                        float *dpar) {
+__global__ __launch_bounds__(1024) void gates_bwd_kernel(GateArgs g, const float *dalpha, const float *dbeta, const float *dmu,
+                                                         const float *deta, float *dxa, float *dxm, float *dxb, float *dxe,
+                                                         float *dpar) {
     extern __shared__ float s_par[]; // [4][H]
     const int lane = threadIdx.x & 63;
-    for (int c = threadIdx.x; c < 4 * g.H; c += GT) s_par[c] = 0.f;
+    for (int c = threadIdx.x; c < 4 * g.H; c += blockDim.x) s_par[c] = 0.f;
     __syncthreads();
-    for (long long i = (long long)blockIdx.x * GT + threadIdx.x; i < g.n; i += (long long)gridDim.x * GT) {
-        const int h = (int)(i % g.H);
+    const unsigned stride = gridDim.x * blockDim.x, i0 = blockIdx.x * blockDim.x + threadIdx.x;
+    const int dh = (int)(stride % (unsigned)g.H);
+    int h = (int)(i0 % (unsigned)g.H);
+    // A lane that keeps its head from trip to trip (H divides the stride) sums its parameter gradients in registers.
+    float p0 = 0.f, p1 = 0.f, p2 = 0.f, p3 = 0.f;
+    auto flush = [&]() {
+        atomicAdd(&s_par[0 * g.H + h], p0);
+        atomicAdd(&s_par[1 * g.H + h], p1);
+        atomicAdd(&s_par[2 * g.H + h], p2);
+        atomicAdd(&s_par[3 * g.H + h], p3);
+        p0 = p1 = p2 = p3 = 0.f;
+    };
+    for (long long i = i0; i < g.n; i += stride) {
         const float th = tanhf(g.xe[i] / g.tau), e = th + 1.f, u = e * g.s, den = 1.f + u * u;
         const float dmax = 2.f * u * g.s / (den * den); // d beta_max / d eta = - d alpha_max / d eta
         const float za = g.xa[i] + g.b_alpha[h], zm = g.xm[i] + g.b_mu[h];
@@ -64,32 +76,33 @@ __global__ __launch_bounds__(GT) void gates_bwd_kernel(GateArgs g, const float *
         dxm[i] = gxm;
         dxb[i] = db * (u * u / den) * sb * (1.f - sb);
         dxe[i] = (deta[i] - da * decay * dmax + db * sb * dmax) * (1.f - th * th) / g.tau;
-        if (dpar) {
-            // lanes 32 (16) apart hold the same head when H divides 32 (16): their contributions are summed across
-            // the wave's halves (rows) first, so that one lane per head and wave goes to the LDS atomics instead of four
-            // (a loop trip is taken by whole waves except in the last one, whose stragglers take the plain path)
-            float p0 = dfa * -spa, p1 = gxa, p2 = dfm * -spm, p3 = gxm;
-            const bool whole = i - lane + 63 < g.n;
-            int active = 64;
-            if (whole && 32 % g.H == 0) {
-                p0 = add_xor32(p0); p1 = add_xor32(p1); p2 = add_xor32(p2); p3 = add_xor32(p3);
-                active = 32;
-                if (16 % g.H == 0) {
-                    p0 = add_xor16(p0); p1 = add_xor16(p1); p2 = add_xor16(p2); p3 = add_xor16(p3);
-                    active = 16;
-                }
-            }
-            if (lane < active) {
-                atomicAdd(&s_par[0 * g.H + h], p0);
-                atomicAdd(&s_par[1 * g.H + h], p1);
-                atomicAdd(&s_par[2 * g.H + h], p2);
-                atomicAdd(&s_par[3 * g.H + h], p3);
+        p0 += dfa * -spa;
+        p1 += gxa;
+        p2 += dfm * -spm;
+        p3 += gxm;
+        if (dh != 0) {
+            if (dpar) flush();
+            h += dh;
+            h -= h >= g.H ? g.H : 0;
+        }
+    }
+    if (dpar && dh == 0) {
+        // lanes 32 (16) apart hold the same head when H divides 32 (16): their sums are added across the wave's halves
+        // (rows) first, so that one lane per head and wave goes to the LDS atomics instead of four
+        int active = 64;
+        if (32 % g.H == 0) {
+            p0 = add_xor32(p0); p1 = add_xor32(p1); p2 = add_xor32(p2); p3 = add_xor32(p3);
+            active = 32;
+            if (16 % g.H == 0) {
+                p0 = add_xor16(p0); p1 = add_xor16(p1); p2 = add_xor16(p2); p3 = add_xor16(p3);
+                active = 16;
             }
         }
+        if (lane < active) flush();
     }
     __syncthreads();
     if (dpar)
-        for (int c = threadIdx.x; c < 4 * g.H; c += GT) atomicAdd(&dpar[c], s_par[c]);
+        for (int c = threadIdx.x; c < 4 * g.H; c += blockDim.x) atomicAdd(&dpar[c], s_par[c]);
 }
 
 __global__ void gates_zero_kernel(float *p, int n) {
@@ -144,10 +157,11 @@ int mdn_gates_bwd(const mdn_gate_params *params, const float *x_alpha, const flo
     g.xa = x_alpha; g.xm = x_mu; g.xb = x_beta; g.xe = x_eta;
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (dparams) hipLaunchKernelGGL(gates_zero_kernel, dim3(1), dim3(256), 0, s, dparams, 4 * g.H);
-    // (with parameter gradients every workgroup ends in 4 H atomic adds on the same 4 H addresses, which the L2 takes one
-    //  after the other: few workgroups with many tokens each)
-    const int wgs = dparams ? (grid_for(g.n) < 256 ? grid_for(g.n) : 256) : grid_for(g.n);
-    hipLaunchKernelGGL(gates_bwd_kernel, dim3(wgs), dim3(GT), 4 * g.H * sizeof(float), s, g, dalpha, dbeta, dmu,
+    // With parameter gradients every workgroup ends in 4 H atomic adds on the same 4 H addresses, which are taken one
+    // after the other (~20 ns each): workgroups of 1 024 threads, at most 128 of them.
+    const long long big = (g.n + 1023) / 1024;
+    const int block = dparams && big >= 16 ? 1024 : GT, wgs = block == GT ? grid_for(g.n) : (int)(big < 128 ? big : 128);
+    hipLaunchKernelGGL(gates_bwd_kernel, dim3(wgs), dim3(block), 4 * g.H * sizeof(float), s, g, dalpha, dbeta, dmu,
                        deta, dx_alpha, dx_mu, dx_beta, dx_eta, dparams);
     return hipGetLastError() == hipSuccess ? MDN_OK : MDN_ERR_LAUNCH;
 }

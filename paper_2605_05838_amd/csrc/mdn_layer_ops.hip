@@ -3,11 +3,18 @@
 //     q' = SiLU(x_q),  k' = SiLU(x_k),  v = SiLU(x_v);   q = L2Norm(q' - d_h k')  (output correction, before the
 //     normalisation);   k = L2Norm(k');   L2Norm(x) = x / sqrt(sum x^2 + eps)
 // Back end:  y = sigmoid(g) * w * o / sqrt(mean(o^2) + eps)   (head-wise RMS norm with one weight vector, output gate).
-// One wave per (token, head) row, a lane holds d/64 elements; the row sums are wave reductions.  HBM-bound streaming
-// (arithmetic in fp32, tensors in the storage dtype).  Parameter gradients (dd [H], dw [dv]) are summed per workgroup
-// in LDS, then added with one floating-point atomic per entry and workgroup.
+// Streaming kernels (arithmetic in fp32, tensors in the storage dtype): a lane holds 8 consecutive elements of a row, so
+// that every access is 16 bytes (two for 32-bit storage) and a row sum is 3 or 4 lane exchanges.  With 4 bytes per lane and
+// a row per wave the adjoints were bound by the vector unit: IEEE divisions in the sigmoids, row sums over 64 lanes and
+// the 64-bit remainder of the row index took ~60 instructions per element.  At 131 072 rows of 128 bf16 elements
+// (B = 4, T = 2 048, H = 16), before -> now: front end forward 47 -> 37 us, adjoint 75 -> 52 us; back end forward 25 -> 22 us,
+// adjoint 57 -> 32 us (4.9 to 5.9 TB/s; a large device copy reaches 5.1).
+// Parameter gradients (dd [H], dw [dv]) are summed per workgroup in LDS, then added with one floating-point atomic per
+// entry and workgroup.  Those kernels run at most one workgroup of 1 024 threads per CU: atomics of several dies on one
+// address are taken one after the other, ~20 ns each.
 #include "../../include/mdn.h"
 #include "mdn_device.h"
+#include "mdn_kernels.h"
 
 #include <hip/hip_runtime.h>
 
@@ -15,184 +22,242 @@ namespace mdn {
 
 namespace {
 
-constexpr int LT = 256; // 4 rows per workgroup
+constexpr int LT = 256; // threads of the kernels without parameter gradients
 
-__device__ __forceinline__ float sigm(float x) { return 1.f / (1.f + __expf(-x)); }
-__device__ __forceinline__ float silu(float x) { return x * sigm(x); }
-__device__ __forceinline__ float dsilu(float x) {
-    const float s = sigm(x);
-    return s * (1.f + x * (1.f - s));
+// sigmoid; 16-bit storage: the reciprocal instruction (1 ulp of fp32, far below the rounding of the result)
+template <typename T> __device__ __forceinline__ float sigm(float x) {
+    const float d = 1.f + __expf(-x);
+    if constexpr (sizeof(T) == 2) return __builtin_amdgcn_rcpf(d);
+    else return 1.f / d;
 }
 
-template <typename T, int D> struct Row { // the D/64 elements of a row that this lane holds
-    static constexpr int E = D / 64;
+// This lane's 8 elements of a row of D: D / 8 lanes hold a row, 512 / D rows a wave.
+template <typename T, int D> struct Row {
+    static constexpr int E = 8, LPR = D / E, RPW = 64 / LPR;
     float v[E];
-    __device__ __forceinline__ void load(const T *p, int lane) {
+    __device__ __forceinline__ void load(const T *p) {
+        if constexpr (sizeof(T) == 2) {
+            const bf16x8 x = *reinterpret_cast<const bf16x8 *>(p);
 #pragma unroll
-        for (int e = 0; e < E; ++e) v[e] = to_f32(p[lane * E + e]);
+            for (int e = 0; e < E; ++e) v[e] = (float)x[e];
+        } else {
+            const f32x4 a = *reinterpret_cast<const f32x4 *>(p), b = *reinterpret_cast<const f32x4 *>(p + 4);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = a[e], v[4 + e] = b[e];
+        }
     }
-    __device__ __forceinline__ void store(T *p, int lane) const {
+    __device__ __forceinline__ void store(T *p) const {
+        if constexpr (sizeof(T) == 2) {
+            bf16x8 x;
 #pragma unroll
-        for (int e = 0; e < E; ++e) p[lane * E + e] = from_f32<T>(v[e]);
+            for (int e = 0; e < E; ++e) x[e] = (bf16_t)v[e];
+            *reinterpret_cast<bf16x8 *>(p) = x;
+        } else {
+            *reinterpret_cast<f32x4 *>(p) = f32x4{v[0], v[1], v[2], v[3]};
+            *reinterpret_cast<f32x4 *>(p + 4) = f32x4{v[4], v[5], v[6], v[7]};
+        }
+    }
+    // sum of x over the lanes of a row, in every one of them
+    static __device__ __forceinline__ float row_sum(float x) {
+        if constexpr (LPR == 16) {
+            return reduce16(x);
+        } else {
+            static_assert(LPR == 8, "rows of 64 or 128 elements");
+            x += dpp_move<0xB1>(x);         // quad_perm [1,0,3,2]
+            x += dpp_move<0x4E>(x);         // quad_perm [2,3,0,1]
+            return x + dpp_move<0x141>(x);  // row_half_mirror: the other quad of the 8 lanes
+        }
     }
 };
 
 struct LayerDims {
-    long long rows; // B*T*H
+    unsigned rows; // B*T*H
     int H;
 };
 
-template <typename T, int DK, int DV>
+// The rows of one lane: row0, row0 + step, ... and their heads (row % H, carried along).
+struct RowWalk {
+    unsigned row, step;
+    int h, dh;
+    __device__ __forceinline__ RowWalk(const LayerDims &d, int rows_per_wave, int lanes_per_row) {
+        const unsigned waves = blockDim.x >> 6;
+        row = (blockIdx.x * waves + wave_id()) * rows_per_wave + lane_id() / lanes_per_row;
+        step = gridDim.x * waves * rows_per_wave;
+        h = (int)(row % (unsigned)d.H);
+        dh = (int)(step % (unsigned)d.H);
+    }
+    __device__ __forceinline__ void next(const LayerDims &d) {
+        row += step;
+        h += dh;
+        h = h >= d.H ? h - d.H : h;
+    }
+};
+
+template <typename T, int D>
 __global__ __launch_bounds__(LT) void frontend_fwd_kernel(LayerDims d, const T *xq, const T *xk, const T *xv, const float *dh,
                                                            float eps, T *q, T *k, T *v) {
-    const int lane = lane_id();
-    for (long long row = (long long)blockIdx.x * 4 + wave_id(); row < d.rows; row += (long long)gridDim.x * 4) {
-        const float dc = dh[row % d.H];
-        Row<T, DK> a, b;
-        Row<T, DV> c;
-        a.load(xq + row * DK, lane);
-        b.load(xk + row * DK, lane);
-        c.load(xv + row * DV, lane);
+    typedef Row<T, D> R;
+    for (RowWalk w(d, R::RPW, R::LPR); w.row < d.rows; w.next(d)) {
+        const size_t o = (size_t)w.row * D + (lane_id() % R::LPR) * R::E;
+        R a, b, c;
+        a.load(xq + o);
+        b.load(xk + o);
+        c.load(xv + o);
+        const float dc = dh[w.h];
         float sq = 0.f, sk = 0.f;
 #pragma unroll
-        for (int e = 0; e < Row<T, DK>::E; ++e) {
-            b.v[e] = silu(b.v[e]);
-            a.v[e] = silu(a.v[e]) - dc * b.v[e];
+        for (int e = 0; e < R::E; ++e) {
+            b.v[e] *= sigm<T>(b.v[e]);
+            a.v[e] = a.v[e] * sigm<T>(a.v[e]) - dc * b.v[e];
             sq += a.v[e] * a.v[e];
             sk += b.v[e] * b.v[e];
         }
-        const float iq = rsqrtf(reduce64(sq) + eps), ik = rsqrtf(reduce64(sk) + eps);
+        const float iq = rsqrtf(R::row_sum(sq) + eps), ik = rsqrtf(R::row_sum(sk) + eps);
 #pragma unroll
-        for (int e = 0; e < Row<T, DK>::E; ++e) {
+        for (int e = 0; e < R::E; ++e) {
             a.v[e] *= iq;
             b.v[e] *= ik;
+            c.v[e] *= sigm<T>(c.v[e]);
         }
-#pragma unroll
-        for (int e = 0; e < Row<T, DV>::E; ++e) c.v[e] = silu(c.v[e]);
-        a.store(q + row * DK, lane);
-        b.store(k + row * DK, lane);
-        c.store(v + row * DV, lane);
+        a.store(q + o);
+        b.store(k + o);
+        c.store(v + o);
     }
 }
 
-template <typename T, int DK, int DV>
-__global__ __launch_bounds__(LT) void frontend_bwd_kernel(LayerDims d, const T *xq, const T *xk, const T *xv, const float *dh,
-                                                           float eps, const T *dq, const T *dk, const T *dv, T *dxq, T *dxk,
-                                                           T *dxv, float *dd) {
+template <typename T, int D>
+__global__ __launch_bounds__(1024) void frontend_bwd_kernel(LayerDims d, const T *xq, const T *xk, const T *xv, const float *dh,
+                                                             float eps, const T *dq, const T *dk, const T *dv, T *dxq, T *dxk,
+                                                             T *dxv, float *dd) {
+    typedef Row<T, D> R;
     extern __shared__ float s_dd[]; // [H]
-    for (int c = threadIdx.x; c < d.H; c += LT) s_dd[c] = 0.f;
+    for (int c = threadIdx.x; c < d.H; c += blockDim.x) s_dd[c] = 0.f;
     __syncthreads();
-    const int lane = lane_id();
-    for (long long row = (long long)blockIdx.x * 4 + wave_id(); row < d.rows; row += (long long)gridDim.x * 4) {
-        const int h = (int)(row % d.H);
-        const float dc = dh[h];
-        Row<T, DK> a, b, ga, gb;
-        Row<T, DV> c, gc;
-        a.load(xq + row * DK, lane);
-        b.load(xk + row * DK, lane);
-        c.load(xv + row * DV, lane);
-        ga.load(dq + row * DK, lane);
-        gb.load(dk + row * DK, lane);
-        gc.load(dv + row * DV, lane);
-        float qc[Row<T, DK>::E], ks[Row<T, DK>::E], sq = 0.f, sk = 0.f;
+    for (RowWalk w(d, R::RPW, R::LPR); w.row < d.rows; w.next(d)) {
+        const size_t o = (size_t)w.row * D + (lane_id() % R::LPR) * R::E;
+        R a, b, c, ga, gb, gc;
+        a.load(xq + o);
+        b.load(xk + o);
+        ga.load(dq + o);
+        gb.load(dk + o);
+        c.load(xv + o);
+        gc.load(dv + o);
+        const float dc = dh[w.h];
+        // SiLU(x) = x s, SiLU'(x) = s (1 + x (1 - s)): the derivatives replace the inputs
+        float qc[R::E], ks[R::E], sq = 0.f, sk = 0.f;
 #pragma unroll
-        for (int e = 0; e < Row<T, DK>::E; ++e) {
-            ks[e] = silu(b.v[e]);
-            qc[e] = silu(a.v[e]) - dc * ks[e];
+        for (int e = 0; e < R::E; ++e) {
+            const float sa = sigm<T>(a.v[e]), sb = sigm<T>(b.v[e]);
+            ks[e] = b.v[e] * sb;
+            qc[e] = a.v[e] * sa - dc * ks[e];
+            a.v[e] = sa * (1.f + a.v[e] * (1.f - sa));
+            b.v[e] = sb * (1.f + b.v[e] * (1.f - sb));
             sq += qc[e] * qc[e];
             sk += ks[e] * ks[e];
         }
-        const float iq = rsqrtf(reduce64(sq) + eps), ik = rsqrtf(reduce64(sk) + eps);
+        const float iq = rsqrtf(R::row_sum(sq) + eps), ik = rsqrtf(R::row_sum(sk) + eps);
         float dotq = 0.f, dotk = 0.f;
 #pragma unroll
-        for (int e = 0; e < Row<T, DK>::E; ++e) {
-            dotq += qc[e] * iq * ga.v[e];
-            dotk += ks[e] * ik * gb.v[e];
+        for (int e = 0; e < R::E; ++e) {
+            qc[e] *= iq;
+            dotq += qc[e] * ga.v[e];
+            dotk += ks[e] * gb.v[e];
         }
-        dotq = reduce64(dotq);
-        dotk = reduce64(dotk);
+        dotq = R::row_sum(dotq);
+        dotk = R::row_sum(dotk) * ik * ik;
         float ddp = 0.f;
 #pragma unroll
-        for (int e = 0; e < Row<T, DK>::E; ++e) {
-            const float dqc = (ga.v[e] - qc[e] * iq * dotq) * iq; // through the L2 norm of q' - d k'
-            const float dks = (gb.v[e] - ks[e] * ik * dotk) * ik - dc * dqc;
+        for (int e = 0; e < R::E; ++e) {
+            const float dqc = (ga.v[e] - qc[e] * dotq) * iq; // through the L2 norm of q' - d k'
+            const float dks = (gb.v[e] - ks[e] * dotk) * ik - dc * dqc;
             ddp -= dqc * ks[e];
-            a.v[e] = dqc * dsilu(a.v[e]);
-            b.v[e] = dks * dsilu(b.v[e]);
+            a.v[e] *= dqc;
+            b.v[e] *= dks;
+            const float sc = sigm<T>(c.v[e]);
+            c.v[e] = gc.v[e] * (sc * (1.f + c.v[e] * (1.f - sc)));
         }
-#pragma unroll
-        for (int e = 0; e < Row<T, DV>::E; ++e) c.v[e] = gc.v[e] * dsilu(c.v[e]);
-        a.store(dxq + row * DK, lane);
-        b.store(dxk + row * DK, lane);
-        c.store(dxv + row * DV, lane);
+        a.store(dxq + o);
+        b.store(dxk + o);
+        c.store(dxv + o);
         if (dd) {
-            ddp = reduce64(ddp);
-            if (lane == 0) atomicAdd(&s_dd[h], ddp);
+            ddp = R::row_sum(ddp);
+            if (lane_id() % R::LPR == 0) atomicAdd(&s_dd[w.h], ddp);
         }
     }
     __syncthreads();
     if (dd)
-        for (int c = threadIdx.x; c < d.H; c += LT) atomicAdd(&dd[c], s_dd[c]);
+        for (int c = threadIdx.x; c < d.H; c += blockDim.x) atomicAdd(&dd[c], s_dd[c]);
 }
 
-template <typename T, int DV>
+template <typename T, int D>
 __global__ __launch_bounds__(LT) void epilogue_fwd_kernel(LayerDims d, const T *o, const T *g, const float *w, float eps, T *y) {
-    const int lane = lane_id();
-    for (long long row = (long long)blockIdx.x * 4 + wave_id(); row < d.rows; row += (long long)gridDim.x * 4) {
-        Row<T, DV> a, b;
-        a.load(o + row * DV, lane);
-        b.load(g + row * DV, lane);
+    typedef Row<T, D> R;
+    Row<float, D> wr;
+    wr.load(w + (lane_id() % R::LPR) * R::E);
+    for (RowWalk k(d, R::RPW, R::LPR); k.row < d.rows; k.next(d)) {
+        const size_t off = (size_t)k.row * D + (lane_id() % R::LPR) * R::E;
+        R a, b;
+        a.load(o + off);
+        b.load(g + off);
         float ss = 0.f;
 #pragma unroll
-        for (int e = 0; e < Row<T, DV>::E; ++e) ss += a.v[e] * a.v[e];
-        const float ir = rsqrtf(reduce64(ss) * (1.f / DV) + eps);
+        for (int e = 0; e < R::E; ++e) ss += a.v[e] * a.v[e];
+        const float ir = rsqrtf(R::row_sum(ss) * (1.f / D) + eps);
 #pragma unroll
-        for (int e = 0; e < Row<T, DV>::E; ++e) a.v[e] = sigm(b.v[e]) * w[lane * Row<T, DV>::E + e] * a.v[e] * ir;
-        a.store(y + row * DV, lane);
+        for (int e = 0; e < R::E; ++e) a.v[e] = sigm<T>(b.v[e]) * wr.v[e] * a.v[e] * ir;
+        a.store(y + off);
     }
 }
 
-template <typename T, int DV>
-__global__ __launch_bounds__(LT) void epilogue_bwd_kernel(LayerDims d, const T *o, const T *g, const float *w, float eps,
-                                                           const T *dy, T *dout, T *dg, float *dw) {
-    __shared__ float s_dw[DV];
-    for (int c = threadIdx.x; c < DV; c += LT) s_dw[c] = 0.f;
+template <typename T, int D>
+__global__ __launch_bounds__(1024) void epilogue_bwd_kernel(LayerDims d, const T *o, const T *g, const float *w, float eps,
+                                                             const T *dy, T *dout, T *dg, float *dw) {
+    typedef Row<T, D> R;
+    __shared__ float s_dw[D];
+    for (int c = threadIdx.x; c < D; c += blockDim.x) s_dw[c] = 0.f;
     __syncthreads();
-    const int lane = lane_id();
-    constexpr int E = Row<T, DV>::E;
-    float dwp[E];
+    const int col = (lane_id() % R::LPR) * R::E;
+    Row<float, D> wr;
+    wr.load(w + col);
+    float dwp[R::E];
 #pragma unroll
-    for (int e = 0; e < E; ++e) dwp[e] = 0.f;
-    for (long long row = (long long)blockIdx.x * 4 + wave_id(); row < d.rows; row += (long long)gridDim.x * 4) {
-        Row<T, DV> a, b, c;
-        a.load(o + row * DV, lane);
-        b.load(g + row * DV, lane);
-        c.load(dy + row * DV, lane);
+    for (int e = 0; e < R::E; ++e) dwp[e] = 0.f;
+    for (RowWalk k(d, R::RPW, R::LPR); k.row < d.rows; k.next(d)) {
+        const size_t off = (size_t)k.row * D + col;
+        R a, b, c;
+        a.load(o + off);
+        b.load(g + off);
+        c.load(dy + off);
         float ss = 0.f;
 #pragma unroll
-        for (int e = 0; e < E; ++e) ss += a.v[e] * a.v[e];
-        const float ir = rsqrtf(reduce64(ss) * (1.f / DV) + eps);
-        float n[E], dn[E], dot = 0.f;
+        for (int e = 0; e < R::E; ++e) ss += a.v[e] * a.v[e];
+        const float ir = rsqrtf(R::row_sum(ss) * (1.f / D) + eps);
+        float dn[R::E], dot = 0.f;
 #pragma unroll
-        for (int e = 0; e < E; ++e) {
-            const float sg = sigm(b.v[e]), we = w[lane * E + e];
-            n[e] = a.v[e] * ir;
-            dn[e] = c.v[e] * sg * we;
-            dot += n[e] * dn[e];
-            dwp[e] += c.v[e] * sg * n[e];
-            b.v[e] = c.v[e] * we * n[e] * sg * (1.f - sg);
+        for (int e = 0; e < R::E; ++e) {
+            const float sg = sigm<T>(b.v[e]), t = c.v[e] * sg;
+            a.v[e] *= ir; // normalised output
+            dn[e] = t * wr.v[e];
+            dot += a.v[e] * dn[e];
+            dwp[e] += t * a.v[e];
+            b.v[e] = dn[e] * a.v[e] * (1.f - sg);
         }
-        dot = reduce64(dot) * (1.f / DV);
+        dot = R::row_sum(dot) * (1.f / D);
 #pragma unroll
-        for (int e = 0; e < E; ++e) a.v[e] = (dn[e] - n[e] * dot) * ir;
-        a.store(dout + row * DV, lane);
-        b.store(dg + row * DV, lane);
+        for (int e = 0; e < R::E; ++e) a.v[e] = (dn[e] - a.v[e] * dot) * ir;
+        a.store(dout + off);
+        b.store(dg + off);
     }
     if (dw) {
+        // the rows of a wave first (lanes with the same columns), then the waves in LDS
 #pragma unroll
-        for (int e = 0; e < E; ++e) atomicAdd(&s_dw[lane * E + e], dwp[e]);
+        for (int e = 0; e < R::E; ++e) {
+            if (R::LPR == 8) dwp[e] += dpp_move<0x128>(dwp[e]); // row_ror 8
+            dwp[e] = add_xor32(add_xor16(dwp[e]));
+            if (lane_id() < R::LPR) atomicAdd(&s_dw[col + e], dwp[e]);
+        }
         __syncthreads();
-        for (int c = threadIdx.x; c < DV; c += LT) atomicAdd(&dw[c], s_dw[c]);
+        for (int c = threadIdx.x; c < D; c += blockDim.x) atomicAdd(&dw[c], s_dw[c]);
     }
 }
 
@@ -205,16 +270,25 @@ int check(const mdn_shape *s, LayerDims *d) {
     if (s->dtype != MDN_DTYPE_BF16 && s->dtype != MDN_DTYPE_F32) return MDN_ERR_DTYPE;
     if (s->B < 1 || s->T < 1 || s->H < 1 || s->H > 4096) return MDN_ERR_SHAPE;
     if (!((s->dk == 64 && s->dv == 64) || (s->dk == 128 && s->dv == 128))) return MDN_ERR_SHAPE;
-    d->rows = (long long)s->B * s->T * s->H;
+    const long long rows = (long long)s->B * s->T * s->H;
+    if (rows > 0x7fffffffLL) return MDN_ERR_SHAPE; // (more than 288 GB of tensors)
+    d->rows = (unsigned)rows;
     d->H = s->H;
     return MDN_OK;
 }
 
-// workgroups of a row-streaming launch; kernels that end with atomic adds on a parameter gradient take a lower cap
-// (every workgroup adds to the same few addresses: 8192 workgroups x 128 adds ran the back end's adjoint at 1.5 TB/s)
-int grid_for(long long rows, int cap = 8192) {
-    const long long b = (rows + 3) / 4;
-    return (int)(b < cap ? b : cap);
+// launch shape of a row-streaming kernel: workgroups of 256 threads, at most 32 per CU
+struct Launch { int grid, block; };
+Launch stream_launch(unsigned rows, int dim) {
+    const unsigned per = (unsigned)(LT / 64 * (512 / dim)), need = (rows + per - 1) / per, most = 32u * (unsigned)num_cus();
+    return Launch{(int)(need < most ? need : most), LT};
+}
+// the same for a kernel that ends in atomic adds on a few addresses: one workgroup per CU at most, of 1 024 threads once
+// there are rows enough to give every CU one (below that, smaller workgroups reach more CUs)
+Launch reduce_launch(unsigned rows, int dim) {
+    const unsigned rpw = (unsigned)(512 / dim), cus = (unsigned)num_cus();
+    const unsigned waves = rows >= cus * 16u * rpw ? 16u : 4u, need = (rows + waves * rpw - 1) / (waves * rpw);
+    return Launch{(int)(need < cus ? need : cus), (int)waves * 64};
 }
 
 int status() { return hipGetLastError() == hipSuccess ? MDN_OK : MDN_ERR_LAUNCH; }
@@ -244,7 +318,8 @@ int mdn_frontend_fwd(const mdn_shape *shape, const void *x_q, const void *x_k, c
     return dispatch(shape, [&](auto t, auto dim) {
         typedef decltype(t) T;
         constexpr int D = decltype(dim)::value;
-        hipLaunchKernelGGL((frontend_fwd_kernel<T, D, D>), dim3(grid_for(ld.rows)), dim3(LT), 0, s, ld,
+        const Launch l = stream_launch(ld.rows, D);
+        hipLaunchKernelGGL((frontend_fwd_kernel<T, D>), dim3(l.grid), dim3(l.block), 0, s, ld,
                            static_cast<const T *>(x_q), static_cast<const T *>(x_k), static_cast<const T *>(x_v), d, eps,
                            static_cast<T *>(q), static_cast<T *>(k), static_cast<T *>(v));
         return status();
@@ -263,7 +338,8 @@ int mdn_frontend_bwd(const mdn_shape *shape, const void *x_q, const void *x_k, c
     return dispatch(shape, [&](auto t, auto dim) {
         typedef decltype(t) T;
         constexpr int D = decltype(dim)::value;
-        hipLaunchKernelGGL((frontend_bwd_kernel<T, D, D>), dim3(grid_for(ld.rows, 2048)), dim3(LT), ld.H * sizeof(float), s, ld,
+        const Launch l = reduce_launch(ld.rows, D);
+        hipLaunchKernelGGL((frontend_bwd_kernel<T, D>), dim3(l.grid), dim3(l.block), ld.H * sizeof(float), s, ld,
                            static_cast<const T *>(x_q), static_cast<const T *>(x_k), static_cast<const T *>(x_v), d, eps,
                            static_cast<const T *>(dq), static_cast<const T *>(dk), static_cast<const T *>(dv),
                            static_cast<T *>(dx_q), static_cast<T *>(dx_k), static_cast<T *>(dx_v), dd);
@@ -280,7 +356,8 @@ int mdn_epilogue_fwd(const mdn_shape *shape, const void *o, const void *g, const
     return dispatch(shape, [&](auto t, auto dim) {
         typedef decltype(t) T;
         constexpr int D = decltype(dim)::value;
-        hipLaunchKernelGGL((epilogue_fwd_kernel<T, D>), dim3(grid_for(ld.rows)), dim3(LT), 0, s, ld, static_cast<const T *>(o),
+        const Launch l = stream_launch(ld.rows, D);
+        hipLaunchKernelGGL((epilogue_fwd_kernel<T, D>), dim3(l.grid), dim3(l.block), 0, s, ld, static_cast<const T *>(o),
                            static_cast<const T *>(g), w, eps, static_cast<T *>(y));
         return status();
     });
@@ -297,7 +374,8 @@ int mdn_epilogue_bwd(const mdn_shape *shape, const void *o, const void *g, const
     return dispatch(shape, [&](auto t, auto dim) {
         typedef decltype(t) T;
         constexpr int D = decltype(dim)::value;
-        hipLaunchKernelGGL((epilogue_bwd_kernel<T, D>), dim3(grid_for(ld.rows, 1024)), dim3(LT), 0, s, ld, static_cast<const T *>(o),
+        const Launch l = reduce_launch(ld.rows, D);
+        hipLaunchKernelGGL((epilogue_bwd_kernel<T, D>), dim3(l.grid), dim3(l.block), 0, s, ld, static_cast<const T *>(o),
                            static_cast<const T *>(g), w, eps, static_cast<const T *>(dy), static_cast<T *>(d_o),
                            static_cast<T *>(dg), dw);
         return status();
