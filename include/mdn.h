@@ -36,12 +36,12 @@
  *     beyond rounding).  The packed variable-length calls take C = 64 only.
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).  All work is
  *     ordered after what the stream already holds and is complete when the stream reaches the
- *     end of the call; no call synchronises.  When the serial scans would leave at least half
- *     of the GPU idle (few batch*head pairs, many chunks) mdn_chunk_fwd / mdn_chunk_bwd split
- *     the sequence into segments and run the chunk-parallel kernel of one segment beside the
+ *     end of the call; no call synchronises.  When the serial scan would leave at least half
+ *     of the GPU idle (few batch*head pairs, many chunks) mdn_chunk_bwd splits
+ *     the sequence into segments and runs the chunk-parallel kernel of one segment beside the
  *     scan of its neighbour on a second stream that the library creates once per device
  *     (default priority) and joins back into `stream` with events, also when a launch fails on the
- *     way; see mdn_set_segments().
+ *     way; mdn_chunk_fwd does so when mdn_set_segments() asks for it.
  *   - Return value: MDN_OK (0) or a negative MDN_ERR_* code; nothing is launched when an
  *     error is returned from validation.  NaN/Inf in the inputs propagate, they are not detected.
  *   - No environment variable or other hidden setting influences a call.

@@ -139,27 +139,35 @@ template <typename F> int timed(int id, hipStream_t s, F &&launch) {
     return r0 && r1 ? rc : MDN_ERR_LAUNCH;
 }
 
-// ---- splitting a call into segments of the sequence.  When the serial scans occupy at most half of the CUs
-// (few (batch, head) pairs, long sequences), the chunk-parallel kernel of segment i+1 (forward) or of segment
-// i (backward) runs beside the scan of the neighbouring segment, on a second stream of the library's own:
-// the scan's workgroups leave the other CUs to it.  States cross a segment boundary through two small fp32
-// buffers in the workspace.
+// ---- splitting a backward call into segments of the sequence.  When the serial reverse scan occupies at most half of
+// the CUs (few (batch, head) pairs, long sequences), the gradient kernel of segment i runs beside the scan of segment
+// i-1, on a second stream of the library's own: the scan's workgroups leave the other CUs to it.  Adjoints cross a
+// segment boundary through two small fp32 buffers in the workspace.  The forward is split on request only: its
+// chunk-local kernel takes a twentieth to a seventh of the scan's time, less than the boundaries cost.
 std::atomic<int> g_segments{0}; // 0: automatic
 
 // the serial scans of a call would occupy at most half of the CUs
 bool few_scan_workgroups(const Dims &d) { return 2 * scan_workgroups(d) <= num_cus(); }
 
-int segments(const Dims &d) {
-    int k;
+// A boundary costs ~10 us (an event pair, the scan's start and its drain) and a segment hides its gradient launch, ~50 us
+// per 1 024 chunk blocks of d = 128: one segment per 1 024.  Backward in us, unsplit / 2 / 4 / 8 segments, d = 128:
+//   blocks  1 024 (16 heads, T =  4 096):   168 /   178 /   185 /   217
+//   blocks  2 048 (16 heads, T =  8 192):   357 /   343 /   345 /   372     (4 heads, T = 32 768: 978 / 965 / 968 / 1 000)
+//   blocks  4 096 (16 heads, T = 16 384):   707 /   651 /   626 /   650
+//   blocks  8 192 (16 heads, T = 32 768): 1 448 / 1 281 / 1 205 / 1 189
+// and 192 / 189 / 190 / 211 for 2 048 blocks of d = 64.  32-bit storage takes four times as long per block (512 blocks, 8
+// heads: 462 / 427 / 440 / 615; 2 048 of d = 64, 4 heads: 1 751 / 1 668 / 1 633 / 1 641); segments of fewer than 32 chunks
+// are all start and drain (512 blocks in 32 chunks of 16 heads: 304 / 315 / 352 / 594).  Forward: 271 / 289 / 299 / 328 for the second row, 1 159 / 1 190 /
+// 1 194 / 1 232 for the last, and slower split than unsplit at every other size measured.
+int segments(const Dims &d, bool backward) {
     if (t_no_alloc || d.seqs) return 1; // (packed batches: the scans of the sequences run beside each other)
-    const int forced = g_segments.load(std::memory_order_relaxed);
-    if (forced > 0) {
-        k = forced;
-    } else {
-        k = (few_scan_workgroups(d) && d.N >= 32) ? 4 : 1;
+    long long k = g_segments.load(std::memory_order_relaxed);
+    if (k <= 0) {
+        const long long grad = (long long)d.N * d.BH * d.dk * (d.dtype == MDN_DTYPE_F32 ? 4 : 1); // its time, in 1/128 blocks
+        k = backward && few_scan_workgroups(d) ? std::min({8LL, d.N / 32LL, grad / (128 * 1024)}) : 1;
     }
-    if (k > d.N / 4) k = d.N / 4;
-    return k < 1 ? 1 : (k > 16 ? 16 : k);
+    k = std::min(k, (long long)d.N / 4);
+    return (int)std::max(1LL, std::min(16LL, k));
 }
 
 // The library's second stream and its events, one set per device, shared by every call on that device.  A call that
@@ -225,7 +233,7 @@ int run_fwd(const Dims &d, const FwdCall &c, const FwdWs &w, hipStream_t s) {
     // K^T for this forward alone: not written if its scan forms K^T out of the k rows itself
     if (!c.operands_saved && !scan_fwd_reads_KT(d)) ia.KT = nullptr, sa.KT = nullptr;
     const int mode = c.operands_saved ? 2 : 0;
-    const int nseg = segments(d);
+    const int nseg = segments(d, false);
     if (nseg == 1) {
         rc = timed(MDN_KERNEL_INTRA_FWD, s, [&] { return launch_intra(d, mode, ia, s); });
         if (rc) return rc;
@@ -320,7 +328,7 @@ int bwd_run(const Dims &d, const BwdCall &c, const BwdWs &w, const Prepared &p, 
     ga.states = p.states; ga.dstates = w.dstates;
     ga.states_lo = precise ? w.states_lo : nullptr; ga.dstates_lo = precise ? w.dstates_lo : nullptr;
     ga.dq = c.dq; ga.dk = c.dk; ga.dalpha = c.dalpha; ga.dbeta = c.dbeta; ga.dmu = c.dmu; ga.deta = c.deta;
-    const int nseg = segments(d);
+    const int nseg = segments(d, true);
     if (nseg == 1) {
         rc = timed(MDN_KERNEL_SCAN_BWD, s, [&] { return launch_scan_bwd(d, sb, s); });
         if (rc) return rc;

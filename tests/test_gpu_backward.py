@@ -124,6 +124,27 @@ def test_split_into_segments_on_two_streams_equals_the_unsplit_call(dtype, d, T,
     for name in ("dq", "dk", "dv", "dalpha", "dbeta", "dmu", "deta", "dS0", "dM0"):
         assert torch.equal(g1[name], g2[name]), name
 
+# the smallest backward that splits by itself, and the same one chunk short of it (16-bit: 1 024 chunk blocks of 128 per
+# segment; 32-bit: 256)
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,H,d,T", [("bf16", 8, 128, 16384), ("bf16", 8, 128, 16320), ("f32", 8, 64, 8192)])
+def test_the_automatic_split_of_a_backward_equals_the_unsplit_call(dtype, H, d, T):
+    import torch
+    w = synth.custom(B=1, T=T, H=H, dk=d, dv=d, dtype=dtype, seed=37, backward=True)
+    t = to_dev(w)
+    x = [t[n] for n in ("q", "k", "v", "beta", "alpha", "mu")]
+    f = binding.mdn_chunk_fwd(*x, scale=w.scale, save_vt=True, save_states=True, save_operands=True)
+    g = []
+    for k in (1, 0):
+        old = binding.set_segments(k)
+        try:
+            g.append(binding.mdn_chunk_bwd(*x, f["vt"], t["dO"], states=f["states"], operands=f["operands"], scale=w.scale))
+            torch.cuda.synchronize()
+        finally:
+            binding.set_segments(old)
+    for name in ("dq", "dk", "dv", "dalpha", "dbeta", "dmu", "dS0", "dM0"):
+        assert torch.equal(g[0][name], g[1][name]), name
+
 
 @pytest.mark.parametrize("dtype,d,T,keep_states,keep_operands",
                          [("f32", 64, 200, False, False), ("bf16", 128, 200, True, True), ("f32", 128, 40, False, False),
