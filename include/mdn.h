@@ -160,9 +160,12 @@ int mdn_chunk_bwd(const mdn_shape *shape, const void *q, const void *k, const vo
  * sequences lie one after another along T of [1, T, H, *] tensors, sequence i being the tokens
  * [cu_seqlens[i], cu_seqlens[i+1]); cu_seqlens is a HOST array of n_seq + 1 increasing offsets with cu_seqlens[0] = 0
  * and cu_seqlens[n_seq] = shape.T; shape.B must be 1.  States are [n_seq, H, dk, dv].  Any lengths >= 1.
- * One set of launches however many the sequences and whatever states are given or asked for: every kernel looks its
+ * One set of launches whatever states are given or asked for: every kernel looks its
  * sequence up in two small tables that the call builds in the workspace from cu_seqlens (which is read before the call
- * returns), and the scans of all sequences run beside each other, the longest first.  The backward reconstructs the
+ * returns), and the scans of all sequences run beside each other, the longest first.  Sequences far shorter than a chunk:
+ * a call without states (S0, M0, S_final, M_final or S0, M0, dS_final, dM_final, dS0, dM0 all NULL) merges neighbours into
+ * pieces of up to 512 tokens whose state is cut at the inner starts by zeroed alpha and mu (in copies); a call with states
+ * goes group by group, so that its workspace stays bounded.  The backward reconstructs the
  * states and recomputes the operands (no states_saved / operands_saved here).  workspace: mdn_workspace_bytes_varlen
  * (MDN_WS_FWD or MDN_WS_BWD; the latter is enough for calls with adjoints of the final states as well).
  * Errors as for the fixed-length calls; MDN_ERR_SHAPE also for inconsistent cu_seqlens.

@@ -8,6 +8,7 @@
 #include <algorithm>
 #include <atomic>
 #include <mutex>
+#include <new>
 #include <vector>
 
 using namespace mdn;
@@ -52,6 +53,10 @@ struct Carver {
 
 struct FwdWs { float *coef; void *KT, *Tm, *Bm; float *carryS, *carryM; size_t total; };
 
+// a state tensor that crosses segment boundaries.  (Packed batches are not split: room for one sequence, so that their
+// workspace is never below that of one unbroken sequence of as many tokens.)
+size_t carry_bytes(const Dims &d) { return (size_t)(d.packed ? d.H : d.BH) * d.dk * d.dv * sizeof(float); }
+
 FwdWs carve_fwd(const Dims &d, void *ws) {
     const size_t es = d.dtype == MDN_DTYPE_F32 ? 4 : 2, nb = chunk_blocks(d);
     Carver c(ws);
@@ -61,8 +66,8 @@ FwdWs carve_fwd(const Dims &d, void *ws) {
     w.Tm = c.take(nb * 4096 * es);
     w.Bm = c.take(nb * 4096 * es);
     // states handed from one segment of the sequence to the next when the call is split (see segments())
-    w.carryS = static_cast<float *>(c.take((size_t)d.BH * d.dk * d.dv * sizeof(float)));
-    w.carryM = static_cast<float *>(c.take((size_t)d.BH * d.dk * d.dv * sizeof(float)));
+    w.carryS = static_cast<float *>(c.take(carry_bytes(d)));
+    w.carryM = static_cast<float *>(c.take(carry_bytes(d)));
     w.total = c.off;
     return w;
 }
@@ -98,8 +103,8 @@ BwdWs carve_bwd(const Dims &d, void *ws, bool precise) {
     w.states = c.take(nb * 2 * d.dk * d.dv * es);
     w.dstates_lo = precise ? c.take(nb * 2 * d.dk * d.dv * es) : nullptr;
     w.states_lo = precise ? c.take(nb * 2 * d.dk * d.dv * es) : nullptr;
-    w.carryS = static_cast<float *>(c.take((size_t)d.BH * d.dk * d.dv * sizeof(float)));
-    w.carryM = static_cast<float *>(c.take((size_t)d.BH * d.dk * d.dv * sizeof(float)));
+    w.carryS = static_cast<float *>(c.take(carry_bytes(d)));
+    w.carryM = static_cast<float *>(c.take(carry_bytes(d)));
     w.total = c.off;
     return w;
 }
@@ -160,7 +165,7 @@ bool few_scan_workgroups(const Dims &d) { return 2 * scan_workgroups(d) <= num_c
 // are all start and drain (512 blocks in 32 chunks of 16 heads: 304 / 315 / 352 / 594).  Forward: 271 / 289 / 299 / 328 for the second row, 1 159 / 1 190 /
 // 1 194 / 1 232 for the last, and slower split than unsplit at every other size measured.
 int segments(const Dims &d, bool backward) {
-    if (t_no_alloc || d.seqs) return 1; // (packed batches: the scans of the sequences run beside each other)
+    if (t_no_alloc || d.packed) return 1; // (packed batches: the scans of the sequences run beside each other)
     long long k = g_segments.load(std::memory_order_relaxed);
     if (k <= 0) {
         const long long grad = (long long)d.N * d.BH * d.dk * (d.dtype == MDN_DTYPE_F32 ? 4 : 1); // its time, in 1/128 blocks
@@ -511,26 +516,41 @@ int check_varlen(const mdn_shape *shape, const int32_t *cu, int32_t n_seq, Dims 
     if (shape->C != 64) return MDN_ERR_SHAPE; // (packed batches: chunk size 64 only)
     if (!cu) return MDN_ERR_NULL;
     if (shape->B != 1 || n_seq < 1 || cu[0] != 0 || cu[n_seq] != shape->T) return MDN_ERR_SHAPE;
-    long long chunks = 0, longest = 0;
-    for (int i = 0; i < n_seq; ++i) {
+    for (int i = 0; i < n_seq; ++i)
         if (cu[i + 1] <= cu[i]) return MDN_ERR_SHAPE;
-        const long long N = ((long long)cu[i + 1] - cu[i] + 63) / 64;
-        chunks += N;
-        longest = N > longest ? N : longest;
-    }
-    if (n_seq == 1) return MDN_OK; // an ordinary batch of one
-    if ((long long)n_seq * d->H > (1 << 24) || chunks * d->H > (1LL << 31) - 1) return MDN_ERR_SHAPE;
-    d->B = n_seq; d->BH = n_seq * d->H; d->N = d->n1 = (int)longest; d->nchunks = (int)chunks;
     return MDN_OK;
+}
+
+// Every sequence has chunk blocks of its own, so sequences far shorter than a chunk need up to 64 times the blocks of
+// their tokens.  Such a batch runs group by group on one workspace: a group ends before it needs more blocks than three times
+// those of T unbroken tokens, or than 65 536 (256 per CU, with which a group fills the GPU long enough for its boundary
+// not to matter).  Sequences of 32 tokens and more on average are always one group.
+struct SeqGroup { int s0, s1; Dims d; }; // sequences [s0, s1); a single sequence is an ordinary batch of one (no tables)
+SeqGroup next_group(const Dims &d, const int32_t *cu, int32_t n_seq, int s0) {
+    SeqGroup g{s0, n_seq, d};
+    if (n_seq == 1) return g;
+    const long long most = std::max(65536LL / d.H, 3LL * d.N), most_seqs = std::max(1, (1 << 24) / d.H);
+    long long chunks = 0, longest = 0;
+    int i = s0;
+    for (; i < n_seq && i - s0 < most_seqs; ++i) {
+        const long long N = ((long long)cu[i + 1] - cu[i] + 63) / 64;
+        if (i > s0 && chunks + N > most) break;
+        chunks += N;
+        longest = std::max(longest, N);
+    }
+    g.s1 = i;
+    g.d.B = i - s0; g.d.BH = g.d.B * d.H; g.d.N = g.d.n1 = (int)longest; g.d.nchunks = (int)chunks;
+    g.d.packed = true;
+    return g;
 }
 
 // the tables at the start of the workspace (none for a single sequence), the rest behind them
 struct PackedWs { SeqEntry *seqs; ChunkEntry *chunks; void *rest; size_t head; };
-PackedWs carve_packed(const Dims &d, int32_t n_seq, void *ws) {
+PackedWs carve_packed(const Dims &d, void *ws) {
     Carver c(ws);
     PackedWs w = {};
-    if (n_seq > 1) {
-        w.seqs = static_cast<SeqEntry *>(c.take((size_t)n_seq * sizeof(SeqEntry)));
+    if (d.packed) {
+        w.seqs = static_cast<SeqEntry *>(c.take((size_t)d.B * sizeof(SeqEntry)));
         w.chunks = static_cast<ChunkEntry *>(c.take((size_t)d.nchunks * sizeof(ChunkEntry)));
     }
     w.head = c.off;
@@ -538,26 +558,122 @@ PackedWs carve_packed(const Dims &d, int32_t n_seq, void *ws) {
     return w;
 }
 
-// builds the tables on the stream and points d at them
-int packed_tables(Dims *d, const int32_t *cu, int32_t n_seq, const PackedWs &w, hipStream_t s) {
-    if (n_seq == 1) return MDN_OK;
-    std::vector<SeqEntry> e(n_seq);
+// what the largest group needs (`precise`: see carve_bwd)
+size_t packed_ws_total(const Dims &d, const int32_t *cu, int32_t n_seq, bool backward, bool precise) {
+    size_t most = 0;
+    for (int s0 = 0; s0 < n_seq;) {
+        const SeqGroup g = next_group(d, cu, n_seq, s0);
+        most = std::max(most, carve_packed(g.d, nullptr).head +
+                                  (backward ? carve_bwd(g.d, nullptr, precise).total : carve_fwd(g.d, nullptr).total));
+        s0 = g.s1;
+    }
+    return most;
+}
+
+// builds the tables on the stream and points the group's sizes at them
+int packed_tables(SeqGroup *g, const int32_t *cu, const PackedWs &w, hipStream_t s) {
+    if (!g->d.packed) return MDN_OK;
+    const int n = g->s1 - g->s0;
+    std::vector<SeqEntry> e;
+    try {
+        e.resize(n);
+    } catch (const std::bad_alloc &) {
+        return MDN_ERR_LAUNCH;
+    }
     int cb = 0;
-    for (int i = 0; i < n_seq; ++i) {
-        e[i] = SeqEntry{cu[i], cu[i + 1] - cu[i], cb, i};
+    for (int i = 0; i < n; ++i) {
+        const int32_t *c = cu + g->s0 + i;
+        e[i] = SeqEntry{c[0], c[1] - c[0], cb, g->s0 + i};
         cb += (e[i].len + 63) / 64;
     }
-    std::stable_sort(e.begin(), e.end(), [](const SeqEntry &a, const SeqEntry &b) { return a.len > b.len; });
+    std::sort(e.begin(), e.end(), [](const SeqEntry &a, const SeqEntry &b) { return a.len != b.len ? a.len > b.len : a.t0 < b.t0; });
     SeqList l;
-    l.H = d->H;
-    for (l.first = 0; l.first < n_seq; l.first += l.n) {
-        l.n = n_seq - l.first < kSeqsPerLaunch ? n_seq - l.first : kSeqsPerLaunch;
+    l.H = g->d.H;
+    for (l.first = 0; l.first < n; l.first += l.n) {
+        l.n = n - l.first < kSeqsPerLaunch ? n - l.first : kSeqsPerLaunch;
         memcpy(l.e, e.data() + l.first, (size_t)l.n * sizeof(SeqEntry));
         if (launch_seq_tables(l, w.seqs, w.chunks, s) != hipSuccess) return MDN_ERR_LAUNCH;
     }
-    d->seqs = w.seqs;
-    d->chunks = w.chunks;
+    g->d.seqs = w.seqs;
+    g->d.chunks = w.chunks;
     return MDN_OK;
+}
+
+// run(sizes of a group, workspace behind its tables) for every group, one after the other on the stream
+template <typename F>
+int packed_run(const Dims &d, const int32_t *cu, int32_t n_seq, void *workspace, hipStream_t s, F &&run) {
+    for (int s0 = 0; s0 < n_seq;) {
+        SeqGroup g = next_group(d, cu, n_seq, s0);
+        const PackedWs w = carve_packed(g.d, workspace);
+        int rc = packed_tables(&g, cu, w, s);
+        if (!rc) rc = run(g.d, w.rest);
+        if (rc) return rc;
+        s0 = g.s1;
+    }
+    return MDN_OK;
+}
+
+// ---- short sequences without states.  A sequence shorter than a chunk leaves most of its chunk empty.  By Eq.
+// Mt.recurrent / St.recurrent a token with alpha = mu = 0 sees nothing of the states before it (e = v, M = -eta k e^T,
+// S = -beta M: what a sequence that starts from zero states computes at its first token, whose own alpha and mu multiply
+// those zeros) and passes no adjoint back to them.  So a call that neither gives nor asks for states may merge
+// neighbouring sequences into one piece, with alpha and mu zeroed (in copies) at the starts inside it; the gradients of
+// those gates are zero and are set so.  Pieces hold up to 512 tokens, fewer (down to 128) where the scans of longer ones
+// would leave CUs idle; a longer sequence is a piece of its own.  Merging costs 2 launches forward and 3 backward, so it
+// is done where it saves at least an eighth of the chunks.  Forward + backward in us, one piece per sequence / merged (16 heads of 128, bf16):
+//   32 768 tokens:   512 sequences  2 470 / 1 772;   1 024   3 610 / 1 683;   4 096   12 359 / 1 682
+//    4 096 tokens:   128 sequences    502 /   260;     512   1 558 /   248
+//    1 024 tokens:    64 sequences    208 /   106
+struct Merged { std::vector<int32_t> cu, starts; bool used = false; }; // piece offsets; starts inside the pieces
+
+int merge_short(const Dims &d, const int32_t *cu, int32_t n_seq, Merged *m) {
+    if (n_seq == 1) return MDN_OK;
+    const long long limit = std::max(128LL, std::min(512LL, (long long)d.T * d.H * (d.dv / 32) / std::max(1, num_cus())));
+    long long own = 0, merged = 0;
+    try {
+        m->cu.assign(1, 0);
+        for (int i = 0; i < n_seq; ++i) {
+            own += ((long long)cu[i + 1] - cu[i] + 63) / 64;
+            if (cu[i] > m->cu.back()) { // the piece holds sequences already
+                if (cu[i + 1] - m->cu.back() <= limit) m->starts.push_back(cu[i]);
+                else m->cu.push_back(cu[i]);
+            }
+        }
+        m->cu.push_back(cu[n_seq]);
+    } catch (const std::bad_alloc &) {
+        return MDN_ERR_LAUNCH;
+    }
+    for (size_t i = 0; i + 1 < m->cu.size(); ++i) merged += ((long long)m->cu[i + 1] - m->cu[i] + 63) / 64;
+    m->used = 8 * merged <= 7 * own;
+    return MDN_OK;
+}
+
+int clear_at_starts(const Dims &d, const Merged &m, float *a, float *b, hipStream_t s) {
+    StartList l;
+    l.H = d.H;
+    const int n = (int)m.starts.size();
+    for (int i = 0; i < n; i += l.n) {
+        l.n = std::min(n - i, kStartsPerLaunch);
+        memcpy(l.t, m.starts.data() + i, (size_t)l.n * sizeof(int));
+        if (launch_clear_at_starts(l, a, b, s) != hipSuccess) return MDN_ERR_LAUNCH;
+    }
+    return MDN_OK;
+}
+
+// the copies of alpha and mu at the start of the workspace, the rest behind them
+struct MergedWs { float *alpha, *mu; void *rest; size_t head; };
+MergedWs carve_merged(const Dims &d, void *ws) {
+    Carver c(ws);
+    MergedWs w = {};
+    w.alpha = static_cast<float *>(c.take((size_t)d.T * d.H * sizeof(float)));
+    w.mu = static_cast<float *>(c.take((size_t)d.T * d.H * sizeof(float)));
+    w.head = c.off;
+    w.rest = ws ? static_cast<char *>(ws) + c.off : nullptr;
+    return w;
+}
+int merged_gates(const Dims &d, const Merged &m, const float *alpha, const float *mu, const MergedWs &w, hipStream_t s) {
+    if (launch_copy_gates(alpha, mu, w.alpha, w.mu, (long long)d.T * d.H, s) != hipSuccess) return MDN_ERR_LAUNCH;
+    return clear_at_starts(d, m, w.alpha, w.mu, s);
 }
 
 // ---- the forward's workspace as a fixed array in device memory, for callers that cannot allocate.  Every GPU the
@@ -746,8 +862,14 @@ int mdn_workspace_bytes_varlen(const mdn_shape *shape, const int32_t *cu_seqlens
     if (rc) return rc;
     if (which != MDN_WS_FWD && which != MDN_WS_BWD) return MDN_ERR_SHAPE;
     // (a backward call may bring adjoints of the final states in: room for the rounding remainders as well)
-    *bytes_out = carve_packed(d, n_seq, nullptr).head +
-                 (which == MDN_WS_FWD ? carve_fwd(d, nullptr).total : carve_bwd(d, nullptr, d.dtype == MDN_DTYPE_BF16).total);
+    size_t most = packed_ws_total(d, cu_seqlens, n_seq, which == MDN_WS_BWD, d.dtype == MDN_DTYPE_BF16);
+    Merged m; // (without states the call may take this form)
+    const int rm = merge_short(d, cu_seqlens, n_seq, &m);
+    if (rm) return rm;
+    if (m.used)
+        most = std::max(most, carve_merged(d, nullptr).head +
+                                  packed_ws_total(d, m.cu.data(), (int)m.cu.size() - 1, which == MDN_WS_BWD, false));
+    *bytes_out = most;
     return MDN_OK;
 }
 
@@ -767,11 +889,21 @@ int mdn_chunk_fwd_varlen(const mdn_shape *shape, const int32_t *cu_seqlens, int3
     if (rc) return rc;
     if (workspace_bytes < need) return MDN_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const PackedWs w = carve_packed(d, n_seq, workspace);
-    rc = packed_tables(&d, cu_seqlens, n_seq, w, s);
-    if (rc) return rc;
-    const FwdCall c = {q, k, v, beta, alpha, mu, eta, S0, M0, o, S_final, M_final, vt_saved, nullptr, nullptr};
-    return run_fwd(d, c, carve_fwd(d, w.rest), s);
+    FwdCall c = {q, k, v, beta, alpha, mu, eta, S0, M0, o, S_final, M_final, vt_saved, nullptr, nullptr};
+    if (!S0 && !M0 && !S_final && !M_final) {
+        Merged m;
+        rc = merge_short(d, cu_seqlens, n_seq, &m);
+        if (rc) return rc;
+        if (m.used) {
+            const MergedWs w = carve_merged(d, workspace);
+            rc = merged_gates(d, m, alpha, mu, w, s);
+            if (rc) return rc;
+            c.alpha = w.alpha; c.mu = w.mu;
+            return packed_run(d, m.cu.data(), (int)m.cu.size() - 1, w.rest, s,
+                              [&](const Dims &g, void *ws) { return run_fwd(g, c, carve_fwd(g, ws), s); });
+        }
+    }
+    return packed_run(d, cu_seqlens, n_seq, workspace, s, [&](const Dims &g, void *ws) { return run_fwd(g, c, carve_fwd(g, ws), s); });
 }
 
 int mdn_chunk_bwd_varlen(const mdn_shape *shape, const int32_t *cu_seqlens, int32_t n_seq, const void *q, const void *k,
@@ -794,12 +926,23 @@ int mdn_chunk_bwd_varlen(const mdn_shape *shape, const int32_t *cu_seqlens, int3
     if (rc) return rc;
     if (workspace_bytes < need) return MDN_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const PackedWs w = carve_packed(d, n_seq, workspace);
-    rc = packed_tables(&d, cu_seqlens, n_seq, w, s);
-    if (rc) return rc;
-    const BwdCall c = {q, k, v, beta, alpha, mu, eta, S0, M0, vt_saved, nullptr, nullptr, dO, dS_final, dM_final,
-                       dq, dk, dv, dbeta, dalpha, dmu, deta, dS0, dM0};
-    return bwd_all(d, c, w.rest, s);
+    BwdCall c = {q, k, v, beta, alpha, mu, eta, S0, M0, vt_saved, nullptr, nullptr, dO, dS_final, dM_final,
+                 dq, dk, dv, dbeta, dalpha, dmu, deta, dS0, dM0};
+    if (!S0 && !M0 && !dS_final && !dM_final && !dS0 && !dM0) {
+        Merged m;
+        rc = merge_short(d, cu_seqlens, n_seq, &m);
+        if (rc) return rc;
+        if (m.used) {
+            const MergedWs w = carve_merged(d, workspace);
+            rc = merged_gates(d, m, alpha, mu, w, s);
+            if (rc) return rc;
+            c.alpha = w.alpha; c.mu = w.mu;
+            rc = packed_run(d, m.cu.data(), (int)m.cu.size() - 1, w.rest, s,
+                            [&](const Dims &g, void *ws) { return bwd_all(g, c, ws, s); });
+            return rc ? rc : clear_at_starts(d, m, dalpha, dmu, s);
+        }
+    }
+    return packed_run(d, cu_seqlens, n_seq, workspace, s, [&](const Dims &g, void *ws) { return bwd_all(g, c, ws, s); });
 }
 
 int mdn_recurrent_step(const mdn_shape *shape, const void *q, const void *k, const void *v, const float *beta,

@@ -28,6 +28,7 @@ struct Dims {
     int nchunks;              // chunks of all sequences together (B * N unless packed)
     const SeqEntry *seqs;     // packed batches: [B], longest first (the scans' order of dispatch); otherwise null
     const ChunkEntry *chunks; // packed batches: [nchunks], memory order; otherwise null
+    bool packed;              // sizes of a packed batch (host side; the tables are set for its launches)
 };
 
 // Chunk-parallel precompute ("intra") kernel arguments.  Workspace tensors are chunk-blocked,
@@ -161,6 +162,13 @@ struct SeqList {
     int n, first, H;
     SeqEntry e[kSeqsPerLaunch];
 };
+// first tokens of the sequences of a packed batch that follow another one in a merged piece, part of the list
+constexpr int kStartsPerLaunch = 960; // (a kernel's arguments end at 4 KB)
+struct StartList { int n, H; int t[kStartsPerLaunch]; };
+// a = b = 0 at the tokens of the list, all heads ([T,H] tensors)
+hipError_t launch_clear_at_starts(const StartList &l, float *a, float *b, hipStream_t s);
+// dst_a = a, dst_b = b: n floats each, 16-byte aligned
+hipError_t launch_copy_gates(const float *a, const float *b, float *dst_a, float *dst_b, long long n, hipStream_t s);
 hipError_t launch_seq_tables(const SeqList &l, SeqEntry *seqs, ChunkEntry *chunks, hipStream_t s);
 
 } // namespace mdn

@@ -18,6 +18,22 @@ __global__ __launch_bounds__(64) void seq_tables_kernel(SeqList l, SeqEntry *seq
         chunks[e.cb + n] = ChunkEntry{e.t0 + n * 64, min(64, e.len - n * 64), e.cb * l.H + n, N};
 }
 
+// blockIdx.x = token of the list; threads over the heads
+__global__ __launch_bounds__(64) void clear_at_starts_kernel(StartList l, float *a, float *b) {
+    const size_t row = (size_t)l.t[blockIdx.x] * l.H;
+    for (int h = threadIdx.x; h < l.H; h += 64) a[row + h] = b[row + h] = 0.f;
+}
+
+// blockIdx.y = tensor
+__global__ __launch_bounds__(256) void copy_gates_kernel(const float *a, const float *b, float *dst_a, float *dst_b, long long n) {
+    const float *src = blockIdx.y ? b : a;
+    float *dst = blockIdx.y ? dst_b : dst_a;
+    const long long step = (long long)gridDim.x * 256;
+    for (long long x = (long long)blockIdx.x * 256 + threadIdx.x; x < n / 4; x += step)
+        reinterpret_cast<float4 *>(dst)[x] = reinterpret_cast<const float4 *>(src)[x];
+    if (blockIdx.x == 0 && threadIdx.x < n % 4) dst[n / 4 * 4 + threadIdx.x] = src[n / 4 * 4 + threadIdx.x];
+}
+
 // chunks of C < 64 tokens as 64-token tiles: blockIdx.y = tensor, blockIdx.x = (b, chunk, i, h) row of the padded tensor
 template <bool EXPAND> __global__ __launch_bounds__(64) void chunk_copy_kernel(ChunkCopy c) {
     const TileTensor t = c.t[blockIdx.y];
@@ -40,6 +56,20 @@ hipError_t launch_seq_tables(const SeqList &l, SeqEntry *seqs, ChunkEntry *chunk
     if (l.n < 1) return hipSuccess;
     if (l.n > kSeqsPerLaunch || l.first < 0 || l.H < 1 || !seqs || !chunks) return hipErrorInvalidValue;
     hipLaunchKernelGGL(seq_tables_kernel, dim3(l.n), dim3(64), 0, s, l, seqs, chunks);
+    return hipGetLastError();
+}
+
+hipError_t launch_clear_at_starts(const StartList &l, float *a, float *b, hipStream_t s) {
+    if (l.n < 1) return hipSuccess;
+    if (l.n > kStartsPerLaunch || l.H < 1 || !a || !b) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(clear_at_starts_kernel, dim3(l.n), dim3(64), 0, s, l, a, b);
+    return hipGetLastError();
+}
+
+hipError_t launch_copy_gates(const float *a, const float *b, float *dst_a, float *dst_b, long long n, hipStream_t s) {
+    if (n < 1 || !a || !b || !dst_a || !dst_b) return hipErrorInvalidValue;
+    const unsigned blocks = (unsigned)(n / 1024 + 1 < 1024 ? n / 1024 + 1 : 1024);
+    hipLaunchKernelGGL(copy_gates_kernel, dim3(blocks, 2), dim3(256), 0, s, a, b, dst_a, dst_b, n);
     return hipGetLastError();
 }
 

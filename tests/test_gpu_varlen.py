@@ -144,3 +144,40 @@ def test_packed_states_in_and_out_of_many_short_and_of_uneven_sequences(dtype, n
     for k, parts in ref.items():
         x = np.concatenate(parts, axis=0 if k in ("S", "M", "dS0", "dM0") else 1)
         assert worst_err(host((f if k in f else g)[k]), x) <= TOL[dtype], k
+
+
+def test_packed_batch_of_very_short_sequences_runs_group_by_group():
+    """16 heads x 5 000 sequences of 1 .. 7 tokens need 80 000 chunk blocks, more than one group's 65 536: outputs, states
+    and gradients are bit for bit those of the same sequences in two calls that are one group each."""
+    H, d, n = 16, 64, 5000
+    lens = [1 + (5 * i + i // 7) % 7 for i in range(n)]
+    cu = np.concatenate([[0], np.cumsum(lens)]).tolist()
+    w = synth.custom(B=1, T=cu[-1], H=H, dk=d, dv=d, dtype="bf16", seed=74, with_eta=True, backward=True)
+    t = to_dev(w)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    S0, M0, dS, dM = (0.2 * torch.randn((n, H, d, d), device="cuda", generator=gen) for _ in range(4))
+
+    def run(a, b):
+        x = [t[k][:, cu[a]:cu[b]].contiguous() for k in ("q", "k", "v", "beta", "alpha", "mu")]
+        eta, dO = (t[k][:, cu[a]:cu[b]].contiguous() for k in ("eta", "dO"))
+        c = [v - cu[a] for v in cu[a:b + 1]]
+        s0, m0, ds, dm = (z[a:b].contiguous() for z in (S0, M0, dS, dM))
+        f = binding.mdn_chunk_fwd_varlen(*x, c, eta=eta, S0=s0, M0=m0, scale=w.scale, save_vt=True)
+        g = binding.mdn_chunk_bwd_varlen(*x, f["vt"], dO, c, eta=eta, S0=s0, M0=m0, dS_final=ds, dM_final=dm, scale=w.scale,
+                                         want_deta=True)
+        return {k: v for k, v in {**f, **g}.items() if torch.is_tensor(v) and k != "workspace"}
+
+    whole, left, right = run(0, n), run(0, n // 2), run(n // 2, n)
+    for k in whole:
+        dim = 0 if k in ("S", "M", "dS0", "dM0") else 1
+        assert torch.equal(whole[k], torch.cat((left[k], right[k]), dim=dim)), k
+
+
+@pytest.mark.parametrize("dtype,d,lens", [("f32", 64, (3, 17, 1, 40, 64, 2, 130, 9, 9, 9, 300, 5)),
+                                          ("bf16", 128, (3, 17, 1, 40, 64, 2, 130, 9, 9, 9, 300, 5)),
+                                          ("bf16", 64, (7, 9)), ("f32", 128, (20, 30, 14)),
+                                          ("bf16", 64, (1, 2, 3) * 400)])
+def test_short_sequences_merged_into_pieces(dtype, d, lens):
+    """Calls without states that save an eighth of their chunks by merging neighbours (one piece for everything, starts on
+    and off chunk boundaries, more starts than one launch takes), every sequence against the oracle by itself."""
+    test_packed_sequences_as_one_stream_of_tokens(dtype, d, lens)
