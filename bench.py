@@ -169,7 +169,8 @@ def handoff_bench(args, torch, binding, synth):
 
 def varlen_bench(args, torch, binding, synth):
     """Packed variable-length batches, forward + backward (the backward rebuilds states and operands): the batch as one
-    stream of tokens (no per-sequence states asked for) against the same batch run sequence by sequence."""
+    stream of tokens (no per-sequence states asked for: "one_stream" keys) against the same batch with per-sequence final
+    states and adjoints of the initial states ("sequence_by_sequence" keys)."""
     total, H, dk = args.varlen, 16, 128
     rows = []
     for nseq in (8, 64, 256):
@@ -197,8 +198,8 @@ def varlen_bench(args, torch, binding, synth):
             key = "one_stream" if one_stream else "sequence_by_sequence"
             row[key + "_ms"] = round(ms, 3)
             row[key + "_tokens_per_s"] = round(nseq * L / (ms * 1e-3), 1)
-        # prefill of the same batch as prompts: forward only, final states of every sequence wanted (zero initial
-        # states: the stream form plus one batch of last chunks; with initial states given: sequence by sequence)
+        # prefill of the same batch as prompts: forward only, final states of every sequence wanted, with zero initial
+        # states ("one_stream" keys) or with initial states given ("sequence_by_sequence" keys)
         zeros = torch.zeros((nseq, H, dk, dk), dtype=torch.float32, device="cuda")
         for one_stream in (True, False):
             def prefill():
