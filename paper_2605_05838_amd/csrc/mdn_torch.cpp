@@ -97,15 +97,25 @@ int dtype_code(const at::Tensor &t) {
     fail("q/k/v must be bfloat16 or float32");
 }
 
-// the library call itself, without the interpreter lock (a launch may wait for room in the stream's queue)
-template <typename F> void call(const char *what, F &&f) {
+// without the interpreter lock from here to the end of the scope, however it is left
+struct Unlocked {
     PyThreadState *t = PyEval_SaveThread();
-    const int rc = f();
-    PyEval_RestoreThread(t);
-    if (rc) fail(std::string(what) + ": " + mdn_strerror(rc) + " (code " + std::to_string(rc) + ")");
-}
+    Unlocked() = default;
+    Unlocked(const Unlocked &) = delete;
+    ~Unlocked() { PyEval_RestoreThread(t); }
+};
 void check(int rc, const char *what) {
     if (rc) fail(std::string(what) + ": " + mdn_strerror(rc) + " (code " + std::to_string(rc) + ")");
+}
+// The library call itself, without the interpreter lock (a launch may wait for room in the stream's queue).  The arguments
+// are values by then: taking a pointer can raise (a tensor that has no storage), which needs the lock.
+template <typename... P, typename... A> void call(const char *what, int (*f)(P...), A... args) {
+    int rc;
+    {
+        const Unlocked u;
+        rc = f(args...);
+    }
+    check(rc, what);
 }
 
 double number(PyObject *o) {
@@ -290,11 +300,9 @@ PyObject *chunk_fwd(PyObject *const *x) {
     at::Tensor ws = workspace(x[14], workspace_bytes(in.s, MDN_WS_FWD), in.q);
     on_gpu(in.q);
     void *st = stream();
-    call("mdn_chunk_fwd", [&] {
-        return mdn_chunk_fwd(&in.s, ptr(in.q), ptr(in.k), ptr(in.v), ptr<float>(in.beta), ptr<float>(in.alpha), ptr<float>(in.mu),
-                        ptr<float>(in.eta), ptr<float>(in.S0), ptr<float>(in.M0), ptr(o), ptr<float>(S), ptr<float>(M), ptr(vt),
-                        ptr(states), ptr(operands), ptr(ws), size_of(ws), st);
-    });
+    call("mdn_chunk_fwd", mdn_chunk_fwd, &in.s, ptr(in.q), ptr(in.k), ptr(in.v), ptr<float>(in.beta), ptr<float>(in.alpha),
+         ptr<float>(in.mu), ptr<float>(in.eta), ptr<float>(in.S0), ptr<float>(in.M0), ptr(o), ptr<float>(S), ptr<float>(M),
+         ptr(vt), ptr(states), ptr(operands), ptr(ws), size_of(ws), st);
     Dict r;
     r.set("o", o);
     r.set("S", S);
@@ -317,11 +325,9 @@ PyObject *chunk_fwd_noalloc(PyObject *const *x) {
     expect("out['vt']", vt, {in.B, in.T, in.H, in.dv}, in.dt, in.q);
     on_gpu(in.q);
     void *st = stream();
-    call("mdn_chunk_fwd_noalloc", [&] {
-        return mdn_chunk_fwd_noalloc(&in.s, ptr(in.q), ptr(in.k), ptr(in.v), ptr<float>(in.beta), ptr<float>(in.alpha),
-                                ptr<float>(in.mu), ptr<float>(in.eta), ptr<float>(in.S0), ptr<float>(in.M0), ptr(o), ptr<float>(S),
-                                ptr<float>(M), ptr(vt), st);
-    });
+    call("mdn_chunk_fwd_noalloc", mdn_chunk_fwd_noalloc, &in.s, ptr(in.q), ptr(in.k), ptr(in.v), ptr<float>(in.beta),
+         ptr<float>(in.alpha), ptr<float>(in.mu), ptr<float>(in.eta), ptr<float>(in.S0), ptr<float>(in.M0), ptr(o),
+         ptr<float>(S), ptr<float>(M), ptr(vt), st);
     Py_INCREF(x[6]);
     return x[6];
 }
@@ -370,12 +376,10 @@ PyObject *chunk_bwd(PyObject *const *x) {
     at::Tensor ws = workspace(x[18], workspace_bytes(in.s, dS || dM ? MDN_WS_BWD_STATE_ADJOINTS : MDN_WS_BWD), in.q);
     on_gpu(in.q);
     void *st = stream();
-    call("mdn_chunk_bwd", [&] {
-        return mdn_chunk_bwd(&in.s, ptr(in.q), ptr(in.k), ptr(in.v), ptr<float>(in.beta), ptr<float>(in.alpha), ptr<float>(in.mu),
-                        ptr<float>(in.eta), ptr<float>(in.S0), ptr<float>(in.M0), ptr(vt), ptr(states), ptr(operands), ptr(dO),
-                        ptr<float>(dS), ptr<float>(dM), ptr(g.dq), ptr(g.dk), ptr(g.dv), ptr<float>(g.dbeta), ptr<float>(g.dalpha),
-                        ptr<float>(g.dmu), ptr<float>(g.deta), ptr<float>(g.dS0), ptr<float>(g.dM0), ptr(ws), size_of(ws), st);
-    });
+    call("mdn_chunk_bwd", mdn_chunk_bwd, &in.s, ptr(in.q), ptr(in.k), ptr(in.v), ptr<float>(in.beta), ptr<float>(in.alpha),
+         ptr<float>(in.mu), ptr<float>(in.eta), ptr<float>(in.S0), ptr<float>(in.M0), ptr(vt), ptr(states), ptr(operands),
+         ptr(dO), ptr<float>(dS), ptr<float>(dM), ptr(g.dq), ptr(g.dk), ptr(g.dv), ptr<float>(g.dbeta), ptr<float>(g.dalpha),
+         ptr<float>(g.dmu), ptr<float>(g.deta), ptr<float>(g.dS0), ptr<float>(g.dM0), ptr(ws), size_of(ws), st);
     Dict r;
     g.into(r);
     r.set("workspace", ws);
@@ -391,10 +395,8 @@ PyObject *recurrent_step(PyObject *const *x) {
     at::Tensor o = given ? *given : empty({in.B, in.T, in.H, in.dv}, in.dt, in.q);
     on_gpu(in.q);
     void *st = stream();
-    call("mdn_recurrent_step", [&] {
-        return mdn_recurrent_step(&in.s, ptr(in.q), ptr(in.k), ptr(in.v), ptr<float>(in.beta), ptr<float>(in.alpha), ptr<float>(in.mu),
-                             ptr<float>(in.eta), ptr<float>(in.S0), ptr<float>(in.M0), ptr(o), st);
-    });
+    call("mdn_recurrent_step", mdn_recurrent_step, &in.s, ptr(in.q), ptr(in.k), ptr(in.v), ptr<float>(in.beta),
+         ptr<float>(in.alpha), ptr<float>(in.mu), ptr<float>(in.eta), ptr<float>(in.S0), ptr<float>(in.M0), ptr(o), st);
     if (given) {
         Py_INCREF(x[10]);
         return x[10];
@@ -421,11 +423,9 @@ PyObject *chunk_fwd_varlen(PyObject *const *x) {
     at::Tensor ws = bytes(nb, q);
     on_gpu(q);
     void *st = stream();
-    call("mdn_chunk_fwd_varlen", [&] {
-        return mdn_chunk_fwd_varlen(&in.s, cu.data(), (int32_t)n, ptr(q), ptr(in.k), ptr(in.v), ptr<float>(in.beta), ptr<float>(in.alpha),
-                               ptr<float>(in.mu), ptr<float>(in.eta), ptr<float>(in.S0), ptr<float>(in.M0), ptr(o), ptr<float>(S),
-                               ptr<float>(M), ptr(vt), ptr(ws), nb, st);
-    });
+    call("mdn_chunk_fwd_varlen", mdn_chunk_fwd_varlen, &in.s, cu.data(), (int32_t)n, ptr(q), ptr(in.k), ptr(in.v),
+         ptr<float>(in.beta), ptr<float>(in.alpha), ptr<float>(in.mu), ptr<float>(in.eta), ptr<float>(in.S0), ptr<float>(in.M0),
+         ptr(o), ptr<float>(S), ptr<float>(M), ptr(vt), ptr(ws), nb, st);
     Dict r;
     r.set("o", o);
     r.set("S", S);
@@ -453,13 +453,10 @@ PyObject *chunk_bwd_varlen(PyObject *const *x) {
     at::Tensor ws = bytes(nb, q);
     on_gpu(q);
     void *st = stream();
-    call("mdn_chunk_bwd_varlen", [&] {
-        return mdn_chunk_bwd_varlen(&in.s, cu.data(), (int32_t)n, ptr(q), ptr(in.k), ptr(in.v), ptr<float>(in.beta), ptr<float>(in.alpha),
-                               ptr<float>(in.mu), ptr<float>(in.eta), ptr<float>(in.S0), ptr<float>(in.M0), ptr(vt), ptr(dO),
-                               ptr<float>(dS), ptr<float>(dM), ptr(g.dq), ptr(g.dk), ptr(g.dv), ptr<float>(g.dbeta),
-                               ptr<float>(g.dalpha), ptr<float>(g.dmu), ptr<float>(g.deta), ptr<float>(g.dS0), ptr<float>(g.dM0),
-                               ptr(ws), nb, st);
-    });
+    call("mdn_chunk_bwd_varlen", mdn_chunk_bwd_varlen, &in.s, cu.data(), (int32_t)n, ptr(q), ptr(in.k), ptr(in.v),
+         ptr<float>(in.beta), ptr<float>(in.alpha), ptr<float>(in.mu), ptr<float>(in.eta), ptr<float>(in.S0), ptr<float>(in.M0),
+         ptr(vt), ptr(dO), ptr<float>(dS), ptr<float>(dM), ptr(g.dq), ptr(g.dk), ptr(g.dv), ptr<float>(g.dbeta),
+         ptr<float>(g.dalpha), ptr<float>(g.dmu), ptr<float>(g.deta), ptr<float>(g.dS0), ptr<float>(g.dM0), ptr(ws), nb, st);
     Dict r;
     g.into(r);
     return r.release();
@@ -505,10 +502,8 @@ PyObject *gates_fwd(PyObject *const *x) {
     at::Tensor alpha = empty(in.xa.sizes(), at::kFloat, in.xa), beta = empty(in.xa.sizes(), at::kFloat, in.xa),
                mu = empty(in.xa.sizes(), at::kFloat, in.xa), eta = empty(in.xa.sizes(), at::kFloat, in.xa);
     void *st = stream();
-    call("mdn_gates_fwd", [&] {
-        return mdn_gates_fwd(&in.p, ptr<float>(in.xa), ptr<float>(in.xm), ptr<float>(in.xb), ptr<float>(in.xe), ptr<float>(alpha),
-                        ptr<float>(beta), ptr<float>(mu), ptr<float>(eta), st);
-    });
+    call("mdn_gates_fwd", mdn_gates_fwd, &in.p, ptr<float>(in.xa), ptr<float>(in.xm), ptr<float>(in.xb), ptr<float>(in.xe),
+         ptr<float>(alpha), ptr<float>(beta), ptr<float>(mu), ptr<float>(eta), st);
     Dict r;
     r.set("alpha", alpha);
     r.set("beta", beta);
@@ -531,11 +526,9 @@ PyObject *gates_bwd(PyObject *const *x) {
     c10::optional<at::Tensor> par;
     if (truth(x[15])) par = empty({4, in.xa.size(2)}, at::kFloat, in.xa);
     void *st = stream();
-    call("mdn_gates_bwd", [&] {
-        return mdn_gates_bwd(&in.p, ptr<float>(in.xa), ptr<float>(in.xm), ptr<float>(in.xb), ptr<float>(in.xe), ptr<float>(da),
-                        ptr<float>(db), ptr<float>(dm), ptr<float>(de), ptr<float>(xa), ptr<float>(xm), ptr<float>(xb),
-                        ptr<float>(xe), ptr<float>(par), st);
-    });
+    call("mdn_gates_bwd", mdn_gates_bwd, &in.p, ptr<float>(in.xa), ptr<float>(in.xm), ptr<float>(in.xb), ptr<float>(in.xe),
+         ptr<float>(da), ptr<float>(db), ptr<float>(dm), ptr<float>(de), ptr<float>(xa), ptr<float>(xm), ptr<float>(xb),
+         ptr<float>(xe), ptr<float>(par), st);
     Dict r;
     r.set("dx_alpha", xa);
     r.set("dx_mu", xm);
@@ -568,9 +561,8 @@ PyObject *frontend_fwd(PyObject *const *x) {
     on_gpu(in.q);
     at::Tensor q = empty(in.q.sizes(), in.dt, in.q), k = empty(in.k.sizes(), in.dt, in.q), v = empty(in.v.sizes(), in.dt, in.q);
     void *st = stream();
-    call("mdn_frontend_fwd", [&] {
-        return mdn_frontend_fwd(&in.s, ptr(in.q), ptr(in.k), ptr(in.v), ptr<float>(in.d), (float)eps, ptr(q), ptr(k), ptr(v), st);
-    });
+    call("mdn_frontend_fwd", mdn_frontend_fwd, &in.s, ptr(in.q), ptr(in.k), ptr(in.v), ptr<float>(in.d), (float)eps, ptr(q),
+         ptr(k), ptr(v), st);
     Dict r;
     r.set("q", q);
     r.set("k", k);
@@ -592,10 +584,8 @@ PyObject *frontend_bwd(PyObject *const *x) {
     c10::optional<at::Tensor> dd;
     if (truth(x[8])) dd = empty(in.d.sizes(), at::kFloat, in.q);
     void *st = stream();
-    call("mdn_frontend_bwd", [&] {
-        return mdn_frontend_bwd(&in.s, ptr(in.q), ptr(in.k), ptr(in.v), ptr<float>(in.d), (float)eps, ptr(dq), ptr(dk), ptr(dv), ptr(q),
-                           ptr(k), ptr(v), ptr<float>(dd), st);
-    });
+    call("mdn_frontend_bwd", mdn_frontend_bwd, &in.s, ptr(in.q), ptr(in.k), ptr(in.v), ptr<float>(in.d), (float)eps, ptr(dq),
+         ptr(dk), ptr(dv), ptr(q), ptr(k), ptr(v), ptr<float>(dd), st);
     Dict r;
     r.set("dx_q", q);
     r.set("dx_k", k);
@@ -626,9 +616,7 @@ PyObject *epilogue_fwd(PyObject *const *x) {
     on_gpu(in.o);
     at::Tensor y = empty(in.o.sizes(), in.dt, in.o);
     void *st = stream();
-    call("mdn_epilogue_fwd", [&] {
-        return mdn_epilogue_fwd(&in.s, ptr(in.o), ptr(in.g), ptr<float>(in.w), (float)eps, ptr(y), st);
-    });
+    call("mdn_epilogue_fwd", mdn_epilogue_fwd, &in.s, ptr(in.o), ptr(in.g), ptr<float>(in.w), (float)eps, ptr(y), st);
     return THPVariable_Wrap(y);
 }
 
@@ -643,9 +631,8 @@ PyObject *epilogue_bwd(PyObject *const *x) {
     c10::optional<at::Tensor> dw;
     if (truth(x[5])) dw = empty(in.w.sizes(), at::kFloat, in.o);
     void *st = stream();
-    call("mdn_epilogue_bwd", [&] {
-        return mdn_epilogue_bwd(&in.s, ptr(in.o), ptr(in.g), ptr<float>(in.w), (float)eps, ptr(dy), ptr(d_o), ptr(dg), ptr<float>(dw), st);
-    });
+    call("mdn_epilogue_bwd", mdn_epilogue_bwd, &in.s, ptr(in.o), ptr(in.g), ptr<float>(in.w), (float)eps, ptr(dy), ptr(d_o),
+         ptr(dg), ptr<float>(dw), st);
     Dict r;
     r.set("do", d_o);
     r.set("dg", dg);

@@ -226,3 +226,45 @@ def test_host_side_entry_points_from_several_threads():
     assert not wrong
     assert set().union(*seen) <= set(range(0, 8)) and 1 <= last <= 7
     assert lib.mdn_set_segments(old) == old
+
+
+# stand-ins for the four device queries on the way to a call's stream, so that a call gets as far as its pointers without
+# a device; the library refuses the null pointers of the unwrapped call before it launches anything
+STUB = """
+int hipGetDeviceCount(int *n) { *n = 1; return 0; }
+int hipGetDevice(int *d) { *d = 0; return 0; }
+int hipSetDevice(int d) { return d != 0; }
+int hipDeviceGetStreamPriorityRange(int *least, int *greatest) { *least = *greatest = 0; return 0; }
+"""
+NO_STORAGE = """
+import ctypes, sys
+ctypes.CDLL(sys.argv[1], ctypes.RTLD_GLOBAL)
+import torch
+import torch._subclasses.fake_tensor as fake
+from paper_2605_05838_amd import binding
+fake.init_gpu_context = lambda device: None
+with fake.FakeTensorMode():
+    x, g, S = (torch.empty(s, device="cuda:0") for s in ((3, 1, 1, 1, 64), (3, 1, 1, 1), (3, 1, 1, 64, 64)))
+    one = [torch.empty(t.shape[1:], device="cuda:0") for t in (x, g, S)]
+step = lambda x, g, S: binding.mdn_recurrent_step(x, x, x, g, g, g, S, S, out=x)
+for f, args, error, text in ((step, one, binding.MdnError, "NULL"), (torch.vmap(step), (x, g, S), RuntimeError, "storage")):
+    try:
+        f(*args)
+    except error as e:
+        assert text in str(e), e
+    else:
+        raise AssertionError("accepted")
+print("raised")
+"""
+
+
+def test_a_tensor_without_storage_raises_and_the_interpreter_goes_on(tmp_path):
+    """Inside torch.vmap the tensors have no storage: taking their pointers raises, which has to happen while the binding
+    holds the interpreter lock."""
+    import subprocess
+    import sys
+    (tmp_path / "stub.c").write_text(STUB)
+    stub = str(tmp_path / "stub.so")
+    subprocess.run(["gcc", "-shared", "-fPIC", "-o", stub, str(tmp_path / "stub.c")], check=True)
+    p = subprocess.run([sys.executable, "-c", NO_STORAGE, stub], cwd=ROOT, capture_output=True, text=True, timeout=300)
+    assert p.returncode == 0 and p.stdout.strip() == "raised", (p.returncode, p.stderr[-2000:])
