@@ -24,11 +24,20 @@ namespace {
 
 constexpr int LT = 256; // threads of the kernels without parameter gradients
 
-// sigmoid; 16-bit storage: the reciprocal instruction (1 ulp of fp32, far below the rounding of the result)
+// sigmoid.  16-bit storage: 1 / (1 + e^-x) by the reciprocal instruction (1 ulp) and one Newton step.  Compared for every fp32
+// value of e^-x from 0 to infinity, the quotient is bit for bit that of the IEEE division (ten instructions: the kernels were
+// bound by them), denormal quotients to one unit in their last place.  The reciprocal flushes denormal results, which is why
+// it is taken of 2^-32 times its argument; at e^-x = infinity its residual is not a number, which the maximum replaces.
+// (The bare reciprocal: front end forward 33.6 us where it takes 35.7, adjoint 54.9 / 55.6; back end 18.7 / 18.7, 32.6 / 33.6.)
 template <typename T> __device__ __forceinline__ float sigm(float x) {
-    const float d = 1.f + __expf(-x);
-    if constexpr (sizeof(T) == 2) return __builtin_amdgcn_rcpf(d);
-    else return 1.f / d;
+    const float t = __expf(-x);
+    if constexpr (sizeof(T) == 2) {
+        const float d = __builtin_fmaf(t, 0x1p-32f, 0x1p-32f), r = __builtin_amdgcn_rcpf(d);
+        const float e = fmaxf(__builtin_fmaf(-d, r, 1.f), -1.f);
+        return __builtin_fmaf(r, e, r) * 0x1p-32f;
+    } else {
+        return 1.f / (1.f + t);
+    }
 }
 
 // This lane's 8 elements of a row of D: D / 8 lanes hold a row, 512 / D rows a wave.

@@ -54,3 +54,18 @@ def test_frontend_and_epilogue_match_the_oracle(dtype, d):
     re_ = lo.epilogue_backward(o, g, w, dy)
     assert rel(_h(e["do"]), re_["do"]) <= tol and rel(_h(e["dg"]), re_["dg"]) <= tol
     assert rel(_h(e["dw"]), re_["dw"]) <= max(tol, 1e-4)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_parameter_gradients_of_16_bit_tensors_are_computed_in_32_bits(d):
+    """One row (nothing is summed in an order that could differ): dd and dw of 16-bit tensors are bit for bit those of the
+    same values in 32-bit tensors."""
+    gen = torch.Generator(device="cuda").manual_seed(62)
+    for _ in range(8):
+        x = [3.0 * torch.randn((1, 1, 1, d), device="cuda", generator=gen) for _ in range(9)]
+        dh, w = torch.rand(1, device="cuda", generator=gen), 0.5 + torch.rand(d, device="cuda", generator=gen)
+        got = []
+        for dt in (torch.bfloat16, torch.float32):
+            y = [t.bfloat16().to(dt) for t in x]
+            got.append((binding.mdn_frontend_bwd(*y[:3], dh, *y[3:6])["dd"], binding.mdn_epilogue_bwd(*y[6:8], w, y[8])["dw"]))
+        assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
