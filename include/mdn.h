@@ -27,7 +27,7 @@
  *   - shape.dtype selects the storage type of q, k, v, o, dO, dq, dk, dv and of every
  *     intermediate the library stores: MDN_DTYPE_BF16 (bf16 MFMA operands, fp32 accumulation
  *     and fp32 states) or MDN_DTYPE_F32 (fp32 MFMA throughout).
- *   - All pointers must be 16-byte aligned.  dk, dv in {64, 128}; C in {16, 32, 64} (Algorithm 1's chunk sizes);
+ *   - All pointers must be 16-byte aligned (gates, front end and back end: aligned to their elements).  dk, dv in {64, 128}; C in {16, 32, 64} (Algorithm 1's chunk sizes);
  *     any T >= 1: when T is not a multiple of C the last chunk is partial (Algorithm 1 pads it; here the kernels fill
  *     the chunk up with exact identity steps, k = v = q = 0, alpha = mu = 1, beta = 0, on chip, so outputs, final states
  *     and gradients are those of the T tokens given).  C = 64 is the tuned path: the kernels

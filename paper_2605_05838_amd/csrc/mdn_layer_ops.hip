@@ -40,17 +40,21 @@ template <typename T> __device__ __forceinline__ float sigm(float x) {
     }
 }
 
-// This lane's 8 elements of a row of D: D / 8 lanes hold a row, 512 / D rows a wave.
+// This lane's 8 elements of a row of D: D / 8 lanes hold a row, 512 / D rows a wave.  Tensors need no more than the alignment
+// of their elements (a weight sliced out of a flat buffer): the vector types say so, and the accesses stay 16 bytes wide,
+// which the hardware takes at any address.
 template <typename T, int D> struct Row {
     static constexpr int E = 8, LPR = D / E, RPW = 64 / LPR;
+    typedef bf16x8 __attribute__((aligned(2))) Half8;
+    typedef f32x4 __attribute__((aligned(4))) Float4;
     float v[E];
     __device__ __forceinline__ void load(const T *p) {
         if constexpr (sizeof(T) == 2) {
-            const bf16x8 x = *reinterpret_cast<const bf16x8 *>(p);
+            const bf16x8 x = *reinterpret_cast<const Half8 *>(p);
 #pragma unroll
             for (int e = 0; e < E; ++e) v[e] = (float)x[e];
         } else {
-            const f32x4 a = *reinterpret_cast<const f32x4 *>(p), b = *reinterpret_cast<const f32x4 *>(p + 4);
+            const f32x4 a = *reinterpret_cast<const Float4 *>(p), b = *reinterpret_cast<const Float4 *>(p + 4);
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[e] = a[e], v[4 + e] = b[e];
         }
@@ -60,10 +64,10 @@ template <typename T, int D> struct Row {
             bf16x8 x;
 #pragma unroll
             for (int e = 0; e < E; ++e) x[e] = (bf16_t)v[e];
-            *reinterpret_cast<bf16x8 *>(p) = x;
+            *reinterpret_cast<Half8 *>(p) = x;
         } else {
-            *reinterpret_cast<f32x4 *>(p) = f32x4{v[0], v[1], v[2], v[3]};
-            *reinterpret_cast<f32x4 *>(p + 4) = f32x4{v[4], v[5], v[6], v[7]};
+            *reinterpret_cast<Float4 *>(p) = f32x4{v[0], v[1], v[2], v[3]};
+            *reinterpret_cast<Float4 *>(p + 4) = f32x4{v[4], v[5], v[6], v[7]};
         }
     }
     // sum of x over the lanes of a row, in every one of them

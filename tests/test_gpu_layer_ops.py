@@ -69,3 +69,19 @@ def test_parameter_gradients_of_16_bit_tensors_are_computed_in_32_bits(d):
             y = [t.bfloat16().to(dt) for t in x]
             got.append((binding.mdn_frontend_bwd(*y[:3], dh, *y[3:6])["dd"], binding.mdn_epilogue_bwd(*y[6:8], w, y[8])["dw"]))
         assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_tensors_at_any_element_offset(dtype):
+    """Contiguous views that start at an odd element of their buffer give the results of aligned copies, bit for bit (one
+    row, as above)."""
+    d, gen = 128, torch.Generator(device="cuda").manual_seed(63)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    flat = torch.randn(10 * (d + 1), device="cuda", generator=gen).to(dt)
+    par = torch.rand(2 * d, device="cuda", generator=gen)
+    odd = [flat[1 + i * (d + 1):][:d].view(1, 1, 1, d) for i in range(9)]
+    got = []
+    for x, w, dh in ((odd, par[1:1 + d], par[:1]), ([t.clone() for t in odd], par[1:1 + d].clone(), par[:1].clone())):
+        got.append([*binding.mdn_frontend_fwd(*x[:3], dh).values(), *binding.mdn_frontend_bwd(*x[:3], dh, *x[3:6]).values(),
+                    binding.mdn_epilogue_fwd(*x[6:8], w), *binding.mdn_epilogue_bwd(*x[6:8], w, x[8]).values()])
+    assert any(t.data_ptr() % 16 for t in odd) and all(torch.equal(a, b) for a, b in zip(*got))
