@@ -180,37 +180,48 @@ template <typename T> __device__ __forceinline__ T *at32(T *base, unsigned elem_
 
 // A chunk's rows of a [tokens, H, D] tensor as a store target: `rows` rows of stride rs elements from `base` on, `len`
 // elements of a row in reach.  Lanes of rows behind them may store too: the hardware's bounds check drops what lies
-// beyond the last real row, at no cost to a whole chunk (a branch around the store splits the schedule of everything
-// next to it: the gradient kernel took 229 us with branches where it takes 221 us).
-struct RowStore {
-    __amdgpu_buffer_rsrc_t rsrc;
-    template <typename T> __device__ __forceinline__ RowStore(T *base, int rows, unsigned rs, int len)
-        : rsrc(__builtin_amdgcn_make_buffer_rsrc(base, 0, (int)((((unsigned)rows - 1u) * rs + (unsigned)len) * sizeof(T)), 0x00020000)) {}
+// beyond the last real row (a branch around the store splits the schedule of everything next to it: the gradient kernel
+// took 3.6 % longer with branches).  WHOLE (see whole_chunks): there are no such rows, and a plain store does without the four
+// scalar registers of a descriptor.
+template <typename T, bool WHOLE> struct RowStore {
+    struct Checked {
+        __amdgpu_buffer_rsrc_t rsrc;
+        __device__ __forceinline__ Checked(T *base, int rows, unsigned rs, int len)
+            : rsrc(__builtin_amdgcn_make_buffer_rsrc(base, 0, (int)((((unsigned)rows - 1u) * rs + (unsigned)len) * sizeof(T)), 0x00020000)) {}
+    };
+    struct Plain {
+        T *base;
+        __device__ __forceinline__ Plain(T *b, int, unsigned, int) : base(b) {}
+    };
+    typename std::conditional<WHOLE, Plain, Checked>::type to;
+    __device__ __forceinline__ RowStore(T *base, int rows, unsigned rs, int len) : to(base, rows, rs, len) {}
     // one lane's 8 or 16 bytes at element offset `off`
-    template <typename T, typename V> __device__ __forceinline__ void put(unsigned off, V v) const {
-        if constexpr (sizeof(V) == 16) {
+    template <typename V> __device__ __forceinline__ void put(unsigned off, V v) const {
+        if constexpr (WHOLE) {
+            *reinterpret_cast<V *>(at32(to.base, off)) = v;
+        } else if constexpr (sizeof(V) == 16) {
             typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rsrc, off * (unsigned)sizeof(T), 0, 0);
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), to.rsrc, off * (unsigned)sizeof(T), 0, 0);
         } else {
             static_assert(sizeof(V) == 8, "8 or 16 bytes");
             typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), rsrc, off * (unsigned)sizeof(T), 0, 0);
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), to.rsrc, off * (unsigned)sizeof(T), 0, 0);
         }
     }
     // MV * 4 consecutive elements in storage form (see store_cols_raw)
-    template <typename T, int MV> __device__ __forceinline__ void put_cols(unsigned off, const typename Raw4<T>::type (&u)[MV]) const {
+    template <int MV> __device__ __forceinline__ void put_cols(unsigned off, const typename Raw4<T>::type (&u)[MV]) const {
         if constexpr (sizeof(T) == 2 && MV == 2) {
-            put<T>(off, __builtin_shufflevector(u[0], u[1], 0, 1, 2, 3, 4, 5, 6, 7));
+            put(off, __builtin_shufflevector(u[0], u[1], 0, 1, 2, 3, 4, 5, 6, 7));
         } else {
 #pragma unroll
-            for (int mv = 0; mv < MV; ++mv) put<T>(off + mv * 4, u[mv]);
+            for (int mv = 0; mv < MV; ++mv) put(off + mv * 4, u[mv]);
         }
     }
-    template <typename T, int MV> __device__ __forceinline__ void put_narrowed(unsigned off, const f32x4 (&v)[MV]) const {
+    template <int MV> __device__ __forceinline__ void put_narrowed(unsigned off, const f32x4 (&v)[MV]) const {
         typename Raw4<T>::type u[MV];
 #pragma unroll
         for (int mv = 0; mv < MV; ++mv) u[mv] = narrow4<T>(v[mv]);
-        put_cols<T, MV>(off, u);
+        put_cols<MV>(off, u);
     }
 };
 
@@ -274,14 +285,14 @@ template <int M, int K> struct ATile<bf16_t, M, K> {
 // at the next LDS instruction.  Waiting for the transfer is the caller's job (a vector-memory wait of the
 // issuing wave that covers it, before the barrier that publishes the tile); the compiler's own waits for loads
 // it knows of can only become longer through the extra entries in the queue, never shorter (loads return in
-// order).  last: the last row that exists (rows behind it receive copies of it).
-template <typename T, int D, int NW = 2>
-__device__ __forceinline__ void dma_token_tile(T *ldst, const T *src, unsigned rs, int lw, int lane, int last = 63) {
+// order).  !WHOLE: `last` is the last row that exists (rows behind it receive copies of it).
+template <typename T, int D, int NW, bool WHOLE>
+__device__ __forceinline__ void dma_token_tile(T *ldst, const T *src, unsigned rs, int lw, int lane, int last) {
     constexpr int E = Op<T>::EPL, CPR = D / E, XM = (CPR < 16 ? CPR : 16) - 1, NDMA = CPR / NW;
 #pragma unroll
     for (int u = 0; u < NDMA; ++u) {
         const int blk64 = u * NW + lw, sl = blk64 * 64 + lane, row = sl / CPR, pc = (sl % CPR) ^ (row & XM);
-        const T *g = at32(src, min(row, last) * rs + pc * E);
+        const T *g = at32(src, (WHOLE ? row : min(row, last)) * rs + pc * E);
         const unsigned l = (unsigned)(size_t)((__attribute__((address_space(3))) T *)(ldst + blk64 * 64 * E));
         asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(g), "s"(l) : "memory", "m0");
     }

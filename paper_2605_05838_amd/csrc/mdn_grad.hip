@@ -81,7 +81,8 @@ __device__ __forceinline__ void sched_fence() { __builtin_amdgcn_sched_barrier(0
 
 // LO: the rounding remainders of the four state tensors are given as well (GradArgs::states_lo, dstates_lo): the three
 // state traces and the products of dS', dM' with V~ then take hi + lo of their factors.
-template <typename T, int DK, int DV, bool STAGED, bool LO>
+// WHOLE: see whole_chunks.
+template <typename T, int DK, int DV, bool STAGED, bool LO, bool WHOLE>
 __global__ __launch_bounds__(GT) void grad_kernel(Dims d, GradArgs a) {
     typedef Op<T> O;
     typedef typename O::Frag Frag;
@@ -169,17 +170,18 @@ __global__ __launch_bounds__(GT) void grad_kernel(Dims d, GradArgs a) {
 
     // The workgroup walks the chunks c, c + gridDim.x, ... of this launch (c counts the chunks [n0, n1) of all
     // (batch, head) pairs, chunk index fastest; packed batches: the chunks of all sequences, then the heads).
-    const int nper = d.chunks ? d.nchunks : d.n1 - d.n0, nchunks = nper * (d.chunks ? d.H : d.BH);
+    const bool tables = !WHOLE && d.chunks;
+    const int nper = tables ? d.nchunks : d.n1 - d.n0, nchunks = nper * (tables ? d.H : d.BH);
     int chunk = blockIdx.x;
     if (chunk >= nchunks) return;
     size_t tok0, blk;
     int rows; // tokens of the chunk being requested; rows behind them are identity steps of the recurrence
     const T *qg, *kgl, *vtg, *dog, *drg, *KTg, *QTg, *Sg, *Mg, *dSg, *dMg, *Slg = nullptr, *dSlg = nullptr;
     auto set_chunk = [&](int c) {
-        const ChunkPos cp = chunk_pos(d, c % nper, c / nper);
+        const ChunkPos cp = chunk_pos<WHOLE>(d, c % nper, c / nper);
         tok0 = cp.tok;
         blk = cp.blk;
-        rows = cp.rows;
+        rows = WHOLE ? 64 : cp.rows;
         qg = static_cast<const T *>(a.q) + tok0 * DK;
         kgl = static_cast<const T *>(a.k) + tok0 * DK;
         vtg = static_cast<const T *>(a.vt_saved) + tok0 * DV;
@@ -201,8 +203,8 @@ __global__ __launch_bounds__(GT) void grad_kernel(Dims d, GradArgs a) {
     // fragment of row `row`, contraction step st of a token tile (in LDS, or in global memory with row stride ld)
     auto tfrag = [&](const T *tile, int ld, int row, int st) -> Frag {
         if (STAGED) return O::load(tile + row * D + (((st * CPS + kg) ^ (row & XM)) * E));
-        const Frag f = O::load(at32(tile, min(row, rows - 1) * ld + st * O::KSTEP + kg * E));
-        return row < rows ? f : Frag{};
+        const Frag f = O::load(at32(tile, (WHOLE ? row : min(row, rows - 1)) * ld + st * O::KSTEP + kg * E));
+        return WHOLE || row < rows ? f : Frag{};
     };
     // A fragment (row dk = 16 kt + r, tokens 32 s + 8 kg ..) of the transpose of a token tile in LDS: two transposing
     // reads; lane 4e + c of a 16-lane group addresses tokens 32 s + 8 kg (+ 4) + e, dk 16 kt + 4c .. 4c+3
@@ -240,7 +242,7 @@ __global__ __launch_bounds__(GT) void grad_kernel(Dims d, GradArgs a) {
     float n_al = 0.f, n_be = 0.f, n_mu = 0.f, n_et = 1.f; // gates of token `lane` of the chunk being requested
     auto request_gates = [&]() {
         if (w < 6) { // waves 6, 7 never use them, and must not wait for anything behind their tile transfers
-            const unsigned g = min(gl, (unsigned)((rows - 1) * d.H));
+            const unsigned g = WHOLE ? gl : min(gl, (unsigned)((rows - 1) * d.H));
             n_al = *at32(a.alpha + tok0, g);
             n_be = *at32(a.beta + tok0, g);
             n_mu = *at32(a.mu + tok0, g);
@@ -248,7 +250,7 @@ __global__ __launch_bounds__(GT) void grad_kernel(Dims d, GradArgs a) {
         }
     };
     auto request_tile = [&](T *ldst, const T *src, unsigned rs) { // (waves 6, 7)
-        dma_token_tile<T, D>(ldst, src, rs, w - 6, lane, rows - 1);
+        dma_token_tile<T, D, 2, WHOLE>(ldst, src, rs, w - 6, lane, rows - 1);
     };
     // ---- phase 0: forward coefficients of the chunk whose gates are in n_*: waves 0-3 the matrices Gamma, Rho
     //      (16 rows each), wave 4 the vectors by wave scans
@@ -259,7 +261,7 @@ __global__ __launch_bounds__(GT) void grad_kernel(Dims d, GradArgs a) {
         g_be = n_be;
         g_mu = n_mu;
         g_et = n_et;
-        if (lane >= rows) {
+        if (!WHOLE && lane >= rows) {
             g_al = g_mu = 1.f;
             g_be = g_et = 0.f;
         }
@@ -301,7 +303,7 @@ __global__ __launch_bounds__(GT) void grad_kernel(Dims d, GradArgs a) {
     const T *tVt = STAGED ? sVt : vtg, *tK = STAGED ? sK : kgl, *tQ = STAGED ? sQ : qg, *tDR = STAGED ? sDR : drg, *tDO = STAGED ? sDO : dog;
     if (STAGED && w >= 6) __builtin_amdgcn_s_waitcnt(0x0F70); // vmcnt(0): this chunk's tiles have landed
     __syncthreads(); // token tiles in LDS, coefficients ready
-    const int rows_cur = rows;
+    const int rows_cur = WHOLE ? 64 : rows;
     if (STAGED && rows_cur < 64) { // a partial chunk: the rows behind its tokens arrived as copies of the last one
 #pragma unroll 1
         for (int x = tid; x < (64 - rows_cur) * CPR; x += GT) {
@@ -447,10 +449,10 @@ __global__ __launch_bounds__(GT) void grad_kernel(Dims d, GradArgs a) {
 #pragma unroll
         for (int t = 0; t < TT; ++t) {
             const int it = (tg * TT + t) * 16 + r;
-            const unsigned o = (unsigned)min(it, rows_cur - 1) * rsk + kt * 16 + kg * 4;
+            const unsigned o = (unsigned)(WHOLE ? it : min(it, rows_cur - 1)) * rsk + kt * 16 + kg * 4;
             kv[t] = load4_raw(at32(kgl, o));
             qv[t] = load4_raw(at32(qg, o));
-            if (it >= rows_cur) kv[t] = qv[t] = typename Raw4<T>::type{};
+            if (!WHOLE && it >= rows_cur) kv[t] = qv[t] = typename Raw4<T>::type{};
         }
         sched_fence(); // q, k rows are needed first: keep them ahead of the state tiles in the return order
     }
@@ -513,7 +515,6 @@ __global__ __launch_bounds__(GT) void grad_kernel(Dims d, GradArgs a) {
     float p1 = 0.f, p2 = 0.f, p3 = 0.f; // partial <dS',S>, <dS',M>, <dM',M>
     f32x4 t1[TT], t2[TT];
 
-    const RowStore st_dq(static_cast<T *>(a.dq) + tok0 * DK, rows_cur, rsk, DK), st_dk(static_cast<T *>(a.dk) + tok0 * DK, rows_cur, rsk, DK);
     // C: S and M against dO
     if (!DEEP) load_state(fM, Mg);
     state_product2(fS, fM, tDO, t1, t2);
@@ -528,7 +529,7 @@ __global__ __launch_bounds__(GT) void grad_kernel(Dims d, GradArgs a) {
         ra[t] = dot4(t1[t], qw);
         rb[t] = dot4(t2[t], qw);
         accQ[t] += s_a[it] * t1[t] - s_b[it] * t2[t];
-        st_dq.template put<T>(it * rsk + kt * 16 + kg * 4, narrow4<T>(d.scale * accQ[t]));
+        RowStore<T, WHOLE>(static_cast<T *>(a.dq) + tok0 * DK, rows_cur, rsk, DK).put(it * rsk + kt * 16 + kg * 4, narrow4<T>(d.scale * accQ[t]));
     }
     {
         const float da = d.scale * reduce_tiles(ra), db = -d.scale * reduce_tiles(rb);
@@ -593,7 +594,7 @@ __global__ __launch_bounds__(GT) void grad_kernel(Dims d, GradArgs a) {
         rb[t] = dot4(t2[t], kw);
         accK[t] += s_gC[it] * t1[t] - s_rC[it] * t2[t];
         rc[t] = dot4(accK[t], kw);
-        st_dk.template put<T>(it * rsk + kt * 16 + kg * 4, narrow4<T>(s_et[it] * accK[t] + s_al[it] * accP[t]));
+        RowStore<T, WHOLE>(static_cast<T *>(a.dk) + tok0 * DK, rows_cur, rsk, DK).put(it * rsk + kt * 16 + kg * 4, narrow4<T>(s_et[it] * accK[t] + s_al[it] * accP[t]));
     }
     {
         const float et_i = s_et[itg];
@@ -723,7 +724,7 @@ __global__ __launch_bounds__(GT) void grad_kernel(Dims d, GradArgs a) {
         const float bprev = wave_up1(pb, 0.f, lane), mprev = wave_up1(pm, 1.f, lane);
         const float b_prev = (li > 0) ? bprev : 0.f, m_prev = (li > 0) ? mprev : 1.f;
         const unsigned g = (unsigned)(li * d.H);
-        if (li < rows_cur) {
+        if (WHOLE || li < rows_cur) {
             *at32(a.dalpha + tok0_cur, g) = s_ga[li] + db * b_prev + s_da[li];
             *at32(a.dbeta + tok0_cur, g) = s_gb[li] + db * pm;
             *at32(a.dmu + tok0_cur, g) = s_gm[li] + dm * m_prev;
@@ -740,13 +741,17 @@ __global__ __launch_bounds__(GT) void grad_kernel(Dims d, GradArgs a) {
     } // chunks of this workgroup
 }
 
-template <typename T, int DK, int DV, bool STAGED, bool LO = false>
-hipError_t launch_t(const Dims &d, const GradArgs &a, hipStream_t s) {
+template <typename T, int DK, int DV, bool STAGED, bool LO, bool WHOLE>
+hipError_t launch_w(const Dims &d, const GradArgs &a, hipStream_t s) {
     // staged (bf16): one workgroup per CU, each walking its share of the chunks; otherwise one per chunk
     const int nchunks = chunk_grid_x(d) * chunk_grid_y(d);
     dim3 grid(STAGED && nchunks > num_cus() ? num_cus() : nchunks), block(GT);
-    hipLaunchKernelGGL((grad_kernel<T, DK, DV, STAGED, LO>), grid, block, 0, s, d, a);
+    hipLaunchKernelGGL((grad_kernel<T, DK, DV, STAGED, LO, WHOLE>), grid, block, 0, s, d, a);
     return hipGetLastError();
+}
+template <typename T, int DK, int DV, bool STAGED, bool LO = false>
+hipError_t launch_t(const Dims &d, const GradArgs &a, hipStream_t s) {
+    return whole_chunks(d) ? launch_w<T, DK, DV, STAGED, LO, true>(d, a, s) : launch_w<T, DK, DV, STAGED, LO, false>(d, a, s);
 }
 
 } // namespace

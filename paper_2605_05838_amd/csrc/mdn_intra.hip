@@ -47,7 +47,8 @@ __device__ __forceinline__ void store_tile_64cols(T *dst, const T *src, int ld, 
 
 // MODE 0: forward operands; 1: operands of the reverse pass; 2: both (training forward that keeps the
 // reverse pass's operands instead of recomputing them)
-template <typename T, int DK, int DV, int MODE>
+// WHOLE: see whole_chunks.
+template <typename T, int DK, int DV, int MODE, bool WHOLE>
 __global__ __launch_bounds__(kThreads) void intra_kernel(Dims d, IntraArgs a) {
     constexpr bool FWD = MODE != 1, BWD = MODE != 0;
     typedef Op<T> O;
@@ -74,10 +75,10 @@ __global__ __launch_bounds__(kThreads) void intra_kernel(Dims d, IntraArgs a) {
     T *sKT = sR, *sXT = sR + DK * LDT;    // phase B (aliases phase A)
 
     const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
-    const ChunkPos cp = chunk_pos(d, blockIdx.x, blockIdx.y);
+    const ChunkPos cp = chunk_pos<WHOLE>(d, blockIdx.x, blockIdx.y);
     const size_t tok0 = cp.tok, blk = cp.blk; // (blk: chunk-block index into the workspace tensors)
     // rows from `rows` on are identity steps: their loads go to the last real row and are replaced
-    const int rows = cp.rows;
+    const int rows = WHOLE ? 64 : cp.rows;
     const T *qg = static_cast<const T *>(a.q) + tok0 * DK;
     const T *kg_ = static_cast<const T *>(a.k) + tok0 * DK;
     const size_t rsk = (size_t)d.H * DK;
@@ -85,14 +86,14 @@ __global__ __launch_bounds__(kThreads) void intra_kernel(Dims d, IntraArgs a) {
 
     // ---- the gates first, then the K, Q tiles: all loads in flight at once; the coefficient scans below need
     //      only the gates and run while the tiles are on their way
-    const size_t gtok = tok0 + (size_t)min(lane, rows - 1) * d.H;
+    const size_t gtok = tok0 + (size_t)(WHOLE ? lane : min(lane, rows - 1)) * d.H;
     float g_al = a.alpha[gtok], g_be = a.beta[gtok], g_mu = a.mu[gtok], g_et = a.eta ? a.eta[gtok] : 1.f;
     typename O::Frag rk[NVK], rq[NVK];
     {
         constexpr int CPR = DK / E;
 #pragma unroll
         for (int u = 0; u < NVK; ++u) {
-            const int c = tid + u * kThreads, row = min(c / CPR, rows - 1), cc = c % CPR;
+            const int c = tid + u * kThreads, row = WHOLE ? c / CPR : min(c / CPR, rows - 1), cc = c % CPR;
             rk[u] = O::load(kg_ + row * rsk + cc * E);
             rq[u] = O::load(qg + row * rsk + cc * E);
         }
@@ -106,18 +107,18 @@ __global__ __launch_bounds__(kThreads) void intra_kernel(Dims d, IntraArgs a) {
     if constexpr (!TRT) {
 #pragma unroll
         for (int u = 0; u < NVK; ++u) {
-            const int c = tid + u * kThreads, row = min(c % 64, rows - 1), cc = c / 64;
+            const int c = tid + u * kThreads, row = WHOLE ? c % 64 : min(c % 64, rows - 1), cc = c / 64;
             rkt[u] = *reinterpret_cast<const Vec16<T> *>(kg_ + row * rsk + cc * E);
         }
         if (BWD) {
 #pragma unroll
             for (int u = 0; u < NVX; ++u) {
-                const int c = tid + u * kThreads, row = min(c % 64, rows - 1), cc = c / 64;
+                const int c = tid + u * kThreads, row = WHOLE ? c % 64 : min(c % 64, rows - 1), cc = c / 64;
                 rxt[u] = *reinterpret_cast<const Vec16<T> *>(qg + row * rsk + cc * E);
             }
         }
     }
-    if (rows < 64) { // (wave-uniform: a whole chunk skips this)
+    if (!WHOLE && rows < 64) { // (wave-uniform: a whole chunk skips this)
         if (lane >= rows) g_al = g_mu = 1.f, g_be = g_et = 0.f;
         constexpr int CPR = DK / E;
 #pragma unroll
@@ -302,13 +303,17 @@ __global__ __launch_bounds__(kThreads) void intra_kernel(Dims d, IntraArgs a) {
     }
 }
 
+template <typename T, int DK, int DV, bool WHOLE>
+hipError_t launch_intra_w(const Dims &d, int mode, const IntraArgs &a, hipStream_t s) {
+    dim3 grid(chunk_grid_x(d), chunk_grid_y(d)), block(kThreads);
+    if (mode == 0) hipLaunchKernelGGL((intra_kernel<T, DK, DV, 0, WHOLE>), grid, block, 0, s, d, a);
+    else if (mode == 1) hipLaunchKernelGGL((intra_kernel<T, DK, DV, 1, WHOLE>), grid, block, 0, s, d, a);
+    else hipLaunchKernelGGL((intra_kernel<T, DK, DV, 2, WHOLE>), grid, block, 0, s, d, a);
+    return hipGetLastError();
+}
 template <typename T, int DK, int DV>
 hipError_t launch_intra_t(const Dims &d, int mode, const IntraArgs &a, hipStream_t s) {
-    dim3 grid(chunk_grid_x(d), chunk_grid_y(d)), block(kThreads);
-    if (mode == 0) hipLaunchKernelGGL((intra_kernel<T, DK, DV, 0>), grid, block, 0, s, d, a);
-    else if (mode == 1) hipLaunchKernelGGL((intra_kernel<T, DK, DV, 1>), grid, block, 0, s, d, a);
-    else hipLaunchKernelGGL((intra_kernel<T, DK, DV, 2>), grid, block, 0, s, d, a);
-    return hipGetLastError();
+    return whole_chunks(d) ? launch_intra_w<T, DK, DV, true>(d, mode, a, s) : launch_intra_w<T, DK, DV, false>(d, mode, a, s);
 }
 
 } // namespace

@@ -100,7 +100,8 @@ __device__ __forceinline__ void fetch_chunk(RevOps<T, DK, DVB / 16> &c, const Di
     fetch_part<T, DK, DV, DVB, 4>(c, d, a, sq, n, dv0, itok);
 }
 
-template <typename T, int DK, int DV, int DVB>
+// WHOLE: see whole_chunks.
+template <typename T, int DK, int DV, int DVB, bool WHOLE>
 __global__ __launch_bounds__(kThreads) void scan_bwd_kernel(Dims d, ScanBwdArgs a) {
     typedef Op<T> O;
     typedef RevOps<T, DK, DVB / 16> CO;
@@ -119,12 +120,12 @@ __global__ __launch_bounds__(kThreads) void scan_bwd_kernel(Dims d, ScanBwdArgs 
     int bh, blkv;
     xcd_map(blockIdx.x, G, bh, blkv);
     if (bh >= d.BH) return;
-    const ScanSeq sq = scan_seq(d, bh);
+    const ScanSeq sq = scan_seq<WHOLE>(d, bh);
     const int dv0 = blkv * DVB;
     const int lane = lane_id(), w = wave_id(), r = lane & 15, kg = lane >> 4, i = w * 16 + r;
     // a partial last chunk (the first one here): its loads stop at the last real token
-    const int ragged = sq.len & 63 ? sq.len >> 6 : -1, last = (sq.len & 63) - 1; // that chunk (or none), its last row
-    const unsigned iH = (unsigned)(i * d.H), itok = sq.n1 - 1 == ragged ? (unsigned)(min(i, last) * d.H) : iH;
+    const int ragged = !WHOLE && (sq.len & 63) ? sq.len >> 6 : -1, last = (sq.len & 63) - 1; // that chunk (or none), its last row
+    const unsigned iH = (unsigned)(i * d.H), itok = !WHOLE && sq.n1 - 1 == ragged ? (unsigned)(min(i, last) * d.H) : iH;
 
     // element x of tile (mv, nd): dS[dk = (w*ND + nd)*16 + r][dv = mv*16 + kg*4 + x]
     f32x4 accS[MV][ND], accM[MV][ND];
@@ -141,7 +142,7 @@ __global__ __launch_bounds__(kThreads) void scan_bwd_kernel(Dims d, ScanBwdArgs 
     auto step = [&](int n, const CO &cur, CO &nxt) {
         const size_t blk = sq.blk + n;
         const int nn = n > sq.n0 ? n - 1 : sq.n0;
-        const unsigned itn = nn == ragged ? itok : iH;
+        const unsigned itn = !WHOLE && nn == ragged ? itok : iH;
         fetch_part<T, DK, DV, DVB, 0>(nxt, d, a, sq, nn, dv0, itn);
 
         // adjoints of this chunk's END states: operand copy to LDS, storage copy to HBM.  (The stores cost this
@@ -234,8 +235,8 @@ __global__ __launch_bounds__(kThreads) void scan_bwd_kernel(Dims d, ScanBwdArgs 
                     dR[mv] = O::mma(TV::frag(sDV, mv, s * O::KSTEP, r, kg), cur.tT[s], dR[mv]);
             fetch_part<T, DK, DV, DVB, 4>(nxt, d, a, sq, nn, dv0, itn);
             const size_t tok0 = sq.tok + (size_t)n * 64 * d.H;
-            RowStore(static_cast<T *>(a.dv) + tok0 * DV + dv0, n == ragged ? last + 1 : 64, d.H * DV, DVB)
-                .template put_narrowed<T, MV>(iH * DV + kg * (4 * MV), dR);
+            RowStore<T, WHOLE>(static_cast<T *>(a.dv) + tok0 * DV + dv0, !WHOLE && n == ragged ? last + 1 : 64, d.H * DV, DVB)
+                .template put_narrowed<MV>(iH * DV + kg * (4 * MV), dR);
 #pragma unroll
             for (int mv = 0; mv < MV; ++mv) {
                 TV::put4(sRa, mv * 16 + kg * 4, i, -cur.c0[COEF_A] * dR[mv]);
@@ -297,15 +298,20 @@ __global__ __launch_bounds__(kThreads) void scan_bwd_kernel(Dims d, ScanBwdArgs 
         }
 }
 
-template <typename T, int DK, int DV, int DVB>
-hipError_t launch_t(const Dims &d, const ScanBwdArgs &a, hipStream_t s) {
+template <typename T, int DK, int DV, int DVB, bool WHOLE>
+hipError_t launch_w(const Dims &d, const ScanBwdArgs &a, hipStream_t s) {
     constexpr int G = DV / DVB;
     dim3 grid(((d.BH + 7) / 8) * 8 * G), block(kThreads);
     static const size_t spread =
-        lds_bytes_for_one_workgroup_per_cu(reinterpret_cast<const void *>(&scan_bwd_kernel<T, DK, DV, DVB>));
+        lds_bytes_for_one_workgroup_per_cu(reinterpret_cast<const void *>(&scan_bwd_kernel<T, DK, DV, DVB, WHOLE>));
     const size_t dyn = (int)grid.x <= num_cus() ? spread : 0; // no more workgroups than CUs: one per CU
-    hipLaunchKernelGGL((scan_bwd_kernel<T, DK, DV, DVB>), grid, block, dyn, s, d, a);
+    hipLaunchKernelGGL((scan_bwd_kernel<T, DK, DV, DVB, WHOLE>), grid, block, dyn, s, d, a);
     return hipGetLastError();
+}
+
+template <typename T, int DK, int DV, int DVB>
+hipError_t launch_t(const Dims &d, const ScanBwdArgs &a, hipStream_t s) {
+    return whole_chunks(d) ? launch_w<T, DK, DV, DVB, true>(d, a, s) : launch_w<T, DK, DV, DVB, false>(d, a, s);
 }
 
 template <typename T, int DK, int DV> hipError_t pick_dvb(const Dims &d, const ScanBwdArgs &a, hipStream_t s) {

@@ -132,7 +132,8 @@ __device__ __forceinline__ void publish_state(T *sSt, const f32x4 (&accS)[MV][DK
 
 // REBUILD = false: full forward scan.  REBUILD = true: state reconstruction from saved V~ only
 // (the update lines), writing the chunk-start states.
-template <typename T, int DK, int DV, int DVB, bool REBUILD>
+// WHOLE: see whole_chunks.
+template <typename T, int DK, int DV, int DVB, bool REBUILD, bool WHOLE>
 __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(Dims d, ScanFwdArgs a) {
     typedef Op<T> O;
     typedef ChunkOps<T, DK, DVB / 16> CO;
@@ -156,11 +157,11 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(Dims d, ScanFwdArgs 
     int bh, blkv;
     xcd_map(blockIdx.x, G, bh, blkv);
     if (bh >= d.BH) return;
-    const ScanSeq sq = scan_seq(d, bh);
+    const ScanSeq sq = scan_seq<WHOLE>(d, bh);
     const int dv0 = blkv * DVB;
     const int lane = lane_id(), w = wave_id(), r = lane & 15, kg = lane >> 4, i = w * 16 + r;
     // a partial last chunk: its loads stop at the last real token
-    const int ragged = sq.len & 63 ? sq.len >> 6 : -1, last = (sq.len & 63) - 1; // that chunk (or none), its last row
+    const int ragged = !WHOLE && (sq.len & 63) ? sq.len >> 6 : -1, last = (sq.len & 63) - 1; // that chunk (or none), its last row
     const unsigned iH = (unsigned)(i * d.H);
     unsigned itok = iH;
 
@@ -171,13 +172,13 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(Dims d, ScanFwdArgs 
             T *dst = sKr + slot * (64 * DK);
             const unsigned rs = (unsigned)(d.H * DK);
             const int ws = __builtin_amdgcn_readfirstlane(w);
-            if (n == ragged) dma_token_tile<T, DK, 4>(dst, kg0, rs, ws, lane, last);
-            else dma_token_tile<T, DK, 4>(dst, kg0, rs, ws, lane);
+            if (!WHOLE && n == ragged) dma_token_tile<T, DK, 4, false>(dst, kg0, rs, ws, lane, last);
+            else dma_token_tile<T, DK, 4, true>(dst, kg0, rs, ws, lane, 63);
         }
     };
     request_k(sq.n0, 0);
     request_k(sq.n0 + 1 < sq.n1 ? sq.n0 + 1 : sq.n0, 1);
-    if (sq.n0 == ragged) itok = (unsigned)(min(i, last) * d.H);
+    if (!WHOLE && sq.n0 == ragged) itok = (unsigned)(min(i, last) * d.H);
 
     f32x4 accS[MV][ND], accM[MV][ND];
 #pragma unroll
@@ -258,8 +259,8 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(Dims d, ScanFwdArgs 
         const size_t blk = sq.blk + n;
         const size_t tok0 = sq.tok + (size_t)n * 64 * d.H; // (uniform base + 32-bit lane offset, as in fetch_part)
         const int nn = (n + 1 < sq.n1) ? n + 1 : n;
-        const int rows = n == ragged ? last + 1 : 64; // tokens of this chunk: their outputs are stored
-        if (nn == ragged) itok = (unsigned)(min(i, last) * d.H); // (the chunk requested from here on is the partial one)
+        const int rows = !WHOLE && n == ragged ? last + 1 : 64; // tokens of this chunk: their outputs are stored
+        if (!WHOLE && nn == ragged) itok = (unsigned)(min(i, last) * d.H); // (the chunk requested from here on is the partial one)
         const T *kc = sKr + slot * (64 * DK);
         if (n + 2 < sq.n1) request_k(n + 2, slot >= 1 ? slot - 1 : 2);
         slot = slot == 2 ? 0 : slot + 1;
@@ -332,7 +333,7 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(Dims d, ScanFwdArgs 
                 vt[mv] = widen4_packed(vb[mv]);
             }
             if (a.vt_saved) {
-                RowStore(static_cast<T *>(a.vt_saved) + tok0 * DV + dv0, rows, d.H * DV, DVB).template put_cols<T, MV>(iH * DV + kg * (4 * MV), vb);
+                RowStore<T, WHOLE>(static_cast<T *>(a.vt_saved) + tok0 * DV + dv0, rows, d.H * DV, DVB).template put_cols<MV>(iH * DV + kg * (4 * MV), vb);
             }
         } else {
 #pragma unroll
@@ -404,7 +405,7 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(Dims d, ScanFwdArgs 
                 sblk = blk + 1;
                 emit_states(std::integral_constant<int, 0>{});
             }
-            RowStore(static_cast<T *>(a.o) + tok0 * DV + dv0, rows, d.H * DV, DVB).template put_narrowed<T, MV>(iH * DV + kg * (4 * MV), accO);
+            RowStore<T, WHOLE>(static_cast<T *>(a.o) + tok0 * DV + dv0, rows, d.H * DV, DVB).template put_narrowed<MV>(iH * DV + kg * (4 * MV), accO);
         }
         emit_in_step(std::integral_constant<int, 7>{});
         __syncthreads();
@@ -433,15 +434,20 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(Dims d, ScanFwdArgs 
 }
 
 
-template <typename T, int DK, int DV, int DVB, bool REBUILD>
-hipError_t launch_scan_t(const Dims &d, const ScanFwdArgs &a, hipStream_t s) {
+template <typename T, int DK, int DV, int DVB, bool REBUILD, bool WHOLE>
+hipError_t launch_scan_w(const Dims &d, const ScanFwdArgs &a, hipStream_t s) {
     constexpr int G = DV / DVB;
     dim3 grid(((d.BH + 7) / 8) * 8 * G), block(kThreads);
     static const size_t spread = lds_bytes_for_one_workgroup_per_cu(
-        reinterpret_cast<const void *>(&scan_fwd_kernel<T, DK, DV, DVB, REBUILD>));
+        reinterpret_cast<const void *>(&scan_fwd_kernel<T, DK, DV, DVB, REBUILD, WHOLE>));
     const size_t dyn = (int)grid.x <= num_cus() ? spread : 0; // no more workgroups than CUs: one per CU
-    hipLaunchKernelGGL((scan_fwd_kernel<T, DK, DV, DVB, REBUILD>), grid, block, dyn, s, d, a);
+    hipLaunchKernelGGL((scan_fwd_kernel<T, DK, DV, DVB, REBUILD, WHOLE>), grid, block, dyn, s, d, a);
     return hipGetLastError();
+}
+
+template <typename T, int DK, int DV, int DVB, bool REBUILD>
+hipError_t launch_scan_t(const Dims &d, const ScanFwdArgs &a, hipStream_t s) {
+    return whole_chunks(d) ? launch_scan_w<T, DK, DV, DVB, REBUILD, true>(d, a, s) : launch_scan_w<T, DK, DV, DVB, REBUILD, false>(d, a, s);
 }
 
 template <typename T, int DK, int DV, bool REBUILD>

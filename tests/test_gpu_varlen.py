@@ -181,3 +181,26 @@ def test_short_sequences_merged_into_pieces(dtype, d, lens):
     """Calls without states that save an eighth of their chunks by merging neighbours (one piece for everything, starts on
     and off chunk boundaries, more starts than one launch takes), every sequence against the oracle by itself."""
     test_packed_sequences_as_one_stream_of_tokens(dtype, d, lens)
+
+
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("bf16", 64), ("f32", 128), ("bf16", 128)])
+def test_packed_sequences_of_whole_chunks_equal_the_fixed_length_batch(dtype, d):
+    """The kernels' instances for whole chunks against the general ones: a batch of two sequences and the same sequences packed
+    (with states: one set of launches, nothing merged) go through the same arithmetic, so every output agrees bit for bit."""
+    B, T, H = 2, 192, 3
+    w = synth.custom(B=B, T=T, H=H, dk=d, dv=d, dtype=dtype, seed=75, with_eta=True, s0_std=0.2, backward=True)
+    t = to_dev(w)
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    M0, dS, dM = (0.2 * torch.randn((B, H, d, d), device="cuda", generator=gen) for _ in range(3))
+    row = lambda x: x.reshape(1, B * T, *x.shape[2:])
+    x = [t[k] for k in ("q", "k", "v", "beta", "alpha", "mu")]
+    for adjoints in ({}, dict(dS_final=dS, dM_final=dM)):
+        kw = dict(S0=t["S0"], M0=M0, scale=w.scale)
+        f = binding.mdn_chunk_fwd(*x, eta=t["eta"], save_vt=True, **kw)
+        g = binding.mdn_chunk_bwd(*x, f["vt"], t["dO"], eta=t["eta"], want_deta=True, **adjoints, **kw)
+        p, cu = [row(a) for a in x], [0, T, 2 * T]
+        pf = binding.mdn_chunk_fwd_varlen(*p, cu, eta=row(t["eta"]), save_vt=True, **kw)
+        pg = binding.mdn_chunk_bwd_varlen(*p, pf["vt"], row(t["dO"]), cu, eta=row(t["eta"]), want_deta=True, **adjoints, **kw)
+        for k, v in {**pf, **pg}.items():
+            ref = f[k] if k in f else g[k]
+            assert torch.equal(v.reshape(ref.shape), ref), k
