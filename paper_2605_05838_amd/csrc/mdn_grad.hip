@@ -124,6 +124,7 @@ __global__ __launch_bounds__(GT) void grad_kernel(Dims d, GradArgs a) {
     __shared__ __align__(16) float s_al[64], s_et[64], s_a[64], s_b[64];
     __shared__ float sRowC[3 * 64]; // reverse scan: the three per-row coefficients
     __shared__ float s_gC[64], s_rC[64];
+    __shared__ float s_m[STAGED ? 1 : 64]; // (32-bit storage has no register for m_lane from here to the end of the chunk)
     __shared__ float s_ga[64], s_gb[64], s_gm[64];
     __shared__ float s_da[64], s_de[64]; // wave 5's share of dalpha, and deta, for wave 4's final sums
     __shared__ float s_red[8][3];
@@ -202,9 +203,8 @@ __global__ __launch_bounds__(GT) void grad_kernel(Dims d, GradArgs a) {
 
     // fragment of row `row`, contraction step st of a token tile (in LDS, or in global memory with row stride ld)
     auto tfrag = [&](const T *tile, int ld, int row, int st) -> Frag {
-        if (STAGED) return O::load(tile + row * D + (((st * CPS + kg) ^ (row & XM)) * E));
-        const Frag f = O::load(at32(tile, (WHOLE ? row : min(row, rows - 1)) * ld + st * O::KSTEP + kg * E));
-        return WHOLE || row < rows ? f : Frag{};
+        if constexpr (STAGED) return O::load(tile + row * D + (((st * CPS + kg) ^ (row & XM)) * E));
+        else return load_row_or_zeros(tile, rows, (unsigned)ld, D, row * ld + st * O::KSTEP + kg * E);
     };
     // A fragment (row dk = 16 kt + r, tokens 32 s + 8 kg ..) of the transpose of a token tile in LDS: two transposing
     // reads; lane 4e + c of a 16-lane group addresses tokens 32 s + 8 kg (+ 4) + e, dk 16 kt + 4c .. 4c+3
@@ -283,6 +283,7 @@ __global__ __launch_bounds__(GT) void grad_kernel(Dims d, GradArgs a) {
             s_et[lane] = g_et;
             s_a[lane] = pa;
             s_b[lane] = pb;
+            if (!STAGED) s_m[lane] = pm;
         }
     };
 
@@ -445,14 +446,13 @@ __global__ __launch_bounds__(GT) void grad_kernel(Dims d, GradArgs a) {
         }
     }
     __syncthreads();
-    if (!STAGED) { // (staged: taken from the tiles in LDS before the W matrices replaced them)
+    if constexpr (!STAGED) { // (staged: taken from the tiles in LDS before the W matrices replaced them)
 #pragma unroll
         for (int t = 0; t < TT; ++t) {
             const int it = (tg * TT + t) * 16 + r;
-            const unsigned o = (unsigned)(WHOLE ? it : min(it, rows_cur - 1)) * rsk + kt * 16 + kg * 4;
-            kv[t] = load4_raw(at32(kgl, o));
-            qv[t] = load4_raw(at32(qg, o));
-            if (!WHOLE && it >= rows_cur) kv[t] = qv[t] = typename Raw4<T>::type{};
+            const unsigned o = it * rsk + kt * 16 + kg * 4;
+            kv[t] = load_row_or_zeros(kgl, rows_cur, rsk, D, o);
+            qv[t] = load_row_or_zeros(qg, rows_cur, rsk, D, o);
         }
         sched_fence(); // q, k rows are needed first: keep them ahead of the state tiles in the return order
     }
@@ -721,6 +721,7 @@ __global__ __launch_bounds__(GT) void grad_kernel(Dims d, GradArgs a) {
     __syncthreads();
     if (w == 4) {
         const int li = lane;
+        if (!STAGED) pb = s_b[li], pm = s_m[li];
         const float bprev = wave_up1(pb, 0.f, lane), mprev = wave_up1(pm, 1.f, lane);
         const float b_prev = (li > 0) ? bprev : 0.f, m_prev = (li > 0) ? mprev : 1.f;
         const unsigned g = (unsigned)(li * d.H);
@@ -751,7 +752,9 @@ hipError_t launch_w(const Dims &d, const GradArgs &a, hipStream_t s) {
 }
 template <typename T, int DK, int DV, bool STAGED, bool LO = false>
 hipError_t launch_t(const Dims &d, const GradArgs &a, hipStream_t s) {
-    return whole_chunks(d) ? launch_w<T, DK, DV, STAGED, LO, true>(d, a, s) : launch_w<T, DK, DV, STAGED, LO, false>(d, a, s);
+    if constexpr (STAGED)
+        if (whole_chunks(d)) return launch_w<T, DK, DV, STAGED, LO, true>(d, a, s);
+    return launch_w<T, DK, DV, STAGED, LO, false>(d, a, s); // (32-bit: row limits cost nothing, see load_row_or_zeros)
 }
 
 } // namespace

@@ -6,10 +6,10 @@
 namespace mdn {
 
 // Whether every chunk of a launch has 64 tokens and lies where arithmetic finds it.  The kernels' instances for that case
-// (WHOLE) carry neither tables nor row limits.  Those cost registers that the kernels are short of: the 16-bit d = 128 gradient
-// kernel spills 15 scalar registers with them and 4 without, the 32-bit one 4 vector registers and none.  A pass in us, all
-// launches by the general instances / by these: 8 x 2 048 tokens of 8 heads of 128 forward 92.5 / 91.4; forward and backward,
-// 4 x 4 096 of 16 heads of 128 695 / 685, of 64 442 / 434, 32-bit 4 x 1 024 of 8 heads of 128 369 / 354.
+// (WHOLE) carry neither tables nor row limits, which cost registers that the kernels are short of: the 16-bit d = 128 gradient
+// kernel spills 15 scalar registers with them and 4 without.  A pass in us, all launches by the general instances / by these:
+// 8 x 2 048 tokens of 8 heads of 128 forward 92.5 / 91.4; forward and backward, 4 x 4 096 of 16 heads of 128 695 / 685, of 64
+// 442 / 434.
 inline bool whole_chunks(const Dims &d) { return !d.packed && d.T % 64 == 0; }
 
 // one (sequence, head) pair of a scan

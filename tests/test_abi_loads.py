@@ -268,3 +268,28 @@ def test_a_tensor_without_storage_raises_and_the_interpreter_goes_on(tmp_path):
     subprocess.run(["gcc", "-shared", "-fPIC", "-o", stub, str(tmp_path / "stub.c")], check=True)
     p = subprocess.run([sys.executable, "-c", NO_STORAGE, stub], cwd=ROOT, capture_output=True, text=True, timeout=300)
     assert p.returncode == 0 and p.stdout.strip() == "raised", (p.returncode, p.stderr[-2000:])
+
+
+def test_no_kernel_spills_vector_registers(tmp_path):
+    """The kernels are laid out to fit the register file: what the compiler puts into scratch memory instead is stored and
+    loaded again by every lane.  Read from the metadata of the kernels as built here."""
+    import glob
+    import subprocess
+    objs = sorted(glob.glob(os.path.join(ROOT, "paper_2605_05838_amd", "_build", "mdn_*.o")))
+    tools = "/opt/rocm/llvm/bin/"
+    if not objs or not os.path.exists(tools + "llvm-readelf"):
+        pytest.skip("needs the objects of a build and the LLVM tools")
+    kernels = {}
+    for obj in objs:
+        bundle, code = str(tmp_path / "bundle"), str(tmp_path / "code")
+        if subprocess.run([tools + "llvm-objcopy", "--dump-section", ".hip_fatbin=" + bundle, obj, "/dev/null"],
+                          capture_output=True).returncode:
+            continue                                          # (the binding's module holds no kernels)
+        subprocess.run([tools + "clang-offload-bundler", "--unbundle", "--type=o", "--input=" + bundle, "--output=" + code,
+                        "--targets=hipv4-amdgcn-amd-amdhsa--gfx950"], check=True, capture_output=True)
+        notes = subprocess.run([tools + "llvm-readelf", "--notes", code], check=True, capture_output=True, text=True).stdout
+        for k in notes.split("- .agpr_count:")[1:]:
+            field = lambda name: re.search(rf"\.{name}:\s+(\S+)", k)[1]
+            kernels[field("name")] = int(field("private_segment_fixed_size")), int(field("vgpr_spill_count"))
+    assert len(kernels) > 50 and any("grad_kernel" in k for k in kernels)
+    assert not [k for k, v in kernels.items() if v != (0, 0)]
