@@ -69,7 +69,11 @@ enum {
     MDN_ERR_DEVICE = -7     /* the current device is not a gfx950 GPU */
 };
 
-enum { MDN_WS_FWD = 0, MDN_WS_BWD = 1, MDN_WS_BWD_STATE_ADJOINTS = 2 };
+enum {
+    MDN_WS_FWD = 0, MDN_WS_BWD = 1, MDN_WS_BWD_STATE_ADJOINTS = 2,
+    /* mdn_workspace_bytes_varlen only */
+    MDN_WS_FWD_NO_STATES = 3, MDN_WS_BWD_NO_STATES = 4, MDN_WS_BWD_NO_STATE_ADJOINTS = 5
+};
 
 typedef struct mdn_shape {
     int32_t B, T, H;  /* batch, sequence length, heads */
@@ -165,9 +169,13 @@ int mdn_chunk_bwd(const mdn_shape *shape, const void *q, const void *k, const vo
  * returns), and the scans of all sequences run beside each other, the longest first.  Sequences far shorter than a chunk:
  * a call without states (S0, M0, S_final, M_final or S0, M0, dS_final, dM_final, dS0, dM0 all NULL) merges neighbours into
  * pieces of up to 512 tokens whose state is cut at the inner starts by zeroed alpha and mu (in copies); a call with states
- * goes group by group, so that its workspace stays bounded.  The backward reconstructs the
- * states and recomputes the operands (no states_saved / operands_saved here).  workspace: mdn_workspace_bytes_varlen
- * (MDN_WS_FWD or MDN_WS_BWD; the latter is enough for calls with adjoints of the final states as well).
+ * goes group by group, so that its workspace stays bounded: forward by 3 times that of T unbroken tokens (or, if more, 65 536 chunk
+ * blocks, 1.2 GB of 16-bit storage), backward by 5/4 of it (or 512 MiB), also with adjoints of the final states; one sequence
+ * by itself takes what it needs.  The backward reconstructs the states and recomputes the operands (no states_saved /
+ * operands_saved here).
+ * workspace: a call needs what mdn_workspace_bytes_varlen reports for what it passes.  MDN_WS_FWD and MDN_WS_BWD are enough for
+ * any call; MDN_WS_FWD_NO_STATES and MDN_WS_BWD_NO_STATES for calls without states as above; MDN_WS_BWD_NO_STATE_ADJOINTS for
+ * calls with dS_final and dM_final NULL.
  * Errors as for the fixed-length calls; MDN_ERR_SHAPE also for inconsistent cu_seqlens.
  */
 int mdn_workspace_bytes_varlen(const mdn_shape *shape, const int32_t *cu_seqlens, int32_t n_seq, int which, size_t *bytes_out);

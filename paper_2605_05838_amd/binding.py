@@ -20,6 +20,7 @@ LIB_PATH = os.path.join(_HERE, "libmdn_hip.so")
 
 MDN_DTYPE_BF16, MDN_DTYPE_F32 = 0, 1
 MDN_WS_FWD, MDN_WS_BWD, MDN_WS_BWD_STATE_ADJOINTS = 0, 1, 2
+MDN_WS_FWD_NO_STATES, MDN_WS_BWD_NO_STATES, MDN_WS_BWD_NO_STATE_ADJOINTS = 3, 4, 5 # packed batches only
 
 EXPORTS = ("mdn_version", "mdn_strerror", "mdn_workspace_bytes", "mdn_saved_states_bytes",
            "mdn_saved_operands_bytes", "mdn_chunk_fwd", "mdn_chunk_fwd_noalloc",

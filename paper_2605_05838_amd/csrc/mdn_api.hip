@@ -521,24 +521,55 @@ int check_varlen(const mdn_shape *shape, const int32_t *cu, int32_t n_seq, Dims 
     return MDN_OK;
 }
 
+// bytes that a chunk block takes in the workspace of a backward call (see carve_bwd)
+size_t bwd_block_bytes(const Dims &d, bool precise) {
+    const size_t state = (size_t)2 * d.dk * d.dv; // S and M of a chunk, elements
+    return 64 * kCoefBlockCols * sizeof(float) + (2 * d.dk * 64 + 2 * 4096 + (precise ? 4 : 2) * state) * elem_size(d);
+}
+
 // Every sequence has chunk blocks of its own, so sequences far shorter than a chunk need up to 64 times the blocks of
-// their tokens.  Such a batch runs group by group on one workspace: a group ends before it needs more blocks than three times
-// those of T unbroken tokens, or than 65 536 (256 per CU, with which a group fills the GPU long enough for its boundary
-// not to matter).  Sequences of 32 tokens and more on average are always one group.
-struct SeqGroup { int s0, s1; Dims d; }; // sequences [s0, s1); a single sequence is an ordinary batch of one (no tables)
-SeqGroup next_group(const Dims &d, const int32_t *cu, int32_t n_seq, int s0) {
-    SeqGroup g{s0, n_seq, d};
-    if (n_seq == 1) return g;
-    const long long most = std::max(65536LL / d.H, 3LL * d.N), most_seqs = std::max(1, (1 << 24) / d.H);
+// their tokens, and the remainders of a `precise` backward double the largest part of a block.  A batch that needs too much
+// at once runs group by group on one workspace.  A forward's group ends before it needs more than three times the blocks of T
+// unbroken tokens, or than 65 536 (1.2 GB of 16-bit storage, d = 128); a backward's before it needs more bytes than 5/4
+// of what T unbroken tokens take, or than 512 MiB (3 000 such blocks, 12 per CU: the boundary between two groups costs a few
+// launches and the wait for the longest sequence of the first).  Sequences of 128 tokens and more on average are one group
+// unless they are precise; a longer sequence than that is a group of its own, whatever it needs.
+struct SeqGroup { int s0, s1; Dims d; }; // sequences [s0, s1); a single one is an ordinary batch of one (no tables)
+struct Grouping { long long limit, left; }; // chunks of one group at most; chunks of the groups still to come
+int seq_chunks(const int32_t *cu, int i) { return (int)(((long long)cu[i + 1] - cu[i] + 63) / 64); }
+Dims one_sequence(const Dims &d, const int32_t *cu, int i) {
+    Dims r = d;
+    r.B = 1; r.T = cu[i + 1] - cu[i]; r.BH = d.H; r.N = r.n1 = r.nchunks = seq_chunks(cu, i);
+    r.packed = false;
+    return r;
+}
+Grouping grouping(const Dims &d, const int32_t *cu, int32_t n_seq, bool backward, bool precise) {
+    Grouping g{std::max(65536LL / d.H, 3LL * d.N), 0};
+    if (backward) {
+        const size_t most = std::max((size_t)512 << 20, (size_t)d.N * d.H * bwd_block_bytes(d, false) / 4 * 5);
+        g.limit = std::max(1LL, (long long)(most / (d.H * bwd_block_bytes(d, precise))));
+    }
+    for (int i = 0; i < n_seq; ++i) g.left += seq_chunks(cu, i);
+    return g;
+}
+SeqGroup next_group(const Dims &d, const int32_t *cu, int32_t n_seq, int s0, Grouping *gr) {
+    // (as few groups as the limit allows share the chunks evenly)
+    const long long groups = (gr->left + gr->limit - 1) / gr->limit, share = (gr->left + groups - 1) / groups;
+    const int last = std::min(n_seq, s0 + std::max(1, (1 << 24) / d.H));
     long long chunks = 0, longest = 0;
     int i = s0;
-    for (; i < n_seq && i - s0 < most_seqs; ++i) {
-        const long long N = ((long long)cu[i + 1] - cu[i] + 63) / 64;
-        if (i > s0 && chunks + N > most) break;
+    for (; i < last && chunks < share; ++i) {
+        const long long N = seq_chunks(cu, i);
+        if (i > s0 && chunks + N > gr->limit) break;
         chunks += N;
         longest = std::max(longest, N);
     }
-    g.s1 = i;
+    gr->left -= chunks;
+    SeqGroup g{s0, i, d};
+    if (i - s0 == 1) {
+        g.d = one_sequence(d, cu, s0);
+        return g;
+    }
     g.d.B = i - s0; g.d.BH = g.d.B * d.H; g.d.N = g.d.n1 = (int)longest; g.d.nchunks = (int)chunks;
     g.d.packed = true;
     return g;
@@ -558,13 +589,20 @@ PackedWs carve_packed(const Dims &d, void *ws) {
     return w;
 }
 
-// what the largest group needs (`precise`: see carve_bwd)
-size_t packed_ws_total(const Dims &d, const int32_t *cu, int32_t n_seq, bool backward, bool precise) {
+// What a packed call brings in and asks for, which decides the form it runs in: without states it may be merged (see
+// merge_short); with adjoints of the final states a 16-bit backward is precise (see precise_call).
+struct PackedForm { bool backward, states, adjoints; };
+bool precise_form(const Dims &d, PackedForm f) { return f.adjoints && d.dtype == MDN_DTYPE_BF16; }
+
+// what the largest group needs
+size_t packed_ws_total(const Dims &d, const int32_t *cu, int32_t n_seq, PackedForm f) {
+    const bool precise = precise_form(d, f);
+    Grouping gr = grouping(d, cu, n_seq, f.backward, precise);
     size_t most = 0;
     for (int s0 = 0; s0 < n_seq;) {
-        const SeqGroup g = next_group(d, cu, n_seq, s0);
+        const SeqGroup g = next_group(d, cu, n_seq, s0, &gr);
         most = std::max(most, carve_packed(g.d, nullptr).head +
-                                  (backward ? carve_bwd(g.d, nullptr, precise).total : carve_fwd(g.d, nullptr).total));
+                                  (f.backward ? carve_bwd(g.d, nullptr, precise).total : carve_fwd(g.d, nullptr).total));
         s0 = g.s1;
     }
     return most;
@@ -599,14 +637,42 @@ int packed_tables(SeqGroup *g, const int32_t *cu, const PackedWs &w, hipStream_t
     return MDN_OK;
 }
 
-// run(sizes of a group, workspace behind its tables) for every group, one after the other on the stream
-template <typename F>
-int packed_run(const Dims &d, const int32_t *cu, int32_t n_seq, void *workspace, hipStream_t s, F &&run) {
+// A call on one sequence of a packed batch, as a batch of one: its first token (a row of the [T, H, *] tensors) and its index
+// in the state tensors.
+struct SeqOffset {
+    size_t qk, v, gate, state; // bytes
+    SeqOffset(const Dims &d, int token, int seq)
+        : qk((size_t)token * d.H * d.dk * elem_size(d)), v((size_t)token * d.H * d.dv * elem_size(d)),
+          gate((size_t)token * d.H * sizeof(float)), state((size_t)seq * d.H * d.dk * d.dv * sizeof(float)) {}
+    template <typename P> static void move(P *&p, size_t bytes) {
+        if (p) p = reinterpret_cast<P *>(reinterpret_cast<uintptr_t>(p) + bytes);
+    }
+};
+FwdCall at_sequence(FwdCall c, const SeqOffset &o) {
+    o.move(c.q, o.qk); o.move(c.k, o.qk); o.move(c.v, o.v); o.move(c.o, o.v); o.move(c.vt_saved, o.v);
+    o.move(c.beta, o.gate); o.move(c.alpha, o.gate); o.move(c.mu, o.gate); o.move(c.eta, o.gate);
+    o.move(c.S0, o.state); o.move(c.M0, o.state); o.move(c.S_final, o.state); o.move(c.M_final, o.state);
+    return c;
+}
+BwdCall at_sequence(BwdCall c, const SeqOffset &o) {
+    o.move(c.q, o.qk); o.move(c.k, o.qk); o.move(c.dq, o.qk); o.move(c.dk, o.qk);
+    o.move(c.v, o.v); o.move(c.vt_saved, o.v); o.move(c.dO, o.v); o.move(c.dv, o.v);
+    o.move(c.beta, o.gate); o.move(c.alpha, o.gate); o.move(c.mu, o.gate); o.move(c.eta, o.gate);
+    o.move(c.dbeta, o.gate); o.move(c.dalpha, o.gate); o.move(c.dmu, o.gate); o.move(c.deta, o.gate);
+    o.move(c.S0, o.state); o.move(c.M0, o.state); o.move(c.dS_final, o.state); o.move(c.dM_final, o.state);
+    o.move(c.dS0, o.state); o.move(c.dM0, o.state);
+    return c;
+}
+
+// run(sizes of a group, its call, workspace behind its tables) for every group, one after the other on the stream
+template <typename C, typename F>
+int packed_run(const Dims &d, const int32_t *cu, int32_t n_seq, PackedForm f, const C &c, void *workspace, hipStream_t s, F &&run) {
+    Grouping gr = grouping(d, cu, n_seq, f.backward, precise_form(d, f));
     for (int s0 = 0; s0 < n_seq;) {
-        SeqGroup g = next_group(d, cu, n_seq, s0);
+        SeqGroup g = next_group(d, cu, n_seq, s0, &gr);
         const PackedWs w = carve_packed(g.d, workspace);
         int rc = packed_tables(&g, cu, w, s);
-        if (!rc) rc = run(g.d, w.rest);
+        if (!rc) rc = run(g.d, g.d.packed ? c : at_sequence(c, SeqOffset(d, cu[s0], s0)), w.rest);
         if (rc) return rc;
         s0 = g.s1;
     }
@@ -670,6 +736,16 @@ MergedWs carve_merged(const Dims &d, void *ws) {
     w.head = c.off;
     w.rest = ws ? static_cast<char *>(ws) + c.off : nullptr;
     return w;
+}
+// the workspace of a call of this form, and whether (and how) it is merged
+int packed_need(const Dims &d, const int32_t *cu, int32_t n_seq, PackedForm f, Merged *m, size_t *bytes) {
+    if (!f.states) {
+        const int rc = merge_short(d, cu, n_seq, m);
+        if (rc) return rc;
+    }
+    *bytes = m->used ? carve_merged(d, nullptr).head + packed_ws_total(d, m->cu.data(), (int)m->cu.size() - 1, f)
+                     : packed_ws_total(d, cu, n_seq, f);
+    return MDN_OK;
 }
 int merged_gates(const Dims &d, const Merged &m, const float *alpha, const float *mu, const MergedWs &w, hipStream_t s) {
     if (launch_copy_gates(alpha, mu, w.alpha, w.mu, (long long)d.T * d.H, s) != hipSuccess) return MDN_ERR_LAUNCH;
@@ -860,15 +936,18 @@ int mdn_workspace_bytes_varlen(const mdn_shape *shape, const int32_t *cu_seqlens
     if (!bytes_out) return MDN_ERR_NULL;
     const int rc = check_varlen(shape, cu_seqlens, n_seq, &d);
     if (rc) return rc;
-    if (which != MDN_WS_FWD && which != MDN_WS_BWD) return MDN_ERR_SHAPE;
-    // (a backward call may bring adjoints of the final states in: room for the rounding remainders as well)
-    size_t most = packed_ws_total(d, cu_seqlens, n_seq, which == MDN_WS_BWD, d.dtype == MDN_DTYPE_BF16);
-    Merged m; // (without states the call may take this form)
-    const int rm = merge_short(d, cu_seqlens, n_seq, &m);
-    if (rm) return rm;
-    if (m.used)
-        most = std::max(most, carve_merged(d, nullptr).head +
-                                  packed_ws_total(d, m.cu.data(), (int)m.cu.size() - 1, which == MDN_WS_BWD, false));
+    const bool backward = which == MDN_WS_BWD || which == MDN_WS_BWD_NO_STATES || which == MDN_WS_BWD_NO_STATE_ADJOINTS;
+    if (!backward && which != MDN_WS_FWD && which != MDN_WS_FWD_NO_STATES) return MDN_ERR_SHAPE;
+    // of the forms that such a call may take, the most that one of them needs
+    const bool states = which != MDN_WS_FWD_NO_STATES && which != MDN_WS_BWD_NO_STATES, adjoints = which == MDN_WS_BWD;
+    size_t most = 0;
+    for (int i = 0; i < 1 + states + adjoints; ++i) {
+        Merged m;
+        size_t bytes = 0;
+        const int rf = packed_need(d, cu_seqlens, n_seq, PackedForm{backward, i > 0, i > 1}, &m, &bytes);
+        if (rf) return rf;
+        most = std::max(most, bytes);
+    }
     *bytes_out = most;
     return MDN_OK;
 }
@@ -884,26 +963,21 @@ int mdn_chunk_fwd_varlen(const mdn_shape *shape, const int32_t *cu_seqlens, int3
     const void *ptrs[] = {q, k, v, beta, alpha, mu, eta, S0, M0, o, S_final, M_final, vt_saved, workspace};
     for (const void *p : ptrs)
         if (p && misaligned(p)) return MDN_ERR_ALIGN;
+    const PackedForm form = {false, S0 || M0 || S_final || M_final, false};
+    Merged m;
     size_t need = 0;
-    rc = mdn_workspace_bytes_varlen(shape, cu_seqlens, n_seq, MDN_WS_FWD, &need);
+    rc = packed_need(d, cu_seqlens, n_seq, form, &m, &need);
     if (rc) return rc;
     if (workspace_bytes < need) return MDN_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
     FwdCall c = {q, k, v, beta, alpha, mu, eta, S0, M0, o, S_final, M_final, vt_saved, nullptr, nullptr};
-    if (!S0 && !M0 && !S_final && !M_final) {
-        Merged m;
-        rc = merge_short(d, cu_seqlens, n_seq, &m);
-        if (rc) return rc;
-        if (m.used) {
-            const MergedWs w = carve_merged(d, workspace);
-            rc = merged_gates(d, m, alpha, mu, w, s);
-            if (rc) return rc;
-            c.alpha = w.alpha; c.mu = w.mu;
-            return packed_run(d, m.cu.data(), (int)m.cu.size() - 1, w.rest, s,
-                              [&](const Dims &g, void *ws) { return run_fwd(g, c, carve_fwd(g, ws), s); });
-        }
-    }
-    return packed_run(d, cu_seqlens, n_seq, workspace, s, [&](const Dims &g, void *ws) { return run_fwd(g, c, carve_fwd(g, ws), s); });
+    auto run = [&](const Dims &g, const FwdCall &cg, void *ws) { return run_fwd(g, cg, carve_fwd(g, ws), s); };
+    if (!m.used) return packed_run(d, cu_seqlens, n_seq, form, c, workspace, s, run);
+    const MergedWs w = carve_merged(d, workspace);
+    rc = merged_gates(d, m, alpha, mu, w, s);
+    if (rc) return rc;
+    c.alpha = w.alpha; c.mu = w.mu;
+    return packed_run(d, m.cu.data(), (int)m.cu.size() - 1, form, c, w.rest, s, run);
 }
 
 int mdn_chunk_bwd_varlen(const mdn_shape *shape, const int32_t *cu_seqlens, int32_t n_seq, const void *q, const void *k,
@@ -921,28 +995,23 @@ int mdn_chunk_bwd_varlen(const mdn_shape *shape, const int32_t *cu_seqlens, int3
                           dmu, deta, dS0, dM0, workspace};
     for (const void *p : ptrs)
         if (p && misaligned(p)) return MDN_ERR_ALIGN;
+    const PackedForm form = {true, S0 || M0 || dS_final || dM_final || dS0 || dM0, dS_final || dM_final};
+    Merged m;
     size_t need = 0;
-    rc = mdn_workspace_bytes_varlen(shape, cu_seqlens, n_seq, MDN_WS_BWD, &need);
+    rc = packed_need(d, cu_seqlens, n_seq, form, &m, &need);
     if (rc) return rc;
     if (workspace_bytes < need) return MDN_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
     BwdCall c = {q, k, v, beta, alpha, mu, eta, S0, M0, vt_saved, nullptr, nullptr, dO, dS_final, dM_final,
                  dq, dk, dv, dbeta, dalpha, dmu, deta, dS0, dM0};
-    if (!S0 && !M0 && !dS_final && !dM_final && !dS0 && !dM0) {
-        Merged m;
-        rc = merge_short(d, cu_seqlens, n_seq, &m);
-        if (rc) return rc;
-        if (m.used) {
-            const MergedWs w = carve_merged(d, workspace);
-            rc = merged_gates(d, m, alpha, mu, w, s);
-            if (rc) return rc;
-            c.alpha = w.alpha; c.mu = w.mu;
-            rc = packed_run(d, m.cu.data(), (int)m.cu.size() - 1, w.rest, s,
-                            [&](const Dims &g, void *ws) { return bwd_all(g, c, ws, s); });
-            return rc ? rc : clear_at_starts(d, m, dalpha, dmu, s);
-        }
-    }
-    return packed_run(d, cu_seqlens, n_seq, workspace, s, [&](const Dims &g, void *ws) { return bwd_all(g, c, ws, s); });
+    auto run = [&](const Dims &g, const BwdCall &cg, void *ws) { return bwd_all(g, cg, ws, s); };
+    if (!m.used) return packed_run(d, cu_seqlens, n_seq, form, c, workspace, s, run);
+    const MergedWs w = carve_merged(d, workspace);
+    rc = merged_gates(d, m, alpha, mu, w, s);
+    if (rc) return rc;
+    c.alpha = w.alpha; c.mu = w.mu;
+    rc = packed_run(d, m.cu.data(), (int)m.cu.size() - 1, form, c, w.rest, s, run);
+    return rc ? rc : clear_at_starts(d, m, dalpha, dmu, s);
 }
 
 int mdn_recurrent_step(const mdn_shape *shape, const void *q, const void *k, const void *v, const float *beta,

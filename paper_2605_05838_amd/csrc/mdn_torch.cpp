@@ -419,7 +419,8 @@ PyObject *chunk_fwd_varlen(PyObject *const *x) {
     }
     if (truth(x[11])) vt = empty({1, in.T, in.H, in.dv}, in.dt, q);
     size_t nb = 0;
-    check(mdn_workspace_bytes_varlen(&in.s, cu.data(), (int32_t)n, MDN_WS_FWD, &nb), "mdn_workspace_bytes_varlen");
+    const int which = in.S0 || in.M0 || S ? MDN_WS_FWD : MDN_WS_FWD_NO_STATES;
+    check(mdn_workspace_bytes_varlen(&in.s, cu.data(), (int32_t)n, which, &nb), "mdn_workspace_bytes_varlen");
     at::Tensor ws = bytes(nb, q);
     on_gpu(q);
     void *st = stream();
@@ -449,7 +450,8 @@ PyObject *chunk_bwd_varlen(PyObject *const *x) {
     expect("dM_final", dM, {n, in.H, in.dk, in.dv}, at::kFloat, q);
     const Grads g(nullptr, in, truth(x[15]), truth(x[16]), n);
     size_t nb = 0;
-    check(mdn_workspace_bytes_varlen(&in.s, cu.data(), (int32_t)n, MDN_WS_BWD, &nb), "mdn_workspace_bytes_varlen");
+    const int which = dS || dM ? MDN_WS_BWD : in.S0 || in.M0 || g.dS0 ? MDN_WS_BWD_NO_STATE_ADJOINTS : MDN_WS_BWD_NO_STATES;
+    check(mdn_workspace_bytes_varlen(&in.s, cu.data(), (int32_t)n, which, &nb), "mdn_workspace_bytes_varlen");
     at::Tensor ws = bytes(nb, q);
     on_gpu(q);
     void *st = stream();

@@ -114,6 +114,41 @@ def test_varlen_workspace_query_validates_the_offsets():
     assert lib.mdn_workspace_bytes_varlen(ctypes.byref(s1), None, 2, 0, ctypes.byref(n)) == -1
 
 
+@pytest.mark.parametrize("n", [1, 2, 8, 64, 512, 4096])
+def test_varlen_workspace_follows_what_the_call_brings_in_and_stays_bounded(n):
+    """32 768 tokens of 16 heads of 128 in n sequences.  Calls without adjoints of the final states need what one unbroken sequence
+    does, up to a quarter more for partial chunks and 64 bytes a token for tables and copies of the gates; so do calls with
+    adjoints, unless one long sequence by itself needs more (it also keeps the rounding remainders of its states)."""
+    T, H = 32768, 16
+    s = shape(B=1, T=T, H=H)
+    w = [1 + (7 * i) % 13 for i in range(n)]
+    at = lambda i: sum(w[:i]) * (T - n) // sum(w) + i
+    cu = (ctypes.c_int32 * (n + 1))(*[at(i) for i in range(n)], T)
+    lib = binding.load_library()
+
+    def need(which):
+        b = ctypes.c_size_t(0)
+        assert lib.mdn_workspace_bytes_varlen(ctypes.byref(s), cu, n, which, ctypes.byref(b)) == 0
+        return b.value
+    whole = binding.workspace_bytes(s, binding.MDN_WS_BWD)
+    extra = 64 * T
+    assert need(binding.MDN_WS_BWD_NO_STATES) <= 5 * whole // 4 + extra
+    assert need(binding.MDN_WS_BWD_NO_STATES) <= need(binding.MDN_WS_BWD_NO_STATE_ADJOINTS) <= 5 * whole // 4 + extra
+    longest = shape(B=1, T=max(cu[i + 1] - cu[i] for i in range(n)), H=H)
+    most = max(5 * whole // 4, binding.workspace_bytes(longest, binding.MDN_WS_BWD_STATE_ADJOINTS))
+    assert need(binding.MDN_WS_BWD_NO_STATE_ADJOINTS) <= need(binding.MDN_WS_BWD) <= most + extra
+    assert need(binding.MDN_WS_FWD_NO_STATES) <= need(binding.MDN_WS_FWD)
+    bytes_out = ctypes.c_size_t(0)
+    for which in (2, 6, -1):
+        assert lib.mdn_workspace_bytes_varlen(ctypes.byref(s), cu, n, which, ctypes.byref(bytes_out)) == -2
+    g = ctypes.c_void_p(4096)
+    inputs = [g] * 6 + [None]                             # q k v beta alpha mu eta
+    for state, adjoint in ((None, None), (g, None), (g, g)):
+        assert lib.mdn_chunk_fwd_varlen(ctypes.byref(s), cu, n, *inputs, state, None, g, None, None, None, g, 1 << 20, None) == -4
+        assert lib.mdn_chunk_bwd_varlen(ctypes.byref(s), cu, n, *inputs, state, None, g, g, adjoint, None, *[g] * 6, None, None, None,
+                                        g, 1 << 20, None) == -4
+
+
 def _cpu_inputs(B=1, T=64, H=2, d=64, dtype=None):
     import torch
     dtype = dtype or torch.float32

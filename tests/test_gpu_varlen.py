@@ -147,8 +147,8 @@ def test_packed_states_in_and_out_of_many_short_and_of_uneven_sequences(dtype, n
 
 
 def test_packed_batch_of_very_short_sequences_runs_group_by_group():
-    """16 heads x 5 000 sequences of 1 .. 7 tokens need 80 000 chunk blocks, more than one group's 65 536: outputs, states
-    and gradients are bit for bit those of the same sequences in two calls that are one group each."""
+    """16 heads x 5 000 sequences of 1 .. 7 tokens need 80 000 chunk blocks, more than one group takes: outputs, states and
+    gradients are bit for bit those of the same sequences in two calls (whose groups are others)."""
     H, d, n = 16, 64, 5000
     lens = [1 + (5 * i + i // 7) % 7 for i in range(n)]
     cu = np.concatenate([[0], np.cumsum(lens)]).tolist()
@@ -204,3 +204,40 @@ def test_packed_sequences_of_whole_chunks_equal_the_fixed_length_batch(dtype, d)
         for k, v in {**pf, **pg}.items():
             ref = f[k] if k in f else g[k]
             assert torch.equal(v.reshape(ref.shape), ref), k
+
+
+def _by_sequence(t, cu, scale, states=None, adjoints=None):
+    """The gradients of a packed batch from one call per sequence (and the forward's outputs): states S0, M0, adjoints dS, dM of
+    all sequences, or None."""
+    parts = {}
+    for i in range(len(cu) - 1):
+        sl = slice(cu[i], cu[i + 1])
+        x = [t[k][:, sl].clone() for k in ("q", "k", "v", "beta", "alpha", "mu")]
+        kw = dict(scale=scale, eta=t["eta"][:, sl].clone())
+        if states:
+            kw.update(S0=states[0][i:i + 1], M0=states[1][i:i + 1])
+        f = binding.mdn_chunk_fwd(*x, save_vt=True, **kw)
+        if adjoints:
+            kw.update(dS_final=adjoints[0][i:i + 1], dM_final=adjoints[1][i:i + 1])
+        g = binding.mdn_chunk_bwd(*x, f["vt"], t["dO"][:, sl].clone(), want_deta=True, **kw)
+        for k, v in {**f, **g}.items():
+            if torch.is_tensor(v) and k != "workspace":
+                parts.setdefault(k, []).append(v)
+    return {k: torch.cat(v, dim=0 if k in ("S", "M", "dS0", "dM0") else 1) for k, v in parts.items()}
+
+
+def test_sequences_that_are_groups_of_their_own_equal_calls_on_each():
+    """Adjoints of the final states come in and each of the two sequences needs more than half of a group's limit: they run one
+    after the other, as batches of one (17 heads: the second one's gates are not 16-byte aligned)."""
+    H, d, cu = 17, 128, [0, 3845, 7685]
+    w = synth.custom(B=1, T=cu[-1], H=H, dk=d, dv=d, dtype="bf16", seed=76, with_eta=True, backward=True)
+    t = to_dev(w)
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    S0, M0, dS, dM = (0.2 * torch.randn((2, H, d, d), device="cuda", generator=gen) for _ in range(4))
+    ref = _by_sequence(t, cu, w.scale, (S0, M0), (dS, dM))
+    x = [t[k] for k in ("q", "k", "v", "beta", "alpha", "mu")]
+    kw = dict(eta=t["eta"], S0=S0, M0=M0, scale=w.scale)
+    f = binding.mdn_chunk_fwd_varlen(*x, cu, save_vt=True, **kw)
+    g = binding.mdn_chunk_bwd_varlen(*x, f["vt"], t["dO"], cu, dS_final=dS, dM_final=dM, want_deta=True, **kw)
+    for k, v in {**f, **g}.items():
+        assert torch.equal(v, ref[k]), k
