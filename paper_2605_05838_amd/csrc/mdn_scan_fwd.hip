@@ -172,8 +172,7 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(Dims d, ScanFwdArgs 
             T *dst = sKr + slot * (64 * DK);
             const unsigned rs = (unsigned)(d.H * DK);
             const int ws = __builtin_amdgcn_readfirstlane(w);
-            if (!WHOLE && n == ragged) dma_token_tile<T, DK, 4, false>(dst, kg0, rs, ws, lane, last);
-            else dma_token_tile<T, DK, 4, true>(dst, kg0, rs, ws, lane, 63);
+            dma_token_tile<T, DK, 4, WHOLE>(dst, kg0, rs, ws, lane, n == ragged ? last : 63);
         }
     };
     request_k(sq.n0, 0);
