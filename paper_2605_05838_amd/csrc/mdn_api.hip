@@ -164,13 +164,14 @@ bool few_scan_workgroups(const Dims &d) { return 2 * scan_workgroups(d) <= num_c
 // heads: 462 / 427 / 440 / 615; 2 048 of d = 64, 4 heads: 1 751 / 1 668 / 1 633 / 1 641); segments of fewer than 32 chunks
 // are all start and drain (512 blocks in 32 chunks of 16 heads: 304 / 315 / 352 / 594).  Forward: 271 / 289 / 299 / 328 for the second row, 1 159 / 1 190 /
 // 1 194 / 1 232 for the last, and slower split than unsplit at every other size measured.
+long long backward_segments(const Dims &d) {
+    const long long grad = (long long)d.N * d.BH * d.dk * (d.dtype == MDN_DTYPE_F32 ? 4 : 1); // its time, in 1/128 blocks
+    return few_scan_workgroups(d) ? std::min({8LL, d.N / 32LL, grad / (128 * 1024)}) : 1;
+}
 int segments(const Dims &d, bool backward) {
     if (t_no_alloc || d.packed) return 1; // (packed batches: the scans of the sequences run beside each other)
     long long k = g_segments.load(std::memory_order_relaxed);
-    if (k <= 0) {
-        const long long grad = (long long)d.N * d.BH * d.dk * (d.dtype == MDN_DTYPE_F32 ? 4 : 1); // its time, in 1/128 blocks
-        k = backward && few_scan_workgroups(d) ? std::min({8LL, d.N / 32LL, grad / (128 * 1024)}) : 1;
-    }
+    if (k <= 0) k = backward ? backward_segments(d) : 1;
     k = std::min(k, (long long)d.N / 4);
     return (int)std::max(1LL, std::min(16LL, k));
 }
@@ -535,7 +536,10 @@ size_t bwd_block_bytes(const Dims &d, bool precise) {
 // launches and the wait for the longest sequence of the first).  Sequences of 128 tokens and more on average are one group
 // unless they are precise; a longer sequence than that is a group of its own, whatever it needs.
 struct SeqGroup { int s0, s1; Dims d; }; // sequences [s0, s1); a single one is an ordinary batch of one (no tables)
-struct Grouping { long long limit, left; }; // chunks of one group at most; chunks of the groups still to come
+struct Grouping {
+    long long limit, left; // chunks of one group at most; chunks of the groups still to come
+    int alone;             // a sequence that is a group of its own, or -1
+};
 int seq_chunks(const int32_t *cu, int i) { return (int)(((long long)cu[i + 1] - cu[i] + 63) / 64); }
 Dims one_sequence(const Dims &d, const int32_t *cu, int i) {
     Dims r = d;
@@ -543,19 +547,48 @@ Dims one_sequence(const Dims &d, const int32_t *cu, int i) {
     r.packed = false;
     return r;
 }
+// The longest sequence of a backward call by itself, before or behind the others, where its gradient kernel can run beside its
+// scans (see backward_segments) and that hides more than running them beside the others' scans would: per 1 024 chunk blocks of
+// the long one ~44 us hidden, against ~40 us for every group that is added and what the others' scans then take by themselves, ~3.8 us
+// a step of their longest or ~0.06 us a chunk block, whichever is more.  (In the unit of a hidden chunk block: 1 000, 88, 3/2.)
+// Backward in us, together / alone, d = 128: 29 500 tokens and 16 of 205, 16 heads 2 122 / 1 947, 8 heads 1 649 / 1 596; 31 130 and
+// 1 638, 16 heads 2 174 / 2 002; not taken: 16 384 and 32 of 512, 8 heads 1 115 / 1 165, 24 576 and 8 192, 16 heads 1 903 / 2 060.
+int long_sequence(const Dims &d, const int32_t *cu, int32_t n_seq) {
+    int a = 0;
+    for (int i = 1; i < n_seq; ++i)
+        if (cu[i + 1] - cu[i] > cu[a + 1] - cu[a]) a = i;
+    const Dims r = one_sequence(d, cu, a);
+    if (backward_segments(r) < 2) return -1;
+    long long groups = 0, steps = 0, blocks = 0;
+    auto others = [&](int i0, int i1) {
+        long long longest = 0;
+        for (int i = i0; i < i1; ++i) {
+            const long long N = seq_chunks(cu, i);
+            longest = std::max(longest, N);
+            blocks += N * d.H;
+        }
+        groups += i1 > i0;
+        steps += longest;
+    };
+    others(0, a);
+    others(a + 1, n_seq);
+    return (long long)r.N * d.H > 1000 * groups + std::max(88 * steps, 3 * blocks / 2) ? a : -1;
+}
 Grouping grouping(const Dims &d, const int32_t *cu, int32_t n_seq, bool backward, bool precise) {
-    Grouping g{std::max(65536LL / d.H, 3LL * d.N), 0};
+    Grouping g{std::max(65536LL / d.H, 3LL * d.N), 0, -1};
     if (backward) {
         const size_t most = std::max((size_t)512 << 20, (size_t)d.N * d.H * bwd_block_bytes(d, false) / 4 * 5);
         g.limit = std::max(1LL, (long long)(most / (d.H * bwd_block_bytes(d, precise))));
     }
     for (int i = 0; i < n_seq; ++i) g.left += seq_chunks(cu, i);
+    if (backward && n_seq > 1) g.alone = long_sequence(d, cu, n_seq);
     return g;
 }
 SeqGroup next_group(const Dims &d, const int32_t *cu, int32_t n_seq, int s0, Grouping *gr) {
     // (as few groups as the limit allows share the chunks evenly)
     const long long groups = (gr->left + gr->limit - 1) / gr->limit, share = (gr->left + groups - 1) / groups;
-    const int last = std::min(n_seq, s0 + std::max(1, (1 << 24) / d.H));
+    const int end = s0 == gr->alone ? s0 + 1 : s0 < gr->alone ? gr->alone : n_seq;
+    const int last = std::min(end, s0 + std::max(1, (1 << 24) / d.H));
     long long chunks = 0, longest = 0;
     int i = s0;
     for (; i < last && chunks < share; ++i) {

@@ -120,8 +120,12 @@ int num_cus();
 // dv columns per workgroup of the scans for this shape: 32, unless that leaves a quarter of the CUs or more without
 // a workgroup or (32-bit storage, d = 128) the prefetched fragments of 32 columns do not fit the registers: then 16
 int scan_dvb(const Dims &d);
-// workgroups of one scan launch: (batch*head rounded up to 8) x dv / scan_dvb
+// workgroups of one scan launch: (batch*head rounded up to 8) x dv / scan_dvb; packed batches: those it takes the longest
+// sequence's time to run
 int scan_workgroups(const Dims &d);
+// Whether a scan launch keeps a second workgroup off every CU (see lds_bytes_for_one_workgroup_per_cu): where the workgroups
+// of the longest sequence's length do not outnumber the CUs.
+bool scan_one_per_cu(const Dims &d);
 
 // mode 0: forward operands, 1: reverse-pass operands, 2: both
 hipError_t launch_intra(const Dims &d, int mode, const IntraArgs &a, hipStream_t s);

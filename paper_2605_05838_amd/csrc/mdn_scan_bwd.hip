@@ -304,7 +304,7 @@ hipError_t launch_w(const Dims &d, const ScanBwdArgs &a, hipStream_t s) {
     dim3 grid(((d.BH + 7) / 8) * 8 * G), block(kThreads);
     static const size_t spread =
         lds_bytes_for_one_workgroup_per_cu(reinterpret_cast<const void *>(&scan_bwd_kernel<T, DK, DV, DVB, WHOLE>));
-    const size_t dyn = (int)grid.x <= num_cus() ? spread : 0; // no more workgroups than CUs: one per CU
+    const size_t dyn = scan_one_per_cu(d) ? spread : 0;
     hipLaunchKernelGGL((scan_bwd_kernel<T, DK, DV, DVB, WHOLE>), grid, block, dyn, s, d, a);
     return hipGetLastError();
 }

@@ -439,7 +439,7 @@ hipError_t launch_scan_w(const Dims &d, const ScanFwdArgs &a, hipStream_t s) {
     dim3 grid(((d.BH + 7) / 8) * 8 * G), block(kThreads);
     static const size_t spread = lds_bytes_for_one_workgroup_per_cu(
         reinterpret_cast<const void *>(&scan_fwd_kernel<T, DK, DV, DVB, REBUILD, WHOLE>));
-    const size_t dyn = (int)grid.x <= num_cus() ? spread : 0; // no more workgroups than CUs: one per CU
+    const size_t dyn = scan_one_per_cu(d) ? spread : 0;
     hipLaunchKernelGGL((scan_fwd_kernel<T, DK, DV, DVB, REBUILD, WHOLE>), grid, block, dyn, s, d, a);
     return hipGetLastError();
 }
@@ -478,12 +478,27 @@ int num_cus() {
     return n;
 }
 
-int scan_dvb(const Dims &d) {
-    const bool f32 = d.dtype == 1;
-    return (4 * d.BH * (d.dv / 32) < 3 * num_cus() || (f32 && d.dk == 128)) ? 16 : 32;
+// (batch, head) pairs of a launch; packed batches: as many as sequences of the longest one's length would make up the batch,
+// every sequence counted with the ~4 steps that its states' way in and out takes.  The launch lasts at least the longest sequence's
+// chain of steps, which is shorter with 16 columns per workgroup and with a CU for each of its workgroups, however many short
+// sequences run beside it.  Forward and backward in us by the number of sequences / by this: 29 500 tokens and 16 of 205, 16 heads
+// of 128 930 + 2 327 / 838 + 2 122, 4 heads of twice that 1 644 + 3 326 / 1 372 + 2 866; 16 384 and 32 of 512, 8 heads
+// 507 + 1 250 / 447 + 1 115.
+static long long scan_pairs(const Dims &d) {
+    return d.packed ? ((long long)d.nchunks + 4LL * d.B) * d.H / (d.N + 4) : d.BH;
 }
 
-int scan_workgroups(const Dims &d) { return (d.BH + 7) / 8 * 8 * (d.dv / scan_dvb(d)); }
+int scan_dvb(const Dims &d) {
+    const bool f32 = d.dtype == 1;
+    return (4 * scan_pairs(d) * (d.dv / 32) < 3 * num_cus() || (f32 && d.dk == 128)) ? 16 : 32;
+}
+
+bool scan_one_per_cu(const Dims &d) {
+    const int wgs = scan_workgroups(d);
+    return wgs <= num_cus() || (d.packed && d.BH >= 2 * scan_pairs(d) && 4 * wgs <= 5 * num_cus());
+}
+
+int scan_workgroups(const Dims &d) { return (int)((scan_pairs(d) + 7) / 8 * 8 * (d.dv / scan_dvb(d))); }
 
 size_t lds_bytes_for_one_workgroup_per_cu(const void *kernel) {
     hipFuncAttributes fa;

@@ -241,3 +241,26 @@ def test_sequences_that_are_groups_of_their_own_equal_calls_on_each():
     g = binding.mdn_chunk_bwd_varlen(*x, f["vt"], t["dO"], cu, dS_final=dS, dM_final=dM, want_deta=True, **kw)
     for k, v in {**f, **g}.items():
         assert torch.equal(v, ref[k]), k
+
+
+@pytest.mark.parametrize("states", [False, True], ids=["without_states", "with_states"])
+def test_a_long_sequence_among_short_ones(states):
+    """One sequence that is nearly the whole batch: the scans take it for what the launch lasts (16 columns per workgroup, a CU
+    for each), and the backward runs it by itself, split into two
+    segments.  Every output agrees bit for bit with the calls on each sequence."""
+    H, d, cu = 8, 128, [0, 100, 20137, 20200]
+    w = synth.custom(B=1, T=cu[-1], H=H, dk=d, dv=d, dtype="bf16", seed=77, with_eta=True, backward=True)
+    t = to_dev(w)
+    gen = torch.Generator(device="cuda").manual_seed(8)
+    S0, M0 = (0.2 * torch.randn((3, H, d, d), device="cuda", generator=gen) for _ in range(2))
+    ref = _by_sequence(t, cu, w.scale, (S0, M0) if states else None)
+    x = [t[k] for k in ("q", "k", "v", "beta", "alpha", "mu")]
+    kw = dict(eta=t["eta"], scale=w.scale, **(dict(S0=S0, M0=M0) if states else {}))
+    f = binding.mdn_chunk_fwd_varlen(*x, cu, save_vt=True, want_states=states, **kw)
+    binding.profile_begin()
+    g = binding.mdn_chunk_bwd_varlen(*x, f["vt"], t["dO"], cu, want_deta=True, want_state_grads=states, **kw)
+    launches = binding.profile_end(with_launch_counts=True)
+    assert launches["grad"][2] == launches["scan_bwd"][2] == 4 and launches["rebuild"][2] == 3
+    for k, v in {**f, **g}.items():
+        if v is not None:
+            assert torch.equal(v, ref[k]), k
