@@ -256,29 +256,23 @@ size_t size_of(const at::Tensor &t) { return (size_t)t.numel() * t.element_size(
 
 // the host array of sequence offsets of a packed batch
 std::vector<int32_t> offsets(PyObject *o, int64_t T) {
-    Ref seq(PySequence_Fast(o, "cu_seqlens must be a sequence of integers"));
+    const Ref seq(PySequence_Tuple(o)); // (a tuple of its own: int(item) may run code that changes a list)
     if (!seq.p) throw Fail{};
-    const Py_ssize_t n = PySequence_Fast_GET_SIZE(seq.p);
+    const Py_ssize_t n = PyTuple_GET_SIZE(seq.p);
     std::vector<int32_t> cu((size_t)n);
+    std::string seen;
     bool good = n >= 2;
     for (Py_ssize_t i = 0; i < n; ++i) {
-        PyObject *item = PySequence_Fast_GET_ITEM(seq.p, i);
-        long v;
-        if (PyLong_Check(item)) {
-            v = integer(item);
-        } else {
-            Ref l(PyNumber_Long(item));
-            if (!l.p) throw Fail{};
-            v = integer(l.p);
-        }
-        good = good && v >= 0 && v <= 0x7fffffffL && (i == 0 ? v == 0 : v > cu[i - 1]);
+        const Ref item(PyNumber_Long(PyTuple_GET_ITEM(seq.p, i)));
+        if (!item.p) throw Fail{};
+        int overflow;
+        const long v = PyLong_AsLongAndOverflow(item.p, &overflow);
+        good = good && !overflow && v >= 0 && v <= 0x7fffffffL && (i == 0 ? v == 0 : v > cu[i - 1]);
         cu[i] = (int32_t)v;
+        if (i < 8) seen += (i ? ", " : "") + (overflow ? std::string("out of range") : std::to_string(v));
     }
-    if (!good || cu[n - 1] != T) {
-        std::string s;
-        for (Py_ssize_t i = 0; i < n && i < 8; ++i) s += (i ? ", " : "") + std::to_string(cu[i]);
-        fail("cu_seqlens must rise from 0 to T = " + std::to_string(T) + " without empty sequences; got [" + s + "]" + (n > 8 ? "..." : ""));
-    }
+    if (!good || cu[n - 1] != T)
+        fail("cu_seqlens must rise from 0 to T = " + std::to_string(T) + " without empty sequences; got [" + seen + "]" + (n > 8 ? "..." : ""));
     return cu;
 }
 

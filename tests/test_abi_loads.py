@@ -206,6 +206,9 @@ def test_binding_checks_the_backward_and_the_other_entry_points_too():
         binding.mdn_chunk_fwd_varlen(*(t[k] for k in names), [0, 40, 63])
     with pytest.raises(binding.MdnError, match="cu_seqlens"):
         binding.mdn_chunk_fwd_varlen(*(t[k] for k in names), [0, 40, 40, 64])
+    for huge in ([0, 40, 2 ** 70], [-2 ** 70, 64], [0, 2 ** 31 + 64]):
+        with pytest.raises(binding.MdnError, match="cu_seqlens"):
+            binding.mdn_chunk_fwd_varlen(*(t[k] for k in names), huge)
     with pytest.raises(binding.MdnError, match="S0"):     # per-sequence states: [n_seq, H, dk, dv]
         binding.mdn_chunk_fwd_varlen(*(t[k] for k in names), [0, 40, 64], S0=torch.zeros(1, 2, 64, 64))
     x = torch.zeros(1, 64, 2)
