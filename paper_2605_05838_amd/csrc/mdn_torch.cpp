@@ -118,10 +118,11 @@ template <typename... P, typename... A> void call(const char *what, int (*f)(P..
     check(rc, what);
 }
 
-double number(PyObject *o) {
-    const double v = PyFloat_AsDouble(o);
-    if (v == -1.0 && PyErr_Occurred()) throw Fail{};
-    return v;
+double number(PyObject *o) { // float(o)
+    if (PyFloat_CheckExact(o)) return PyFloat_AS_DOUBLE(o);
+    const Ref v(PyNumber_Float(o));
+    if (!v.p) throw Fail{};
+    return PyFloat_AS_DOUBLE(v.p);
 }
 long integer(PyObject *o) {
     const long v = PyLong_AsLong(o);

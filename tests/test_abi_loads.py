@@ -211,6 +211,9 @@ def test_binding_checks_the_backward_and_the_other_entry_points_too():
             binding.mdn_chunk_fwd_varlen(*(t[k] for k in names), huge)
     with pytest.raises(binding.MdnError, match="S0"):     # per-sequence states: [n_seq, H, dk, dv]
         binding.mdn_chunk_fwd_varlen(*(t[k] for k in names), [0, 40, 64], S0=torch.zeros(1, 2, 64, 64))
+    for scale in ("0.125", 1, torch.tensor(0.125)):       # whatever float() takes
+        with pytest.raises(binding.MdnError, match="GPU"):
+            binding.mdn_chunk_fwd(*(t[k] for k in names), scale=scale)
     x = torch.zeros(1, 64, 2)
     h = torch.zeros(2)
     with pytest.raises(binding.MdnError, match="b_mu"):
