@@ -158,9 +158,18 @@ int mdn_gates_bwd(const mdn_gate_params *params, const float *x_alpha, const flo
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (dparams) hipLaunchKernelGGL(gates_zero_kernel, dim3(1), dim3(256), 0, s, dparams, 4 * g.H);
     // With parameter gradients every workgroup ends in 4 H atomic adds on the same 4 H addresses, which are taken one
-    // after the other (~20 ns each): workgroups of 1 024 threads, at most 128 of them.
+    // after the other (~20 ns each): workgroups of 1 024 threads, at most 128 of them.  Few tokens reach more CUs with 256
+    // threads, and so do heads that several lanes of a wave share without their sums meeting in registers (H < 32, 32 % H != 0), whose
+    // lanes go to the same LDS addresses.  (us, 1 024 threads / 256: 16 384 token-heads of 8 heads 7.4 / 6.3, 65 536 8.0 / 8.7; of
+    // 5 heads 10.3 / 7.0 and 11.0 / 9.6.)  Where a lane makes several trips, as many workgroups as make H divide the threads of the
+    // grid, so that it keeps its head (524 288 of 5 heads: 28.2 -> 19.6).
     const long long big = (g.n + 1023) / 1024;
-    const int block = dparams && big >= 16 ? 1024 : GT, wgs = block == GT ? grid_for(g.n) : (int)(big < 128 ? big : 128);
+    const bool shared = g.H < 32 && 32 % g.H != 0;
+    const int block = dparams && big >= 48 && !shared ? 1024 : GT, most = block == 1024 ? 128 : dparams ? 256 : 4096;
+    const long long need = (g.n + block - 1) / block;
+    int wgs = (int)(need < most ? need : most), odd = g.H; // odd: the factor of H that the workgroups have to bring in
+    while (odd % 2 == 0) odd /= 2;
+    if (dparams && need > most && odd <= most) wgs = (most + odd - 1) / odd * odd;
     hipLaunchKernelGGL(gates_bwd_kernel, dim3(wgs), dim3(block), 4 * g.H * sizeof(float), s, g, dalpha, dbeta, dmu,
                        deta, dx_alpha, dx_mu, dx_beta, dx_eta, dparams);
     return hipGetLastError() == hipSuccess ? MDN_OK : MDN_ERR_LAUNCH;

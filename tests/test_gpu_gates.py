@@ -22,7 +22,11 @@ def rel(x, ref):
     return float(np.abs(x.astype(np.float64) - ref).max() / max(np.abs(ref).max(), 1e-30))
 
 
-@pytest.mark.parametrize("B,T,H,s,tau", [(2, 300, 16, 0.7, 11.3), (1, 77, 3, 1.5, 1.0), (3, 4096, 16, 0.3, 8.0)])
+@pytest.mark.parametrize("B,T,H,s,tau", [(2, 300, 16, 0.7, 11.3), (1, 77, 3, 1.5, 1.0), (3, 4096, 16, 0.3, 8.0),
+                                           # several trips of the adjoint's grid, whose threads H divides only by the rule
+                                           # for it, or (129) not at all
+                                           (1, 28001, 5, 0.7, 2.0), (1, 12001, 12, 0.7, 2.0), (2, 3001, 33, 0.7, 2.0),
+                                           (1, 1301, 129, 0.7, 2.0), (1, 17, 1024, 0.7, 2.0)])
 def test_gates_forward_and_backward_match_the_oracle(B, T, H, s, tau):
     x, par, d = _case(B, T, H, 5)
     dev = lambda a: torch.from_numpy(a).cuda()
