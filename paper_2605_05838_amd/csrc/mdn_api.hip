@@ -137,9 +137,13 @@ template <typename F> int timed(int id, hipStream_t s, F &&launch) {
     const bool r0 = hipEventRecord(t.start, s) == hipSuccess;
     const int rc = launch_status(launch());
     const bool r1 = hipEventRecord(t.stop, s) == hipSuccess;
-    {
+    try {
         std::lock_guard<std::mutex> lock(g_timed_mutex);
         g_timed.push_back(t);
+    } catch (const std::bad_alloc &) {
+        (void)hipEventDestroy(t.start);
+        (void)hipEventDestroy(t.stop);
+        return MDN_ERR_LAUNCH;
     }
     return r0 && r1 ? rc : MDN_ERR_LAUNCH;
 }
@@ -198,6 +202,11 @@ Side *side(int n) {
     if (!xp) return nullptr;
     Side &x = *xp;
     if (!x.stream && hipStreamCreateWithFlags(&x.stream, hipStreamNonBlocking) != hipSuccess) return nullptr;
+    try {
+        x.ev.reserve(n);
+    } catch (const std::bad_alloc &) {
+        return nullptr;
+    }
     while ((int)x.ev.size() < n) {
         hipEvent_t e;
         if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) return nullptr;

@@ -334,3 +334,71 @@ def test_no_kernel_spills_vector_registers(tmp_path):
             kernels[field("name")] = int(field("private_segment_fixed_size")), int(field("vgpr_spill_count"))
     assert len(kernels) > 50 and any("grad_kernel" in k for k in kernels)
     assert not [k for k, v in kernels.items() if v != (0, 0)]
+
+
+# a runtime that accepts everything and an allocator that can be told to fail
+NO_MEMORY_STUB = """
+#include <new>
+#include <cstdlib>
+extern "C" {
+int no_memory = 0;
+int hipGetDevice(int *d) { *d = 0; return 0; }
+int hipDeviceGetAttribute(int *v, int, int) { *v = 256; return 0; }
+int hipFuncGetAttributes(void *, const void *) { return 1; }
+int hipEventCreate(void **e) { *e = &no_memory; return 0; }
+int hipEventCreateWithFlags(void **e, unsigned) { *e = &no_memory; return 0; }
+int hipEventRecord(void *, void *) { return 0; }
+int hipEventDestroy(void *) { return 0; }
+int hipStreamCreateWithFlags(void **s, unsigned) { *s = &no_memory; return 0; }
+int hipStreamWaitEvent(void *, void *, unsigned) { return 0; }
+int hipLaunchKernel(const void *, unsigned long, unsigned, unsigned long, unsigned, void **, unsigned long, void *) { return 0; }
+int hipGetLastError() { return 0; }
+}
+void *operator new(std::size_t n) {
+    if (no_memory) throw std::bad_alloc();
+    return std::malloc(n);
+}
+void operator delete(void *p) noexcept { std::free(p); }
+void operator delete(void *p, std::size_t) noexcept { std::free(p); }
+"""
+NO_MEMORY = """
+import ctypes, sys
+stub = ctypes.CDLL(sys.argv[1], ctypes.RTLD_GLOBAL)
+lib = ctypes.CDLL(sys.argv[2])
+fail = ctypes.c_int.in_dll(stub, "no_memory")
+class Shape(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int32) for n in "BTHdvCt"] + [("scale", ctypes.c_float)]
+s, g, none = Shape(1, 1, 1, 64, 64, 64, 0, 0.1), ctypes.c_void_p(4096), ctypes.c_void_p(None)
+step = lambda: lib.mdn_recurrent_step(ctypes.byref(s), g, g, g, g, g, g, none, g, g, g, none)
+codes = [step()]
+lib.mdn_profile_begin()
+fail.value = 1
+codes.append(step())
+fail.value = 0
+lib.mdn_profile_end(None, None, 0)
+s.T = 1024
+cu = (ctypes.c_int32 * 3)(0, 500, 1024)
+fwd = lambda: lib.mdn_chunk_fwd(ctypes.byref(s), g, g, g, g, g, g, none, none, none, g, none, none, none, none, none, g, ctypes.c_size_t(1 << 40), none)
+packed = lambda: lib.mdn_chunk_fwd_varlen(ctypes.byref(s), cu, 2, g, g, g, g, g, g, none, none, none, g, none, none, none, g, ctypes.c_size_t(1 << 40), none)
+lib.mdn_set_segments(2)
+fail.value = 1
+codes += [fwd(), packed()]
+fail.value = 0
+codes += [fwd(), packed()]
+print(codes)
+"""
+
+
+def test_running_out_of_host_memory_is_an_error_code(tmp_path):
+    """No C++ exception leaves an entry point: the event list of the timing facility, the second stream's events, the offsets
+    of a packed batch.  (The pointers given are no memory: only where there is no device that could read them.)"""
+    import subprocess
+    import sys
+    import torch
+    if torch.cuda.device_count():
+        pytest.skip("for machines without a GPU")
+    (tmp_path / "stub.cpp").write_text(NO_MEMORY_STUB)
+    stub = str(tmp_path / "stub.so")
+    subprocess.run(["g++", "-shared", "-fPIC", "-w", "-o", stub, str(tmp_path / "stub.cpp")], check=True)
+    p = subprocess.run([sys.executable, "-c", NO_MEMORY, stub, binding.LIB_PATH], capture_output=True, text=True, timeout=300)
+    assert p.returncode == 0 and p.stdout.split("\n")[0] == "[0, -6, -6, -6, 0, 0]", (p.returncode, p.stdout, p.stderr[-2000:])
