@@ -78,7 +78,6 @@ struct RebuildArgs {
     const float *S0, *M0;
     void *states;                           // [BH][N][2] x vblk [dk][dv]
     void *states_lo;                        // or null: the rounding remainders of `states` (16-bit storage)
-    float *S_final, *M_final;               // states after the last chunk, or null
 };
 
 struct ScanBwdArgs {

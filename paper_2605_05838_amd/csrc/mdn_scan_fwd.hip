@@ -521,8 +521,6 @@ hipError_t launch_rebuild(const Dims &d, const RebuildArgs &r, hipStream_t s) {
     a.M0 = r.M0;
     a.states_saved = r.states;
     a.states_lo = r.states_lo;
-    a.S_final = r.S_final;
-    a.M_final = r.M_final;
     return dispatch_scan<true>(d, a, s);
 }
 
