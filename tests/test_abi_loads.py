@@ -42,7 +42,7 @@ def test_workspace_query_validates_shapes():
     assert lib.mdn_workspace_bytes(ctypes.byref(shape()), 0, ctypes.byref(n)) == 0 and n.value > 0
     fwd = n.value
     assert lib.mdn_workspace_bytes(ctypes.byref(shape()), 1, ctypes.byref(n)) == 0 and n.value > fwd
-    # a partial last chunk runs on padded copies in the workspace: more workspace than the full chunks alone
+    # a partial last chunk has chunk blocks like a whole one: more workspace than the full chunks alone
     assert lib.mdn_workspace_bytes(ctypes.byref(shape(T=100)), 0, ctypes.byref(n)) == 0
     ragged = n.value
     assert lib.mdn_workspace_bytes(ctypes.byref(shape(T=64)), 0, ctypes.byref(n)) == 0 and ragged > n.value
@@ -100,8 +100,7 @@ def test_varlen_workspace_query_validates_the_offsets():
     cu = lambda *v: (ctypes.c_int32 * len(v))(*v)
     s1 = shape(B=1, T=300)
     assert lib.mdn_workspace_bytes_varlen(ctypes.byref(s1), cu(0, 100, 300), 2, 0, ctypes.byref(n)) == 0 and n.value > 0
-    # enough for either way of running the batch: sequence by sequence (the longest one decides), or as one stream
-    # of all T tokens with its own copies of alpha and mu
+    # enough for whatever the call brings in: 6 chunks, where one sequence of all T tokens has 5 and needs no table
     whole = ctypes.c_size_t(0)
     assert lib.mdn_workspace_bytes(ctypes.byref(s1), 0, ctypes.byref(whole)) == 0
     assert n.value >= whole.value + 2 * 300 * s1.H * 4

@@ -124,11 +124,13 @@ def test_split_into_segments_on_two_streams_equals_the_unsplit_call(dtype, d, T,
     for name in ("dq", "dk", "dv", "dalpha", "dbeta", "dmu", "deta", "dS0", "dM0"):
         assert torch.equal(g1[name], g2[name]), name
 
-# the smallest backward that splits by itself, and the same one chunk short of it (16-bit: 1 024 chunk blocks of 128 per
-# segment; 32-bit: 256)
+# the smallest backward that splits by itself (also with a partial last chunk), and the same one chunk short of it (16-bit:
+# 1 024 chunk blocks of 128 per segment; 32-bit: 256)
 @pytest.mark.gpu
-@pytest.mark.parametrize("dtype,H,d,T", [("bf16", 8, 128, 16384), ("bf16", 8, 128, 16320), ("f32", 8, 64, 8192)])
-def test_the_automatic_split_of_a_backward_equals_the_unsplit_call(dtype, H, d, T):
+@pytest.mark.parametrize("dtype,H,d,T,nseg", [("bf16", 8, 128, 16384, 2), ("bf16", 8, 128, 16320, 1), ("f32", 8, 64, 8192, 2),
+                                              ("bf16", 8, 128, 16384 + 37, 2), ("bf16", 8, 128, 16320 - 27, 1),
+                                              ("f32", 8, 64, 8192 + 1, 2)])
+def test_the_automatic_split_of_a_backward_equals_the_unsplit_call(dtype, H, d, T, nseg):
     import torch
     w = synth.custom(B=1, T=T, H=H, dk=d, dv=d, dtype=dtype, seed=37, backward=True)
     t = to_dev(w)
@@ -138,10 +140,12 @@ def test_the_automatic_split_of_a_backward_equals_the_unsplit_call(dtype, H, d, 
     for k in (1, 0):
         old = binding.set_segments(k)
         try:
+            binding.profile_begin()
             g.append(binding.mdn_chunk_bwd(*x, f["vt"], t["dO"], states=f["states"], operands=f["operands"], scale=w.scale))
-            torch.cuda.synchronize()
+            launches = binding.profile_end(with_launch_counts=True)
         finally:
             binding.set_segments(old)
+        assert launches["grad"][2] == launches["scan_bwd"][2] == (nseg if k == 0 else 1)
     for name in ("dq", "dk", "dv", "dalpha", "dbeta", "dmu", "dS0", "dM0"):
         assert torch.equal(g[0][name], g[1][name]), name
 
@@ -152,8 +156,7 @@ def test_the_automatic_split_of_a_backward_equals_the_unsplit_call(dtype, H, d, 
                           ("f32", 64, 1, True, False)])
 def test_backward_of_a_sequence_length_that_is_not_a_multiple_of_the_chunk_size(dtype, d, T, keep_states, keep_operands):
     """All gradients of the T tokens given, with adjoints of the final states coming in, whether the forward kept
-    its states / operands or the backward rebuilds them (the partial chunk goes first in the reverse pass and takes
-    its start states from what the full chunks leave)."""
+    its states / operands or the backward rebuilds them."""
     w = synth.custom(B=2, T=T, H=2, dk=d, dv=d, dtype=dtype, seed=43, with_eta=True, s0_std=0.3, backward=True)
     rng = np.random.default_rng(9)
     w.arrays["M0"] = (rng.standard_normal((2, 2, d, d)) * 0.2).astype(np.float32)
@@ -162,8 +165,8 @@ def test_backward_of_a_sequence_length_that_is_not_a_multiple_of_the_chunk_size(
 
 @pytest.mark.parametrize("T,nseg", [(2048 + 37, 4), (1024 + 63, 2)])
 def test_partial_last_chunk_together_with_segments_on_two_streams(T, nseg):
-    """The full chunks split into segments on two streams, the partial chunk after them (before them in the reverse
-    pass): same results as the oracle, and as the unsplit call bit for bit."""
+    """The partial chunk in the last segment, which comes first in the reverse pass: same results as the oracle, and as the
+    unsplit call bit for bit."""
     w = synth.custom(B=1, T=T, H=2, dk=64, dv=64, dtype="bf16", seed=47, with_eta=True, s0_std=0.2, backward=True)
     t = to_dev(w)
     prev = binding.set_segments(1)

@@ -1,7 +1,7 @@
 """Parity at the full sizes of the five measurement configurations, on ALL (batch, head) pairs (the oracle does a
 whole configuration in seconds).  The training configurations (3, 4) run in both launch configurations: the one the
 benchmark times (the forward keeps the chunk-start states and the reverse pass's operands; configuration 4 with the
-automatic split into segments on two streams active) and the memory-lean one (the backward reconstructs and
+automatic split of the backward into segments on two streams active) and the memory-lean one (the backward reconstructs and
 recomputes)."""
 import pytest
 
@@ -34,6 +34,6 @@ def test_config3_1p3B_forward_backward(keep):
 @pytest.mark.parametrize("keep", [True, False], ids=["forward_keeps_states_and_operands", "backward_rebuilds"])
 def test_config4_long_context_forward_backward(keep):
     w = synth.config(4)
-    assert binding.set_segments(0) == 0   # the automatic choice (4 segments for this shape) is what runs
+    assert binding.set_segments(0) == 0   # the automatic choice (the backward in 8 segments) is what runs
     check_fwd(w, save_states=keep, save_operands=keep)
     check_bwd(w, save_states=keep, save_operands=keep)

@@ -6,11 +6,13 @@ import pytest
 from paper_2605_05838_amd import binding
 
 
-# 64 columns from BH * d / 64 = 4 workgroups per CU on; states past the caches from 352 MiB (2 816 pairs of 128) on
+# 64 columns from BH * d / 64 = 4 workgroups per CU on; states past the caches above 352 MiB (2 816 pairs of 128, 11 264 of 64)
 @pytest.mark.gpu
 @pytest.mark.parametrize("BH,d,T,dtype,eta", [((73, 7), 128, 2, "bf16", True), ((32, 16), 128, 3, "f32", False),
                                               ((33, 31), 64, 2, "f32", True), ((64, 16), 64, 3, "bf16", False),
-                                              ((256, 11), 128, 1, "bf16", False), ((939, 3), 128, 2, "f32", True)])
+                                              ((256, 11), 128, 1, "bf16", False), ((939, 3), 128, 2, "f32", True),
+                                              ((313, 9), 128, 2, "bf16", True), ((1610, 7), 64, 2, "bf16", False),
+                                              ((1610, 7), 64, 1, "f32", True)])
 def test_recurrent_step_on_both_sides_of_every_size_rule(BH, d, T, dtype, eta):
     """o, S and M of every (batch, head) pair against the recurrence in float64.  Bounds: fp32 sums of d terms 1e-5; a
     16-bit o is rounded once more, 2^-8 / sqrt(3) = 2.3e-3 of its value at most in the root mean square."""

@@ -1,6 +1,6 @@
 """Calls from several host threads at once, each on a stream of its own (the header of the C ABI says they are safe):
-shapes with few (batch, head) pairs, which the library splits into segments on its per-device second stream, so the
-threads meet at the one piece of state that calls share.  Every thread's results must be bit-identical to the same
+calls split into segments on the library's per-device second stream, so the threads meet at the one piece of state that
+calls share.  Every thread's results must be bit-identical to the same
 calls made alone, and the calls made alone are checked against the oracle."""
 import threading
 
@@ -26,13 +26,25 @@ def fwd_bwd(w, t):
 
 
 def test_concurrent_calls_from_three_threads_match_the_calls_made_alone():
-    # 2 (batch, head) pairs, 32 chunks: split into 4 segments automatically; a different length per thread
+    # 2 (batch, head) pairs, 32 chunks and more: far below what is split automatically, so the split is asked for
+    old = binding.set_segments(4)
+    try:
+        concurrent_calls()
+    finally:
+        binding.set_segments(old)
+
+
+def concurrent_calls():
+    # a different length per thread
     loads = [synth.custom(B=1, T=T, H=2, dk=128, dv=128, dtype="bf16", seed=300 + i, s0_std=0.1, backward=True)
              for i, T in enumerate((2048, 2112, 2304))]
     devs = [to_dev(w) for w in loads]
     alone = []
     for w, t in zip(loads, devs):
+        binding.profile_begin()
         f, g = fwd_bwd(w, t)
+        launches = binding.profile_end(with_launch_counts=True)
+        assert all(launches[k][2] == 4 for k in ("intra_fwd", "scan_fwd", "scan_bwd", "grad")), launches
         torch.cuda.synchronize()
         alone.append(({k: f[k].clone() for k in ("o", "S", "M")}, {k: g[k].clone() for k in GRADS}))
     # the calls made alone against the oracle (first workload; the others differ in length only)

@@ -53,10 +53,9 @@ def test_packed_sequences_forward_and_backward(dtype, d, lens):
                                           ("bf16", 64, (40,) * 9), ("f32", 128, (300,)),
                                           ("f32", 64, (700, 333, 64, 1, 900, 250)), ("bf16", 128, (1030, 1100))])
 def test_packed_sequences_as_one_stream_of_tokens(dtype, d, lens):
-    """No per-sequence states in or out: the library runs the batch as one stream with alpha = mu = 0 at the sequence
-    starts.  Every sequence must come out as the oracle computes it by itself from zero states (sequence starts inside
-    chunks, on chunk boundaries, sequences of one token; the two longest batches are cut in two halves that run beside
-    each other on two streams), and the caller's alpha, mu must be left as they were."""
+    """No per-sequence states in or out: the library may merge neighbours, with alpha = mu = 0 at the sequence starts.  Every
+    sequence must come out as the oracle computes it by itself from zero states (sequence starts inside chunks, on chunk
+    boundaries, sequences of one token), and the caller's alpha, mu must be left as they were."""
     T, H = sum(lens), 3
     w = synth.custom(B=1, T=T, H=H, dk=d, dv=d, dtype=dtype, seed=72, with_eta=True, backward=True)
     t = to_dev(w)
@@ -90,10 +89,9 @@ def test_packed_sequences_as_one_stream_of_tokens(dtype, d, lens):
                                           ("bf16", 64, (40,) * 9), ("f32", 128, (300,)), ("f32", 64, (7, 9)),
                                           ("f32", 64, (700, 333, 64, 1, 900, 250)), ("bf16", 128, (1030, 1100))])
 def test_packed_prompts_with_final_states_of_every_sequence(dtype, d, lens):
-    """Zero initial states, final states wanted (prefill of a batch of prompts): the stream form, then one batch of the
-    sequences' last chunks run again from their start states.  o and every sequence's S, M against the oracle
-    (sequences that end inside a chunk, on a chunk boundary, several sequences inside one chunk, a total length below
-    one chunk, batches long enough to be cut in two halves that run beside each other)."""
+    """Zero initial states, final states wanted (prefill of a batch of prompts): o and every sequence's S, M against the oracle
+    (sequences that end inside a chunk, on a chunk boundary, sequences shorter than a chunk, a total length below one
+    chunk, lengths far apart)."""
     T, H = sum(lens), 2
     w = synth.custom(B=1, T=T, H=H, dk=d, dv=d, dtype=dtype, seed=73, with_eta=True)
     t = to_dev(w)
