@@ -168,9 +168,8 @@ def handoff_bench(args, torch, binding, synth):
 
 
 def varlen_bench(args, torch, binding, synth):
-    """Packed variable-length batches, forward + backward (the backward rebuilds states and operands): the batch as one
-    stream of tokens (no per-sequence states asked for: "one_stream" keys) against the same batch with per-sequence final
-    states and adjoints of the initial states ("sequence_by_sequence" keys)."""
+    """Packed variable-length batches, forward + backward (the backward rebuilds states and operands): without states
+    ("without_states" keys), and with per-sequence final states and adjoints of the initial states ("with_states" keys)."""
     total, H, dk = args.varlen, 16, 128
     rows = []
     for nseq in (8, 64, 256):
@@ -180,12 +179,12 @@ def varlen_bench(args, torch, binding, synth):
         cu = [i * L for i in range(nseq + 1)]
         names = ("q", "k", "v", "beta", "alpha", "mu")
         row = {"sequences": nseq, "tokens_each": L}
-        for one_stream in (True, False):
+        for states in (False, True):
             def step():
                 f = binding.mdn_chunk_fwd_varlen(*(t[k] for k in names), cu, scale=w.scale, save_vt=True,
-                                                 want_states=not one_stream)
+                                                 want_states=states)
                 binding.mdn_chunk_bwd_varlen(*(t[k] for k in names), f["vt"], t["dO"], cu, scale=w.scale,
-                                             want_state_grads=not one_stream)
+                                             want_state_grads=states)
             for _ in range(2):
                 step()
             torch.cuda.synchronize()
@@ -195,16 +194,16 @@ def varlen_bench(args, torch, binding, synth):
                 step()
             torch.cuda.synchronize()
             ms = (time.perf_counter() - t0) * 1e3 / n
-            key = "one_stream" if one_stream else "sequence_by_sequence"
+            key = "with_states" if states else "without_states"
             row[key + "_ms"] = round(ms, 3)
             row[key + "_tokens_per_s"] = round(nseq * L / (ms * 1e-3), 1)
         # prefill of the same batch as prompts: forward only, final states of every sequence wanted, with zero initial
-        # states ("one_stream" keys) or with initial states given ("sequence_by_sequence" keys)
+        # states ("prefill_from_zero" keys) or with initial states given ("prefill_from_states" keys)
         zeros = torch.zeros((nseq, H, dk, dk), dtype=torch.float32, device="cuda")
-        for one_stream in (True, False):
+        for states in (False, True):
             def prefill():
                 binding.mdn_chunk_fwd_varlen(*(t[k] for k in names), cu, scale=w.scale,
-                                             S0=None if one_stream else zeros, M0=None if one_stream else zeros)
+                                             S0=zeros if states else None, M0=zeros if states else None)
             for _ in range(2):
                 prefill()
             torch.cuda.synchronize()
@@ -214,15 +213,15 @@ def varlen_bench(args, torch, binding, synth):
                 prefill()
             torch.cuda.synchronize()
             ms = (time.perf_counter() - t0) * 1e3 / n
-            key = "prefill_one_stream" if one_stream else "prefill_sequence_by_sequence"
+            key = "prefill_from_states" if states else "prefill_from_zero"
             row[key + "_ms"] = round(ms, 3)
             row[key + "_tokens_per_s"] = round(nseq * L / (ms * 1e-3), 1)
         rows.append(row)
         del t, zeros
         torch.cuda.empty_cache()
     print(json.dumps({
-        "metric": "MDN packed variable-length batch fwd+bwd tokens/sec", "value": rows[1]["one_stream_tokens_per_s"],
-        "unit": "tokens/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "ms_per_step": rows[1]["one_stream_ms"],
+        "metric": "MDN packed variable-length batch fwd+bwd tokens/sec", "value": rows[1]["without_states_tokens_per_s"],
+        "unit": "tokens/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "ms_per_step": rows[1]["without_states_ms"],
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "bf16", "data": "synthetic",
         "config": {"workload": f"varlen_{total}tokens_H{H}_d{dk}", "H": H, "dk": dk, "dv": dk}, "roofline": None,
         "by_batch": rows, "cpu_baseline": None}))
