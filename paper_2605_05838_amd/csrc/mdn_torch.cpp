@@ -1,6 +1,6 @@
 // The entry points of binding.py, natively: argument checks, output allocation, stream and pointer marshalling for the
-// C ABI of include/mdn.h.  A small call (a decode step: two loads and two stores of 1 MB) is a few microseconds of GPU
-// time, and the same work done in Python over ctypes took 12 of them per call; here it takes about one.
+// C ABI of include/mdn.h.  A small call (a decode step: two loads and two stores of 1 MB) is 3.2 us of GPU time; with the
+// same work done in Python over ctypes it took 12.9 us from call to call, here 4.4.
 // Functions take every argument positionally (binding.py gives them their names and defaults) and raise
 // binding.MdnError.  Nothing of the path runs here, and there is no CPU path: PyTorch supplies memory and the stream.
 #define PY_SSIZE_T_CLEAN
