@@ -40,17 +40,18 @@ def bytes_per_tokhd(C, dk, dv, es, keep):
     stored element; gates and coefficients are fp32).  `keep`: the training forward also writes the
     reverse pass's operands and the chunk-start states."""
     coef = 8 * 4                                          # one row of 8 fp32 coefficients per token
-    kt_fwd = dk * es if es == 4 else 0                    # K^T for the forward scan: 16-bit storage makes it on chip
-    fwd_ops = kt_fwd + 2 * C * es + coef                  # (K^T,) T, Bm, coefficient block
-    rev_ops = (2 * dk + 2 * C) * es + coef                # K^T, Q^T, Bm^T, T^T, coefficient block
+    # 16-bit storage: one set of operands, T, Bm and the coefficients, for both directions (what else the scans need of k and q
+    # they read out of tiles on chip); 32-bit storage: K^T as well, and for the reverse pass K^T, Q^T, Bm^T, T^T
+    fwd_ops = (dk * es if es == 4 else 0) + 2 * C * es + coef
+    rev_ops = (2 * dk + 2 * C) * es + coef if es == 4 else fwd_ops
     states = 2 * dk * dv * es // C                        # S, M of one chunk, per token
     qk = 2 * dk * es
     return {
-        "intra_fwd": qk + 16 + (2 * C * es + rev_ops if keep else fwd_ops),
+        "intra_fwd": qk + 16 + (2 * C * es + rev_ops if keep and es == 4 else fwd_ops),
         "scan_fwd": fwd_ops + qk + dv * es + 2 * dv * es + (states if keep else 0),   # + q, k, v; V~ and o out
         "intra_bwd": qk + 16 + rev_ops,
         "rebuild": dk * es + dv * es + coef + states,
-        "scan_bwd": rev_ops + dk * es + dv * es + dv * es + states,                   # + k, dO; dv, dstates out
+        "scan_bwd": rev_ops + (dk if es == 4 else 2 * dk) * es + dv * es + dv * es + states, # + k (and q), dO; dv, dstates out
         # q, k, V~, dO, dV and both state pairs in; dq, dk and the gate gradients out (with 16-bit storage K^T and Q^T
         # come out of the k, q tiles on chip; the fp32 path still reads them: 2 dk es more)
         "grad": 2 * dk * es + 3 * dv * es + 2 * states + 16 + 2 * dk * es + 12 + (2 * dk * es if es == 4 else 0),

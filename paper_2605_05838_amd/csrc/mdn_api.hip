@@ -51,6 +51,9 @@ struct Carver {
     }
 };
 
+// 32-bit storage: K^T and, for the reverse pass, operands in other orientations (mdn_kernels.h)
+bool wide(const Dims &d) { return d.dtype == MDN_DTYPE_F32; }
+
 struct FwdWs { float *coef; void *KT, *Tm, *Bm; float *carryS, *carryM; size_t total; };
 
 // a state tensor that crosses segment boundaries.  (Packed batches are not split: room for one sequence, so that their
@@ -62,7 +65,7 @@ FwdWs carve_fwd(const Dims &d, void *ws) {
     Carver c(ws);
     FwdWs w;
     w.coef = static_cast<float *>(c.take(nb * (size_t)(64 * kCoefBlockCols * sizeof(float))));
-    w.KT = scan_fwd_reads_KT(d) ? c.take(nb * d.dk * 64 * es) : nullptr; // (16-bit storage: made on chip from the k rows)
+    w.KT = wide(d) ? c.take(nb * d.dk * 64 * es) : nullptr;
     w.Tm = c.take(nb * 4096 * es);
     w.Bm = c.take(nb * 4096 * es);
     // states handed from one segment of the sequence to the next when the call is split (see segments())
@@ -72,15 +75,21 @@ FwdWs carve_fwd(const Dims &d, void *ws) {
     return w;
 }
 
-// Operands of the reverse pass (what intra mode 1 / 2 writes); lives in the backward workspace or in
-// the buffer a training forward keeps for the backward.
-struct RevOps { float *coef; void *KT, *QT, *BmT, *TmT; size_t total; };
+// Operands of the reverse pass; lives in the backward workspace or in the buffer a training forward keeps for the
+// backward.  16-bit storage: the forward's own.
+struct RevOps { float *coef; void *Tm, *Bm, *KT, *QT, *BmT, *TmT; size_t total; };
 
 RevOps carve_rev(const Dims &d, void *p) {
     const size_t es = d.dtype == MDN_DTYPE_F32 ? 4 : 2, nb = chunk_blocks(d);
     Carver c(p);
-    RevOps w;
+    RevOps w = {};
     w.coef = static_cast<float *>(c.take(nb * (size_t)(64 * kCoefBlockCols * sizeof(float))));
+    if (!wide(d)) {
+        w.Tm = c.take(nb * 4096 * es);
+        w.Bm = c.take(nb * 4096 * es);
+        w.total = c.off;
+        return w;
+    }
     w.KT = c.take(nb * d.dk * 64 * es);
     w.QT = c.take(nb * d.dk * 64 * es);
     w.BmT = c.take(nb * 4096 * es);
@@ -237,17 +246,16 @@ int run_fwd(const Dims &d, const FwdCall &c, const FwdWs &w, hipStream_t s) {
     ia.q = c.q; ia.k = c.k; ia.alpha = c.alpha; ia.beta = c.beta; ia.mu = c.mu; ia.eta = c.eta;
     ia.coef = w.coef; ia.KT = w.KT; ia.Tm = w.Tm; ia.Bm = w.Bm;
     if (c.operands_saved) {
-        // training forward: one precompute pass writes the reverse pass's operands as well
+        // training forward: one precompute pass writes the reverse pass's operands as well (16-bit storage: they are the same)
         const RevOps ro = carve_rev(d, c.operands_saved);
         ia.coef = ro.coef; ia.KT = ro.KT; ia.QT = ro.QT; ia.BmT = ro.BmT; ia.TmT = ro.TmT;
+        if (!wide(d)) ia.Tm = ro.Tm, ia.Bm = ro.Bm;
     }
     ScanFwdArgs sa = {};
-    sa.q = c.q; sa.k = c.k; sa.v = c.v; sa.coef = ia.coef; sa.KT = ia.KT; sa.Tm = w.Tm; sa.Bm = w.Bm;
+    sa.q = c.q; sa.k = c.k; sa.v = c.v; sa.coef = ia.coef; sa.KT = ia.KT; sa.Tm = ia.Tm; sa.Bm = ia.Bm;
     sa.S0 = c.S0; sa.M0 = c.M0; sa.o = c.o; sa.vt_saved = c.vt_saved; sa.states_saved = c.states_saved;
     sa.S_final = c.S_final; sa.M_final = c.M_final;
-    // K^T for this forward alone: not written if its scan forms K^T out of the k rows itself
-    if (!c.operands_saved && !scan_fwd_reads_KT(d)) ia.KT = nullptr, sa.KT = nullptr;
-    const int mode = c.operands_saved ? 2 : 0;
+    const int mode = c.operands_saved && wide(d) ? 2 : 0;
     const int nseg = segments(d, false);
     if (nseg == 1) {
         rc = timed(MDN_KERNEL_INTRA_FWD, s, [&] { return launch_intra(d, mode, ia, s); });
@@ -314,7 +322,8 @@ int bwd_prepare(const Dims &d, const BwdCall &c, const BwdWs &w, hipStream_t s, 
         IntraArgs ia = {};
         ia.q = c.q; ia.k = c.k; ia.alpha = c.alpha; ia.beta = c.beta; ia.mu = c.mu; ia.eta = c.eta;
         ia.coef = out->ro.coef; ia.KT = out->ro.KT; ia.QT = out->ro.QT; ia.BmT = out->ro.BmT; ia.TmT = out->ro.TmT;
-        rc = timed(MDN_KERNEL_INTRA_BWD, s, [&] { return launch_intra(d, 1, ia, s); });
+        ia.Tm = out->ro.Tm; ia.Bm = out->ro.Bm;
+        rc = timed(MDN_KERNEL_INTRA_BWD, s, [&] { return launch_intra(d, wide(d) ? 1 : 0, ia, s); });
         if (rc) return rc;
     }
     // chunk-start states: given by the forward, or reconstructed from V~
@@ -334,7 +343,7 @@ int bwd_run(const Dims &d, const BwdCall &c, const BwdWs &w, const Prepared &p, 
     int rc;
     const RevOps &ro = p.ro;
     ScanBwdArgs sb = {};
-    sb.k = c.k; sb.dO = c.dO; sb.coef = ro.coef; sb.QT = ro.QT; sb.KT = ro.KT; sb.BmT = ro.BmT;
+    sb.q = c.q; sb.k = c.k; sb.dO = c.dO; sb.coef = ro.coef; sb.Tm = ro.Tm; sb.Bm = ro.Bm; sb.QT = ro.QT; sb.KT = ro.KT; sb.BmT = ro.BmT;
     sb.TmT = ro.TmT; sb.dS_final = c.dS_final; sb.dM_final = c.dM_final; sb.dv = c.dv; sb.dstates = w.dstates;
     sb.dS0 = c.dS0; sb.dM0 = c.dM0; sb.dstates_lo = precise ? w.dstates_lo : nullptr;
     GradArgs ga = {};
@@ -534,7 +543,7 @@ int check_varlen(const mdn_shape *shape, const int32_t *cu, int32_t n_seq, Dims 
 // bytes that a chunk block takes in the workspace of a backward call (see carve_bwd)
 size_t bwd_block_bytes(const Dims &d, bool precise) {
     const size_t state = (size_t)2 * d.dk * d.dv; // S and M of a chunk, elements
-    return 64 * kCoefBlockCols * sizeof(float) + (2 * d.dk * 64 + 2 * 4096 + (precise ? 4 : 2) * state) * elem_size(d);
+    return 64 * kCoefBlockCols * sizeof(float) + ((wide(d) ? 2 * d.dk * 64 : 0) + 2 * 4096 + (precise ? 4 : 2) * state) * elem_size(d);
 }
 
 // Every sequence has chunk blocks of its own, so sequences far shorter than a chunk need up to 64 times the blocks of

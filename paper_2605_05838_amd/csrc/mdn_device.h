@@ -219,6 +219,16 @@ template <typename T, bool WHOLE> struct RowStore {
             __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), to.rsrc, off * (unsigned)sizeof(T), 0, 0);
         }
     }
+    // the same for 16 bytes that no workgroup soon reads (non-temporal)
+    template <typename V> __device__ __forceinline__ void put_nt(unsigned off, V v) const {
+        static_assert(sizeof(V) == 16, "16 bytes");
+        if constexpr (WHOLE) {
+            __builtin_nontemporal_store(v, reinterpret_cast<V *>(at32(to.base, off)));
+        } else {
+            typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), to.rsrc, off * (unsigned)sizeof(T), 0, 2);
+        }
+    }
     // MV * 4 consecutive elements in storage form (see store_cols_raw)
     template <int MV> __device__ __forceinline__ void put_cols(unsigned off, const typename Raw4<T>::type (&u)[MV]) const {
         if constexpr (sizeof(T) == 2 && MV == 2) {

@@ -50,14 +50,14 @@ __device__ __forceinline__ void store_tile_64cols(T *dst, const T *src, int ld, 
 // WHOLE: see whole_chunks.
 template <typename T, int DK, int DV, int MODE, bool WHOLE>
 __global__ __launch_bounds__(kThreads) void intra_kernel(Dims d, IntraArgs a) {
-    constexpr bool FWD = MODE != 1, BWD = MODE != 0;
+    constexpr bool FWD = MODE != 1, BWD = MODE != 0, HALF = sizeof(T) == 2;
+    static_assert(!HALF || MODE == 0, "16-bit storage: one set of operands");
     typedef Op<T> O;
     constexpr int E = O::EPL;
     constexpr int LDN = DK + O::PAD; // natural tiles
     constexpr int LDT = 64 + O::PAD; // transposed tiles (32-bit storage)
     constexpr int DX = BWD ? DK : 0; // second transposed tile: Q^T (reverse-pass operands only)
-    // (16-bit storage reads the transposed tiles out of the natural ones and needs no space for them)
-    constexpr int REG_NAT = 2 * 64 * LDN, REG_TR = sizeof(T) == 2 ? 0 : (DK + DX) * LDT;
+    constexpr int REG_NAT = 2 * 64 * LDN, REG_TR = HALF ? 0 : (DK + DX) * LDT;
     constexpr int REGION = REG_NAT > REG_TR ? REG_NAT : REG_TR;
     constexpr int NVK = 64 * DK / E / kThreads, NVX = BWD ? NVK : 1; // 16-byte vectors per thread
 
@@ -98,13 +98,10 @@ __global__ __launch_bounds__(kThreads) void intra_kernel(Dims d, IntraArgs a) {
             rq[u] = O::load(qg + row * rsk + cc * E);
         }
     }
-    // 16-bit storage: the transposed tiles K^T, Q^T come straight out of the natural tiles in LDS through
-    // transposing reads (a fragment of such a read is one 16-byte piece of the blocked layout).  32-bit storage:
-    // the rows are loaded a second time in the order of the transposed tiles (in flight until the K, Q tiles are
-    // no longer needed) and transposed through LDS.
-    constexpr bool TRT = sizeof(T) == 2;
-    Vec16<T> rkt[TRT ? 1 : NVK], rxt[TRT ? 1 : NVX];
-    if constexpr (!TRT) {
+    // 32-bit storage: the rows are loaded a second time in the order of the transposed tiles (in flight until the K, Q
+    // tiles are no longer needed) and transposed through LDS.
+    Vec16<T> rkt[HALF ? 1 : NVK], rxt[HALF ? 1 : NVX];
+    if constexpr (!HALF) {
 #pragma unroll
         for (int u = 0; u < NVK; ++u) {
             const int c = tid + u * kThreads, row = WHOLE ? c % 64 : min(c % 64, rows - 1), cc = c / 64;
@@ -124,7 +121,7 @@ __global__ __launch_bounds__(kThreads) void intra_kernel(Dims d, IntraArgs a) {
 #pragma unroll
         for (int u = 0; u < NVK; ++u) {
             if ((tid + u * kThreads) / CPR >= rows) rk[u] = rq[u] = typename O::Frag{};
-            if constexpr (!TRT) {
+            if constexpr (!HALF) {
                 if ((tid + u * kThreads) % 64 >= rows) {
                     rkt[u] = Vec16<T>{};
                     if (BWD) rxt[u] = Vec16<T>{};
@@ -170,26 +167,6 @@ __global__ __launch_bounds__(kThreads) void intra_kernel(Dims d, IntraArgs a) {
     }
     __syncthreads();
 
-    // ---- K^T, Q^T first (they only need the tiles), so that the tile region is free once the products are done
-    if constexpr (TRT) {
-        // in the blocked layout, where asked for (the reverse scan and the state reconstruction read
-        // them; the forward scan makes K^T itself out of the k rows): (dk tile, 32-token step) blocks dealt over
-        // the waves; lane (r, kq) reads (dk = 16 dt + r, tokens 32 ks + 8 kq ..) and owns exactly that
-        // 16-byte piece of the blocked layout, so a wave stores 1 KB of consecutive bytes
-        if (a.KT || (BWD && a.QT)) {
-            const int r = lane & 15, kq = lane >> 4;
-            T *KTo = a.KT ? static_cast<T *>(a.KT) + blk * (DK * 64) : nullptr;
-            T *QTo = BWD && a.QT ? static_cast<T *>(a.QT) + blk * (DK * 64) : nullptr;
-#pragma unroll
-            for (int t = 0; t < (DK / 16) * 2 / 4; ++t) {
-                const int tt = w + 4 * t, dt = tt >> 1, ks = tt & 1;
-                const size_t o = kblk<T>(DK, dt * 16 + r, ks * 32 + kq * 8);
-                if (KTo) *reinterpret_cast<typename O::Frag *>(KTo + o) = tr_frag(sK, LDN, ks * 32, dt * 16, r, kq);
-                if (QTo) *reinterpret_cast<typename O::Frag *>(QTo + o) = tr_frag(sQ, LDN, ks * 32, dt * 16, r, kq);
-            }
-        }
-    }
-
     // ---- masked intra-chunk products: wave w owns rows i0..i0+15.
     //      The Q K^T product is formed in the orientation whose accumulator lanes hold 4 consecutive
     //      entries along the contraction index of the consumer (j for Bm, i for Bm^T).
@@ -228,10 +205,10 @@ __global__ __launch_bounds__(kThreads) void intra_kernel(Dims d, IntraArgs a) {
                 f32x4 v;
 #pragma unroll
                 for (int x = 0; x < 4; ++x) v[x] = (j0 + x <= i) ? d.scale * et[x] * gr[x] * qk[nt][x] : 0.f;
-                store4(out + kblk<T>(64, i, i0 + kq * 4), v);
+                store4(out + (HALF ? (size_t)(i * 64 + i0 + kq * 4) : kblk<T>(64, i, i0 + kq * 4)), v);
             }
         }
-        if constexpr (!TRT) {
+        if constexpr (!HALF) {
             // ---- 32-bit storage: the transposed tiles take the space of the K, Q tiles (dst[d][row] = src[row][d]),
             //      go out from there, and only then does A move in
             __syncthreads();
@@ -292,13 +269,13 @@ __global__ __launch_bounds__(kThreads) void intra_kernel(Dims d, IntraArgs a) {
 
     if (FWD) {
         T *tm = static_cast<T *>(a.Tm) + blk * 4096; // T: row i, k = j
-        constexpr int PPS = O::KSTEP / E;
+        constexpr int PPS = HALF ? 64 / E : O::KSTEP / E; // consecutive lanes, consecutive pieces of the destination
         for (int c = tid; c < 64 * (64 / E); c += kThreads) {
             const int pp = c % PPS, ii = (c / PPS) & 63, cc = (c / (PPS * 64)) * PPS + pp;
             Vec16<T> v;
 #pragma unroll
             for (int e = 0; e < E; ++e) v.e[e] = from_f32<T>(sA[ii * LDA + cc * E + e]);
-            *reinterpret_cast<Vec16<T> *>(tm + kblk<T>(64, ii, cc * E)) = v;
+            *reinterpret_cast<Vec16<T> *>(tm + (HALF ? (size_t)(ii * 64 + cc * E) : kblk<T>(64, ii, cc * E))) = v;
         }
     }
 }
@@ -306,9 +283,13 @@ __global__ __launch_bounds__(kThreads) void intra_kernel(Dims d, IntraArgs a) {
 template <typename T, int DK, int DV, bool WHOLE>
 hipError_t launch_intra_w(const Dims &d, int mode, const IntraArgs &a, hipStream_t s) {
     dim3 grid(chunk_grid_x(d), chunk_grid_y(d)), block(kThreads);
-    if (mode == 0) hipLaunchKernelGGL((intra_kernel<T, DK, DV, 0, WHOLE>), grid, block, 0, s, d, a);
-    else if (mode == 1) hipLaunchKernelGGL((intra_kernel<T, DK, DV, 1, WHOLE>), grid, block, 0, s, d, a);
-    else hipLaunchKernelGGL((intra_kernel<T, DK, DV, 2, WHOLE>), grid, block, 0, s, d, a);
+    if constexpr (sizeof(T) == 2) {
+        hipLaunchKernelGGL((intra_kernel<T, DK, DV, 0, WHOLE>), grid, block, 0, s, d, a);
+    } else {
+        if (mode == 0) hipLaunchKernelGGL((intra_kernel<T, DK, DV, 0, WHOLE>), grid, block, 0, s, d, a);
+        else if (mode == 1) hipLaunchKernelGGL((intra_kernel<T, DK, DV, 1, WHOLE>), grid, block, 0, s, d, a);
+        else hipLaunchKernelGGL((intra_kernel<T, DK, DV, 2, WHOLE>), grid, block, 0, s, d, a);
+    }
     return hipGetLastError();
 }
 template <typename T, int DK, int DV>

@@ -33,8 +33,10 @@ struct Dims {
 
 // Chunk-parallel precompute ("intra") kernel arguments.  Workspace tensors are chunk-blocked,
 // [sequence][H][chunk of the sequence][tile] (written [BH][N] below: what it is for a fixed-length batch), in the storage
-// dtype unless noted; inside a tile, an MFMA operand [rows][k] is in the kblk layout and a [rows][dv] tensor in
-// the vblk layout of mdn_device.h.
+// dtype unless noted; inside a tile, a [rows][dv] tensor is in the vblk layout of mdn_device.h, and an MFMA operand [rows][k] in its
+// kblk layout (32-bit storage) or row by row (16-bit storage, whose scans read tiles through LDS).
+// 16-bit storage has one set of operands, coef, T and Bm, for the forward and the reverse pass: their transposes and those of k and
+// q are transposing LDS reads there.
 // A chunk of fewer than 64 tokens (the last one of a sequence) is filled up with identity steps of the recurrence:
 // k = q = eta = 0, alpha = mu = 1, beta = 0.  The intra kernel writes its operands that way (rows of K^T, Q^T, Bm zero,
 // rows of T those of the unit matrix, Gamma_C = Rho_C = 0), after which whatever finite values the scans read for V, k,
@@ -45,11 +47,11 @@ struct IntraArgs {
     const void *q, *k;                      // [B,T,H,dk]
     const float *alpha, *beta, *mu, *eta;   // [B,T,H]; eta may be null
     float *coef;                            // [BH][N][64][kCoefBlockCols] fp32 (one row of coefficients per token)
+    void *Tm;                               // [64][64]        T = (I + A)^-1: row i, contraction index j
+    void *Bm;                               // [64][64]        (Q~ K~^T) .* Gamma
+    // 32-bit storage
     void *KT;                               // kblk [dk][64]   raw k, transposed
-    // forward mode
-    void *Tm;                               // kblk [64][64]   T = (I + A)^-1: row i, contraction index j
-    void *Bm;                               // kblk [64][64]   (Q~ K~^T) .* Gamma
-    // backward mode
+    // 32-bit storage, backward mode
     void *QT;                               // kblk [dk][64]   raw q, transposed
     void *BmT;                              // kblk [64][64]   Bm transposed
     void *TmT;                              // kblk [64][64]   T transposed
@@ -72,8 +74,8 @@ struct ScanFwdArgs {
 // State reconstruction from saved V~ (backward, when the forward did not keep the states).
 struct RebuildArgs {
     const float *coef;
-    const void *k;                          // [B,T,H,dk] (16-bit storage reads K^T out of the k rows)
-    const void *KT;
+    const void *k;                          // [B,T,H,dk]
+    const void *KT;                         // 32-bit storage
     const void *vt_saved;                   // [B,T,H,dv]
     const float *S0, *M0;
     void *states;                           // [BH][N][2] x vblk [dk][dv]
@@ -81,10 +83,11 @@ struct RebuildArgs {
 };
 
 struct ScanBwdArgs {
-    const void *k;                          // [B,T,H,dk]
+    const void *q, *k;                      // [B,T,H,dk]
     const void *dO;                         // [B,T,H,dv]
     const float *coef;
-    const void *QT, *KT, *BmT, *TmT;
+    const void *Tm, *Bm;                    // 16-bit storage
+    const void *QT, *KT, *BmT, *TmT;        // 32-bit storage
     const float *dS_final, *dM_final;       // or null
     void *dv;                               // [B,T,H,dv]  dV = T^T dV~
     void *dstates;                          // [BH][N][2] x vblk [dk][dv]: adjoints of the chunk-END states
@@ -126,7 +129,7 @@ int scan_workgroups(const Dims &d);
 // of the longest sequence's length do not outnumber the CUs.
 bool scan_one_per_cu(const Dims &d);
 
-// mode 0: forward operands, 1: reverse-pass operands, 2: both
+// mode 0: forward operands, 1: reverse-pass operands, 2: both (16-bit storage: the same ones, always mode 0)
 hipError_t launch_intra(const Dims &d, int mode, const IntraArgs &a, hipStream_t s);
 hipError_t launch_scan_fwd(const Dims &d, const ScanFwdArgs &a, hipStream_t s);
 // Dynamic LDS bytes that keep a second workgroup of `kernel` off a CU (0 if one workgroup fills more than half of the
@@ -134,8 +137,9 @@ hipError_t launch_scan_fwd(const Dims &d, const ScanFwdArgs &a, hipStream_t s);
 // and leaves other CUs empty, and two scan workgroups that share a CU take turns at everything.
 size_t lds_bytes_for_one_workgroup_per_cu(const void *kernel);
 
-// whether that launch reads a.KT (32-bit storage; 16-bit storage forms K^T out of the k rows in LDS)
-bool scan_fwd_reads_KT(const Dims &d);
+// 16-bit storage (what launch_scan_fwd, launch_rebuild and launch_scan_bwd go on to)
+hipError_t launch_scan_fwd16(const Dims &d, const ScanFwdArgs &a, bool rebuild, hipStream_t s);
+hipError_t launch_scan_bwd16(const Dims &d, const ScanBwdArgs &a, hipStream_t s);
 hipError_t launch_rebuild(const Dims &d, const RebuildArgs &a, hipStream_t s);
 hipError_t launch_scan_bwd(const Dims &d, const ScanBwdArgs &a, hipStream_t s);
 hipError_t launch_grad(const Dims &d, const GradArgs &a, hipStream_t s);

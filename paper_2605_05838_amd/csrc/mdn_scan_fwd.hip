@@ -456,12 +456,10 @@ hipError_t pick_dvb(const Dims &d, const ScanFwdArgs &a, hipStream_t s) {
 }
 
 template <bool REBUILD> hipError_t dispatch_scan(const Dims &d, const ScanFwdArgs &a, hipStream_t s) {
-    const bool f32 = d.dtype == 1;
-    if (!a.coef || !a.k || ((f32 || REBUILD) && !a.KT)) return hipErrorInvalidValue;
-    if (d.dk == 64 && d.dv == 64)
-        return f32 ? pick_dvb<float, 64, 64, REBUILD>(d, a, s) : pick_dvb<bf16_t, 64, 64, REBUILD>(d, a, s);
-    if (d.dk == 128 && d.dv == 128)
-        return f32 ? pick_dvb<float, 128, 128, REBUILD>(d, a, s) : pick_dvb<bf16_t, 128, 128, REBUILD>(d, a, s);
+    if (d.dtype == 0) return launch_scan_fwd16(d, a, REBUILD, s);
+    if (!a.coef || !a.k || !a.KT) return hipErrorInvalidValue;
+    if (d.dk == 64 && d.dv == 64) return pick_dvb<float, 64, 64, REBUILD>(d, a, s);
+    if (d.dk == 128 && d.dv == 128) return pick_dvb<float, 128, 128, REBUILD>(d, a, s);
     return hipErrorInvalidValue;
 }
 
@@ -508,8 +506,6 @@ size_t lds_bytes_for_one_workgroup_per_cu(const void *kernel) {
 }
 
 hipError_t launch_scan_fwd(const Dims &d, const ScanFwdArgs &a, hipStream_t s) { return dispatch_scan<false>(d, a, s); }
-
-bool scan_fwd_reads_KT(const Dims &d) { return d.dtype == 1; }
 
 hipError_t launch_rebuild(const Dims &d, const RebuildArgs &r, hipStream_t s) {
     ScanFwdArgs a = {};
