@@ -263,7 +263,8 @@ enum {
                                  (and the reverse pass's operands when operands_saved is given) */
     MDN_KERNEL_SCAN_FWD = 1,  /* sequential inter-chunk propagation of S and M, outputs */
     MDN_KERNEL_INTRA_BWD = 2, /* same as 0 in the operand layouts of the reverse pass */
-    MDN_KERNEL_REBUILD = 3,   /* chunk-start states reconstructed from V~ */
+    MDN_KERNEL_REBUILD = 3,   /* chunk-start states reconstructed from V~; where that shares a launch with the
+                                 reverse scan it is counted here and timed there */
     MDN_KERNEL_SCAN_BWD = 4,  /* reverse inter-chunk scan of dS, dM */
     MDN_KERNEL_GRAD = 5,      /* chunk-parallel gradients dq, dk, dv, dalpha, dbeta, dmu, deta */
     MDN_KERNEL_RECURRENT = 6, /* token-by-token recurrent form */

@@ -136,6 +136,10 @@ std::vector<TimedLaunch> g_timed;
 // this thread is inside the entry point that must not allocate: no timing events, no second stream
 thread_local bool t_no_alloc = false;
 
+void count_launch(int id) {
+    if (g_profiling.load(std::memory_order_relaxed) && !t_no_alloc) g_launched[id].fetch_add(1, std::memory_order_relaxed);
+}
+
 template <typename F> int timed(int id, hipStream_t s, F &&launch) {
     if (t_no_alloc || !g_profiling.load(std::memory_order_relaxed)) return launch_status(launch());
     if (id >= 0 && id < MDN_KERNEL_COUNT) g_launched[id].fetch_add(1, std::memory_order_relaxed);
@@ -302,6 +306,8 @@ struct BwdCall {
 struct Prepared {
     RevOps ro;
     const void *states;
+    bool pending;    // the states are still to be reconstructed, in one launch with the reverse scan:
+    RebuildArgs how;
 };
 
 // Adjoints of the final states that come in from outside can be large against everything dO puts into the states;
@@ -312,7 +318,13 @@ bool precise_call(const Dims &d, const BwdCall &c) {
     return d.dtype == MDN_DTYPE_BF16 && (c.dS_final || c.dM_final);
 }
 
-int bwd_prepare(const Dims &d, const BwdCall &c, const BwdWs &w, hipStream_t s, Prepared *out, bool precise) {
+// Whether the reconstruction and the reverse scan run as one launch (`nseg`: the segments of this call): never slower where
+// the reverse scan is one launch (see scan_pair16_kernel).  32-bit storage has scans of another form.
+bool rebuild_beside_scan(const Dims &d, int nseg) {
+    return !wide(d) && nseg == 1;
+}
+
+int bwd_prepare(const Dims &d, const BwdCall &c, const BwdWs &w, hipStream_t s, Prepared *out, bool precise, int nseg) {
     int rc;
     // chunk-local operands in the layouts of the reverse pass: kept by the forward, or recomputed
     out->ro = w.ops;
@@ -328,18 +340,24 @@ int bwd_prepare(const Dims &d, const BwdCall &c, const BwdWs &w, hipStream_t s, 
     }
     // chunk-start states: given by the forward, or reconstructed from V~
     out->states = precise ? nullptr : c.states_saved;
+    out->pending = false;
     if (!out->states) {
         RebuildArgs ra = {};
         ra.coef = out->ro.coef; ra.k = c.k; ra.KT = out->ro.KT; ra.vt_saved = c.vt_saved; ra.S0 = c.S0; ra.M0 = c.M0;
         ra.states = w.states; ra.states_lo = precise ? w.states_lo : nullptr;
+        out->states = w.states;
+        if (rebuild_beside_scan(d, nseg)) {
+            out->how = ra;
+            out->pending = true;
+            return MDN_OK;
+        }
         rc = timed(MDN_KERNEL_REBUILD, s, [&] { return launch_rebuild(d, ra, s); });
         if (rc) return rc;
-        out->states = w.states;
     }
     return MDN_OK;
 }
 
-int bwd_run(const Dims &d, const BwdCall &c, const BwdWs &w, const Prepared &p, hipStream_t s, bool precise) {
+int bwd_run(const Dims &d, const BwdCall &c, const BwdWs &w, const Prepared &p, hipStream_t s, bool precise, int nseg) {
     int rc;
     const RevOps &ro = p.ro;
     ScanBwdArgs sb = {};
@@ -352,9 +370,13 @@ int bwd_run(const Dims &d, const BwdCall &c, const BwdWs &w, const Prepared &p, 
     ga.states = p.states; ga.dstates = w.dstates;
     ga.states_lo = precise ? w.states_lo : nullptr; ga.dstates_lo = precise ? w.dstates_lo : nullptr;
     ga.dq = c.dq; ga.dk = c.dk; ga.dalpha = c.dalpha; ga.dbeta = c.dbeta; ga.dmu = c.dmu; ga.deta = c.deta;
-    const int nseg = segments(d, true);
     if (nseg == 1) {
-        rc = timed(MDN_KERNEL_SCAN_BWD, s, [&] { return launch_scan_bwd(d, sb, s); });
+        if (p.pending) {
+            count_launch(MDN_KERNEL_REBUILD); // (its time stands with the reverse scan's)
+            rc = timed(MDN_KERNEL_SCAN_BWD, s, [&] { return launch_rebuild_and_scan_bwd(d, p.how, sb, s); });
+        } else {
+            rc = timed(MDN_KERNEL_SCAN_BWD, s, [&] { return launch_scan_bwd(d, sb, s); });
+        }
         if (rc) return rc;
         return timed(MDN_KERNEL_GRAD, s, [&] { return launch_grad(d, ga, s); });
     }
@@ -389,9 +411,10 @@ int bwd_run(const Dims &d, const BwdCall &c, const BwdWs &w, const Prepared &p, 
 int bwd_all(const Dims &d, const BwdCall &c, void *workspace, hipStream_t s) {
     const bool precise = precise_call(d, c);
     const BwdWs w = carve_bwd(d, workspace, precise);
+    const int nseg = segments(d, true); // (asked for once: another thread may change the setting)
     Prepared p;
-    const int rc = bwd_prepare(d, c, w, s, &p, precise);
-    return rc ? rc : bwd_run(d, c, w, p, s, precise);
+    const int rc = bwd_prepare(d, c, w, s, &p, precise, nseg);
+    return rc ? rc : bwd_run(d, c, w, p, s, precise, nseg);
 }
 
 // ---- chunk sizes below 64 (Algorithm 1 lists C in {16, 32, 64}).  The kernels are built around 64-token tiles (four

@@ -141,6 +141,10 @@ size_t lds_bytes_for_one_workgroup_per_cu(const void *kernel);
 hipError_t launch_scan_fwd16(const Dims &d, const ScanFwdArgs &a, bool rebuild, hipStream_t s);
 hipError_t launch_scan_bwd16(const Dims &d, const ScanBwdArgs &a, hipStream_t s);
 hipError_t launch_rebuild(const Dims &d, const RebuildArgs &a, hipStream_t s);
+// the same as arguments of the forward scan's kernels
+ScanFwdArgs rebuild_args(const RebuildArgs &a);
+// 16-bit storage: both in one launch
+hipError_t launch_rebuild_and_scan_bwd(const Dims &d, const RebuildArgs &r, const ScanBwdArgs &b, hipStream_t s);
 hipError_t launch_scan_bwd(const Dims &d, const ScanBwdArgs &a, hipStream_t s);
 hipError_t launch_grad(const Dims &d, const GradArgs &a, hipStream_t s);
 hipError_t launch_recurrent(const Dims &d, const RecurrentArgs &a, hipStream_t s);

@@ -1,245 +1,31 @@
-// Reverse scan for 16-bit storage: the adjoint recurrence of mdn_scan_bwd.hip, chunks from last to first,
-//     dV~ = Bm^T dO + (Gamma_C eta . K) dS' - (Rho_C eta . K) dM'        dV = T^T dV~
-//     dS  = a_C dS' + (a . Q~)^T dO - K^T (a . dV)        dM = m_C dM' - b_C dS' - (b . Q~)^T dO + K^T (pb . dV)
-// one workgroup per (sequence, head) and DVB dv columns, its waves' jobs as in mdn_scan_tiles.h, products transposed as in
-// mdn_scan_fwd16.hip.  K^T, Q^T, Bm^T and T^T are transposing reads of the same tiles that the forward uses: nothing is written
-// to HBM a second time in another orientation for this kernel.
-//
-// A step has three phases, each ended by a barrier:
-//   A  dV~^T of the wave's 16 tokens from the adjoints' copy, the k rows, Bm and dO, left in LDS; dO in the two scalings
-//      with which it enters the states;
-//   B  dV^T = dV~^T T over all tokens, left raw (the output) and in two scalings; (a . Q~)^T dO and (b . Q~)^T dO into the states,
-//      whose products fill the waits of this short phase;
-//   C  K^T (a . dV), K^T (pb . dV) into the states, the new copy.
-#include "mdn_scan_tiles.h"
-#include "mdn_kernels.h"
+// Launches of the reverse scan for 16-bit storage (mdn_scan_bwd16.h), alone or together with the state reconstruction.
+#include "mdn_scan_bwd16.h"
+#include "mdn_scan_fwd16.h"
 
 namespace mdn {
 
 namespace {
 
-typedef bf16_t T;
-typedef Op<T> O;
-
 template <int DK, int DV, int DVB, bool WHOLE>
 __global__ __launch_bounds__(kScanThreads) void scan_bwd16_kernel(Dims d, ScanBwdArgs a) {
-    constexpr int MV = DVB / 16, ND = DK / 64, G = DV / DVB, KS = DK / 32;
-    typedef ATile<T, DVB, 2 * DK> TD; // the adjoints' copy, contraction over dk: dS' | dM'
-    typedef ATile<T, DVB, 64> TV;     // contraction over the chunk's tokens
-    // operands of two chunks; the k tile, read from the first to the last phase, of three where there is room
-    constexpr int KSLOTS = DVB == 16 || DK == 64 ? 3 : 2;
-    __shared__ __align__(16) T rK[KSLOTS][64 * DK];
-    __shared__ __align__(16) T rQ[2][64 * DK];
-    __shared__ __align__(16) T rT[2][4096];
-    __shared__ __align__(16) T rB[2][4096];
-    __shared__ __align__(16) T rO[2][64 * DVB];
-    __shared__ __align__(16) float rC[2][64 * kCoefRows];
-    // what the chain leaves
-    __shared__ __align__(16) T sD[TD::SIZE];
-    __shared__ __align__(16) T sOa[TV::SIZE]; // (scale a . dO)^T
-    __shared__ __align__(16) T sOb[TV::SIZE]; // (-scale b . dO)^T
-    __shared__ __align__(16) T sDV[TV::SIZE]; // dV~^T
-    __shared__ __align__(16) T sR0[TV::SIZE]; // dV^T
-    __shared__ __align__(16) T sRa[TV::SIZE]; // (-a . dV)^T
-    __shared__ __align__(16) T sRb[TV::SIZE]; // (pb . dV)^T
+    __shared__ ScanBwdLds<DK, DV, DVB> lds;
+    scan_bwd16<DK, DV, DVB, WHOLE>(d, a, blockIdx.x, lds);
+}
 
-    int bh, blkv;
-    xcd_map(blockIdx.x, G, bh, blkv);
-    if (bh >= d.BH) return;
-    const ScanSeq sq = scan_seq<WHOLE>(d, bh);
-    const int dv0 = blkv * DVB, n0 = sq.n0, n1 = sq.n1;
-    const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(wave_id()), w = wv & 3, w2 = wv & 1;
-    const int r = lane & 15, kg = lane >> 4, i = w * 16 + r;
-    // a partial last chunk (the first one here): its loads stop at the last real token
-    const int ragged = !WHOLE && (sq.len & 63) ? sq.len >> 6 : -1, last = (sq.len & 63) - 1; // that chunk (or none), its last row
-    auto first_token = [&](int n) { return sq.tok + (size_t)n * 64 * d.H; };
-
-    if (wv >= 6) {
-        // ---------------------------------------------------------------- stores
-        StateStore<DK, DV, MV> st;
-        constexpr int NS = StateStore<DK, DV, MV>::N;
-        __syncthreads();
-        for (int n = n1 - 1; n >= n0; --n) {
-            T *states = static_cast<T *>(a.dstates) + (sq.blk + n) * (2 * DK * DV); // adjoints of this chunk's END states
-            st.read(sD, w2, lane);
-            st.template put<0, NS / 2>(states, dv0, w2, lane);
-            __syncthreads(); // A
-            st.template put<NS / 2, NS * 3 / 4>(states, dv0, w2, lane);
-            __syncthreads(); // B
-            store_token_rows<DV, MV, WHOLE>(static_cast<T *>(a.dv) + first_token(n) * DV + dv0, sR0, !WHOLE && n == ragged ? last + 1 : 64, d.H, w2, lane);
-            st.template put<NS * 3 / 4, NS>(states, dv0, w2, lane);
-            __syncthreads(); // C
-        }
-    } else if (wv >= 4) {
-        // ---------------------------------------------------------------- loads: two chunks ahead, as the slots become free
-        const int turn = blkv & 3;
-        const unsigned rsk = (unsigned)(d.H * DK), rsv = (unsigned)(d.H * DV);
-        TileLoad<T, DK, true> tk; // (the rows of q lie as those of k)
-        TileLoad<T, 64, true> tm;
-        TileLoad<T, DVB, false> tv;
-        TileLoad<float, kCoefRows, false> tc;
-        tm.aim(64, w2, lane, turn, 63);
-        tc.aim(kCoefRows, w2, lane, turn, 63);
-        auto aim_at = [&](int rows) {
-            tk.aim(rsk, w2, lane, turn, rows);
-            tv.aim(rsv, w2, lane, turn, rows);
-        };
-        auto request_rows = [&](const void *x, int n, const T *ring, int slot) {
-            tk.request(static_cast<const T *>(x) + first_token(n) * DK, lds_addr(ring) + slot * (64 * DK * (int)sizeof(T)), w2, turn);
-        };
-        auto request_m = [&](const void *m, int n, const T *ring, int par) {
-            tm.request(static_cast<const T *>(m) + (sq.blk + n) * 4096, lds_addr(ring) + par * (4096 * (int)sizeof(T)), w2, turn);
-        };
-        auto request_o = [&](int n, int par) {
-            tv.request(static_cast<const T *>(a.dO) + first_token(n) * DV + dv0, lds_addr(rO[0]) + par * (64 * DVB * (int)sizeof(T)), w2, turn);
-        };
-        auto request_c = [&](int n, int par) {
-            tc.request(a.coef + (sq.blk + n) * (64 * kCoefRows), lds_addr(rC[0]) + par * (64 * kCoefRows * 4), w2, turn);
-        };
-        constexpr int NALL = 2 * tk.COUNT + 2 * tm.COUNT + tv.COUNT + tc.COUNT;
-        for (int ahead = 0; ahead < 2; ++ahead) {
-            const int n = n1 - 1 - ahead >= n0 ? n1 - 1 - ahead : n0; // (a single chunk: twice)
-            aim_at(!WHOLE && n == ragged ? last : 63);
-            request_rows(a.k, n, rK[0], ahead);
-            request_c(n, ahead);
-            request_o(n, ahead);
-            request_m(a.Bm, n, rB[0], ahead);
-            request_m(a.Tm, n, rT[0], ahead);
-            request_rows(a.q, n, rQ[0], ahead);
-        }
-        wait_vm<NALL>();
-        __syncthreads();
-        if (!WHOLE && n0 != ragged) aim_at(63); // (what is requested from here on is not the partial chunk, unless that is the only one)
-        int slot = 2, par = 0;
-        for (int n = n1 - 1; n >= n0; --n) {
-            const int nn = n - 2 >= n0 ? n - 2 : n0; // (past the end: the first chunk, into slots that nothing reads any more)
-            if (KSLOTS == 3) request_rows(a.k, nn, rK[0], slot);
-            __syncthreads(); // A: Bm, T, dO and the coefficients of this chunk have been read
-            request_m(a.Bm, nn, rB[0], par);
-            request_m(a.Tm, nn, rT[0], par);
-            request_o(nn, par);
-            request_c(nn, par);
-            __syncthreads(); // B: so have k and q
-            if (KSLOTS == 2) request_rows(a.k, nn, rK[0], par);
-            request_rows(a.q, nn, rQ[0], par);
-            wait_vm<NALL>(); // everything of the next chunk is there
-            slot = slot == 2 ? 0 : slot + 1;
-            par ^= 1;
-            __syncthreads(); // C
-        }
-        wait_vm<0>(); // (no transfer outlives the workgroup)
-    } else {
-        // ---------------------------------------------------------------- the chain
-        __builtin_amdgcn_s_setprio(3);
-        ChainStates<DK, DV, MV> acc;
-        acc.load(a.dS_final, a.dM_final, sq.state, w, dv0, r, kg);
-        acc.publish(sD, w, r, kg);
-        __syncthreads();
-        int slot = 0, par = 0;
-        for (int n = n1 - 1; n >= n0; --n) {
-            if (a.dstates_lo) acc.store_lo(static_cast<T *>(a.dstates_lo) + (sq.blk + n) * (2 * DK * DV), w, dv0, r, kg);
-            const T *kc = rK[slot], *qc = rQ[par], *oc = rO[par];
-            const f32x4 c0 = *reinterpret_cast<const f32x4 *>(rC[par] + i * kCoefRows);
-            const f32x4 c1 = *reinterpret_cast<const f32x4 *>(rC[par] + i * kCoefRows + 4);
-            // ---- phase A
-            f32x4 x1[MV], x2[MV], dv[MV];
-            zero_acc(x1);
-            zero_acc(x2);
-            zero_acc(dv);
-#pragma unroll
-            for (int s = 0; s < KS; ++s) {
-                const O::Frag fk = token_tile_row_frag<DK>(kc, i, s, kg);
-#pragma unroll
-                for (int mv = 0; mv < MV; ++mv) {
-                    x1[mv] = O::mma(TD::frag(sD, mv, s * 32, r, kg), fk, x1[mv]);
-                    x2[mv] = O::mma(TD::frag(sD, mv, DK + s * 32, r, kg), fk, x2[mv]);
-                }
-            }
-            O::Frag tT[2];
-#pragma unroll
-            for (int s = 0; s < 2; ++s) {
-                const O::Frag bT = token_tile_col_frag<64>(rB[par], w, s, r, kg);
-#pragma unroll
-                for (int mv = 0; mv < MV; ++mv) {
-                    // dO^T out of the rows as they are in HBM: lane 4e + c of a 16-lane group addresses the columns of MFMA rows 4c .. 4c+3
-                    const T *p = oc + (s * 32 + kg * 8 + (r >> 2)) * DVB + (r & 3) * (4 * MV) + 4 * mv;
-                    dv[mv] = O::mma(tr_pair(p, p + 4 * DVB), bT, dv[mv]);
-                }
-                tT[s] = token_tile_col_frag<64>(rT[par], w, s, r, kg);
-            }
-            bf16x4 u[MV];
-            load_cols_raw<MV>(oc + i * DVB + kg * (4 * MV), u);
-            // (rows behind a partial chunk hold the last real row of q and dO: they must not reach the states.  In the other
-            //  products Bm, Gamma_C and Rho_C are zero there.)
-            const float real = WHOLE || n != ragged || i <= last ? d.scale : 0.f;
-#pragma unroll
-            for (int mv = 0; mv < MV; ++mv) {
-                const f32x4 ow = widen4(u[mv]);
-                TV::put4(sOa, mv * 16 + kg * 4, i, (real * c0[COEF_A]) * ow);
-                TV::put4(sOb, mv * 16 + kg * 4, i, -(real * c0[COEF_B]) * ow);
-                TV::put4(sDV, mv * 16 + kg * 4, i, dv[mv] + c1[COEF_GC - 4] * x1[mv] - c1[COEF_RC - 4] * x2[mv]);
-            }
-            __syncthreads(); // A
-            // ---- phase B
-            f32x4 dR[MV];
-            zero_acc(dR);
-#pragma unroll
-            for (int s = 0; s < 2; ++s)
-#pragma unroll
-                for (int mv = 0; mv < MV; ++mv) dR[mv] = O::mma(TV::frag(sDV, mv, s * 32, r, kg), tT[s], dR[mv]);
-            const float aC = c0[COEF_AC], bC = c1[COEF_BC - 4], mC = c1[COEF_MC - 4];
-#pragma unroll
-            for (int mv = 0; mv < MV; ++mv)
-#pragma unroll
-                for (int nd = 0; nd < ND; ++nd) {
-                    const f32x4 s = acc.S[mv][nd], m = acc.M[mv][nd];
-                    acc.S[mv][nd] = aC * s;
-                    acc.M[mv][nd] = mC * m - bC * s;
-                }
-            O::Frag kT[2][ND];
-#pragma unroll
-            for (int s = 0; s < 2; ++s) {
-                O::Frag qT[ND];
-#pragma unroll
-                for (int nd = 0; nd < ND; ++nd) qT[nd] = token_tile_col_frag<DK>(qc, w * ND + nd, s, r, kg);
-#pragma unroll
-                for (int mv = 0; mv < MV; ++mv) {
-                    const O::Frag fa = TV::frag(sOa, mv, s * 32, r, kg), fb = TV::frag(sOb, mv, s * 32, r, kg);
-#pragma unroll
-                    for (int nd = 0; nd < ND; ++nd) {
-                        acc.S[mv][nd] = O::mma(fa, qT[nd], acc.S[mv][nd]);
-                        acc.M[mv][nd] = O::mma(fb, qT[nd], acc.M[mv][nd]);
-                    }
-                }
-#pragma unroll
-                for (int nd = 0; nd < ND; ++nd) kT[s][nd] = token_tile_col_frag<DK>(kc, w * ND + nd, s, r, kg);
-            }
-#pragma unroll
-            for (int mv = 0; mv < MV; ++mv) {
-                TV::put4(sR0, mv * 16 + kg * 4, i, dR[mv]);
-                TV::put4(sRa, mv * 16 + kg * 4, i, -c0[COEF_A] * dR[mv]);
-                TV::put4(sRb, mv * 16 + kg * 4, i, c0[COEF_PB] * dR[mv]);
-            }
-            __syncthreads(); // B
-            // ---- phase C
-#pragma unroll
-            for (int s = 0; s < 2; ++s)
-#pragma unroll
-                for (int mv = 0; mv < MV; ++mv) {
-                    const O::Frag fa = TV::frag(sRa, mv, s * 32, r, kg), fb = TV::frag(sRb, mv, s * 32, r, kg);
-#pragma unroll
-                    for (int nd = 0; nd < ND; ++nd) {
-                        acc.S[mv][nd] = O::mma(fa, kT[s][nd], acc.S[mv][nd]);
-                        acc.M[mv][nd] = O::mma(fb, kT[s][nd], acc.M[mv][nd]);
-                    }
-                }
-            acc.publish(sD, w, r, kg);
-            slot = slot == KSLOTS - 1 ? 0 : slot + 1;
-            par ^= 1;
-            __syncthreads(); // C
-        }
-        acc.store(a.dS0, a.dM0, sq.state, w, dv0, r, kg);
-    }
+// Both at once: the first half of the workgroups walks the reverse scan, the second half (its steps are shorter) the
+// reconstruction.  Neither needs anything of the other.  One launch after the other, 3 x 1 500 tokens of 8 heads of 64 take
+// 20 + 29 us with 96 of the 256 CUs at work; together the shorter chain costs nothing.  Where one of them fills the chip the
+// second half's workgroups start as the first half's end, without the drain and the start between two launches.  Forward and
+// backward in us, two launches / one: 3 x 1 500, 8 heads of 64 122 / 105; 2 048, 8 heads of 128 133 / 109; 300, 16 heads 57 / 50;
+// 4 x 1 024, 16 heads 188 / 182; 4 x 4 096, 16 heads 701 / 695; packed 32 768 in 64 sequences, 16 heads 1 586 / 1 585.
+template <int DK, int DV, int DVB, bool WHOLE>
+__global__ __launch_bounds__(kScanThreads) void scan_pair16_kernel(Dims d, ScanBwdArgs b, ScanFwdArgs f) {
+    typedef ScanBwdLds<DK, DV, DVB> LB;
+    typedef ScanFwdLds<DK, DV, DVB, true> LF;
+    __shared__ __align__(16) char lds[sizeof(LB) > sizeof(LF) ? sizeof(LB) : sizeof(LF)];
+    const int half = gridDim.x / 2, block = blockIdx.x;
+    if (block < half) scan_bwd16<DK, DV, DVB, WHOLE>(d, b, block, *reinterpret_cast<LB *>(lds));
+    else scan_fwd16<DK, DV, DVB, true, WHOLE>(d, f, block - half, *reinterpret_cast<LF *>(lds));
 }
 
 template <int DK, int DV, int DVB> hipError_t launch_t(const Dims &d, const ScanBwdArgs &a, hipStream_t s) {
@@ -252,13 +38,32 @@ template <int DK, int DV, int DVB> hipError_t launch_t(const Dims &d, const Scan
 template <int DK, int DV> hipError_t pick_dvb(const Dims &d, const ScanBwdArgs &a, hipStream_t s) {
     return scan_dvb(d) == 16 ? launch_t<DK, DV, 16>(d, a, s) : launch_t<DK, DV, 32>(d, a, s);
 }
+template <int DK, int DV, int DVB> hipError_t launch_pair_t(const Dims &d, const ScanBwdArgs &b, const ScanFwdArgs &f, hipStream_t s) {
+    const dim3 grid(((d.BH + 7) / 8) * 8 * (DV / DVB) * 2), block(kScanThreads);
+    if (whole_chunks(d)) hipLaunchKernelGGL((scan_pair16_kernel<DK, DV, DVB, true>), grid, block, 0, s, d, b, f);
+    else hipLaunchKernelGGL((scan_pair16_kernel<DK, DV, DVB, false>), grid, block, 0, s, d, b, f);
+    return hipGetLastError();
+}
+template <int DK, int DV> hipError_t pick_pair_dvb(const Dims &d, const ScanBwdArgs &b, const ScanFwdArgs &f, hipStream_t s) {
+    return scan_dvb(d) == 16 ? launch_pair_t<DK, DV, 16>(d, b, f, s) : launch_pair_t<DK, DV, 32>(d, b, f, s);
+}
+
+bool operands_there(const ScanBwdArgs &a) { return a.coef && a.q && a.k && a.dO && a.Bm && a.Tm; }
 
 } // namespace
 
 hipError_t launch_scan_bwd16(const Dims &d, const ScanBwdArgs &a, hipStream_t s) {
-    if (!a.coef || !a.q || !a.k || !a.dO || !a.Bm || !a.Tm) return hipErrorInvalidValue;
+    if (!operands_there(a)) return hipErrorInvalidValue;
     if (d.dk == 64 && d.dv == 64) return pick_dvb<64, 64>(d, a, s);
     if (d.dk == 128 && d.dv == 128) return pick_dvb<128, 128>(d, a, s);
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_rebuild_and_scan_bwd(const Dims &d, const RebuildArgs &r, const ScanBwdArgs &b, hipStream_t s) {
+    const ScanFwdArgs f = rebuild_args(r);
+    if (d.dtype != 0 || !operands_there(b) || !f.vt_saved || !f.states_saved) return hipErrorInvalidValue;
+    if (d.dk == 64 && d.dv == 64) return pick_pair_dvb<64, 64>(d, b, f, s);
+    if (d.dk == 128 && d.dv == 128) return pick_pair_dvb<128, 128>(d, b, f, s);
     return hipErrorInvalidValue;
 }
 

@@ -507,7 +507,7 @@ size_t lds_bytes_for_one_workgroup_per_cu(const void *kernel) {
 
 hipError_t launch_scan_fwd(const Dims &d, const ScanFwdArgs &a, hipStream_t s) { return dispatch_scan<false>(d, a, s); }
 
-hipError_t launch_rebuild(const Dims &d, const RebuildArgs &r, hipStream_t s) {
+ScanFwdArgs rebuild_args(const RebuildArgs &r) {
     ScanFwdArgs a = {};
     a.coef = r.coef;
     a.k = r.k;
@@ -517,7 +517,9 @@ hipError_t launch_rebuild(const Dims &d, const RebuildArgs &r, hipStream_t s) {
     a.M0 = r.M0;
     a.states_saved = r.states;
     a.states_lo = r.states_lo;
-    return dispatch_scan<true>(d, a, s);
+    return a;
 }
+
+hipError_t launch_rebuild(const Dims &d, const RebuildArgs &r, hipStream_t s) { return dispatch_scan<true>(d, rebuild_args(r), s); }
 
 } // namespace mdn

@@ -1,277 +1,14 @@
-// Forward scan and state reconstruction for 16-bit storage: the recurrence of mdn_scan_fwd.hip (Sec. 3.1 "Chunkwise Algorithm"),
-//     V~ = T (V - a . (K S) + pb . (K M))        O  = diag(a) Q~ S - diag(b) Q~ M + Bm V~
-//     S' = a_C S - b_C M + (diag(Gamma_C) K~)^T V~        M' = m_C M - (diag(Rho_C) K~)^T V~
-// one workgroup per (sequence, head) and DVB dv columns, its waves' jobs as in mdn_scan_tiles.h.  Products are formed transposed,
-// with the dv index as the MFMA row index; row 4 kg + x of tile mv stands for column dv0 + 4 MV kg + 4 mv + x.
-//
-// A step has three phases, each ended by a barrier:
-//   A  wave w forms (K S)^T, (K M)^T, (Q S)^T, (Q M)^T for its 16 tokens in one pass over the states' copy, leaves R^T in LDS;
-//   B  V~^T = R^T T^T over all tokens, left in LDS in three scalings (raw, Gamma_C eta, -Rho_C eta);
-//   C  the states' update out of K^T (transposing reads of the k tile) and the scaled V~, Bm V~ for the output, the new copy.
-// What a phase reads of the operands is read before the barrier in front of it.  The reconstruction (REBUILD) reads V~ and
-// has the last two phases only.
-//
-// What bounds it: with every CU busy (256 workgroups) the mixture of loads and stores itself; a program that only makes this
-// kernel's requests takes 155-168 us at 4 x 4 096 tokens of 16 heads of 128.  With fewer workgroups or without kept states, the
-// step's chain of LDS reads, products and barriers.
-#include "mdn_scan_tiles.h"
-#include "mdn_kernels.h"
+// Launches of the forward scan and of the state reconstruction for 16-bit storage (mdn_scan_fwd16.h).
+#include "mdn_scan_fwd16.h"
 
 namespace mdn {
 
 namespace {
 
-typedef bf16_t T;
-typedef Op<T> O;
-
 template <int DK, int DV, int DVB, bool REBUILD, bool WHOLE>
 __global__ __launch_bounds__(kScanThreads) void scan_fwd16_kernel(Dims d, ScanFwdArgs a) {
-    constexpr int MV = DVB / 16, ND = DK / 64, G = DV / DVB, KS = DK / 32;
-    typedef ATile<T, DVB, 2 * DK> TS; // the states' copy, contraction over dk: S | M
-    typedef ATile<T, DVB, 64> TV;     // contraction over the chunk's tokens
-    // operands: of three chunks where a tile is read in the last phase, of two where it is done with before
-    __shared__ __align__(16) T rK[3][64 * DK];
-    __shared__ __align__(16) T rT[REBUILD ? 1 : 2][REBUILD ? 8 : 4096];
-    __shared__ __align__(16) T rB[REBUILD ? 1 : 2][REBUILD ? 8 : 4096];
-    __shared__ __align__(16) T rV[3][64 * DVB];
-    __shared__ __align__(16) float rC[3][64 * kCoefRows];
-    // what the chain leaves
-    __shared__ __align__(16) T sSt[TS::SIZE];
-    __shared__ __align__(16) T sRt[REBUILD ? 8 : TV::SIZE];
-    __shared__ __align__(16) T sV0[REBUILD ? 8 : TV::SIZE];
-    __shared__ __align__(16) T sVg[TV::SIZE];
-    __shared__ __align__(16) T sVr[TV::SIZE];
-    __shared__ __align__(16) T sO[REBUILD ? 8 : TV::SIZE];
-
-    int bh, blkv;
-    xcd_map(blockIdx.x, G, bh, blkv);
-    if (bh >= d.BH) return;
-    const ScanSeq sq = scan_seq<WHOLE>(d, bh);
-    const int dv0 = blkv * DVB, n0 = sq.n0, n1 = sq.n1;
-    const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(wave_id()), w = wv & 3, w2 = wv & 1;
-    const int r = lane & 15, kg = lane >> 4, i = w * 16 + r;
-    // a partial last chunk: its loads stop at the last real token
-    const int ragged = !WHOLE && (sq.len & 63) ? sq.len >> 6 : -1, last = (sq.len & 63) - 1; // that chunk (or none), its last row
-    auto first_token = [&](int n) { return sq.tok + (size_t)n * 64 * d.H; };
-
-    if (wv >= 6) {
-        // ---------------------------------------------------------------- stores
-        auto rows_of = [&](int n) { return !WHOLE && n == ragged ? last + 1 : 64; };
-        StateStore<DK, DV, MV> st;
-        constexpr int NS = StateStore<DK, DV, MV>::N;
-        __syncthreads();
-        for (int n = n0; n < n1; ++n) {
-            T *states = static_cast<T *>(a.states_saved) + (sq.blk + n) * (2 * DK * DV); // this chunk's start states
-            if (a.states_saved) st.read(sSt, w2, lane);
-            if (!REBUILD && n > n0) store_token_rows<DV, MV, WHOLE>(static_cast<T *>(a.o) + first_token(n - 1) * DV + dv0, sO, 64, d.H, w2, lane);
-            if (a.states_saved) st.template put<0, NS / 2>(states, dv0, w2, lane);
-            if (!REBUILD) __syncthreads(); // A
-            if (a.states_saved) st.template put<NS / 2, NS * 3 / 4>(states, dv0, w2, lane);
-            __syncthreads(); // B
-            if (!REBUILD && a.vt_saved)
-                store_token_rows<DV, MV, WHOLE>(static_cast<T *>(a.vt_saved) + first_token(n) * DV + dv0, sV0, rows_of(n), d.H, w2, lane);
-            if (a.states_saved) st.template put<NS * 3 / 4, NS>(states, dv0, w2, lane);
-            __syncthreads(); // C
-        }
-        if (!REBUILD) store_token_rows<DV, MV, WHOLE>(static_cast<T *>(a.o) + first_token(n1 - 1) * DV + dv0, sO, rows_of(n1 - 1), d.H, w2, lane);
-    } else if (wv >= 4) {
-        // ---------------------------------------------------------------- loads: two chunks ahead
-        const int turn = blkv & 3;
-        const unsigned rsk = (unsigned)(d.H * DK), rsv = (unsigned)(d.H * DV);
-        TileLoad<T, DK, true> tk;
-        TileLoad<T, 64, true> tm;
-        TileLoad<T, DVB, false> tv;
-        TileLoad<float, kCoefRows, false> tc;
-        constexpr int NK = tk.COUNT, NM = REBUILD ? 0 : tm.COUNT, NV = tv.COUNT + tc.COUNT;
-        tm.aim(64, w2, lane, turn, 63);
-        tc.aim(kCoefRows, w2, lane, turn, 63);
-        tk.aim(rsk, w2, lane, turn, 63);
-        tv.aim(rsv, w2, lane, turn, 63);
-        auto aim_at = [&](int n) {
-            if (!WHOLE && n == ragged) {
-                tk.aim(rsk, w2, lane, turn, last);
-                tv.aim(rsv, w2, lane, turn, last);
-            }
-        };
-        auto request_k = [&](int n, int slot) {
-            tk.request(static_cast<const T *>(a.k) + first_token(n) * DK, lds_addr(rK[0]) + slot * (64 * DK * (int)sizeof(T)), w2, turn);
-        };
-        auto request_v = [&](int n, int slot) { // V (V~) and the coefficients
-            tv.request(static_cast<const T *>(REBUILD ? a.vt_saved : a.v) + first_token(n) * DV + dv0,
-                       lds_addr(rV[0]) + slot * (64 * DVB * (int)sizeof(T)), w2, turn);
-            tc.request(a.coef + (sq.blk + n) * (64 * kCoefRows), lds_addr(rC[0]) + slot * (64 * kCoefRows * 4), w2, turn);
-        };
-        auto request_m = [&](const void *m, int n, const T *ring, int par) {
-            if constexpr (!REBUILD) tm.request(static_cast<const T *>(m) + (sq.blk + n) * 4096, lds_addr(ring) + par * (4096 * (int)sizeof(T)), w2, turn);
-        };
-        for (int ahead = 0; ahead < 2; ++ahead) {
-            const int n = n0 + ahead < n1 ? n0 + ahead : n0; // (a single chunk: twice)
-            aim_at(n);
-            request_k(n, ahead);
-            request_v(n, ahead);
-            request_m(a.Tm, n, rT[0], ahead);
-            request_m(a.Bm, n, rB[0], ahead);
-        }
-        wait_vm<NK + NV + 2 * NM>();
-        __syncthreads();
-        int slot = 2, par = 0;
-        for (int n = n0; n < n1; ++n) {
-            const int nn = n + 2 < n1 ? n + 2 : n1 - 1; // (past the end: the last chunk, into slots that nothing reads any more)
-            aim_at(nn);
-            request_k(nn, slot);
-            if (!REBUILD) __syncthreads(); // A: T of this chunk has been read
-            request_m(a.Tm, nn, rT[0], par);
-            request_v(nn, slot);
-            wait_vm<NK + NM + NV>(); // everything of the next chunk is there
-            __syncthreads(); // B: so has Bm
-            request_m(a.Bm, nn, rB[0], par);
-            slot = slot == 2 ? 0 : slot + 1;
-            par ^= 1;
-            __syncthreads(); // C
-        }
-        wait_vm<0>(); // (no transfer outlives the workgroup)
-    } else {
-        // ---------------------------------------------------------------- the chain
-        __builtin_amdgcn_s_setprio(3);
-        // q rows of two chunks in registers: the only operand without a place in LDS
-        const unsigned iH = (unsigned)(i * d.H), iHr = (unsigned)(min(i, last) * d.H);
-        struct QRows { O::Frag f[KS]; };
-        auto load_q = [&](int n, QRows &q) {
-            if constexpr (!REBUILD) {
-                n = n < n1 ? n : n1 - 1;
-                const T *Qg = static_cast<const T *>(a.q) + first_token(n) * DK;
-                const unsigned it = !WHOLE && n == ragged ? iHr : iH;
-#pragma unroll
-                for (int s = 0; s < KS; ++s) q.f[s] = O::load(at32(Qg, it * DK + kg * 8 + s * 32));
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        };
-        QRows qa, qb;
-        load_q(n0, qa);
-        load_q(n0 + 1, qb);
-        ChainStates<DK, DV, MV> acc;
-        acc.load(a.S0, a.M0, sq.state, w, dv0, r, kg);
-        acc.publish(sSt, w, r, kg);
-        if (REBUILD && a.states_lo) acc.store_lo(static_cast<T *>(a.states_lo) + (sq.blk + n0) * (2 * DK * DV), w, dv0, r, kg);
-        __syncthreads();
-        // what a step needs first, read one barrier early
-        O::Frag fk[KS];
-        f32x4 c0, c1;
-        bf16x4 u[MV];
-        int slot = 0, par = 0;
-        auto first_reads = [&]() {
-            if constexpr (!REBUILD) {
-#pragma unroll
-                for (int s = 0; s < KS; ++s) fk[s] = token_tile_row_frag<DK>(rK[slot], i, s, kg);
-            }
-            c0 = *reinterpret_cast<const f32x4 *>(rC[slot] + i * kCoefRows);
-            c1 = *reinterpret_cast<const f32x4 *>(rC[slot] + i * kCoefRows + 4);
-            load_cols_raw<MV>(rV[slot] + i * DVB + kg * (4 * MV), u);
-        };
-        first_reads();
-        auto step = [&](int n, QRows &q) {
-            f32x4 o[MV];
-            bf16x4 vb[MV]; // V~ in storage form
-            O::Frag kt[2][ND], bm[2];
-            auto read_kt = [&]() {
-#pragma unroll
-                for (int s = 0; s < 2; ++s)
-#pragma unroll
-                    for (int nd = 0; nd < ND; ++nd) kt[s][nd] = token_tile_col_frag<DK>(rK[slot], w * ND + nd, s, r, kg);
-            };
-            if constexpr (!REBUILD) {
-                f32x4 x1[MV], x2[MV], os[MV], om[MV], v[MV];
-                zero_acc(x1);
-                zero_acc(x2);
-                zero_acc(os);
-                zero_acc(om);
-                zero_acc(v);
-#pragma unroll
-                for (int s = 0; s < KS; ++s)
-#pragma unroll
-                    for (int mv = 0; mv < MV; ++mv) {
-                        const O::Frag fs = TS::frag(sSt, mv, s * 32, r, kg), fm = TS::frag(sSt, mv, DK + s * 32, r, kg);
-                        x1[mv] = O::mma(fs, fk[s], x1[mv]);
-                        x2[mv] = O::mma(fm, fk[s], x2[mv]);
-                        os[mv] = O::mma(fs, q.f[s], os[mv]);
-                        om[mv] = O::mma(fm, q.f[s], om[mv]);
-                    }
-                O::Frag tm[2];
-#pragma unroll
-                for (int s = 0; s < 2; ++s) tm[s] = token_tile_row_frag<64>(rT[par], i, s, kg);
-#pragma unroll
-                for (int mv = 0; mv < MV; ++mv)
-                    TV::put4(sRt, mv * 16 + kg * 4, i, widen4(u[mv]) - c0[COEF_A] * x1[mv] + c0[COEF_PB] * x2[mv]);
-                load_q(n + 2, q);
-                __syncthreads(); // A
-#pragma unroll
-                for (int s = 0; s < 2; ++s)
-#pragma unroll
-                    for (int mv = 0; mv < MV; ++mv) v[mv] = O::mma(TV::frag(sRt, mv, s * 32, r, kg), tm[s], v[mv]);
-#pragma unroll
-                for (int s = 0; s < 2; ++s) bm[s] = token_tile_row_frag<64>(rB[par], i, s, kg);
-                read_kt();
-#pragma unroll
-                for (int mv = 0; mv < MV; ++mv) {
-                    o[mv] = d.scale * (c0[COEF_A] * os[mv] - c0[COEF_B] * om[mv]);
-                    vb[mv] = narrow4<T>(v[mv]);
-                    TV::put4_raw(sV0, mv * 16 + kg * 4, i, vb[mv]);
-                }
-            } else {
-                read_kt();
-#pragma unroll
-                for (int mv = 0; mv < MV; ++mv) vb[mv] = u[mv];
-            }
-            const float aC = c0[COEF_AC], bC = c1[COEF_BC - 4], mC = c1[COEF_MC - 4];
-#pragma unroll
-            for (int mv = 0; mv < MV; ++mv) {
-                const f32x4 vt = widen4_packed(vb[mv]);
-                TV::put4(sVg, mv * 16 + kg * 4, i, c1[COEF_GC - 4] * vt);
-                TV::put4(sVr, mv * 16 + kg * 4, i, -c1[COEF_RC - 4] * vt);
-#pragma unroll
-                for (int nd = 0; nd < ND; ++nd) {
-                    acc.S[mv][nd] = aC * acc.S[mv][nd] - bC * acc.M[mv][nd];
-                    acc.M[mv][nd] = mC * acc.M[mv][nd];
-                }
-            }
-            __syncthreads(); // B
-#pragma unroll
-            for (int s = 0; s < 2; ++s)
-#pragma unroll
-                for (int mv = 0; mv < MV; ++mv) {
-                    const O::Frag fg = TV::frag(sVg, mv, s * 32, r, kg), fr = TV::frag(sVr, mv, s * 32, r, kg);
-#pragma unroll
-                    for (int nd = 0; nd < ND; ++nd) {
-                        acc.S[mv][nd] = O::mma(fg, kt[s][nd], acc.S[mv][nd]);
-                        acc.M[mv][nd] = O::mma(fr, kt[s][nd], acc.M[mv][nd]);
-                    }
-                }
-            if constexpr (!REBUILD) {
-#pragma unroll
-                for (int s = 0; s < 2; ++s)
-#pragma unroll
-                    for (int mv = 0; mv < MV; ++mv) o[mv] = O::mma(TV::frag(sV0, mv, s * 32, r, kg), bm[s], o[mv]);
-            }
-            slot = slot == 2 ? 0 : slot + 1;
-            par ^= 1;
-            first_reads();
-            acc.publish(sSt, w, r, kg);
-            if constexpr (!REBUILD) {
-#pragma unroll
-                for (int mv = 0; mv < MV; ++mv) TV::put4(sO, mv * 16 + kg * 4, i, o[mv]);
-            } else if (a.states_lo && n + 1 < n1) {
-                acc.store_lo(static_cast<T *>(a.states_lo) + (sq.blk + n + 1) * (2 * DK * DV), w, dv0, r, kg);
-            }
-            __syncthreads(); // C
-        };
-        int n = n0;
-        for (; n + 1 < n1; n += 2) {
-            step(n, qa);
-            step(n + 1, qb);
-        }
-        if (n < n1) step(n, qa);
-        acc.store(a.S_final, a.M_final, sq.state, w, dv0, r, kg);
-    }
+    __shared__ ScanFwdLds<DK, DV, DVB, REBUILD> lds;
+    scan_fwd16<DK, DV, DVB, REBUILD, WHOLE>(d, a, blockIdx.x, lds);
 }
 
 template <int DK, int DV, int DVB, bool REBUILD> hipError_t launch_t(const Dims &d, const ScanFwdArgs &a, hipStream_t s) {

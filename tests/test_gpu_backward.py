@@ -185,3 +185,33 @@ def test_partial_last_chunk_together_with_segments_on_two_streams(T, nseg):
                        M0=a["M0"], scale=w.scale)
     for name in GRADS:
         assert worst_err(host(g2[name]), ref[name]) <= TOL["bf16"], name
+
+
+@pytest.mark.parametrize("B,H,d,T,adjoints", [(2, 2, 64, 512, False), (1, 3, 128, 500, True), (6, 8, 128, 512, False),
+                                              (6, 8, 128, 449, True), (12, 8, 64, 513, True)])
+def test_states_rebuilt_in_the_launch_of_the_reverse_scan_are_those_of_a_launch_of_their_own(B, H, d, T, adjoints):
+    """16 and 32 dv columns per workgroup, whole and partial last chunks, with and without rounding remainders: a call split
+    into segments reconstructs in a launch of its own, and every gradient agrees bit for bit."""
+    w = synth.custom(B=B, T=T, H=H, dk=d, dv=d, dtype="bf16", seed=53, with_eta=True, s0_std=0.2, backward=True)
+    t = to_dev(w)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    final = [torch.randn((B, H, d, d), device="cuda", generator=gen) if adjoints else None for _ in range(2)]
+    g = []
+    for nseg in (1, 2):
+        old = binding.set_segments(nseg)
+        try:
+            g.append(run_fwd_bwd(w, t, *final)[1])
+        finally:
+            binding.set_segments(old)
+    for name in GRADS:
+        assert torch.equal(g[0][name], g[1][name]), name
+
+
+@pytest.mark.parametrize("keep", [False, True])
+@pytest.mark.parametrize("B,H,d", [(6, 8, 128), (12, 8, 64), (1, 1, 128)])
+@pytest.mark.parametrize("T", [1, 64, 65, 192, 255])
+def test_as_few_chunks_as_the_scans_keep_in_flight(T, B, H, d, keep):
+    """One to four chunks, whole and partial, against the rings of two and three chunks of the 16-bit scans; 32 and 16 columns
+    per workgroup."""
+    w = synth.custom(B=B, T=T, H=H, dk=d, dv=d, dtype="bf16", seed=59, with_eta=True, s0_std=0.2, backward=True)
+    check_bwd(w, pairs=[(0, 0), (B - 1, H - 1)], save_states=keep, save_operands=keep)
