@@ -16,10 +16,10 @@
 // uses Y^T dV~ = K^T (a . T^T dV~).  That trades three 64 x d products and their 1.3 KB per token of HBM
 // round trips for one 64 x 64 x dv product inside the scan.
 //
-// One workgroup (4 waves) per (chunk, batch*head).  Forward mode writes T, Bm and K^T; backward mode writes
-// the transposed operands the reverse scan needs (Bm^T, T^T, K^T, Q^T); a training forward writes both sets
-// at once, so that the backward need not recompute them.  Everything is written in the blocked layout of
-// mdn_device.h (kblk), in which the serial scans' fragment loads are contiguous.
+// One workgroup (4 waves) per (chunk, batch*head).  16-bit storage: T, Bm and the coefficients, row by row, for both scans.
+// 32-bit storage: forward mode writes T, Bm and K^T; backward mode the transposed operands of the reverse scan (Bm^T, T^T, K^T,
+// Q^T); a training forward writes both sets at once, so that the backward need not recompute them; all of them in the blocked
+// layout of mdn_device.h (kblk), in which the serial scans' fragment loads are contiguous.
 #include "mdn_coef.h"
 #include "mdn_device.h"
 #include "mdn_kernels.h"

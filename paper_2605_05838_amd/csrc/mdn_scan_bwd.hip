@@ -1,4 +1,4 @@
-// Reverse inter-chunk scan: adjoint of the forward scan of Sec. 3.1 "Chunkwise Algorithm"
+// Reverse inter-chunk scan for 32-bit storage (16-bit: mdn_scan_bwd16.h): adjoint of the forward scan of Sec. 3.1 "Chunkwise Algorithm"
 // (the paper keeps V~ for the backward pass, "Practical Considerations", but prints no backward
 // equations; these follow from differentiating the chunk formulas).  With dS', dM' the adjoints
 // of the chunk-END states, walking the chunks from last to first:
@@ -167,23 +167,6 @@ __global__ __launch_bounds__(kThreads) void scan_bwd_kernel(Dims d, ScanBwdArgs 
                 const unsigned off = (unsigned)vblk(DK, (w * ND + nd) * 16 + r, kg * (4 * MV));
                 store_cols_raw<MV>(at32(ds + vblk(DK, 0, dv0), off), sv[2 * nd]);
                 store_cols_raw<MV>(at32(ds + DK * DV + vblk(DK, 0, dv0), off), sv[2 * nd + 1]);
-            }
-            if constexpr (sizeof(T) == 2) {
-                if (a.dstates_lo) { // what the rounding above dropped, rounded again (see GradArgs)
-                    T *dl = static_cast<T *>(a.dstates_lo) + blk * (2 * DK * DV);
-#pragma unroll
-                    for (int nd = 0; nd < ND; ++nd) {
-                        typename Raw4<T>::type ls[MV], lm[MV];
-#pragma unroll
-                        for (int mv = 0; mv < MV; ++mv) {
-                            ls[mv] = narrow4<T>(accS[mv][nd] - widen4_packed(sv[2 * nd][mv]));
-                            lm[mv] = narrow4<T>(accM[mv][nd] - widen4_packed(sv[2 * nd + 1][mv]));
-                        }
-                        const unsigned off = (unsigned)vblk(DK, (w * ND + nd) * 16 + r, kg * (4 * MV));
-                        store_cols_raw<MV>(at32(dl + vblk(DK, 0, dv0), off), ls);
-                        store_cols_raw<MV>(at32(dl + DK * DV + vblk(DK, 0, dv0), off), lm);
-                    }
-                }
             }
         }
         fetch_part<T, DK, DV, DVB, 1>(nxt, d, a, sq, nn, dv0, itn);

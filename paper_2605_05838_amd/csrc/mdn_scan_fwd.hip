@@ -1,4 +1,4 @@
-// Sequential inter-chunk propagation of the state S and the momentum M (forward), Sec. 3.1
+// Sequential inter-chunk propagation of the state S and the momentum M (forward) for 32-bit storage (16-bit: mdn_scan_fwd16.h), Sec. 3.1
 // "Chunkwise Algorithm":
 //     V~  = U - Y S + Z M                      with U = T V, Y = T diag(a^-) P, Z = T diag(b^-) P, P = alpha K
 //         = T (V - a . (K S) + pb . (K M))     alpha_i a_{i-1} = a_i, pb_i = alpha_i b_{i-1}  (T pulled out:
@@ -14,7 +14,7 @@
 // row index: an accumulator lane then holds 4 consecutive dv of one token (or of one dk row), which
 // is 8 contiguous bytes of V, V~, O and of the saved states in HBM.  Row m = 4 kg + x of MFMA tile mv stands
 // for column dv0 + kg*4*MV + 4 mv + x of the workgroup's DVB = 16 MV columns, so that the MV tiles of a lane
-// are neighbours in HBM and go as one vector (16-bit storage, MV = 2: 16 bytes); inside LDS the tiles keep
+// are neighbours in HBM; inside LDS the tiles keep
 // their own order (row mv*16 + m), which no one outside the workgroup sees.
 //   S^T, M^T live in fp32 accumulators (wave w owns dk columns [w*dk/4, (w+1)*dk/4)); a storage-type
 //   copy sits in LDS (rows dv, contraction index dk | dk: see ATile) and is the A operand of the dk-contractions of stage 1a
@@ -41,11 +41,11 @@ static_assert(kCoefRows == kCoefBlockCols, "device-side and host-side view of th
 template <typename T, int DK, int MV> struct ChunkOps {
     typedef Op<T> O;
     static constexpr int KS = DK / O::KSTEP, KS2 = 64 / O::KSTEP, ND = DK / 64;
-    typename O::Frag kr[KS];              // stage 1: rows (token i0 + r) of K (32-bit storage)
+    typename O::Frag kr[KS];              // stage 1: rows (token i0 + r) of K
     typename O::Frag q[KS];               // stage 1: rows of Q
     typename O::Frag tm[KS2];             // stage 1: row i0 + r of T = (I + A)^-1
     typename O::Frag bm[KS2];             // stage 2: Bm row i0 + r
-    typename O::Frag kt[ND][KS2];         // stage 2: K^T rows (dk) of this wave's state columns (32-bit storage)
+    typename O::Frag kt[ND][KS2];         // stage 2: K^T rows (dk) of this wave's state columns
     // (everything here is kept exactly as loaded: arithmetic on a freshly loaded value would make the wave wait
     //  for it, and for every load issued before it, at fetch time instead of one chunk later)
     typename Raw4<T>::type u[MV];         // V[token i0 + r][4 MV consecutive dv] (V~ in reconstruction), storage form
@@ -56,7 +56,7 @@ template <typename T, int DK, int MV> struct ChunkOps {
 // chunk: a wave that issues them all at once sits at the issue until the memory pipeline has taken them
 // (the time to move a chunk's operands into the CU), with its matrix work waiting behind.
 // itok: this lane's token of a chunk, in token rows (i * H; in a partial chunk no further than the last real token).
-template <typename T, int DK, int DV, int DVB, bool REBUILD, int P, bool KTILE>
+template <typename T, int DK, int DV, int DVB, bool REBUILD, int P>
 __device__ __forceinline__ void fetch_part(ChunkOps<T, DK, DVB / 16> &c, const Dims &d, const ScanFwdArgs &a, const ScanSeq &sq,
                                            int n, int dv0, unsigned itok) {
     typedef Op<T> O;
@@ -81,7 +81,7 @@ __device__ __forceinline__ void fetch_part(ChunkOps<T, DK, DVB / 16> &c, const D
 #pragma unroll
         for (int s = 0; s < CO::KS; ++s) c.q[s] = O::load(at32(Qg, itok * DK + kg * O::EPL + s * O::KSTEP));
     }
-    if (P == 2 && !KTILE) {
+    if (P == 2) {
         const T *KTg = static_cast<const T *>(a.KT) + blk * (DK * 64);
 #pragma unroll
         for (int nd = 0; nd < CO::ND; ++nd)
@@ -97,7 +97,7 @@ __device__ __forceinline__ void fetch_part(ChunkOps<T, DK, DVB / 16> &c, const D
             c.bm[s] = O::load(at32(Bg, (unsigned)kblk<T>(64, i, s * O::KSTEP + kg * O::EPL)));
         }
     }
-    if (P == 4 && !REBUILD && !KTILE) {
+    if (P == 4 && !REBUILD) {
         const T *Kg = static_cast<const T *>(a.k) + tok0 * DK;
 #pragma unroll
         for (int s = 0; s < CO::KS; ++s) c.kr[s] = O::load(at32(Kg, itok * DK + kg * O::EPL + s * O::KSTEP));
@@ -105,14 +105,14 @@ __device__ __forceinline__ void fetch_part(ChunkOps<T, DK, DVB / 16> &c, const D
     __builtin_amdgcn_sched_barrier(0); // the portion leaves here, not where the scheduler would gather the loads
 }
 
-template <typename T, int DK, int DV, int DVB, bool REBUILD, bool KTILE>
+template <typename T, int DK, int DV, int DVB, bool REBUILD>
 __device__ __forceinline__ void fetch_chunk(ChunkOps<T, DK, DVB / 16> &c, const Dims &d, const ScanFwdArgs &a,
                                             const ScanSeq &sq, int n, int dv0, unsigned itok) {
-    fetch_part<T, DK, DV, DVB, REBUILD, 0, KTILE>(c, d, a, sq, n, dv0, itok);
-    fetch_part<T, DK, DV, DVB, REBUILD, 4, KTILE>(c, d, a, sq, n, dv0, itok);
-    fetch_part<T, DK, DV, DVB, REBUILD, 1, KTILE>(c, d, a, sq, n, dv0, itok);
-    fetch_part<T, DK, DV, DVB, REBUILD, 3, KTILE>(c, d, a, sq, n, dv0, itok);
-    fetch_part<T, DK, DV, DVB, REBUILD, 2, KTILE>(c, d, a, sq, n, dv0, itok);
+    fetch_part<T, DK, DV, DVB, REBUILD, 0>(c, d, a, sq, n, dv0, itok);
+    fetch_part<T, DK, DV, DVB, REBUILD, 4>(c, d, a, sq, n, dv0, itok);
+    fetch_part<T, DK, DV, DVB, REBUILD, 1>(c, d, a, sq, n, dv0, itok);
+    fetch_part<T, DK, DV, DVB, REBUILD, 3>(c, d, a, sq, n, dv0, itok);
+    fetch_part<T, DK, DV, DVB, REBUILD, 2>(c, d, a, sq, n, dv0, itok);
 }
 
 // accumulator element x of tile (mv, nd) of wave w is S[dk = (w*ND + nd)*16 + r][dv = mv*16 + kg*4 + x]
@@ -146,13 +146,6 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(Dims d, ScanFwdArgs 
     __shared__ __align__(16) T sV0[TV::SIZE];
     __shared__ __align__(16) T sVg[TV::SIZE];
     __shared__ __align__(16) T sVr[TV::SIZE];
-    // 16-bit storage, full scan: the chunk's k rows come into LDS once (three chunks in flight) and serve both as
-    // rows (stage 1) and, through transposing reads, as K^T (stage 2): as fast as reading both from HBM into
-    // registers, and K^T need not exist for it.  (The reconstruction, which needs K^T alone, is faster with the K^T
-    // tile from HBM: 128 against 148 us; so is the reverse scan with K, K^T, Q^T from HBM: 203 against 224 us with
-    // k and q tiles in LDS.)  32-bit storage reads the rows and the K^T tile from HBM.
-    constexpr bool KTILE = sizeof(T) == 2 && !REBUILD;
-    __shared__ __align__(16) T sKr[KTILE ? 3 * 64 * DK : 8];
 
     int bh, blkv;
     xcd_map(blockIdx.x, G, bh, blkv);
@@ -165,18 +158,6 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(Dims d, ScanFwdArgs 
     const unsigned iH = (unsigned)(i * d.H);
     unsigned itok = iH;
 
-    // k rows of chunk n into ring slot `slot`
-    auto request_k = [&](int n, int slot) {
-        if constexpr (KTILE) {
-            const T *kg0 = static_cast<const T *>(a.k) + (sq.tok + (size_t)n * 64 * d.H) * DK;
-            T *dst = sKr + slot * (64 * DK);
-            const unsigned rs = (unsigned)(d.H * DK);
-            const int ws = __builtin_amdgcn_readfirstlane(w);
-            dma_token_tile<T, DK, 4, WHOLE>(dst, kg0, rs, ws, lane, n == ragged ? last : 63);
-        }
-    };
-    request_k(sq.n0, 0);
-    request_k(sq.n0 + 1 < sq.n1 ? sq.n0 + 1 : sq.n0, 1);
     if (!WHOLE && sq.n0 == ragged) itok = (unsigned)(min(i, last) * d.H);
 
     f32x4 accS[MV][ND], accM[MV][ND];
@@ -189,7 +170,6 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(Dims d, ScanFwdArgs 
             accM[mv][nd] = a.M0 ? *reinterpret_cast<const f32x4 *>(a.M0 + g) : f32x4{0.f, 0.f, 0.f, 0.f};
         }
     if (!REBUILD) publish_state<T, DK, MV>(sSt, accS, accM);
-    if (KTILE) __builtin_amdgcn_s_waitcnt(0x0F70); // vmcnt(0): this wave's part of the first two k tiles has landed
     __syncthreads();
 
     // The chunk-start states leave for HBM out of a storage-type copy in registers.  Forward scan: narrowed ONCE at
@@ -197,11 +177,8 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(Dims d, ScanFwdArgs 
     // kernel ~75 us whichever wave issues them and whenever).  Reconstruction, which does little else than store:
     // in 8 portions spread over the step (109 against 127 us in one burst).
     constexpr int NS = 2 * ND; // vector stores per lane: S and M, ND rows, MV * 4 consecutive columns each
-    constexpr bool LO = sizeof(T) == 2 && REBUILD;
     typename Raw4<T>::type sv[NS][MV];
-    typename Raw4<T>::type sl[LO ? NS : 1][MV];
-    // sv: the states in storage form; sl: what that rounding dropped, rounded again (16-bit storage, on request: the
-    // reconstruction of a backward call that brings state adjoints in)
+    // sv: the states in storage form
     auto narrow_states = [&]() {
 #pragma unroll
         for (int nd = 0; nd < ND; ++nd)
@@ -210,24 +187,12 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(Dims d, ScanFwdArgs 
                 sv[2 * nd][mv] = narrow4<T>(accS[mv][nd]);
                 sv[2 * nd + 1][mv] = narrow4<T>(accM[mv][nd]);
             }
-        if constexpr (LO) {
-            if (a.states_lo) {
-#pragma unroll
-                for (int nd = 0; nd < ND; ++nd)
-#pragma unroll
-                    for (int mv = 0; mv < MV; ++mv) {
-                        sl[2 * nd][mv] = narrow4<T>(accS[mv][nd] - widen4_packed(sv[2 * nd][mv]));
-                        sl[2 * nd + 1][mv] = narrow4<T>(accM[mv][nd] - widen4_packed(sv[2 * nd + 1][mv]));
-                    }
-            }
-        }
     };
-    // portion PORTION of the stores of sv (and sl) as the start states of chunk block sblk
+    // portion PORTION of the stores of sv as the start states of chunk block sblk
     size_t sblk = 0;
     auto emit_states = [&](auto PORTION) {
         if (!a.states_saved) return;
         T *st = static_cast<T *>(a.states_saved) + sblk * (2 * DK * DV);
-        T *stl = static_cast<T *>(a.states_lo) + sblk * (2 * DK * DV);
         static_for<NS>([&](auto IDX) {
             constexpr int idx = decltype(IDX)::value, nd = idx >> 1;
             if ((REBUILD ? idx * 8 / NS : 0) == decltype(PORTION)::value) {
@@ -235,17 +200,11 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(Dims d, ScanFwdArgs 
                 const unsigned off = (unsigned)vblk(DK, (w * ND + nd) * 16 + r, kg * (4 * MV));
                 const size_t base = ((idx & 1) ? DK * DV : 0) + vblk(DK, 0, dv0);
                 store_cols_raw<MV>(at32(st + base, off), sv[idx]);
-                if constexpr (LO) {
-                    if (a.states_lo) store_cols_raw<MV>(at32(stl + base, off), sl[idx]);
-                }
             }
         });
         __builtin_amdgcn_sched_barrier(0);
     };
     // one chunk: its operands are in `cur`; those of the next chunk go on their way into `nxt`, portion by portion.
-    // The k tile of chunk n+2 is requested first of all; each wave waits for its part of that transfer before the
-    // first barrier of the NEXT step (see the wait there), and that step's barriers publish the tile before chunk
-    // n+2 begins.
     if constexpr (!REBUILD) {
         if (a.states_saved) { // the start states of the first chunk: what came in
             narrow_states();
@@ -253,17 +212,13 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(Dims d, ScanFwdArgs 
             emit_states(std::integral_constant<int, 0>{});
         }
     }
-    int slot = 0;
     auto step = [&](int n, const CO &cur, CO &nxt) {
         const size_t blk = sq.blk + n;
         const size_t tok0 = sq.tok + (size_t)n * 64 * d.H; // (uniform base + 32-bit lane offset, as in fetch_part)
         const int nn = (n + 1 < sq.n1) ? n + 1 : n;
         const int rows = !WHOLE && n == ragged ? last + 1 : 64; // tokens of this chunk: their outputs are stored
         if (!WHOLE && nn == ragged) itok = (unsigned)(min(i, last) * d.H); // (the chunk requested from here on is the partial one)
-        const T *kc = sKr + slot * (64 * DK);
-        if (n + 2 < sq.n1) request_k(n + 2, slot >= 1 ? slot - 1 : 2);
-        slot = slot == 2 ? 0 : slot + 1;
-        fetch_part<T, DK, DV, DVB, REBUILD, 0, KTILE>(nxt, d, a, sq, nn, dv0, itok);
+        fetch_part<T, DK, DV, DVB, REBUILD, 0>(nxt, d, a, sq, nn, dv0, itok);
 
         sblk = blk;
         auto emit_in_step = [&](auto PORTION) {
@@ -274,7 +229,7 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(Dims d, ScanFwdArgs 
         }
         emit_in_step(std::integral_constant<int, 0>{});
 
-        fetch_part<T, DK, DV, DVB, REBUILD, 4, KTILE>(nxt, d, a, sq, nn, dv0, itok);
+        fetch_part<T, DK, DV, DVB, REBUILD, 4>(nxt, d, a, sq, nn, dv0, itok);
         emit_in_step(std::integral_constant<int, 1>{});
         // ---------------- stage 1: R^T = (V - a.(K S) + pb.(K M))^T and the inter-chunk read-outs for token i,
         //                  then V~^T = R^T T^T over all 64 tokens
@@ -288,9 +243,7 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(Dims d, ScanFwdArgs 
             zero_acc(accOM);
 #pragma unroll
             for (int s = 0; s < CO::KS; ++s) {
-                typename O::Frag fk;
-                if constexpr (KTILE) fk = token_tile_row_frag<DK>(kc, i, s, kg);
-                else fk = cur.kr[s];
+                const typename O::Frag fk = cur.kr[s];
 #pragma unroll
                 for (int mv = 0; mv < MV; ++mv) {
                     const typename O::Frag fs = TS::frag(sSt, mv, s * O::KSTEP, r, kg);
@@ -301,22 +254,11 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(Dims d, ScanFwdArgs 
                     accOM[mv] = O::mma(fm, cur.q[s], accOM[mv]);
                 }
             }
-            fetch_part<T, DK, DV, DVB, REBUILD, 1, KTILE>(nxt, d, a, sq, nn, dv0, itok);
+            fetch_part<T, DK, DV, DVB, REBUILD, 1>(nxt, d, a, sq, nn, dv0, itok);
 #pragma unroll
             for (int mv = 0; mv < MV; ++mv) {
                 accO[mv] = d.scale * (cur.c0[COEF_A] * accOS[mv] - cur.c0[COEF_B] * accOM[mv]);
                 TV::put4(sRt, mv * 16 + kg * 4, i, widen4(cur.u[mv]) - cur.c0[COEF_A] * x1[mv] + cur.c0[COEF_PB] * x2[mv]);
-            }
-            if constexpr (KTILE) {
-                // This wave's part of the k tile requested at the start of the PREVIOUS step has landed: at least
-                // AFTER vector-memory instructions were issued behind it (previous step: coefficients and V 3, q KS,
-                // T and Bm 4, o 1; this step: coefficients and V 3, q KS; more with the optional stores and the next
-                // tile's request), they complete in order, and no more than AFTER of them are younger than this
-                // step's own requests (the tile's D/32, 3, the 2 ND state stores, KS) -- so the wait never holds a
-                // wave for a load it has only just issued.
-                constexpr int AFTER = 11 + 2 * CO::KS;
-                static_assert(AFTER <= 63 && DK / 32 + 3 + 2 * ND + CO::KS <= AFTER, "vmcnt immediate");
-                __builtin_amdgcn_s_waitcnt(0x0F70 | (AFTER & 15) | ((AFTER >> 4) << 14));
             }
             __syncthreads();
             f32x4 accV[MV];
@@ -353,7 +295,7 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(Dims d, ScanFwdArgs 
         __syncthreads();
 
         // ---------------- stage 2: intra-chunk output and the state update
-        fetch_part<T, DK, DV, DVB, REBUILD, 2, KTILE>(nxt, d, a, sq, nn, dv0, itok);
+        fetch_part<T, DK, DV, DVB, REBUILD, 2>(nxt, d, a, sq, nn, dv0, itok);
         emit_in_step(std::integral_constant<int, 4>{});
         const float aC = cur.c0[COEF_AC], bC = cur.c1[COEF_BC - 4], mC = cur.c1[COEF_MC - 4];
 #pragma unroll
@@ -365,20 +307,14 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(Dims d, ScanFwdArgs 
             }
 #pragma unroll
         for (int s = 0; s < CO::KS2; ++s) {
-            typename O::Frag fkt[ND];
-#pragma unroll
-            for (int nd = 0; nd < ND; ++nd) {
-                if constexpr (KTILE) fkt[nd] = token_tile_col_frag<DK>(kc, w * ND + nd, s, r, kg);
-                else fkt[nd] = cur.kt[nd][s];
-            }
 #pragma unroll
             for (int mv = 0; mv < MV; ++mv) {
                 const typename O::Frag fg = TV::frag(sVg, mv, s * O::KSTEP, r, kg);
                 const typename O::Frag fr = TV::frag(sVr, mv, s * O::KSTEP, r, kg);
 #pragma unroll
                 for (int nd = 0; nd < ND; ++nd) {
-                    accS[mv][nd] = O::mma(fg, fkt[nd], accS[mv][nd]);
-                    accM[mv][nd] = O::mma(fr, fkt[nd], accM[mv][nd]);
+                    accS[mv][nd] = O::mma(fg, cur.kt[nd][s], accS[mv][nd]);
+                    accM[mv][nd] = O::mma(fr, cur.kt[nd][s], accM[mv][nd]);
                 }
                 if (!REBUILD) {
                     accO[mv] = O::mma(TV::frag(sV0, mv, s * O::KSTEP, r, kg), cur.bm[s], accO[mv]);
@@ -386,7 +322,7 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(Dims d, ScanFwdArgs 
             }
         }
         emit_in_step(std::integral_constant<int, 5>{});
-        fetch_part<T, DK, DV, DVB, REBUILD, 3, KTILE>(nxt, d, a, sq, nn, dv0, itok);
+        fetch_part<T, DK, DV, DVB, REBUILD, 3>(nxt, d, a, sq, nn, dv0, itok);
         emit_in_step(std::integral_constant<int, 6>{});
         if constexpr (!REBUILD) {
             // the states after this chunk, narrowed once: the LDS copy for the next chunk's stage 1 and, in HBM, that
@@ -413,7 +349,7 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(Dims d, ScanFwdArgs 
     // register of the set that was just requested, i.e. wait for all of its loads
     {
         CO opsA, opsB;
-        fetch_chunk<T, DK, DV, DVB, REBUILD, KTILE>(opsA, d, a, sq, sq.n0, dv0, itok);
+        fetch_chunk<T, DK, DV, DVB, REBUILD>(opsA, d, a, sq, sq.n0, dv0, itok);
         int n = sq.n0;
         for (; n + 1 < sq.n1; n += 2) {
             step(n, opsA, opsB);
