@@ -8,9 +8,12 @@
 // A step has three phases, each ended by a barrier:
 //   A  dV~^T of the wave's 16 tokens from the adjoints' copy, the k rows, Bm and dO, left in LDS; dO in the two scalings
 //      with which it enters the states;
-//   B  dV^T = dV~^T T over all tokens, left raw (the output) and in two scalings; (a . Q~)^T dO and (b . Q~)^T dO into the states,
-//      whose products fill the waits of this short phase;
-//   C  K^T (a . dV), K^T (pb . dV) into the states, the new copy.
+//   B  dV^T = dV~^T T over all tokens, left raw (the output) and in two scalings; (a . Q~)^T dO and (b . Q~)^T dO of the first 32
+//      tokens into the states, whose products fill the waits of this short phase;
+//   C  K^T (a . dV), K^T (pb . dV) of those tokens into the states, then both of the other 32, the new copy.
+// The state adjoints thus sum in the order of mdn_scan_bwd.hip, 32 tokens of Q, then of K.  (All of Q in phase B, all of K in phase C
+// is as fast, 4 x 4 096 tokens of 16 heads of 128 forward and backward 604 against 606 us, but every gradient then differs by 1e-3:
+// roundings of the copies, dV~ and dV carry the last bits of a sum on from chunk to chunk.)
 #pragma once
 #include "mdn_scan_tiles.h"
 #include "mdn_kernels.h"
@@ -202,24 +205,26 @@ __device__ __forceinline__ void scan_bwd16(const Dims &d, const ScanBwdArgs &a, 
                     acc.S[mv][nd] = aC * s;
                     acc.M[mv][nd] = mC * m - bC * s;
                 }
-            O::Frag kT[2][ND];
+            O::Frag kT[2][ND], qT[2][ND];
 #pragma unroll
-            for (int s = 0; s < 2; ++s) {
-                O::Frag qT[ND];
+            for (int s = 0; s < 2; ++s)
 #pragma unroll
-                for (int nd = 0; nd < ND; ++nd) qT[nd] = token_tile_col_frag<DK>(qc, w * ND + nd, s, r, kg);
+                for (int nd = 0; nd < ND; ++nd) {
+                    qT[s][nd] = token_tile_col_frag<DK>(qc, w * ND + nd, s, r, kg);
+                    kT[s][nd] = token_tile_col_frag<DK>(kc, w * ND + nd, s, r, kg);
+                }
+            auto q_into_states = [&](int s) {
 #pragma unroll
                 for (int mv = 0; mv < MV; ++mv) {
                     const O::Frag fa = TV::frag(lds.sOa, mv, s * 32, r, kg), fb = TV::frag(lds.sOb, mv, s * 32, r, kg);
 #pragma unroll
                     for (int nd = 0; nd < ND; ++nd) {
-                        acc.S[mv][nd] = O::mma(fa, qT[nd], acc.S[mv][nd]);
-                        acc.M[mv][nd] = O::mma(fb, qT[nd], acc.M[mv][nd]);
+                        acc.S[mv][nd] = O::mma(fa, qT[s][nd], acc.S[mv][nd]);
+                        acc.M[mv][nd] = O::mma(fb, qT[s][nd], acc.M[mv][nd]);
                     }
                 }
-#pragma unroll
-                for (int nd = 0; nd < ND; ++nd) kT[s][nd] = token_tile_col_frag<DK>(kc, w * ND + nd, s, r, kg);
-            }
+            };
+            q_into_states(0);
 #pragma unroll
             for (int mv = 0; mv < MV; ++mv) {
                 TV::put4(lds.sR0, mv * 16 + kg * 4, i, dR[mv]);
@@ -228,8 +233,7 @@ __device__ __forceinline__ void scan_bwd16(const Dims &d, const ScanBwdArgs &a, 
             }
             __syncthreads(); // B
             // ---- phase C
-#pragma unroll
-            for (int s = 0; s < 2; ++s)
+            auto k_into_states = [&](int s) {
 #pragma unroll
                 for (int mv = 0; mv < MV; ++mv) {
                     const O::Frag fa = TV::frag(lds.sRa, mv, s * 32, r, kg), fb = TV::frag(lds.sRb, mv, s * 32, r, kg);
@@ -239,6 +243,10 @@ __device__ __forceinline__ void scan_bwd16(const Dims &d, const ScanBwdArgs &a, 
                         acc.M[mv][nd] = O::mma(fb, kT[s][nd], acc.M[mv][nd]);
                     }
                 }
+            };
+            k_into_states(0);
+            q_into_states(1);
+            k_into_states(1);
             acc.publish(lds.sD, w, r, kg);
             slot = slot == KSLOTS - 1 ? 0 : slot + 1;
             par ^= 1;
