@@ -62,17 +62,31 @@ __device__ __forceinline__ void scan_bwd16(const Dims &d, const ScanBwdArgs &a, 
     // a partial last chunk (the first one here): its loads stop at the last real token
     const int ragged = !WHOLE && (sq.len & 63) ? sq.len >> 6 : -1, last = (sq.len & 63) - 1; // that chunk (or none), its last row
     auto first_token = [&](int n) { return sq.tok + (size_t)n * 64 * d.H; };
+    const int turn = blkv & 3;
+    TileLoad<T, 64, true> tm;
+    auto request_m = [&](const void *m, int n, const T *ring, int par) {
+        tm.request(static_cast<const T *>(m) + (sq.blk + n) * 4096, lds_addr(ring) + par * (4096 * (int)sizeof(T)), w2, turn);
+    };
 
     if (wv >= 6) {
         // ---------------------------------------------------------------- stores
         StateStore<DK, DV, MV> st;
         constexpr int NS = StateStore<DK, DV, MV>::N;
+        // (at the start, with nothing to store yet, these waves bring Bm and T of the first two chunks)
+        tm.aim(64, w2, lane, turn, 63);
+        for (int ahead = 0; ahead < 2 && n1 - 1 - ahead >= n0; ++ahead) {
+            request_m(a.Bm, n1 - 1 - ahead, lds.rB[0], ahead);
+            request_m(a.Tm, n1 - 1 - ahead, lds.rT[0], ahead);
+        }
+        if (n0 + 1 < n1) wait_vm<2 * tm.COUNT>();
+        else wait_vm<0>();
         __syncthreads();
         for (int n = n1 - 1; n >= n0; --n) {
             T *states = static_cast<T *>(a.dstates) + (sq.blk + n) * (2 * DK * DV); // adjoints of this chunk's END states
             st.read(lds.sD, w2, lane);
             st.template put<0, NS / 2>(states, dv0, w2, lane);
             __syncthreads(); // A
+            if (n == n1 - 1) wait_vm<NS / 2>(); // Bm and T of the second chunk are there
             st.template put<NS / 2, NS * 3 / 4>(states, dv0, w2, lane);
             __syncthreads(); // B
             store_token_rows<DV, MV, WHOLE>(static_cast<T *>(a.dv) + first_token(n) * DV + dv0, lds.sR0, !WHOLE && n == ragged ? last + 1 : 64, d.H, w2, lane);
@@ -81,10 +95,8 @@ __device__ __forceinline__ void scan_bwd16(const Dims &d, const ScanBwdArgs &a, 
         }
     } else if (wv >= 4) {
         // ---------------------------------------------------------------- loads: two chunks ahead, as the slots become free
-        const int turn = blkv & 3;
         const unsigned rsk = (unsigned)(d.H * DK), rsv = (unsigned)(d.H * DV);
         TileLoad<T, DK, true> tk; // (the rows of q lie as those of k)
-        TileLoad<T, 64, true> tm;
         TileLoad<T, DVB, false> tv;
         TileLoad<float, kCoefRows, false> tc;
         tm.aim(64, w2, lane, turn, 63);
@@ -96,9 +108,6 @@ __device__ __forceinline__ void scan_bwd16(const Dims &d, const ScanBwdArgs &a, 
         auto request_rows = [&](const void *x, int n, const T *ring, int slot) {
             tk.request(static_cast<const T *>(x) + first_token(n) * DK, lds_addr(ring) + slot * (64 * DK * (int)sizeof(T)), w2, turn);
         };
-        auto request_m = [&](const void *m, int n, const T *ring, int par) {
-            tm.request(static_cast<const T *>(m) + (sq.blk + n) * 4096, lds_addr(ring) + par * (4096 * (int)sizeof(T)), w2, turn);
-        };
         auto request_o = [&](int n, int par) {
             tv.request(static_cast<const T *>(a.dO) + first_token(n) * DV + dv0, lds_addr(lds.rO[0]) + par * (64 * DVB * (int)sizeof(T)), w2, turn);
         };
@@ -106,22 +115,24 @@ __device__ __forceinline__ void scan_bwd16(const Dims &d, const ScanBwdArgs &a, 
             tc.request(a.coef + (sq.blk + n) * (64 * kCoefRows), lds_addr(lds.rC[0]) + par * (64 * kCoefRows * 4), w2, turn);
         };
         constexpr int NALL = 2 * tk.COUNT + 2 * tm.COUNT + tv.COUNT + tc.COUNT;
+        // (only chunks that exist)
         for (int ahead = 0; ahead < 2; ++ahead) {
-            const int n = n1 - 1 - ahead >= n0 ? n1 - 1 - ahead : n0; // (a single chunk: twice)
+            const int n = n1 - 1 - ahead;
+            if (n < n0) break;
             aim_at(!WHOLE && n == ragged ? last : 63);
             request_rows(a.k, n, lds.rK[0], ahead);
             request_c(n, ahead);
             request_o(n, ahead);
-            request_m(a.Bm, n, lds.rB[0], ahead);
-            request_m(a.Tm, n, lds.rT[0], ahead);
             request_rows(a.q, n, lds.rQ[0], ahead);
         }
-        wait_vm<NALL>();
+        if (n0 + 1 < n1) wait_vm<NALL - 2 * tm.COUNT>();
+        else wait_vm<0>();
         __syncthreads();
-        if (!WHOLE && n0 != ragged) aim_at(63); // (what is requested from here on is not the partial chunk, unless that is the only one)
+        // (what is requested from here on is not the partial chunk: the lanes aim at whole ones)
         int slot = 2, par = 0;
-        for (int n = n1 - 1; n >= n0; --n) {
-            const int nn = n - 2 >= n0 ? n - 2 : n0; // (past the end: the first chunk, into slots that nothing reads any more)
+        int n = n1 - 1;
+        for (; n - 2 >= n0; --n) {
+            const int nn = n - 2;
             if (KSLOTS == 3) request_rows(a.k, nn, lds.rK[0], slot);
             __syncthreads(); // A: Bm, T, dO and the coefficients of this chunk have been read
             request_m(a.Bm, nn, lds.rB[0], par);
@@ -136,7 +147,12 @@ __device__ __forceinline__ void scan_bwd16(const Dims &d, const ScanBwdArgs &a, 
             par ^= 1;
             __syncthreads(); // C
         }
-        wait_vm<0>(); // (no transfer outlives the workgroup)
+        for (; n >= n0; --n) {
+            __syncthreads(); // A
+            __syncthreads(); // B
+            wait_vm<0>();
+            __syncthreads(); // C
+        } // (no transfer outlives the workgroup: the last step has waited for all of them)
     } else {
         // ---------------------------------------------------------------- the chain
         __builtin_amdgcn_s_setprio(3);

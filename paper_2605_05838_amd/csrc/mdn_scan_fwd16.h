@@ -59,12 +59,26 @@ __device__ __forceinline__ void scan_fwd16(const Dims &d, const ScanFwdArgs &a, 
     // a partial last chunk: its loads stop at the last real token
     const int ragged = !WHOLE && (sq.len & 63) ? sq.len >> 6 : -1, last = (sq.len & 63) - 1; // that chunk (or none), its last row
     auto first_token = [&](int n) { return sq.tok + (size_t)n * 64 * d.H; };
+    const int turn = blkv & 3;
+    TileLoad<T, 64, true> tm;
+    constexpr int NM = REBUILD ? 0 : tm.COUNT;
+    auto request_m = [&](const void *m, int n, const T *ring, int par) {
+        if constexpr (!REBUILD) tm.request(static_cast<const T *>(m) + (sq.blk + n) * 4096, lds_addr(ring) + par * (4096 * (int)sizeof(T)), w2, turn);
+    };
 
     if (wv >= 6) {
         // ---------------------------------------------------------------- stores
         auto rows_of = [&](int n) { return !WHOLE && n == ragged ? last + 1 : 64; };
         StateStore<DK, DV, MV> st;
         constexpr int NS = StateStore<DK, DV, MV>::N;
+        // (at the start, with nothing to store yet, these waves bring T and Bm of the first chunks)
+        tm.aim(64, w2, lane, turn, 63);
+        for (int ahead = 0; ahead < 2 && n0 + ahead < n1; ++ahead) {
+            request_m(a.Tm, n0 + ahead, lds.rT[0], ahead);
+            request_m(a.Bm, n0 + ahead, lds.rB[0], ahead);
+        }
+        if (n0 + 1 < n1) wait_vm<2 * NM>();
+        else wait_vm<0>();
         __syncthreads();
         for (int n = n0; n < n1; ++n) {
             T *states = static_cast<T *>(a.states_saved) + (sq.blk + n) * (2 * DK * DV); // this chunk's start states
@@ -72,6 +86,10 @@ __device__ __forceinline__ void scan_fwd16(const Dims &d, const ScanFwdArgs &a, 
             if (!REBUILD && n > n0) store_token_rows<DV, MV, WHOLE>(static_cast<T *>(a.o) + first_token(n - 1) * DV + dv0, lds.sO, 64, d.H, w2, lane);
             if (a.states_saved) st.template put<0, NS / 2>(states, dv0, w2, lane);
             if (!REBUILD) __syncthreads(); // A
+            if (!REBUILD && n == n0) { // T and Bm of the second chunk are there
+                if (a.states_saved) wait_vm<NS / 2>();
+                else wait_vm<0>();
+            }
             if (a.states_saved) st.template put<NS / 2, NS * 3 / 4>(states, dv0, w2, lane);
             __syncthreads(); // B
             if (!REBUILD && a.vt_saved)
@@ -82,13 +100,11 @@ __device__ __forceinline__ void scan_fwd16(const Dims &d, const ScanFwdArgs &a, 
         if (!REBUILD) store_token_rows<DV, MV, WHOLE>(static_cast<T *>(a.o) + first_token(n1 - 1) * DV + dv0, lds.sO, rows_of(n1 - 1), d.H, w2, lane);
     } else if (wv >= 4) {
         // ---------------------------------------------------------------- loads: two chunks ahead
-        const int turn = blkv & 3;
         const unsigned rsk = (unsigned)(d.H * DK), rsv = (unsigned)(d.H * DV);
         TileLoad<T, DK, true> tk;
-        TileLoad<T, 64, true> tm;
         TileLoad<T, DVB, false> tv;
         TileLoad<float, kCoefRows, false> tc;
-        constexpr int NK = tk.COUNT, NM = REBUILD ? 0 : tm.COUNT, NV = tv.COUNT + tc.COUNT;
+        constexpr int NK = tk.COUNT, NV = tv.COUNT + tc.COUNT;
         tm.aim(64, w2, lane, turn, 63);
         tc.aim(kCoefRows, w2, lane, turn, 63);
         tk.aim(rsk, w2, lane, turn, 63);
@@ -107,22 +123,21 @@ __device__ __forceinline__ void scan_fwd16(const Dims &d, const ScanFwdArgs &a, 
                        lds_addr(lds.rV[0]) + slot * (64 * DVB * (int)sizeof(T)), w2, turn);
             tc.request(a.coef + (sq.blk + n) * (64 * kCoefRows), lds_addr(lds.rC[0]) + slot * (64 * kCoefRows * 4), w2, turn);
         };
-        auto request_m = [&](const void *m, int n, const T *ring, int par) {
-            if constexpr (!REBUILD) tm.request(static_cast<const T *>(m) + (sq.blk + n) * 4096, lds_addr(ring) + par * (4096 * (int)sizeof(T)), w2, turn);
-        };
+        // (only chunks that exist: a chunk more than there are, requested again, is a third of a three-chunk call's traffic)
         for (int ahead = 0; ahead < 2; ++ahead) {
-            const int n = n0 + ahead < n1 ? n0 + ahead : n0; // (a single chunk: twice)
+            const int n = n0 + ahead;
+            if (n >= n1) break;
             aim_at(n);
             request_k(n, ahead);
             request_v(n, ahead);
-            request_m(a.Tm, n, lds.rT[0], ahead);
-            request_m(a.Bm, n, lds.rB[0], ahead);
         }
-        wait_vm<NK + NV + 2 * NM>();
+        if (n0 + 1 < n1) wait_vm<NK + NV>();
+        else wait_vm<0>();
         __syncthreads();
         int slot = 2, par = 0;
-        for (int n = n0; n < n1; ++n) {
-            const int nn = n + 2 < n1 ? n + 2 : n1 - 1; // (past the end: the last chunk, into slots that nothing reads any more)
+        int n = n0;
+        for (; n + 2 < n1; ++n) {
+            const int nn = n + 2;
             aim_at(nn);
             request_k(nn, slot);
             if (!REBUILD) __syncthreads(); // A: T of this chunk has been read
@@ -135,26 +150,28 @@ __device__ __forceinline__ void scan_fwd16(const Dims &d, const ScanFwdArgs &a, 
             par ^= 1;
             __syncthreads(); // C
         }
-        wait_vm<0>(); // (no transfer outlives the workgroup)
+        for (; n < n1; ++n) {
+            if (!REBUILD) __syncthreads(); // A
+            wait_vm<0>();
+            __syncthreads(); // B
+            __syncthreads(); // C
+        } // (no transfer outlives the workgroup: the last step has waited for all of them)
     } else {
         // ---------------------------------------------------------------- the chain
         __builtin_amdgcn_s_setprio(3);
-        // q rows of two chunks in registers: the only operand without a place in LDS
-        const unsigned iH = (unsigned)(i * d.H), iHr = (unsigned)(min(i, last) * d.H);
+        // the q rows, the only operand without a place in LDS, in registers, requested when those of the chunk before have been used
         struct QRows { O::Frag f[KS]; };
         auto load_q = [&](int n, QRows &q) {
             if constexpr (!REBUILD) {
-                n = n < n1 ? n : n1 - 1;
                 const T *Qg = static_cast<const T *>(a.q) + first_token(n) * DK;
-                const unsigned it = !WHOLE && n == ragged ? iHr : iH;
+                const unsigned it = (unsigned)((!WHOLE && n == ragged ? min(i, last) : i) * d.H);
 #pragma unroll
                 for (int s = 0; s < KS; ++s) q.f[s] = O::load(at32(Qg, it * DK + kg * 8 + s * 32));
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
-        QRows qa, qb;
-        load_q(n0, qa);
-        load_q(n0 + 1, qb);
+        QRows q;
+        load_q(n0, q);
         ChainStates<DK, DV, MV> acc;
         acc.load(a.S0, a.M0, sq.state, w, dv0, r, kg);
         acc.publish(lds.sSt, w, r, kg);
@@ -175,7 +192,7 @@ __device__ __forceinline__ void scan_fwd16(const Dims &d, const ScanFwdArgs &a, 
             load_cols_raw<MV>(lds.rV[slot] + i * DVB + kg * (4 * MV), u);
         };
         first_reads();
-        auto step = [&](int n, QRows &q) {
+        for (int n = n0; n < n1; ++n) {
             f32x4 o[MV];
             bf16x4 vb[MV]; // V~ in storage form
             O::Frag kt[2][ND], bm[2];
@@ -208,7 +225,7 @@ __device__ __forceinline__ void scan_fwd16(const Dims &d, const ScanFwdArgs &a, 
 #pragma unroll
                 for (int mv = 0; mv < MV; ++mv)
                     TV::put4(lds.sRt, mv * 16 + kg * 4, i, widen4(u[mv]) - c0[COEF_A] * x1[mv] + c0[COEF_PB] * x2[mv]);
-                load_q(n + 2, q);
+                if (n + 1 < n1) load_q(n + 1, q);
                 __syncthreads(); // A
 #pragma unroll
                 for (int s = 0; s < 2; ++s)
@@ -260,8 +277,13 @@ __device__ __forceinline__ void scan_fwd16(const Dims &d, const ScanFwdArgs &a, 
             }
             slot = slot == 2 ? 0 : slot + 1;
             par ^= 1;
-            first_reads();
-            acc.publish(lds.sSt, w, r, kg);
+            // (the branch keeps what the next step needs behind this one's products, also where it is always taken: 4 x 2 048 tokens of
+            //  16 heads of 128, forward 83.9 us without it, 82.2 with it; d = 64 is faster with both interleaved, 1 x 2 048 of 16
+            //  heads 40.3 us with it, 38.3 without)
+            if (DK == 64 || n + 1 < n1) {
+                first_reads();
+                acc.publish(lds.sSt, w, r, kg);
+            }
             if constexpr (!REBUILD) {
 #pragma unroll
                 for (int mv = 0; mv < MV; ++mv) TV::put4(lds.sO, mv * 16 + kg * 4, i, o[mv]);
@@ -269,13 +291,7 @@ __device__ __forceinline__ void scan_fwd16(const Dims &d, const ScanFwdArgs &a, 
                 acc.store_lo(static_cast<T *>(a.states_lo) + (sq.blk + n + 1) * (2 * DK * DV), w, dv0, r, kg);
             }
             __syncthreads(); // C
-        };
-        int n = n0;
-        for (; n + 1 < n1; n += 2) {
-            step(n, qa);
-            step(n + 1, qb);
         }
-        if (n < n1) step(n, qa);
         acc.store(a.S_final, a.M_final, sq.state, w, dv0, r, kg);
     }
 }
