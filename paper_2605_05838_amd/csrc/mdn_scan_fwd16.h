@@ -9,7 +9,7 @@
 //   B  V~^T = R^T T^T over all tokens, left in LDS in three scalings (raw, Gamma_C eta, -Rho_C eta);
 //   C  the states' update out of K^T (transposing reads of the k tile) and the scaled V~, Bm V~ for the output, the new copy.
 // What a phase reads of the operands is read before the barrier in front of it.  The reconstruction (REBUILD) reads V~ and
-// has the last two phases only.
+// has the last two phases only, and stops at the last chunk's start states.
 //
 // What bounds it: with every CU busy (256 workgroups) the mixture of loads and stores itself; a program that only makes this
 // kernel's requests takes 155-168 us at 4 x 4 096 tokens of 16 heads of 128.  With fewer workgroups or without kept states, the
@@ -53,7 +53,7 @@ __device__ __forceinline__ void scan_fwd16(const Dims &d, const ScanFwdArgs &a, 
     xcd_map(block, G, bh, blkv);
     if (bh >= d.BH) return;
     const ScanSeq sq = scan_seq<WHOLE>(d, bh);
-    const int dv0 = blkv * DVB, n0 = sq.n0, n1 = sq.n1;
+    const int dv0 = blkv * DVB, n0 = sq.n0, n1 = sq.n1 - (REBUILD ? 1 : 0); // chunks [n0, n1) are walked
     const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(wave_id()), w = wv & 3, w2 = wv & 1;
     const int r = lane & 15, kg = lane >> 4, i = w * 16 + r;
     // a partial last chunk: its loads stop at the last real token
@@ -80,11 +80,16 @@ __device__ __forceinline__ void scan_fwd16(const Dims &d, const ScanFwdArgs &a, 
         if (n0 + 1 < n1) wait_vm<2 * NM>();
         else wait_vm<0>();
         __syncthreads();
-        for (int n = n0; n < n1; ++n) {
+        for (int n = n0;; ++n) {
+            if (!REBUILD && n == n1) break;
             T *states = static_cast<T *>(a.states_saved) + (sq.blk + n) * (2 * DK * DV); // this chunk's start states
             if (a.states_saved) st.read(lds.sSt, w2, lane);
             if (!REBUILD && n > n0) store_token_rows<DV, MV, WHOLE>(static_cast<T *>(a.o) + first_token(n - 1) * DV + dv0, lds.sO, 64, d.H, w2, lane);
             if (a.states_saved) st.template put<0, NS / 2>(states, dv0, w2, lane);
+            if (REBUILD && n == n1) { // the start states of the last chunk
+                st.template put<NS / 2, NS>(states, dv0, w2, lane);
+                break;
+            }
             if (!REBUILD) __syncthreads(); // A
             if (!REBUILD && n == n0) { // T and Bm of the second chunk are there
                 if (a.states_saved) wait_vm<NS / 2>();
@@ -280,19 +285,19 @@ __device__ __forceinline__ void scan_fwd16(const Dims &d, const ScanFwdArgs &a, 
             // (the branch keeps what the next step needs behind this one's products, also where it is always taken: 4 x 2 048 tokens of
             //  16 heads of 128, forward 83.9 us without it, 82.2 with it; d = 64 is faster with both interleaved, 1 x 2 048 of 16
             //  heads 40.3 us with it, 38.3 without)
-            if (DK == 64 || n + 1 < n1) {
+            if (REBUILD || DK == 64 || n + 1 < n1) {
                 first_reads();
                 acc.publish(lds.sSt, w, r, kg);
             }
             if constexpr (!REBUILD) {
 #pragma unroll
                 for (int mv = 0; mv < MV; ++mv) TV::put4(lds.sO, mv * 16 + kg * 4, i, o[mv]);
-            } else if (a.states_lo && n + 1 < n1) {
+            } else if (a.states_lo) {
                 acc.store_lo(static_cast<T *>(a.states_lo) + (sq.blk + n + 1) * (2 * DK * DV), w, dv0, r, kg);
             }
             __syncthreads(); // C
         }
-        acc.store(a.S_final, a.M_final, sq.state, w, dv0, r, kg);
+        if (!REBUILD) acc.store(a.S_final, a.M_final, sq.state, w, dv0, r, kg);
     }
 }
 

@@ -25,7 +25,7 @@ template <int DK, int DV, bool REBUILD> hipError_t pick_dvb(const Dims &d, const
 } // namespace
 
 hipError_t launch_scan_fwd16(const Dims &d, const ScanFwdArgs &a, bool rebuild, hipStream_t s) {
-    if (!a.coef || !a.k) return hipErrorInvalidValue;
+    if (!a.coef || !a.k || (rebuild && (!a.vt_saved || !a.states_saved))) return hipErrorInvalidValue;
     if (d.dk == 64 && d.dv == 64) return rebuild ? pick_dvb<64, 64, true>(d, a, s) : pick_dvb<64, 64, false>(d, a, s);
     if (d.dk == 128 && d.dv == 128) return rebuild ? pick_dvb<128, 128, true>(d, a, s) : pick_dvb<128, 128, false>(d, a, s);
     return hipErrorInvalidValue;
