@@ -318,10 +318,13 @@ bool precise_call(const Dims &d, const BwdCall &c) {
     return d.dtype == MDN_DTYPE_BF16 && (c.dS_final || c.dM_final);
 }
 
-// Whether the reconstruction and the reverse scan run as one launch (`nseg`: the segments of this call): never slower where
-// the reverse scan is one launch (see scan_pair16_kernel).  32-bit storage has scans of another form.
+// Whether the reconstruction and the reverse scan run as one launch (`nseg`: the segments of this call; see scan_pair16_kernel):
+// below two full rounds of workgroups.  From there on the reconstruction alone runs two to a CU, which it cannot beside the reverse
+// scan's LDS.  Forward and backward in us, two launches / one, heads of 128: 8 x 256 tokens of 16 heads (512 workgroups) 107.2 / 109.3,
+// 8 x 2 048 677.5 / 677.1; 16 x 256 203.5 / 205.8; 32 x 512 712 / 723; packed 32 768 in 64 sequences 1 404 / 1 428; of 64: 16 x 256
+// 99.4 / 101.1, 16 x 1 024 349.7 / 343.0.  32-bit storage has scans of another form.
 bool rebuild_beside_scan(const Dims &d, int nseg) {
-    return !wide(d) && nseg == 1;
+    return !wide(d) && nseg == 1 && scan_workgroups(d) < 2 * num_cus();
 }
 
 int bwd_prepare(const Dims &d, const BwdCall &c, const BwdWs &w, hipStream_t s, Prepared *out, bool precise, int nseg) {

@@ -126,7 +126,7 @@ int scan_dvb(const Dims &d);
 // sequence's time to run
 int scan_workgroups(const Dims &d);
 // Whether a scan launch keeps a second workgroup off every CU (see lds_bytes_for_one_workgroup_per_cu): where the workgroups
-// of the longest sequence's length do not outnumber the CUs.
+// of the longest sequence's length do not outnumber the CUs.  Elsewhere 16-bit storage takes the instances that fit twice.
 bool scan_one_per_cu(const Dims &d);
 
 // mode 0: forward operands, 1: reverse-pass operands, 2: both (16-bit storage: the same ones, always mode 0)

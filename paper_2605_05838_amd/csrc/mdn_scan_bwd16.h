@@ -20,18 +20,20 @@
 
 namespace mdn {
 
-template <int DK, int DV, int DVB> struct ScanBwdLds {
+// AHEAD: how many chunks in front of the chain the loads are, 2 or (two workgroups per CU: see scan_one_per_cu) 1, as far as one set
+// of operands allows
+template <int DK, int DV, int DVB, int AHEAD> struct ScanBwdLds {
     typedef bf16_t T;
     typedef ATile<T, DVB, 2 * DK> TD; // the adjoints' copy, contraction over dk: dS' | dM'
     typedef ATile<T, DVB, 64> TV;     // contraction over the chunk's tokens
-    // operands of two chunks; the k tile, read from the first to the last phase, of three where there is room
-    static constexpr int KSLOTS = DVB == 16 || DK == 64 ? 3 : 2;
+    // operands of AHEAD chunks; of two chunks the k tile, read from the first to the last phase, of three where there is room
+    static constexpr int KSLOTS = AHEAD == 1 ? 1 : DVB == 16 || DK == 64 ? 3 : 2;
     __align__(16) T rK[KSLOTS][64 * DK];
-    __align__(16) T rQ[2][64 * DK];
-    __align__(16) T rT[2][4096];
-    __align__(16) T rB[2][4096];
-    __align__(16) T rO[2][64 * DVB];
-    __align__(16) float rC[2][64 * kCoefRows];
+    __align__(16) T rQ[AHEAD][64 * DK];
+    __align__(16) T rT[AHEAD][4096];
+    __align__(16) T rB[AHEAD][4096];
+    __align__(16) T rO[AHEAD][64 * DVB];
+    __align__(16) float rC[AHEAD][64 * kCoefRows];
     // what the chain leaves
     __align__(16) T sD[TD::SIZE];
     __align__(16) T sOa[TV::SIZE]; // (scale a . dO)^T
@@ -43,11 +45,11 @@ template <int DK, int DV, int DVB> struct ScanBwdLds {
 };
 
 // workgroup `block` of ((BH + 7) / 8) * 8 * DV / DVB
-template <int DK, int DV, int DVB, bool WHOLE>
-__device__ __forceinline__ void scan_bwd16(const Dims &d, const ScanBwdArgs &a, int block, ScanBwdLds<DK, DV, DVB> &lds) {
+template <int DK, int DV, int DVB, bool WHOLE, int AHEAD>
+__device__ __forceinline__ void scan_bwd16(const Dims &d, const ScanBwdArgs &a, int block, ScanBwdLds<DK, DV, DVB, AHEAD> &lds) {
     typedef bf16_t T;
     typedef Op<T> O;
-    typedef ScanBwdLds<DK, DV, DVB> L;
+    typedef ScanBwdLds<DK, DV, DVB, AHEAD> L;
     typedef typename L::TD TD;
     typedef typename L::TV TV;
     constexpr int MV = DVB / 16, ND = DK / 64, G = DV / DVB, KS = DK / 32, KSLOTS = L::KSLOTS;
@@ -72,13 +74,13 @@ __device__ __forceinline__ void scan_bwd16(const Dims &d, const ScanBwdArgs &a, 
         // ---------------------------------------------------------------- stores
         StateStore<DK, DV, MV> st;
         constexpr int NS = StateStore<DK, DV, MV>::N;
-        // (at the start, with nothing to store yet, these waves bring Bm and T of the first two chunks)
+        // (at the start, with nothing to store yet, these waves bring Bm and T of the first chunks)
         tm.aim(64, w2, lane, turn, 63);
-        for (int ahead = 0; ahead < 2 && n1 - 1 - ahead >= n0; ++ahead) {
+        for (int ahead = 0; ahead < AHEAD && n1 - 1 - ahead >= n0; ++ahead) {
             request_m(a.Bm, n1 - 1 - ahead, lds.rB[0], ahead);
             request_m(a.Tm, n1 - 1 - ahead, lds.rT[0], ahead);
         }
-        if (n0 + 1 < n1) wait_vm<2 * tm.COUNT>();
+        if (AHEAD == 2 && n0 + 1 < n1) wait_vm<2 * tm.COUNT>();
         else wait_vm<0>();
         __syncthreads();
         for (int n = n1 - 1; n >= n0; --n) {
@@ -86,7 +88,7 @@ __device__ __forceinline__ void scan_bwd16(const Dims &d, const ScanBwdArgs &a, 
             st.read(lds.sD, w2, lane);
             st.template put<0, NS / 2>(states, dv0, w2, lane);
             __syncthreads(); // A
-            if (n == n1 - 1) wait_vm<NS / 2>(); // Bm and T of the second chunk are there
+            if (AHEAD == 2 && n == n1 - 1) wait_vm<NS / 2>(); // Bm and T of the second chunk are there
             st.template put<NS / 2, NS * 3 / 4>(states, dv0, w2, lane);
             __syncthreads(); // B
             store_token_rows<DV, MV, WHOLE>(static_cast<T *>(a.dv) + first_token(n) * DV + dv0, lds.sR0, !WHOLE && n == ragged ? last + 1 : 64, d.H, w2, lane);
@@ -116,7 +118,7 @@ __device__ __forceinline__ void scan_bwd16(const Dims &d, const ScanBwdArgs &a, 
         };
         constexpr int NALL = 2 * tk.COUNT + 2 * tm.COUNT + tv.COUNT + tc.COUNT;
         // (only chunks that exist)
-        for (int ahead = 0; ahead < 2; ++ahead) {
+        for (int ahead = 0; ahead < AHEAD; ++ahead) {
             const int n = n1 - 1 - ahead;
             if (n < n0) break;
             aim_at(!WHOLE && n == ragged ? last : 63);
@@ -125,29 +127,31 @@ __device__ __forceinline__ void scan_bwd16(const Dims &d, const ScanBwdArgs &a, 
             request_o(n, ahead);
             request_rows(a.q, n, lds.rQ[0], ahead);
         }
-        if (n0 + 1 < n1) wait_vm<NALL - 2 * tm.COUNT>();
+        if (AHEAD == 2 && n0 + 1 < n1) wait_vm<NALL - 2 * tm.COUNT>();
         else wait_vm<0>();
         __syncthreads();
-        // (what is requested from here on is not the partial chunk: the lanes aim at whole ones)
+        if (!WHOLE) aim_at(63); // (what is requested from here on is not the partial chunk)
         int slot = 2, par = 0;
         int n = n1 - 1;
-        for (; n - 2 >= n0; --n) {
-            const int nn = n - 2;
+        for (; n - AHEAD >= n0; --n) {
+            const int nn = n - AHEAD;
             if (KSLOTS == 3) request_rows(a.k, nn, lds.rK[0], slot);
+            if (AHEAD == 1) wait_vm<0>(); // q of this chunk is there
             __syncthreads(); // A: Bm, T, dO and the coefficients of this chunk have been read
             request_m(a.Bm, nn, lds.rB[0], par);
             request_m(a.Tm, nn, lds.rT[0], par);
             request_o(nn, par);
             request_c(nn, par);
             __syncthreads(); // B: so have k and q
-            if (KSLOTS == 2) request_rows(a.k, nn, lds.rK[0], par);
+            if (KSLOTS < 3) request_rows(a.k, nn, lds.rK[0], par);
             request_rows(a.q, nn, lds.rQ[0], par);
-            wait_vm<NALL>(); // everything of the next chunk is there
+            wait_vm<AHEAD == 2 ? NALL : tk.COUNT>(); // everything of the next chunk is there (one chunk ahead: q not yet)
             slot = slot == 2 ? 0 : slot + 1;
-            par ^= 1;
+            if (AHEAD == 2) par ^= 1;
             __syncthreads(); // C
         }
         for (; n >= n0; --n) {
+            if (AHEAD == 1) wait_vm<0>();
             __syncthreads(); // A
             __syncthreads(); // B
             wait_vm<0>();
@@ -265,7 +269,7 @@ __device__ __forceinline__ void scan_bwd16(const Dims &d, const ScanBwdArgs &a, 
             k_into_states(1);
             acc.publish(lds.sD, w, r, kg);
             slot = slot == KSLOTS - 1 ? 0 : slot + 1;
-            par ^= 1;
+            if (AHEAD == 2) par ^= 1;
             __syncthreads(); // C
         }
         acc.store(a.dS0, a.dM0, sq.state, w, dv0, r, kg);

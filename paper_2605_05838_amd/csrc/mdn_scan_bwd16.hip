@@ -6,37 +6,44 @@ namespace mdn {
 
 namespace {
 
-template <int DK, int DV, int DVB, bool WHOLE>
-__global__ __launch_bounds__(kScanThreads) void scan_bwd16_kernel(Dims d, ScanBwdArgs a) {
-    __shared__ ScanBwdLds<DK, DV, DVB> lds;
-    scan_bwd16<DK, DV, DVB, WHOLE>(d, a, blockIdx.x, lds);
+template <int DK, int DV, int DVB, bool WHOLE, int AHEAD>
+__global__ __launch_bounds__(kScanThreads, AHEAD == 1 ? 4 : 2) void scan_bwd16_kernel(Dims d, ScanBwdArgs a) {
+    __shared__ ScanBwdLds<DK, DV, DVB, AHEAD> lds;
+    scan_bwd16<DK, DV, DVB, WHOLE, AHEAD>(d, a, blockIdx.x, lds);
 }
 
 // Both at once: the first half of the workgroups walks the reverse scan, the second half (its steps are shorter) the
 // reconstruction.  Neither needs anything of the other.  One launch after the other, 3 x 1 500 tokens of 8 heads of 64 take
-// 20 + 29 us with 96 of the 256 CUs at work; together the shorter chain costs nothing.  Where one of them fills the chip the
-// second half's workgroups start as the first half's end, without the drain and the start between two launches.  Forward and
+// 20 + 29 us with 96 of the 256 CUs at work; together the shorter chain costs nothing.  Up to two rounds of workgroups the
+// second half's start as the first half's end, where the last round would leave CUs empty (see rebuild_beside_scan).  Forward and
 // backward in us, two launches / one: 3 x 1 500, 8 heads of 64 122 / 105; 2 048, 8 heads of 128 133 / 109; 300, 16 heads 57 / 50;
-// 4 x 1 024, 16 heads 188 / 182; 4 x 4 096, 16 heads 701 / 695; packed 32 768 in 64 sequences, 16 heads 1 586 / 1 585.
+// 4 x 1 024, 16 heads 188 / 182; packed 24 sequences of 100 tokens, 16 heads of 128 (320 workgroups) 161 / 149.
 template <int DK, int DV, int DVB, bool WHOLE>
 __global__ __launch_bounds__(kScanThreads) void scan_pair16_kernel(Dims d, ScanBwdArgs b, ScanFwdArgs f) {
-    typedef ScanBwdLds<DK, DV, DVB> LB;
-    typedef ScanFwdLds<DK, DV, DVB, true> LF;
+    typedef ScanBwdLds<DK, DV, DVB, 2> LB;
+    typedef ScanFwdLds<DK, DV, DVB, true, 2> LF;
     __shared__ __align__(16) char lds[sizeof(LB) > sizeof(LF) ? sizeof(LB) : sizeof(LF)];
     const int half = gridDim.x / 2, block = blockIdx.x;
-    if (block < half) scan_bwd16<DK, DV, DVB, WHOLE>(d, b, block, *reinterpret_cast<LB *>(lds));
-    else scan_fwd16<DK, DV, DVB, true, WHOLE>(d, f, block - half, *reinterpret_cast<LF *>(lds));
+    if (block < half) scan_bwd16<DK, DV, DVB, WHOLE, 2>(d, b, block, *reinterpret_cast<LB *>(lds));
+    else scan_fwd16<DK, DV, DVB, true, WHOLE, 2>(d, f, block - half, *reinterpret_cast<LF *>(lds));
 }
 
-template <int DK, int DV, int DVB> hipError_t launch_t(const Dims &d, const ScanBwdArgs &a, hipStream_t s) {
+template <int DK, int DV, int DVB, int AHEAD> hipError_t launch_t(const Dims &d, const ScanBwdArgs &a, hipStream_t s) {
     constexpr int G = DV / DVB;
     const dim3 grid(((d.BH + 7) / 8) * 8 * G), block(kScanThreads);
-    if (whole_chunks(d)) hipLaunchKernelGGL((scan_bwd16_kernel<DK, DV, DVB, true>), grid, block, 0, s, d, a);
-    else hipLaunchKernelGGL((scan_bwd16_kernel<DK, DV, DVB, false>), grid, block, 0, s, d, a);
+    if (whole_chunks(d)) hipLaunchKernelGGL((scan_bwd16_kernel<DK, DV, DVB, true, AHEAD>), grid, block, 0, s, d, a);
+    else hipLaunchKernelGGL((scan_bwd16_kernel<DK, DV, DVB, false, AHEAD>), grid, block, 0, s, d, a);
     return hipGetLastError();
 }
+// Two workgroups per CU as in the forward (heads of 64), one / two in us, forward with kept states and backward: 64 x 64 tokens of 16
+// heads 98.8 / 88.3, 32 x 64 55.0 / 49.8, 32 x 128 87.0 / 81.2, 32 x 1 024 604 / 603.
+template <int DK, int DV, int DVB> hipError_t pick_ahead(const Dims &d, const ScanBwdArgs &a, hipStream_t s) {
+    if constexpr (2 * sizeof(ScanBwdLds<DK, DV, DVB, 1>) <= 160 * 1024)
+        if (!scan_one_per_cu(d)) return launch_t<DK, DV, DVB, 1>(d, a, s);
+    return launch_t<DK, DV, DVB, 2>(d, a, s);
+}
 template <int DK, int DV> hipError_t pick_dvb(const Dims &d, const ScanBwdArgs &a, hipStream_t s) {
-    return scan_dvb(d) == 16 ? launch_t<DK, DV, 16>(d, a, s) : launch_t<DK, DV, 32>(d, a, s);
+    return scan_dvb(d) == 16 ? pick_ahead<DK, DV, 16>(d, a, s) : pick_ahead<DK, DV, 32>(d, a, s);
 }
 template <int DK, int DV, int DVB> hipError_t launch_pair_t(const Dims &d, const ScanBwdArgs &b, const ScanFwdArgs &f, hipStream_t s) {
     const dim3 grid(((d.BH + 7) / 8) * 8 * (DV / DVB) * 2), block(kScanThreads);

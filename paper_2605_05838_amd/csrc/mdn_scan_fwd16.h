@@ -20,16 +20,18 @@
 
 namespace mdn {
 
-template <int DK, int DV, int DVB, bool REBUILD> struct ScanFwdLds {
+// AHEAD: how many chunks in front of the chain the loads are, 2 or (two workgroups per CU: see scan_one_per_cu) 1
+template <int DK, int DV, int DVB, bool REBUILD, int AHEAD> struct ScanFwdLds {
     typedef bf16_t T;
     typedef ATile<T, DVB, 2 * DK> TS; // the states' copy, contraction over dk: S | M
     typedef ATile<T, DVB, 64> TV;     // contraction over the chunk's tokens
-    // operands: of three chunks where a tile is read in the last phase, of two where it is done with before
-    __align__(16) T rK[3][64 * DK];
-    __align__(16) T rT[REBUILD ? 1 : 2][REBUILD ? 8 : 4096];
-    __align__(16) T rB[REBUILD ? 1 : 2][REBUILD ? 8 : 4096];
-    __align__(16) T rV[3][64 * DVB];
-    __align__(16) float rC[3][64 * kCoefRows];
+    // operands: AHEAD chunks, and the chain's own where a tile is read in the last phase
+    static constexpr int SLOTS = AHEAD + 1;
+    __align__(16) T rK[SLOTS][64 * DK];
+    __align__(16) T rT[REBUILD ? 1 : AHEAD][REBUILD ? 8 : 4096];
+    __align__(16) T rB[REBUILD ? 1 : AHEAD][REBUILD ? 8 : 4096];
+    __align__(16) T rV[SLOTS][64 * DVB];
+    __align__(16) float rC[SLOTS][64 * kCoefRows];
     // what the chain leaves
     __align__(16) T sSt[TS::SIZE];
     __align__(16) T sRt[REBUILD ? 8 : TV::SIZE];
@@ -40,14 +42,14 @@ template <int DK, int DV, int DVB, bool REBUILD> struct ScanFwdLds {
 };
 
 // workgroup `block` of ((BH + 7) / 8) * 8 * DV / DVB
-template <int DK, int DV, int DVB, bool REBUILD, bool WHOLE>
-__device__ __forceinline__ void scan_fwd16(const Dims &d, const ScanFwdArgs &a, int block, ScanFwdLds<DK, DV, DVB, REBUILD> &lds) {
+template <int DK, int DV, int DVB, bool REBUILD, bool WHOLE, int AHEAD>
+__device__ __forceinline__ void scan_fwd16(const Dims &d, const ScanFwdArgs &a, int block, ScanFwdLds<DK, DV, DVB, REBUILD, AHEAD> &lds) {
     typedef bf16_t T;
     typedef Op<T> O;
-    typedef ScanFwdLds<DK, DV, DVB, REBUILD> L;
+    typedef ScanFwdLds<DK, DV, DVB, REBUILD, AHEAD> L;
     typedef typename L::TS TS;
     typedef typename L::TV TV;
-    constexpr int MV = DVB / 16, ND = DK / 64, G = DV / DVB, KS = DK / 32;
+    constexpr int MV = DVB / 16, ND = DK / 64, G = DV / DVB, KS = DK / 32, SLOTS = L::SLOTS;
 
     int bh, blkv;
     xcd_map(block, G, bh, blkv);
@@ -73,11 +75,11 @@ __device__ __forceinline__ void scan_fwd16(const Dims &d, const ScanFwdArgs &a, 
         constexpr int NS = StateStore<DK, DV, MV>::N;
         // (at the start, with nothing to store yet, these waves bring T and Bm of the first chunks)
         tm.aim(64, w2, lane, turn, 63);
-        for (int ahead = 0; ahead < 2 && n0 + ahead < n1; ++ahead) {
+        for (int ahead = 0; ahead < AHEAD && n0 + ahead < n1; ++ahead) {
             request_m(a.Tm, n0 + ahead, lds.rT[0], ahead);
             request_m(a.Bm, n0 + ahead, lds.rB[0], ahead);
         }
-        if (n0 + 1 < n1) wait_vm<2 * NM>();
+        if (AHEAD == 2 && n0 + 1 < n1) wait_vm<2 * NM>();
         else wait_vm<0>();
         __syncthreads();
         for (int n = n0;; ++n) {
@@ -91,7 +93,7 @@ __device__ __forceinline__ void scan_fwd16(const Dims &d, const ScanFwdArgs &a, 
                 break;
             }
             if (!REBUILD) __syncthreads(); // A
-            if (!REBUILD && n == n0) { // T and Bm of the second chunk are there
+            if (!REBUILD && AHEAD == 2 && n == n0) { // T and Bm of the second chunk are there
                 if (a.states_saved) wait_vm<NS / 2>();
                 else wait_vm<0>();
             }
@@ -104,7 +106,7 @@ __device__ __forceinline__ void scan_fwd16(const Dims &d, const ScanFwdArgs &a, 
         }
         if (!REBUILD) store_token_rows<DV, MV, WHOLE>(static_cast<T *>(a.o) + first_token(n1 - 1) * DV + dv0, lds.sO, rows_of(n1 - 1), d.H, w2, lane);
     } else if (wv >= 4) {
-        // ---------------------------------------------------------------- loads: two chunks ahead
+        // ---------------------------------------------------------------- loads
         const unsigned rsk = (unsigned)(d.H * DK), rsv = (unsigned)(d.H * DV);
         TileLoad<T, DK, true> tk;
         TileLoad<T, DVB, false> tv;
@@ -129,37 +131,68 @@ __device__ __forceinline__ void scan_fwd16(const Dims &d, const ScanFwdArgs &a, 
             tc.request(a.coef + (sq.blk + n) * (64 * kCoefRows), lds_addr(lds.rC[0]) + slot * (64 * kCoefRows * 4), w2, turn);
         };
         // (only chunks that exist: a chunk more than there are, requested again, is a third of a three-chunk call's traffic)
-        for (int ahead = 0; ahead < 2; ++ahead) {
+        for (int ahead = 0; ahead < AHEAD; ++ahead) {
             const int n = n0 + ahead;
             if (n >= n1) break;
             aim_at(n);
             request_k(n, ahead);
             request_v(n, ahead);
         }
-        if (n0 + 1 < n1) wait_vm<NK + NV>();
-        else wait_vm<0>();
-        __syncthreads();
-        int slot = 2, par = 0;
-        int n = n0;
-        for (; n + 2 < n1; ++n) {
-            const int nn = n + 2;
-            aim_at(nn);
-            request_k(nn, slot);
-            if (!REBUILD) __syncthreads(); // A: T of this chunk has been read
-            request_m(a.Tm, nn, lds.rT[0], par);
-            request_v(nn, slot);
-            wait_vm<NK + NM + NV>(); // everything of the next chunk is there
-            __syncthreads(); // B: so has Bm
-            request_m(a.Bm, nn, lds.rB[0], par);
-            slot = slot == 2 ? 0 : slot + 1;
-            par ^= 1;
-            __syncthreads(); // C
-        }
-        for (; n < n1; ++n) {
-            if (!REBUILD) __syncthreads(); // A
+        if constexpr (AHEAD == 2) {
+            if (n0 + 1 < n1) wait_vm<NK + NV>();
+            else wait_vm<0>();
+            __syncthreads();
+            int slot = 2, par = 0;
+            int n = n0;
+            for (; n + 2 < n1; ++n) {
+                const int nn = n + 2;
+                aim_at(nn);
+                request_k(nn, slot);
+                if (!REBUILD) __syncthreads(); // A: T of this chunk has been read
+                request_m(a.Tm, nn, lds.rT[0], par);
+                request_v(nn, slot);
+                wait_vm<NK + NM + NV>(); // everything of the next chunk is there
+                __syncthreads(); // B: so has Bm
+                request_m(a.Bm, nn, lds.rB[0], par);
+                slot = slot == 2 ? 0 : slot + 1;
+                par ^= 1;
+                __syncthreads(); // C
+            }
+            for (; n < n1; ++n) {
+                if (!REBUILD) __syncthreads(); // A
+                wait_vm<0>();
+                __syncthreads(); // B
+                __syncthreads(); // C
+            }
+        } else {
+            // (the chain reads the rows of a chunk at the end of the step before, T in phase A and Bm in phase B)
+            auto request_rows = [&](int n) {
+                if (n >= n1) return;
+                aim_at(n);
+                request_k(n, (n - n0) & 1);
+                request_v(n, (n - n0) & 1);
+            };
             wait_vm<0>();
-            __syncthreads(); // B
-            __syncthreads(); // C
+            __syncthreads();
+            request_rows(n0 + 1);
+            for (int n = n0; n < n1; ++n) {
+                const bool next = n + 1 < n1;
+                if (!REBUILD) {
+                    if (next) wait_vm<NK + NV>(); // Bm of this chunk is there
+                    else wait_vm<0>();
+                    __syncthreads(); // A: T of this chunk has been read
+                    if (next) request_m(a.Tm, n + 1, lds.rT[0], 0);
+                }
+                wait_vm<NM>(); // the rows of the next chunk are there (nothing is outstanding if there is none)
+                __syncthreads(); // B: this chunk's rows and Bm have been read
+                if (next) request_m(a.Bm, n + 1, lds.rB[0], 0);
+                request_rows(n + 2);
+                if (!REBUILD) {
+                    if (n + 2 < n1) wait_vm<NM + NK + NV>(); // T of the next chunk is there
+                    else wait_vm<NM>();
+                }
+                __syncthreads(); // C
+            }
         } // (no transfer outlives the workgroup: the last step has waited for all of them)
     } else {
         // ---------------------------------------------------------------- the chain
@@ -280,8 +313,8 @@ __device__ __forceinline__ void scan_fwd16(const Dims &d, const ScanFwdArgs &a, 
 #pragma unroll
                     for (int mv = 0; mv < MV; ++mv) o[mv] = O::mma(TV::frag(lds.sV0, mv, s * 32, r, kg), bm[s], o[mv]);
             }
-            slot = slot == 2 ? 0 : slot + 1;
-            par ^= 1;
+            slot = slot == SLOTS - 1 ? 0 : slot + 1;
+            if (AHEAD == 2) par ^= 1;
             // (the branch keeps what the next step needs behind this one's products, also where it is always taken: 4 x 2 048 tokens of
             //  16 heads of 128, forward 83.9 us without it, 82.2 with it; d = 64 is faster with both interleaved, 1 x 2 048 of 16
             //  heads 40.3 us with it, 38.3 without)

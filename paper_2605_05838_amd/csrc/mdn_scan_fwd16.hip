@@ -5,21 +5,35 @@ namespace mdn {
 
 namespace {
 
-template <int DK, int DV, int DVB, bool REBUILD, bool WHOLE>
-__global__ __launch_bounds__(kScanThreads) void scan_fwd16_kernel(Dims d, ScanFwdArgs a) {
-    __shared__ ScanFwdLds<DK, DV, DVB, REBUILD> lds;
-    scan_fwd16<DK, DV, DVB, REBUILD, WHOLE>(d, a, blockIdx.x, lds);
+template <int DK, int DV, int DVB, bool REBUILD, bool WHOLE, int AHEAD>
+__global__ __launch_bounds__(kScanThreads, AHEAD == 1 ? 4 : 2) void scan_fwd16_kernel(Dims d, ScanFwdArgs a) {
+    __shared__ ScanFwdLds<DK, DV, DVB, REBUILD, AHEAD> lds;
+    scan_fwd16<DK, DV, DVB, REBUILD, WHOLE, AHEAD>(d, a, blockIdx.x, lds);
 }
 
-template <int DK, int DV, int DVB, bool REBUILD> hipError_t launch_t(const Dims &d, const ScanFwdArgs &a, hipStream_t s) {
+template <int DK, int DV, int DVB, bool REBUILD, bool WHOLE, int AHEAD>
+hipError_t launch_w(const Dims &d, const ScanFwdArgs &a, hipStream_t s) {
     constexpr int G = DV / DVB;
     const dim3 grid(((d.BH + 7) / 8) * 8 * G), block(kScanThreads);
-    if (whole_chunks(d)) hipLaunchKernelGGL((scan_fwd16_kernel<DK, DV, DVB, REBUILD, true>), grid, block, 0, s, d, a);
-    else hipLaunchKernelGGL((scan_fwd16_kernel<DK, DV, DVB, REBUILD, false>), grid, block, 0, s, d, a);
+    static const size_t spread =
+        AHEAD == 1 ? 0 : lds_bytes_for_one_workgroup_per_cu(reinterpret_cast<const void *>(&scan_fwd16_kernel<DK, DV, DVB, REBUILD, WHOLE, AHEAD>));
+    hipLaunchKernelGGL((scan_fwd16_kernel<DK, DV, DVB, REBUILD, WHOLE, AHEAD>), grid, block, spread, s, d, a);
     return hipGetLastError();
 }
+template <int DK, int DV, int DVB, bool REBUILD, int AHEAD> hipError_t launch_t(const Dims &d, const ScanFwdArgs &a, hipStream_t s) {
+    return whole_chunks(d) ? launch_w<DK, DV, DVB, REBUILD, true, AHEAD>(d, a, s) : launch_w<DK, DV, DVB, REBUILD, false, AHEAD>(d, a, s);
+}
+// Two workgroups per CU where there are more of them than CUs and the operands of one chunk less make them fit (all but the forward
+// of heads of 128): a workgroup's start and the latencies of its chain then lie beside another one's work.  One / two per CU, forward
+// of heads of 64 in us: 64 x 64 tokens of 16 heads 43.4 / 33.9, 32 x 128 36.1 / 30.8, 32 x 1 024 187 / 182, packed 256 sequences of 30
+// tokens of 16 heads 156 / 107.  One chunk ahead costs a single workgroup up to a tenth of a step, so up to one per CU it is two.
+template <int DK, int DV, int DVB, bool REBUILD> hipError_t pick_ahead(const Dims &d, const ScanFwdArgs &a, hipStream_t s) {
+    if constexpr (2 * sizeof(ScanFwdLds<DK, DV, DVB, REBUILD, 1>) <= 160 * 1024)
+        if (!scan_one_per_cu(d)) return launch_t<DK, DV, DVB, REBUILD, 1>(d, a, s);
+    return launch_t<DK, DV, DVB, REBUILD, 2>(d, a, s);
+}
 template <int DK, int DV, bool REBUILD> hipError_t pick_dvb(const Dims &d, const ScanFwdArgs &a, hipStream_t s) {
-    return scan_dvb(d) == 16 ? launch_t<DK, DV, 16, REBUILD>(d, a, s) : launch_t<DK, DV, 32, REBUILD>(d, a, s);
+    return scan_dvb(d) == 16 ? pick_ahead<DK, DV, 16, REBUILD>(d, a, s) : pick_ahead<DK, DV, 32, REBUILD>(d, a, s);
 }
 
 } // namespace

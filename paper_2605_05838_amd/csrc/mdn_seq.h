@@ -24,7 +24,12 @@ template <bool WHOLE> __device__ __forceinline__ ScanSeq scan_seq(const Dims &d,
     const int b = bh / d.H, h = bh % d.H;
     ScanSeq q;
     if (!WHOLE && d.seqs) {
-        const SeqEntry e = d.seqs[b];
+        // (from memory that the kernel also writes, the compiler loads the entry per lane, into vector registers)
+        SeqEntry e = d.seqs[b];
+        e.t0 = __builtin_amdgcn_readfirstlane(e.t0);
+        e.len = __builtin_amdgcn_readfirstlane(e.len);
+        e.cb = __builtin_amdgcn_readfirstlane(e.cb);
+        e.idx = __builtin_amdgcn_readfirstlane(e.idx);
         const int N = (e.len + 63) >> 6;
         q.tok = (size_t)e.t0 * d.H + h;
         q.blk = (size_t)e.cb * d.H + (size_t)h * N;

@@ -215,3 +215,26 @@ def test_as_few_chunks_as_the_scans_keep_in_flight(T, B, H, d, keep):
     per workgroup."""
     w = synth.custom(B=B, T=T, H=H, dk=d, dv=d, dtype="bf16", seed=59, with_eta=True, s0_std=0.2, backward=True)
     check_bwd(w, pairs=[(0, 0), (B - 1, H - 1)], save_states=keep, save_operands=keep)
+
+
+@pytest.mark.parametrize("B,H,d,nseg", [(17, 8, 64, 1), (10, 8, 64, 1), (10, 8, 64, 2), (17, 8, 128, 1), (6, 8, 128, 2)])
+@pytest.mark.parametrize("T", [1, 64, 128, 193, 512])
+def test_more_workgroups_than_cus_give_the_results_of_few(T, B, H, d, nseg):
+    """Launches with two workgroups per CU (the loads one chunk ahead, 16 and 32 columns) against the same sequences in a
+    call that leaves CUs idle (two chunks ahead): every output bit for bit, states and adjoints given and asked for."""
+    w = synth.custom(B=B, T=T, H=H, dk=d, dv=d, dtype="bf16", seed=61, with_eta=True, s0_std=0.2, backward=True)
+    t = to_dev(w)
+    few = {k: None if v is None else v[:1].contiguous() for k, v in t.items()}
+    outs = []
+    for x, k in ((t, nseg), (few, 1)):
+        old = binding.set_segments(k if T >= 512 else 1)
+        try:
+            f = binding.mdn_chunk_fwd(x["q"], x["k"], x["v"], x["beta"], x["alpha"], x["mu"], eta=x["eta"], S0=x["S0"], M0=x["M0"],
+                                      scale=w.scale, save_vt=True)
+            g = binding.mdn_chunk_bwd(x["q"], x["k"], x["v"], x["beta"], x["alpha"], x["mu"], f["vt"], x["dO"], eta=x["eta"],
+                                      S0=x["S0"], M0=x["M0"], dS_final=x["S0"], dM_final=x["M0"], scale=w.scale, want_deta=True)
+        finally:
+            binding.set_segments(old)
+        outs.append({**{n: f[n][:1] for n in ("o", "vt", "S", "M")}, **{n: g[n][:1] for n in GRADS}})
+    for name, x in outs[0].items():
+        assert torch.equal(x, outs[1][name]), name
