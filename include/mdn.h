@@ -145,7 +145,8 @@ int mdn_chunk_fwd_noalloc(const mdn_shape *shape, const void *q, const void *k, 
  *        dS_final, dM_final [B,H,dk,dv] fp32 or NULL (= 0).
  *   out: dq, dk [B,T,H,dk], dv [B,T,H,dv] (storage dtype); dbeta, dalpha, dmu [B,T,H] fp32;
  *        deta [B,T,H] fp32 or NULL; dS0, dM0 [B,H,dk,dv] fp32 or NULL.
- *        Gradients are with respect to the linear gate values.
+ *        Gradients are with respect to the linear gate values.  dS0 and dM0 may be the memory of S0 and M0 (in either order):
+ *        the initial states are read before their gradients are written.
  *   workspace: at least mdn_workspace_bytes(MDN_WS_BWD); with dS_final or dM_final given,
  *        mdn_workspace_bytes(MDN_WS_BWD_STATE_ADJOINTS).  Adjoints that enter from outside can be large against
  *        everything dO puts into the states, so with 16-bit storage such a call carries the chunk states and their

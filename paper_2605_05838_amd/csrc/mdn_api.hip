@@ -302,6 +302,7 @@ struct BwdCall {
     const float *dS_final, *dM_final;
     void *dq, *dk, *dv;
     float *dbeta, *dalpha, *dmu, *deta, *dS0, *dM0;
+    size_t state_bytes; // of a state tensor of the whole call
 };
 struct Prepared {
     RevOps ro;
@@ -318,13 +319,23 @@ bool precise_call(const Dims &d, const BwdCall &c) {
     return d.dtype == MDN_DTYPE_BF16 && (c.dS_final || c.dM_final);
 }
 
+// Whether a state gradient goes where the initial states come from: the reverse scan may then write only when the reconstruction
+// has read them all.
+bool state_gradients_in_place(const BwdCall &c) {
+    auto shared = [&](const float *in, const float *out) {
+        const uintptr_t i = reinterpret_cast<uintptr_t>(in), o = reinterpret_cast<uintptr_t>(out);
+        return in && out && i < o + c.state_bytes && o < i + c.state_bytes;
+    };
+    return shared(c.S0, c.dS0) || shared(c.S0, c.dM0) || shared(c.M0, c.dS0) || shared(c.M0, c.dM0);
+}
+
 // Whether the reconstruction and the reverse scan run as one launch (`nseg`: the segments of this call; see scan_pair16_kernel):
 // below two full rounds of workgroups.  From there on the reconstruction alone runs two to a CU, which it cannot beside the reverse
 // scan's LDS.  Forward and backward in us, two launches / one, heads of 128: 8 x 256 tokens of 16 heads (512 workgroups) 107.2 / 109.3,
 // 8 x 2 048 677.5 / 677.1; 16 x 256 203.5 / 205.8; 32 x 512 712 / 723; packed 32 768 in 64 sequences 1 404 / 1 428; of 64: 16 x 256
 // 99.4 / 101.1, 16 x 1 024 349.7 / 343.0.  32-bit storage has scans of another form.
-bool rebuild_beside_scan(const Dims &d, int nseg) {
-    return !wide(d) && nseg == 1 && scan_workgroups(d) < 2 * num_cus();
+bool rebuild_beside_scan(const Dims &d, const BwdCall &c, int nseg) {
+    return !wide(d) && nseg == 1 && !state_gradients_in_place(c) && scan_workgroups(d) < 2 * num_cus();
 }
 
 int bwd_prepare(const Dims &d, const BwdCall &c, const BwdWs &w, hipStream_t s, Prepared *out, bool precise, int nseg) {
@@ -349,7 +360,7 @@ int bwd_prepare(const Dims &d, const BwdCall &c, const BwdWs &w, hipStream_t s, 
         ra.coef = out->ro.coef; ra.k = c.k; ra.KT = out->ro.KT; ra.vt_saved = c.vt_saved; ra.S0 = c.S0; ra.M0 = c.M0;
         ra.states = w.states; ra.states_lo = precise ? w.states_lo : nullptr;
         out->states = w.states;
-        if (rebuild_beside_scan(d, nseg)) {
+        if (rebuild_beside_scan(d, c, nseg)) {
             out->how = ra;
             out->pending = true;
             return MDN_OK;
@@ -527,7 +538,7 @@ int bwd_small_chunks(const Dims &d, int C, const BwdCall &c, void *workspace, hi
     if (rc) return rc;
     const BwdCall ce = {x.q, x.k, x.v, x.beta, x.alpha, x.mu, c.eta ? x.eta : nullptr, c.S0, c.M0, x.vt, c.states_saved,
                         c.operands_saved, x.dO, c.dS_final, c.dM_final, x.dq, x.dk, x.dv, x.dbeta, x.dalpha, x.dmu,
-                        c.deta ? x.deta : nullptr, c.dS0, c.dM0};
+                        c.deta ? x.deta : nullptr, c.dS0, c.dM0, c.state_bytes};
     rc = bwd_all(e, ce, x.rest, s);
     if (rc) return rc;
     ChunkList out(d, C);
@@ -1001,7 +1012,7 @@ int mdn_chunk_bwd(const mdn_shape *shape, const void *q, const void *k, const vo
     for (const void *p : ptrs)
         if (p && misaligned(p)) return MDN_ERR_ALIGN;
     BwdCall c = {q, k, v, beta, alpha, mu, eta, S0, M0, vt_saved, states_saved, operands_saved, dO, dS_final, dM_final,
-                 dq, dk, dv, dbeta, dalpha, dmu, deta, dS0, dM0};
+                 dq, dk, dv, dbeta, dalpha, dmu, deta, dS0, dM0, (size_t)d.BH * d.dk * d.dv * sizeof(float)};
     if (workspace_bytes < bwd_ws_call(d, shape, precise_call(d, c))) return MDN_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (shape->C != 64) return bwd_small_chunks(d, shape->C, c, workspace, s);
@@ -1080,7 +1091,7 @@ int mdn_chunk_bwd_varlen(const mdn_shape *shape, const int32_t *cu_seqlens, int3
     if (workspace_bytes < need) return MDN_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
     BwdCall c = {q, k, v, beta, alpha, mu, eta, S0, M0, vt_saved, nullptr, nullptr, dO, dS_final, dM_final,
-                 dq, dk, dv, dbeta, dalpha, dmu, deta, dS0, dM0};
+                 dq, dk, dv, dbeta, dalpha, dmu, deta, dS0, dM0, (size_t)n_seq * d.H * d.dk * d.dv * sizeof(float)};
     auto run = [&](const Dims &g, const BwdCall &cg, void *ws) { return bwd_all(g, cg, ws, s); };
     if (!m.used) return packed_run(d, cu_seqlens, n_seq, form, c, workspace, s, run);
     const MergedWs w = carve_merged(d, workspace);

@@ -238,3 +238,25 @@ def test_more_workgroups_than_cus_give_the_results_of_few(T, B, H, d, nseg):
         outs.append({**{n: f[n][:1] for n in ("o", "vt", "S", "M")}, **{n: g[n][:1] for n in GRADS}})
     for name, x in outs[0].items():
         assert torch.equal(x, outs[1][name]), name
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("B,H,d,T,nseg,swapped", [(1, 2, 64, 512, 1, False), (1, 2, 128, 512, 2, True), (5, 8, 128, 1024, 1, True),
+                                                  (3, 8, 128, 300, 1, False), (6, 8, 128, 256, 1, True)])
+def test_state_gradients_may_be_written_over_the_initial_states(dtype, B, H, d, T, nseg, swapped):
+    """dS0, dM0 in the memory of S0, M0 (or of M0, S0): the states of every chunk are reconstructed from them first, however many
+    workgroups the reconstruction and the reverse scan have between them."""
+    w = synth.custom(B=B, T=T, H=H, dk=d, dv=d, dtype=dtype, seed=67, with_eta=True, s0_std=0.2, backward=True)
+    w.arrays["M0"] = np.ascontiguousarray(0.5 * w.arrays["S0"][..., ::-1])
+    t = to_dev(w)
+    old = binding.set_segments(nseg)
+    try:
+        f, g = run_fwd_bwd(w, t)
+        S0, M0 = t["S0"].clone(), t["M0"].clone()
+        h = binding.mdn_chunk_bwd(t["q"], t["k"], t["v"], t["beta"], t["alpha"], t["mu"], f["vt"], t["dO"], eta=t["eta"], S0=S0, M0=M0,
+                                  scale=w.scale, want_deta=True, out={"dS0": M0 if swapped else S0, "dM0": S0 if swapped else M0})
+    finally:
+        binding.set_segments(old)
+    assert h["dS0"].data_ptr() == (M0 if swapped else S0).data_ptr()
+    for name in GRADS:
+        assert torch.equal(g[name], h[name]), name
