@@ -172,23 +172,30 @@ std::atomic<int> g_segments{0}; // 0: automatic
 bool few_scan_workgroups(const Dims &d) { return 2 * scan_workgroups(d) <= num_cus(); }
 
 // A boundary costs ~10 us (an event pair, the scan's start and its drain) and a segment hides its gradient launch, ~50 us
-// per 1 024 chunk blocks of d = 128: one segment per 1 024.  Backward in us, unsplit / 2 / 4 / 8 segments, d = 128:
-//   blocks  1 024 (16 heads, T =  4 096):   168 /   178 /   185 /   217
-//   blocks  2 048 (16 heads, T =  8 192):   357 /   343 /   345 /   372     (4 heads, T = 32 768: 978 / 965 / 968 / 1 000)
-//   blocks  4 096 (16 heads, T = 16 384):   707 /   651 /   626 /   650
-//   blocks  8 192 (16 heads, T = 32 768): 1 448 / 1 281 / 1 205 / 1 189
-// and 192 / 189 / 190 / 211 for 2 048 blocks of d = 64.  32-bit storage takes four times as long per block (512 blocks, 8
-// heads: 462 / 427 / 440 / 615; 2 048 of d = 64, 4 heads: 1 751 / 1 668 / 1 633 / 1 641); segments of fewer than 32 chunks
-// are all start and drain (512 blocks in 32 chunks of 16 heads: 304 / 315 / 352 / 594).  Forward: 271 / 289 / 299 / 328 for the second row, 1 159 / 1 190 /
-// 1 194 / 1 232 for the last, and slower split than unsplit at every other size measured.
-long long backward_segments(const Dims &d) {
+// per 1 024 chunk blocks of d = 128: one segment per 1 024.  Where the states must be reconstructed, 16-bit storage does that in the
+// reverse scan's launch if the call is not split, and on the second stream if it is: then the gradient launches wait for all of it, and
+// less of them is hidden: two segments from 2 400 blocks on, another one per 2 048.  Backward in us, unsplit / 2 / 4 / 8 segments,
+// d = 128, states kept; reconstructed; reconstructed, with adjoints of the final states:
+//   blocks  1 024 (16 heads, T =  4 096):   126 /   142 /   147 /   184;    155 /   165 /   178 /   218;    227 /   241 /   257 /   312
+//   blocks  2 048 (16 heads, T =  8 192):   299 /   279 /   277 /   299;    320 /   336 /   347 /   379;    476 /   477 /   488 /   512
+//                 ( 4 heads, T = 32 768):   699 /   715 /   719 /   750;    700 /   697 /   707 /   732;    948 /   918 /   913 /   944
+//   blocks  2 504 ( 8 heads, T = 20 032):   542 /   518 /   521 /   548;    518 /   520 /   537 /   556;    771 /   716 /   717 /   754
+//   blocks  4 096 (16 heads, T = 16 384):   607 /   541 /   508 /   519;    681 /   641 /   657 /   691;  1 000 /   920 /   936 /   957
+//   blocks  8 192 (16 heads, T = 32 768): 1 173 / 1 031 /   967 /   944;  1 418 / 1 261 / 1 271 / 1 298;  2 015 / 1 814 / 1 817 / 1 806
+// and 421 / 381 / 367 / 400; 418 / 402 / 413 / 444; 535 / 496 / 503 / 532 for 4 096 blocks of d = 64.  (With the reconstruction in
+// front of the segments 4 096 blocks of d = 128 took 752 in 4.)  32-bit storage takes four times as long per block (512 blocks, 8
+// heads, states kept: 445 / 417 / 432 / 555; 2 048 of d = 64, 4 heads: 1 721 / 1 645 / 1 612 / 1 621; reconstructed 582 / 464 / 479 /
+// 646 and 2 314 / 1 707 / 1 672 / 1 689); segments of fewer than 32 chunks are all start and drain.  Forward: 168 / 192 / 195 / 229 for
+// the second row, 834 / 861 / 842 / 844 for the last.
+long long backward_segments(const Dims &d, bool rebuild) {
     const long long grad = (long long)d.N * d.BH * d.dk * (d.dtype == MDN_DTYPE_F32 ? 4 : 1); // its time, in 1/128 blocks
-    return few_scan_workgroups(d) ? std::min({8LL, d.N / 32LL, grad / (128 * 1024)}) : 1;
+    const long long k = rebuild && !wide(d) ? (grad / 128 + 1696) / 2048 : grad / (128 * 1024);
+    return few_scan_workgroups(d) ? std::min({8LL, d.N / 32LL, k}) : 1;
 }
-int segments(const Dims &d, bool backward) {
+int segments(const Dims &d, bool backward, bool rebuild = false) {
     if (t_no_alloc || d.packed) return 1; // (packed batches: the scans of the sequences run beside each other)
     long long k = g_segments.load(std::memory_order_relaxed);
-    if (k <= 0) k = backward ? backward_segments(d) : 1;
+    if (k <= 0) k = backward ? backward_segments(d, rebuild) : 1;
     k = std::min(k, (long long)d.N / 4);
     return (int)std::max(1LL, std::min(16LL, k));
 }
@@ -307,8 +314,8 @@ struct BwdCall {
 struct Prepared {
     RevOps ro;
     const void *states;
-    bool pending;    // the states are still to be reconstructed, in one launch with the reverse scan:
-    RebuildArgs how;
+    enum { DONE, IN_SCAN, BESIDE_SEGMENTS } rebuild; // the states are there, or still to be reconstructed (`how`): in one launch
+    RebuildArgs how;                                 // with the reverse scan, or on the second stream beside its segments
 };
 
 // Adjoints of the final states that come in from outside can be large against everything dO puts into the states;
@@ -329,13 +336,13 @@ bool state_gradients_in_place(const BwdCall &c) {
     return shared(c.S0, c.dS0) || shared(c.S0, c.dM0) || shared(c.M0, c.dS0) || shared(c.M0, c.dM0);
 }
 
-// Whether the reconstruction and the reverse scan run as one launch (`nseg`: the segments of this call; see scan_pair16_kernel):
+// Whether the reconstruction and the reverse scan of a call that is not split run as one launch (see scan_pair16_kernel):
 // below two full rounds of workgroups.  From there on the reconstruction alone runs two to a CU, which it cannot beside the reverse
 // scan's LDS.  Forward and backward in us, two launches / one, heads of 128: 8 x 256 tokens of 16 heads (512 workgroups) 107.2 / 109.3,
 // 8 x 2 048 677.5 / 677.1; 16 x 256 203.5 / 205.8; 32 x 512 712 / 723; packed 32 768 in 64 sequences 1 404 / 1 428; of 64: 16 x 256
 // 99.4 / 101.1, 16 x 1 024 349.7 / 343.0.  32-bit storage has scans of another form.
-bool rebuild_beside_scan(const Dims &d, const BwdCall &c, int nseg) {
-    return !wide(d) && nseg == 1 && !state_gradients_in_place(c) && scan_workgroups(d) < 2 * num_cus();
+bool rebuild_in_scan(const Dims &d) {
+    return !wide(d) && scan_workgroups(d) < 2 * num_cus();
 }
 
 int bwd_prepare(const Dims &d, const BwdCall &c, const BwdWs &w, hipStream_t s, Prepared *out, bool precise, int nseg) {
@@ -354,16 +361,17 @@ int bwd_prepare(const Dims &d, const BwdCall &c, const BwdWs &w, hipStream_t s, 
     }
     // chunk-start states: given by the forward, or reconstructed from V~
     out->states = precise ? nullptr : c.states_saved;
-    out->pending = false;
+    out->rebuild = Prepared::DONE;
     if (!out->states) {
         RebuildArgs ra = {};
         ra.coef = out->ro.coef; ra.k = c.k; ra.KT = out->ro.KT; ra.vt_saved = c.vt_saved; ra.S0 = c.S0; ra.M0 = c.M0;
         ra.states = w.states; ra.states_lo = precise ? w.states_lo : nullptr;
         out->states = w.states;
-        if (rebuild_beside_scan(d, c, nseg)) {
-            out->how = ra;
-            out->pending = true;
-            return MDN_OK;
+        out->how = ra;
+        if (!state_gradients_in_place(c)) {
+            if (nseg > 1) out->rebuild = Prepared::BESIDE_SEGMENTS;
+            else if (rebuild_in_scan(d)) out->rebuild = Prepared::IN_SCAN;
+            if (out->rebuild != Prepared::DONE) return MDN_OK;
         }
         rc = timed(MDN_KERNEL_REBUILD, s, [&] { return launch_rebuild(d, ra, s); });
         if (rc) return rc;
@@ -385,7 +393,7 @@ int bwd_run(const Dims &d, const BwdCall &c, const BwdWs &w, const Prepared &p, 
     ga.states_lo = precise ? w.states_lo : nullptr; ga.dstates_lo = precise ? w.dstates_lo : nullptr;
     ga.dq = c.dq; ga.dk = c.dk; ga.dalpha = c.dalpha; ga.dbeta = c.dbeta; ga.dmu = c.dmu; ga.deta = c.deta;
     if (nseg == 1) {
-        if (p.pending) {
+        if (p.rebuild == Prepared::IN_SCAN) {
             count_launch(MDN_KERNEL_REBUILD); // (its time stands with the reverse scan's)
             rc = timed(MDN_KERNEL_SCAN_BWD, s, [&] { return launch_rebuild_and_scan_bwd(d, p.how, sb, s); });
         } else {
@@ -399,9 +407,14 @@ int bwd_run(const Dims &d, const BwdCall &c, const BwdWs &w, const Prepared &p, 
     Side *sdev = side_device();
     if (!sdev) return MDN_ERR_LAUNCH;
     std::lock_guard<std::mutex> lock(sdev->mutex);
-    Side *sd = side(nseg + 1);
+    Side *sd = side(nseg + 2);
     if (!sd) return MDN_ERR_LAUNCH;
     rc = MDN_OK;
+    if (p.rebuild == Prepared::BESIDE_SEGMENTS) { // in front of the gradient launches, which need it, beside the first scans, which do not
+        if (hipEventRecord(sd->ev[nseg + 1], s) != hipSuccess || hipStreamWaitEvent(sd->stream, sd->ev[nseg + 1], 0) != hipSuccess)
+            return MDN_ERR_LAUNCH;
+        rc = timed(MDN_KERNEL_REBUILD, sd->stream, [&] { return launch_rebuild(d, p.how, sd->stream); });
+    }
     for (int i = nseg - 1; i >= 0 && !rc; --i) {
         const Dims di = segment(d, i, nseg);
         sb.dS_final = i == nseg - 1 ? c.dS_final : w.carryS;
@@ -425,7 +438,7 @@ int bwd_run(const Dims &d, const BwdCall &c, const BwdWs &w, const Prepared &p, 
 int bwd_all(const Dims &d, const BwdCall &c, void *workspace, hipStream_t s) {
     const bool precise = precise_call(d, c);
     const BwdWs w = carve_bwd(d, workspace, precise);
-    const int nseg = segments(d, true); // (asked for once: another thread may change the setting)
+    const int nseg = segments(d, true, precise || !c.states_saved); // (asked for once: another thread may change the setting)
     Prepared p;
     const int rc = bwd_prepare(d, c, w, s, &p, precise, nseg);
     return rc ? rc : bwd_run(d, c, w, p, s, precise, nseg);
@@ -587,7 +600,7 @@ size_t bwd_block_bytes(const Dims &d, bool precise) {
 // their tokens, and the remainders of a `precise` backward double the largest part of a block.  A batch that needs too much
 // at once runs group by group on one workspace.  A forward's group ends before it needs more than three times the blocks of T
 // unbroken tokens, or than 65 536 (1.2 GB of 16-bit storage, d = 128); a backward's before it needs more bytes than 5/4
-// of what T unbroken tokens take, or than 512 MiB (3 000 such blocks, 12 per CU: the boundary between two groups costs a few
+// of what T unbroken tokens take, or than 512 MiB (3 600 blocks of 16-bit storage, 14 per CU: the boundary between two groups costs a few
 // launches and the wait for the longest sequence of the first).  Sequences of 128 tokens and more on average are one group
 // unless they are precise; a longer sequence than that is a group of its own, whatever it needs.
 struct SeqGroup { int s0, s1; Dims d; }; // sequences [s0, s1); a single one is an ordinary batch of one (no tables)
@@ -606,14 +619,17 @@ Dims one_sequence(const Dims &d, const int32_t *cu, int i) {
 // scans (see backward_segments) and that hides more than running them beside the others' scans would: per 1 024 chunk blocks of
 // the long one ~44 us hidden, against ~40 us for every group that is added and what the others' scans then take by themselves, ~3.8 us
 // a step of their longest or ~0.06 us a chunk block, whichever is more.  (In the unit of a hidden chunk block: 1 000, 88, 3/2.)
-// Backward in us, together / alone, d = 128: 29 500 tokens and 16 of 205, 16 heads 2 122 / 1 947, 8 heads 1 649 / 1 596; 31 130 and
-// 1 638, 16 heads 2 174 / 2 002; not taken: 16 384 and 32 of 512, 8 heads 1 115 / 1 165, 24 576 and 8 192, 16 heads 1 903 / 2 060.
+// (The line is drawn for gradient launches that are hidden whole.  Behind a reconstruction on the second stream less of them is, 10 to
+// 30 us per 1 024 blocks, but on either side of it the two orders are within a tenth.)
+// Backward in us, together / alone, 16 heads of 128: 29 500 tokens and 16 of 205 1 414 / 1 350; 31 130 and 1 638 1 428 / 1 319; 60 000 and
+// 16 of 300 2 748 / 2 501; 8 heads 884 / 863, 880 / 904, 1 860 / 1 749; 16 heads of 64 925 / 878, 943 / 905, 1 835 / 1 722; near the
+// line 100, 20 037 and 63 tokens of 8 heads of 128 530 / 589.  Not taken: 16 384 and 32 of 512; 24 576 and 8 192.
 int long_sequence(const Dims &d, const int32_t *cu, int32_t n_seq) {
     int a = 0;
     for (int i = 1; i < n_seq; ++i)
         if (cu[i + 1] - cu[i] > cu[a + 1] - cu[a]) a = i;
     const Dims r = one_sequence(d, cu, a);
-    if (backward_segments(r) < 2) return -1;
+    if (backward_segments(r, true) < 2) return -1;
     long long groups = 0, steps = 0, blocks = 0;
     auto others = [&](int i0, int i1) {
         long long longest = 0;

@@ -15,7 +15,7 @@ __global__ __launch_bounds__(kScanThreads, AHEAD == 1 ? 4 : 2) void scan_bwd16_k
 // Both at once: the first half of the workgroups walks the reverse scan, the second half (its steps are shorter) the
 // reconstruction.  Neither needs anything of the other.  One launch after the other, 3 x 1 500 tokens of 8 heads of 64 take
 // 20 + 29 us with 96 of the 256 CUs at work; together the shorter chain costs nothing.  Up to two rounds of workgroups the
-// second half's start as the first half's end, where the last round would leave CUs empty (see rebuild_beside_scan).  Forward and
+// second half's start as the first half's end, where the last round would leave CUs empty (see rebuild_in_scan).  Forward and
 // backward in us, two launches / one: 3 x 1 500, 8 heads of 64 122 / 105; 2 048, 8 heads of 128 133 / 109; 300, 16 heads 57 / 50;
 // 4 x 1 024, 16 heads 188 / 182; packed 24 sequences of 100 tokens, 16 heads of 128 (320 workgroups) 161 / 149.
 template <int DK, int DV, int DVB, bool WHOLE>

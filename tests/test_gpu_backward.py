@@ -260,3 +260,25 @@ def test_state_gradients_may_be_written_over_the_initial_states(dtype, B, H, d, 
     assert h["dS0"].data_ptr() == (M0 if swapped else S0).data_ptr()
     for name in GRADS:
         assert torch.equal(g[name], h[name]), name
+
+
+@pytest.mark.parametrize("d,H,T,adjoints,nseg", [(128, 8, 19200, False, 2), (128, 8, 19200 - 27, True, 2), (128, 8, 19136, False, 1),
+                                                 (64, 16, 19200, True, 2), (64, 16, 19136, True, 1)])
+def test_the_automatic_split_of_a_backward_that_reconstructs_the_states(d, H, T, adjoints, nseg):
+    """The smallest call that splits by itself (2 400 chunk blocks of heads of 128) and the same one chunk short of it: the
+    reconstruction is one launch, beside the segments of the reverse scan or in its launch, and every gradient is the unsplit call's."""
+    w = synth.custom(B=1, T=T, H=H, dk=d, dv=d, dtype="bf16", seed=71, with_eta=True, s0_std=0.2, backward=True)
+    t = to_dev(w)
+    final = [0.1 * t["S0"] if adjoints else None for _ in range(2)]
+    g = []
+    for k in (1, 0):
+        old = binding.set_segments(k)
+        try:
+            binding.profile_begin()
+            g.append(run_fwd_bwd(w, t, *final)[1])
+            launches = binding.profile_end(with_launch_counts=True)
+        finally:
+            binding.set_segments(old)
+        assert launches["grad"][2] == launches["scan_bwd"][2] == (nseg if k == 0 else 1) and launches["rebuild"][2] == 1
+    for name in GRADS:
+        assert torch.equal(g[0][name], g[1][name]), name
