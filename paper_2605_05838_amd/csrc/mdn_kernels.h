@@ -119,8 +119,9 @@ struct RecurrentArgs {
 
 // compute units of the current device (256 if it cannot be asked)
 int num_cus();
-// dv columns per workgroup of the scans for this shape: 32, unless that leaves a quarter of the CUs or more without
-// a workgroup or (32-bit storage, d = 128) the prefetched fragments of 32 columns do not fit the registers: then 16
+// dv columns per workgroup of the scans for this shape.  16-bit storage: 16 if the CUs hold all workgroups of 16, or 32.  32-bit
+// storage: 32, unless that leaves a quarter of the CUs or more without a workgroup or (d = 128) the prefetched fragments of 32 columns
+// do not fit the registers: then 16
 int scan_dvb(const Dims &d);
 // workgroups of one scan launch: (batch*head rounded up to 8) x dv / scan_dvb; packed batches: those it takes the longest
 // sequence's time to run

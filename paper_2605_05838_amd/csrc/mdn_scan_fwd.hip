@@ -415,16 +415,19 @@ int num_cus() {
 // (batch, head) pairs of a launch; packed batches: as many as sequences of the longest one's length would make up the batch,
 // every sequence counted with the ~4 steps that its states' way in and out takes.  The launch lasts at least the longest sequence's
 // chain of steps, which is shorter with 16 columns per workgroup and with a CU for each of its workgroups, however many short
-// sequences run beside it.  Forward and backward in us by the number of sequences / by this: 29 500 tokens and 16 of 205, 16 heads
-// of 128 930 + 2 327 / 838 + 2 122, 4 heads of twice that 1 644 + 3 326 / 1 372 + 2 866; 16 384 and 32 of 512, 8 heads
-// 507 + 1 250 / 447 + 1 115.
+// sequences run beside it.  Forward and backward in us by the number of sequences / by this, d = 128: 29 500 tokens and 16 of 205,
+// 16 heads 798 + 1 289 / 729 + 1 289, 4 heads 702 + 981 / 501 + 663; 16 384 and 32 of 512, 8 heads 432 + 987 / 335 + 637.
 static long long scan_pairs(const Dims &d) {
     return d.packed ? ((long long)d.nchunks + 4LL * d.B) * d.H / (d.N + 4) : d.BH;
 }
 
+// 16-bit storage: 16 columns as long as their workgroups fit the CUs (they hold one each: a second round costs more than the wider
+// step).  16 / 32 columns in us, forward and forward with kept states and backward: 32 pairs of heads of 128, 1 024 tokens 32.7 / 39.4
+// and 85.7 / 102.0; 40 pairs 51.7 / 41.2 and 133.7 / 115.1, 64 tokens 15.7 / 13.6 and 36.5 / 33.0; heads of 64, 64 pairs, 1 024 tokens
+// 29.6 / 35.3 and 82.0 / 93.2; 72 pairs 41.8 / 38.7 and 112.1 / 103.9.
 int scan_dvb(const Dims &d) {
-    const bool f32 = d.dtype == 1;
-    return (4 * scan_pairs(d) * (d.dv / 32) < 3 * num_cus() || (f32 && d.dk == 128)) ? 16 : 32;
+    if (d.dtype != 1) return scan_pairs(d) * (d.dv / 16) <= num_cus() ? 16 : 32;
+    return 4 * scan_pairs(d) * (d.dv / 32) < 3 * num_cus() || d.dk == 128 ? 16 : 32;
 }
 
 bool scan_one_per_cu(const Dims &d) {
