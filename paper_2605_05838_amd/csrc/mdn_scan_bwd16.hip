@@ -37,13 +37,11 @@ template <int DK, int DV, int DVB, int AHEAD> hipError_t launch_t(const Dims &d,
 }
 // Two workgroups per CU as in the forward (heads of 64), one / two in us, forward with kept states and backward: 64 x 64 tokens of 16
 // heads 98.8 / 88.3, 32 x 64 55.0 / 49.8, 32 x 128 87.0 / 81.2, 32 x 1 024 604 / 603.
-template <int DK, int DV, int DVB> hipError_t pick_ahead(const Dims &d, const ScanBwdArgs &a, hipStream_t s) {
-    if constexpr (2 * sizeof(ScanBwdLds<DK, DV, DVB, 1>) <= 160 * 1024)
-        if (!scan_one_per_cu(d)) return launch_t<DK, DV, DVB, 1>(d, a, s);
-    return launch_t<DK, DV, DVB, 2>(d, a, s);
-}
-template <int DK, int DV> hipError_t pick_dvb(const Dims &d, const ScanBwdArgs &a, hipStream_t s) {
-    return scan_dvb(d) == 16 ? pick_ahead<DK, DV, 16>(d, a, s) : pick_ahead<DK, DV, 32>(d, a, s);
+template <int DK, int DV> hipError_t pick(const Dims &d, const ScanBwdArgs &a, hipStream_t s) {
+    if (scan_dvb(d) == 16) return launch_t<DK, DV, 16, 2>(d, a, s);
+    if constexpr (2 * sizeof(ScanBwdLds<DK, DV, 32, 1>) <= 160 * 1024)
+        if (!scan_one_per_cu(d)) return launch_t<DK, DV, 32, 1>(d, a, s);
+    return launch_t<DK, DV, 32, 2>(d, a, s);
 }
 template <int DK, int DV, int DVB> hipError_t launch_pair_t(const Dims &d, const ScanBwdArgs &b, const ScanFwdArgs &f, hipStream_t s) {
     const dim3 grid(((d.BH + 7) / 8) * 8 * (DV / DVB) * 2), block(kScanThreads);
@@ -51,7 +49,7 @@ template <int DK, int DV, int DVB> hipError_t launch_pair_t(const Dims &d, const
     else hipLaunchKernelGGL((scan_pair16_kernel<DK, DV, DVB, false>), grid, block, 0, s, d, b, f);
     return hipGetLastError();
 }
-template <int DK, int DV> hipError_t pick_pair_dvb(const Dims &d, const ScanBwdArgs &b, const ScanFwdArgs &f, hipStream_t s) {
+template <int DK, int DV> hipError_t pick_pair(const Dims &d, const ScanBwdArgs &b, const ScanFwdArgs &f, hipStream_t s) {
     return scan_dvb(d) == 16 ? launch_pair_t<DK, DV, 16>(d, b, f, s) : launch_pair_t<DK, DV, 32>(d, b, f, s);
 }
 
@@ -61,16 +59,16 @@ bool operands_there(const ScanBwdArgs &a) { return a.coef && a.q && a.k && a.dO 
 
 hipError_t launch_scan_bwd16(const Dims &d, const ScanBwdArgs &a, hipStream_t s) {
     if (!operands_there(a)) return hipErrorInvalidValue;
-    if (d.dk == 64 && d.dv == 64) return pick_dvb<64, 64>(d, a, s);
-    if (d.dk == 128 && d.dv == 128) return pick_dvb<128, 128>(d, a, s);
+    if (d.dk == 64 && d.dv == 64) return pick<64, 64>(d, a, s);
+    if (d.dk == 128 && d.dv == 128) return pick<128, 128>(d, a, s);
     return hipErrorInvalidValue;
 }
 
 hipError_t launch_rebuild_and_scan_bwd(const Dims &d, const RebuildArgs &r, const ScanBwdArgs &b, hipStream_t s) {
     const ScanFwdArgs f = rebuild_args(r);
     if (d.dtype != 0 || !operands_there(b) || !f.vt_saved || !f.states_saved) return hipErrorInvalidValue;
-    if (d.dk == 64 && d.dv == 64) return pick_pair_dvb<64, 64>(d, b, f, s);
-    if (d.dk == 128 && d.dv == 128) return pick_pair_dvb<128, 128>(d, b, f, s);
+    if (d.dk == 64 && d.dv == 64) return pick_pair<64, 64>(d, b, f, s);
+    if (d.dk == 128 && d.dv == 128) return pick_pair<128, 128>(d, b, f, s);
     return hipErrorInvalidValue;
 }
 

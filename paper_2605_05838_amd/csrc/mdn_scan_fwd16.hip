@@ -27,21 +27,20 @@ template <int DK, int DV, int DVB, bool REBUILD, int AHEAD> hipError_t launch_t(
 // of heads of 128): a workgroup's start and the latencies of its chain then lie beside another one's work.  One / two per CU, forward
 // of heads of 64 in us: 64 x 64 tokens of 16 heads 43.4 / 33.9, 32 x 128 36.1 / 30.8, 32 x 1 024 187 / 182, packed 256 sequences of 30
 // tokens of 16 heads 156 / 107.  One chunk ahead costs a single workgroup up to a tenth of a step, so up to one per CU it is two.
-template <int DK, int DV, int DVB, bool REBUILD> hipError_t pick_ahead(const Dims &d, const ScanFwdArgs &a, hipStream_t s) {
-    if constexpr (2 * sizeof(ScanFwdLds<DK, DV, DVB, REBUILD, 1>) <= 160 * 1024)
-        if (!scan_one_per_cu(d)) return launch_t<DK, DV, DVB, REBUILD, 1>(d, a, s);
-    return launch_t<DK, DV, DVB, REBUILD, 2>(d, a, s);
-}
-template <int DK, int DV, bool REBUILD> hipError_t pick_dvb(const Dims &d, const ScanFwdArgs &a, hipStream_t s) {
-    return scan_dvb(d) == 16 ? pick_ahead<DK, DV, 16, REBUILD>(d, a, s) : pick_ahead<DK, DV, 32, REBUILD>(d, a, s);
+// (16 columns have a CU for each workgroup: see scan_dvb.)
+template <int DK, int DV, bool REBUILD> hipError_t pick(const Dims &d, const ScanFwdArgs &a, hipStream_t s) {
+    if (scan_dvb(d) == 16) return launch_t<DK, DV, 16, REBUILD, 2>(d, a, s);
+    if constexpr (2 * sizeof(ScanFwdLds<DK, DV, 32, REBUILD, 1>) <= 160 * 1024)
+        if (!scan_one_per_cu(d)) return launch_t<DK, DV, 32, REBUILD, 1>(d, a, s);
+    return launch_t<DK, DV, 32, REBUILD, 2>(d, a, s);
 }
 
 } // namespace
 
 hipError_t launch_scan_fwd16(const Dims &d, const ScanFwdArgs &a, bool rebuild, hipStream_t s) {
     if (!a.coef || !a.k || (rebuild && (!a.vt_saved || !a.states_saved))) return hipErrorInvalidValue;
-    if (d.dk == 64 && d.dv == 64) return rebuild ? pick_dvb<64, 64, true>(d, a, s) : pick_dvb<64, 64, false>(d, a, s);
-    if (d.dk == 128 && d.dv == 128) return rebuild ? pick_dvb<128, 128, true>(d, a, s) : pick_dvb<128, 128, false>(d, a, s);
+    if (d.dk == 64 && d.dv == 64) return rebuild ? pick<64, 64, true>(d, a, s) : pick<64, 64, false>(d, a, s);
+    if (d.dk == 128 && d.dv == 128) return rebuild ? pick<128, 128, true>(d, a, s) : pick<128, 128, false>(d, a, s);
     return hipErrorInvalidValue;
 }
 

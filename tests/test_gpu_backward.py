@@ -220,8 +220,8 @@ def test_as_few_chunks_as_the_scans_keep_in_flight(T, B, H, d, keep):
 @pytest.mark.parametrize("B,H,d,nseg", [(17, 8, 64, 1), (10, 8, 64, 1), (10, 8, 64, 2), (17, 8, 128, 1), (6, 8, 128, 2)])
 @pytest.mark.parametrize("T", [1, 64, 128, 193, 512])
 def test_more_workgroups_than_cus_give_the_results_of_few(T, B, H, d, nseg):
-    """Launches with two workgroups per CU (the loads one chunk ahead, 16 and 32 columns) against the same sequences in a
-    call that leaves CUs idle (two chunks ahead): every output bit for bit, states and adjoints given and asked for."""
+    """Launches of 32 columns per workgroup, with two workgroups per CU where they fit (the loads one chunk ahead), against the same
+    sequences in a call that leaves CUs idle (16 columns, two chunks ahead): every output bit for bit, states and adjoints given."""
     w = synth.custom(B=B, T=T, H=H, dk=d, dv=d, dtype="bf16", seed=61, with_eta=True, s0_std=0.2, backward=True)
     t = to_dev(w)
     few = {k: None if v is None else v[:1].contiguous() for k, v in t.items()}
