@@ -7,9 +7,9 @@ namespace mdn {
 namespace {
 
 template <int DK, int DV, int DVB, bool WHOLE, int AHEAD>
-__global__ __launch_bounds__(kScanThreads, AHEAD == 1 ? 4 : 2) void scan_bwd16_kernel(Dims d, ScanBwdArgs a) {
+__global__ __launch_bounds__(kScanThreads, AHEAD == 1 ? 4 : 2) void scan_bwd16_kernel(Dims d, ScanBwdArgs a, int first) {
     __shared__ ScanBwdLds<DK, DV, DVB, AHEAD> lds;
-    scan_bwd16<DK, DV, DVB, WHOLE, AHEAD>(d, a, blockIdx.x, lds);
+    scan_bwd16<DK, DV, DVB, WHOLE, AHEAD>(d, a, first + blockIdx.x, lds);
 }
 
 // Both at once: the first half of the workgroups walks the reverse scan, the second half (its steps are shorter) the
@@ -29,11 +29,11 @@ __global__ __launch_bounds__(kScanThreads) void scan_pair16_kernel(Dims d, ScanB
 }
 
 template <int DK, int DV, int DVB, int AHEAD> hipError_t launch_t(const Dims &d, const ScanBwdArgs &a, hipStream_t s) {
-    constexpr int G = DV / DVB;
-    const dim3 grid(((d.BH + 7) / 8) * 8 * G), block(kScanThreads);
-    if (whole_chunks(d)) hipLaunchKernelGGL((scan_bwd16_kernel<DK, DV, DVB, true, AHEAD>), grid, block, 0, s, d, a);
-    else hipLaunchKernelGGL((scan_bwd16_kernel<DK, DV, DVB, false, AHEAD>), grid, block, 0, s, d, a);
-    return hipGetLastError();
+    return launch_in_parts(scan_blocks<DV, DVB>(d), [&](int first, dim3 grid) {
+        const dim3 block(kScanThreads);
+        if (whole_chunks(d)) hipLaunchKernelGGL((scan_bwd16_kernel<DK, DV, DVB, true, AHEAD>), grid, block, 0, s, d, a, first);
+        else hipLaunchKernelGGL((scan_bwd16_kernel<DK, DV, DVB, false, AHEAD>), grid, block, 0, s, d, a, first);
+    });
 }
 // Two workgroups per CU as in the forward (heads of 64), one / two in us, forward with kept states and backward: 64 x 64 tokens of 16
 // heads 98.8 / 88.3, 32 x 64 55.0 / 49.8, 32 x 128 87.0 / 81.2, 32 x 1 024 604 / 603.
@@ -44,7 +44,12 @@ template <int DK, int DV> hipError_t pick(const Dims &d, const ScanBwdArgs &a, h
     return launch_t<DK, DV, 32, 2>(d, a, s);
 }
 template <int DK, int DV, int DVB> hipError_t launch_pair_t(const Dims &d, const ScanBwdArgs &b, const ScanFwdArgs &f, hipStream_t s) {
-    const dim3 grid(((d.BH + 7) / 8) * 8 * (DV / DVB) * 2), block(kScanThreads);
+    const int blocks = scan_blocks<DV, DVB>(d);
+    if (2 * blocks > kScanBlocks) { // (a packed batch with a long sequence among a million: not worth parts of both)
+        const hipError_t e = launch_scan_fwd16(d, f, true, s);
+        return e == hipSuccess ? launch_t<DK, DV, DVB, 2>(d, b, s) : e;
+    }
+    const dim3 grid(2 * blocks), block(kScanThreads);
     if (whole_chunks(d)) hipLaunchKernelGGL((scan_pair16_kernel<DK, DV, DVB, true>), grid, block, 0, s, d, b, f);
     else hipLaunchKernelGGL((scan_pair16_kernel<DK, DV, DVB, false>), grid, block, 0, s, d, b, f);
     return hipGetLastError();

@@ -6,19 +6,18 @@ namespace mdn {
 namespace {
 
 template <int DK, int DV, int DVB, bool REBUILD, bool WHOLE, int AHEAD>
-__global__ __launch_bounds__(kScanThreads, AHEAD == 1 ? 4 : 2) void scan_fwd16_kernel(Dims d, ScanFwdArgs a) {
+__global__ __launch_bounds__(kScanThreads, AHEAD == 1 ? 4 : 2) void scan_fwd16_kernel(Dims d, ScanFwdArgs a, int first) {
     __shared__ ScanFwdLds<DK, DV, DVB, REBUILD, AHEAD> lds;
-    scan_fwd16<DK, DV, DVB, REBUILD, WHOLE, AHEAD>(d, a, blockIdx.x, lds);
+    scan_fwd16<DK, DV, DVB, REBUILD, WHOLE, AHEAD>(d, a, first + blockIdx.x, lds);
 }
 
 template <int DK, int DV, int DVB, bool REBUILD, bool WHOLE, int AHEAD>
 hipError_t launch_w(const Dims &d, const ScanFwdArgs &a, hipStream_t s) {
-    constexpr int G = DV / DVB;
-    const dim3 grid(((d.BH + 7) / 8) * 8 * G), block(kScanThreads);
     static const size_t spread =
         AHEAD == 1 ? 0 : lds_bytes_for_one_workgroup_per_cu(reinterpret_cast<const void *>(&scan_fwd16_kernel<DK, DV, DVB, REBUILD, WHOLE, AHEAD>));
-    hipLaunchKernelGGL((scan_fwd16_kernel<DK, DV, DVB, REBUILD, WHOLE, AHEAD>), grid, block, spread, s, d, a);
-    return hipGetLastError();
+    return launch_in_parts(scan_blocks<DV, DVB>(d), [&](int first, dim3 grid) {
+        hipLaunchKernelGGL((scan_fwd16_kernel<DK, DV, DVB, REBUILD, WHOLE, AHEAD>), grid, dim3(kScanThreads), spread, s, d, a, first);
+    });
 }
 template <int DK, int DV, int DVB, bool REBUILD, int AHEAD> hipError_t launch_t(const Dims &d, const ScanFwdArgs &a, hipStream_t s) {
     return whole_chunks(d) ? launch_w<DK, DV, DVB, REBUILD, true, AHEAD>(d, a, s) : launch_w<DK, DV, DVB, REBUILD, false, AHEAD>(d, a, s);

@@ -10,11 +10,25 @@
 // tokens, 16 heads of 128, in clocks of a step: 6 250, of them 3 400 in the products' phases).
 #pragma once
 #include "mdn_device.h"
+#include "mdn_kernels.h"
 #include "mdn_seq.h"
 
 namespace mdn {
 
 constexpr int kScanThreads = 512;
+
+// Workgroups of a launch at most, a multiple of 8 (see xcd_map): one of 2^32 threads or more is refused, which B * H = 2^24 pairs would
+// reach eight times over.  launch(number of the first workgroup, grid) for every part of `blocks` workgroups.
+constexpr int kScanBlocks = 1 << 22;
+template <typename F> hipError_t launch_in_parts(int blocks, F &&launch) {
+    for (int first = 0; first < blocks; first += kScanBlocks) {
+        launch(first, dim3(blocks - first < kScanBlocks ? blocks - first : kScanBlocks));
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+template <int DV, int DVB> int scan_blocks(const Dims &d) { return (d.BH + 7) / 8 * 8 * (DV / DVB); }
 
 // LDS address of a __shared__ object, as M0 takes it
 __device__ __forceinline__ unsigned lds_addr(const void *p) {

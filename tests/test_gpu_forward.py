@@ -150,3 +150,26 @@ def test_sampled_kernel_timing_counts_every_launch_and_brackets_every_third():
     binding.mdn_chunk_fwd(t["q"], t["k"], t["v"], t["beta"], t["alpha"], t["mu"], scale=w.scale)
     k = binding.profile_end()
     assert k["intra_fwd"][1] == 1 and k["scan_fwd"][1] == 1
+
+
+def test_more_workgroups_than_a_launch_holds():
+    """4 194 313 (batch, head) pairs of one token: 8.4 million workgroups of 512 threads, more than the 2^32 threads that a launch
+    may have.  From zero states v~ = v and o = scale beta (q.k) v: the factor beta (q.k) and o are rounded to 16 bits once each."""
+    B, d = (1 << 22) + 9, 64
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < 240 << 30:
+        pytest.skip("the workspace alone takes 215 GB")
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    q, k, v = (torch.randn((B, 1, 1, d), device="cuda", generator=gen).bfloat16() for _ in range(3))
+    beta, alpha, mu = (torch.sigmoid(torch.randn((B, 1, 1), device="cuda", generator=gen)) for _ in range(3))
+    o = binding.mdn_chunk_fwd(q, k, v, beta, alpha, mu, scale=1.0, output_final_state=False)["o"]
+    torch.cuda.empty_cache()
+    for i in range(0, B, 1 << 19):
+        part = slice(i, i + (1 << 19))
+        qk = (q[part].double() * k[part].double()).sum(-1, keepdim=True)
+        ref = beta[part, ..., None] * qk * v[part].double()
+        terms = beta[part, ..., None] * (q[part].double() * k[part].double()).abs().sum(-1, keepdim=True) * v[part].double()
+        # two roundings to bf16 (eight significant bits: 2^-8 of the value each); 64 additions in fp32 (q.k may cancel)
+        bound = 2 * 2.0 ** -8 * ref.norm(dim=-1) + 64 * 2.0 ** -24 * terms.norm(dim=-1)
+        err = (o[part].double() - ref).norm(dim=-1) / bound
+        assert float(err.max()) <= 1.0, (i, float(err.max()))
