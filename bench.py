@@ -58,6 +58,33 @@ def bytes_per_tokhd(C, dk, dv, es, keep):
     }
 
 
+def kernel_rows(kern, fl, by, tokhd, steps, peak):
+    """Figures per kernel from {name: (ms of the timed launches, timed launches, all launches)}.  A reconstruction that was counted
+    but never timed ran in the reverse scan's launch: that row holds the work of both."""
+    rebuilt = kern.get("rebuild", (0.0, 0, 0))
+    shared = rebuilt[2] > 0 and rebuilt[1] == 0
+    rows = {}
+    for name, (ms, cnt, launched) in kern.items():
+        if not cnt or name not in fl:
+            continue
+        both = shared and name == "scan_bwd"
+        flops = (fl[name] + (fl["rebuild"] if both else 0)) * tokhd
+        nbytes = (by[name] + (by["rebuild"] if both else 0)) * tokhd
+        lps = launched / steps               # launches per step (all of them)
+        per_step = ms / cnt * lps            # average timed launch x launches per step
+        tfl = flops / (per_step * 1e-3) / 1e12
+        gbs = nbytes / (per_step * 1e-3) / 1e9
+        rows[name] = {"ms_per_step": round(per_step, 4), "launches_per_step": round(lps, 2),
+                      "avg_launch_ms": round(ms / cnt, 4), "launches_timed": cnt,
+                      "gflop_per_launch": round(flops / lps / 1e9, 3),
+                      "mib_per_launch": round(nbytes / lps / 2 ** 20, 1),
+                      "tflops": round(tfl, 2), "frac_mfma": round(tfl / peak, 5),
+                      "gbs": round(gbs, 1), "frac_hbm": round(gbs / PEAK_HBM_GBS, 5)}
+        if both:
+            rows[name]["with"] = "rebuild"
+    return rows
+
+
 def read_traffic(path):
     """Measured HBM bytes per launch {kernel: fetch + write}, from the `traffic` lines of a profiles/ summary."""
     out = {}
@@ -373,19 +400,7 @@ def main():
     fl = flops_per_tokhd(w.C, w.dk, w.dv)
     by = bytes_per_tokhd(w.C, w.dk, w.dv, 2 if w.dtype == "bf16" else 4, keep)
     peak = PEAK_BF16_TFLOPS if w.dtype == "bf16" else PEAK_F32_TFLOPS
-    kernels = {}
-    for name, (ms, cnt, launched) in kern.items():
-        if cnt and name in fl:
-            lps = launched / args.steps          # launches per step (all of them)
-            per_step = ms / cnt * lps            # average bracketed launch x launches per step
-            tfl = fl[name] * tokhd / (per_step * 1e-3) / 1e12
-            gbs = by[name] * tokhd / (per_step * 1e-3) / 1e9
-            kernels[name] = {"ms_per_step": round(per_step, 4), "launches_per_step": round(lps, 2),
-                             "avg_launch_ms": round(ms / cnt, 4), "launches_timed": cnt,
-                             "gflop_per_launch": round(fl[name] * tokhd / lps / 1e9, 3),
-                             "mib_per_launch": round(by[name] * tokhd / lps / 2 ** 20, 1),
-                             "tflops": round(tfl, 2), "frac_mfma": round(tfl / peak, 5),
-                             "gbs": round(gbs, 1), "frac_hbm": round(gbs / PEAK_HBM_GBS, 5)}
+    kernels = kernel_rows(kern, fl, by, tokhd, args.steps, peak)
     roofline = roofline_hbm = None
     if kernels:
         dom = max(kernels, key=lambda k: kernels[k]["ms_per_step"])
