@@ -38,8 +38,8 @@
  *     ordered after what the stream already holds and is complete when the stream reaches the
  *     end of the call; no call synchronises.  When the serial scan would leave at least half
  *     of the GPU idle (few batch*head pairs, many chunks) mdn_chunk_bwd splits
- *     the sequence into segments and runs the chunk-parallel kernel of one segment beside the
- *     scan of its neighbour on a second stream that the library creates once per device
+ *     the sequence into segments and runs the chunk-parallel kernel of one segment (and, where the states
+ *     must be reconstructed, that) beside the scan of its neighbour on a second stream that the library creates once per device
  *     (default priority) and joins back into `stream` with events, also when a launch fails on the
  *     way; mdn_chunk_fwd does so when mdn_set_segments() asks for it.
  *   - Return value: MDN_OK (0) or a negative MDN_ERR_* code; nothing is launched when an
@@ -93,8 +93,8 @@ int mdn_workspace_bytes(const mdn_shape *shape, int which, size_t *bytes_out);
 int mdn_saved_states_bytes(const mdn_shape *shape, size_t *bytes_out);
 
 /* Bytes of the optional `operands_saved` buffer: the chunk-local operands of the reverse pass
- * (transposed key and query tiles, masked products and triangular inverse, Sec. 3.1 "Chunkwise
- * Algorithm") that a training forward can keep so that the backward does not recompute them. */
+ * (coefficients, masked products and triangular inverse, Sec. 3.1 "Chunkwise Algorithm"; with 32-bit storage also
+ * transposed key and query tiles) that a training forward can keep so that the backward does not recompute them. */
 int mdn_saved_operands_bytes(const mdn_shape *shape, size_t *bytes_out);
 
 /*
@@ -263,7 +263,8 @@ enum {
     MDN_KERNEL_INTRA_FWD = 0, /* chunk-local coefficients, masked products, triangular solve
                                  (and the reverse pass's operands when operands_saved is given) */
     MDN_KERNEL_SCAN_FWD = 1,  /* sequential inter-chunk propagation of S and M, outputs */
-    MDN_KERNEL_INTRA_BWD = 2, /* same as 0 in the operand layouts of the reverse pass */
+    MDN_KERNEL_INTRA_BWD = 2, /* same as 0 for a backward whose forward kept no operands (32-bit storage: in the layouts of
+                                 the reverse pass) */
     MDN_KERNEL_REBUILD = 3,   /* chunk-start states reconstructed from V~; where that shares a launch with the
                                  reverse scan it is counted here and timed there */
     MDN_KERNEL_SCAN_BWD = 4,  /* reverse inter-chunk scan of dS, dM */

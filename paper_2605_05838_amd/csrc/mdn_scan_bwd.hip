@@ -145,9 +145,7 @@ __global__ __launch_bounds__(kThreads) void scan_bwd_kernel(Dims d, ScanBwdArgs 
         const unsigned itn = !WHOLE && nn == ragged ? itok : iH;
         fetch_part<T, DK, DV, DVB, 0>(nxt, d, a, sq, nn, dv0, itn);
 
-        // adjoints of this chunk's END states: operand copy to LDS, storage copy to HBM.  (The stores cost this
-        // kernel ~45 us whoever issues them and whenever: in one burst here, 208 us; spread over the step in 8
-        // portions, 213 us.  All values are narrowed first, so that the stores leave back to back.)
+        // adjoints of this chunk's END states: operand copy to LDS, copy to HBM in one burst
         {
             typename Raw4<T>::type sv[2 * ND][MV];
             T *ds = static_cast<T *>(a.dstates) + blk * (2 * DK * DV);

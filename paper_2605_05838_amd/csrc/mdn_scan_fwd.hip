@@ -172,10 +172,9 @@ __global__ __launch_bounds__(kThreads) void scan_fwd_kernel(Dims d, ScanFwdArgs 
     if (!REBUILD) publish_state<T, DK, MV>(sSt, accS, accM);
     __syncthreads();
 
-    // The chunk-start states leave for HBM out of a storage-type copy in registers.  Forward scan: narrowed ONCE at
-    // the end of the step that produced them, for the LDS copy and for HBM alike (one burst; the stores cost this
-    // kernel ~75 us whichever wave issues them and whenever).  Reconstruction, which does little else than store:
-    // in 8 portions spread over the step (109 against 127 us in one burst).
+    // The chunk-start states leave for HBM out of a copy in registers.  Forward scan: made at the end of the step that produced
+    // them, for the LDS copy and for HBM alike, stored in one burst.  Reconstruction, which does little else than store: in 8
+    // portions spread over the step.
     constexpr int NS = 2 * ND; // vector stores per lane: S and M, ND rows, MV * 4 consecutive columns each
     typename Raw4<T>::type sv[NS][MV];
     // sv: the states in storage form

@@ -230,6 +230,8 @@ __device__ __forceinline__ void scan_fwd16(const Dims &d, const ScanFwdArgs &a, 
             load_cols_raw<MV>(lds.rV[slot] + i * DVB + kg * (4 * MV), u);
         };
         first_reads();
+        // (one copy of a step: two or three, for q registers two chunks ahead, took 92.0 instead of 89.2 us for 16 x 512 tokens of 16
+        //  heads of 128 and 14.4 instead of 13.9 for 1 x 128)
         for (int n = n0; n < n1; ++n) {
             f32x4 o[MV];
             bf16x4 vb[MV]; // V~ in storage form
