@@ -791,9 +791,9 @@ int packed_run(const Dims &d, const int32_t *cu, int32_t n_seq, PackedForm f, co
 // those gates are zero and are set so.  Pieces hold up to 512 tokens, fewer (down to 128) where the scans of longer ones
 // would leave CUs idle; a longer sequence is a piece of its own.  Merging costs 2 launches forward and 3 backward, so it
 // is done where it saves at least an eighth of the chunks.  Forward + backward in us, one piece per sequence / merged (16 heads of 128, bf16):
-//   32 768 tokens:   512 sequences  2 470 / 1 772;   1 024   3 610 / 1 683;   4 096   12 359 / 1 682
-//    4 096 tokens:   128 sequences    502 /   260;     512   1 558 /   248
-//    1 024 tokens:    64 sequences    208 /   106
+//   32 768 tokens:   512 sequences  2 419 / 1 542;   1 024   3 588 / 1 540;   4 096   12 214 / 1 571
+//    4 096 tokens:   128 sequences    454 /   219;     512   1 550 /   210
+//    1 024 tokens:    64 sequences    214 /    93
 struct Merged { std::vector<int32_t> cu, starts; bool used = false; }; // piece offsets; starts inside the pieces
 
 int merge_short(const Dims &d, const int32_t *cu, int32_t n_seq, Merged *m) {
