@@ -17,8 +17,9 @@ namespace mdn {
 
 constexpr int kScanThreads = 512;
 
-// Workgroups of a launch at most, a multiple of 8 (see xcd_map): one of 2^32 threads or more is refused, which B * H = 2^24 pairs would
-// reach eight times over.  launch(number of the first workgroup, grid) for every part of `blocks` workgroups.
+// Workgroups of a launch at most, a multiple of 8 (see xcd_map).  A launch of 2^32 threads or more reports no error and leaves
+// workgroups out, and B * H = 2^24 pairs would reach that eight times over.  launch(number of the first workgroup, grid) for every part
+// of `blocks` workgroups.
 constexpr int kScanBlocks = 1 << 22;
 template <typename F> hipError_t launch_in_parts(int blocks, F &&launch) {
     for (int first = 0; first < blocks; first += kScanBlocks) {
