@@ -34,10 +34,10 @@ __global__ __launch_bounds__(256) void copy_gates_kernel(const float *a, const f
     if (blockIdx.x == 0 && threadIdx.x < n % 4) dst[n / 4 * 4 + threadIdx.x] = src[n / 4 * 4 + threadIdx.x];
 }
 
-// chunks of C < 64 tokens as 64-token tiles: blockIdx.y = tensor, blockIdx.x = (b, chunk, i, h) row of the padded tensor
-template <bool EXPAND> __global__ __launch_bounds__(64) void chunk_copy_kernel(ChunkCopy c) {
+// chunks of C < 64 tokens as 64-token tiles: blockIdx.y = tensor, first + blockIdx.x = (b, chunk, i, h) row of the padded tensor
+template <bool EXPAND> __global__ __launch_bounds__(64) void chunk_copy_kernel(ChunkCopy c, int first) {
     const TileTensor t = c.t[blockIdx.y];
-    const int row = blockIdx.x, h = row % c.H, i = (row / c.H) % 64, nc = (row / (c.H * 64)) % c.NC, b = row / (c.H * 64 * c.NC);
+    const int row = first + (int)blockIdx.x, h = row % c.H, i = (row / c.H) % 64, nc = (row / (c.H * 64)) % c.NC, b = row / (c.H * 64 * c.NC);
     const int words = t.row_bytes / 4, tok = nc * c.C + i;
     const bool real = i < c.C && tok < c.T;
     uint32_t *pad = reinterpret_cast<uint32_t *>(static_cast<char *>(t.padded) + (size_t)row * t.row_bytes);
@@ -80,12 +80,16 @@ hipError_t launch_chunk_copy(const ChunkCopy &c, bool expand, hipStream_t s) {
         if (!c.t[k].full || !c.t[k].padded || c.t[k].row_bytes < 4 || c.t[k].row_bytes % 4) return hipErrorInvalidValue;
     const long long rows = (long long)c.B * c.NC * 64 * c.H;
     if (rows > 0x7fffffffLL) return hipErrorInvalidValue;
-    dim3 grid((unsigned)rows, c.n), block(64);
-    if (expand)
-        hipLaunchKernelGGL(chunk_copy_kernel<true>, grid, block, 0, s, c);
-    else
-        hipLaunchKernelGGL(chunk_copy_kernel<false>, grid, block, 0, s, c);
-    return hipGetLastError();
+    // (a launch of 2^32 threads or more reports no error and leaves workgroups out)
+    constexpr long long kMost = 1 << 25;
+    for (long long first = 0; first < rows; first += kMost) {
+        const dim3 grid((unsigned)(rows - first < kMost ? rows - first : kMost), c.n), block(64);
+        if (expand) hipLaunchKernelGGL(chunk_copy_kernel<true>, grid, block, 0, s, c, (int)first);
+        else hipLaunchKernelGGL(chunk_copy_kernel<false>, grid, block, 0, s, c, (int)first);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 } // namespace mdn

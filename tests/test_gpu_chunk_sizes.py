@@ -77,3 +77,21 @@ def test_the_allocation_free_forward_takes_the_chunk_size_too():
     torch.cuda.synchronize()
     for name in ("o", "S", "M"):
         assert torch.equal(out[name], ref[name]), name
+
+
+def test_more_padded_rows_than_a_launch_holds():
+    """Chunks of 16 tokens of 16.8 million token-heads become 67.1 million rows of 64 threads each, 2^32 threads and more: every
+    sequence, the last one above all, comes out as with chunks of 64."""
+    B, T, H, d = 32, 32768 + 16, 16, 64
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < 120 << 30:
+        pytest.skip("needs 90 GB")
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    unit = lambda: torch.nn.functional.normalize(torch.randn((B, T, H, d), device="cuda", generator=gen), dim=-1).bfloat16()
+    gate = lambda shift: torch.sigmoid(torch.randn((B, T, H), device="cuda", generator=gen) + shift)
+    x = (unit(), unit(), torch.randn((B, T, H, d), device="cuda", generator=gen).bfloat16(), gate(0), gate(3), gate(2))
+    ref, got = (binding.mdn_chunk_fwd(*x, scale=d ** -0.5, chunk_size=c)["o"] for c in (64, 16))
+    for b in range(B):
+        for part in (slice(0, T // 2), slice(T // 2, T)):
+            e = (got[b, part].float() - ref[b, part].float()).norm() / ref[b, part].float().norm()
+            assert float(e) <= 2e-2, (b, part, float(e))
