@@ -302,73 +302,99 @@ __device__ __forceinline__ void coef_scan_reverse_part2(int ldg, int w, const Re
     }
 }
 
-// ---- T = (I + A)^{-1}, A strictly lower triangular 64x64 fp32 in LDS (row-major, stride lda, zeros on
-//      and above the diagonal), by 16x16 blocks.  Called by 4 waves (w = 0..3); wave w owns block row w.
-//      On return sA holds T (row-major).  sTT is scratch of 64*lda floats.
-//        T_ii = (I + A_ii)^{-1}                              (forward substitution, lane = column)
-//        T_ij = -T_ii * sum_{k=j..i-1} A_ik T_kj   (i > j)    (fp32 MFMA; levels i - j = 1, 2, 3)
-//      The accumulator of the inner sum is, lane for lane, the B fragment of the product with T_ii.
+// ---- T = (I + A)^{-1}, A strictly lower triangular 64x64 fp32 in LDS (row-major, stride lda, zeros on and above the diagonal).
+//      Called by 4 waves (w = 0..3).  On return (behind a barrier of the caller's) sA holds T (row-major).  sTT is scratch of 64*lda
+//      floats, T^T.  Diagonal blocks of 8 by forward substitution, then by doubling: with T1, T2 the inverses of two neighbouring
+//      diagonal blocks and L the block of A between them, the inverse of both has -T2 L T1 in L's place.
+//      8 -> 16: inside a wave, 16 -> 32 and 32 -> 64 in 16x16 blocks over the waves; fp32 MFMA.  (The accumulator of the inner product is,
+//      lane for lane, the B fragment of the outer one.)  What bounds it is the chain of dependent products and LDS
+//      round trips: 3 600 clocks of a chunk's 12 000 with a CU to itself (13 chunks of 16 heads of 128); with diagonal blocks of 16 by
+//      substitution and one block diagonal of T after the other, each behind a barrier, 4 900 of 15 500.
 __device__ __forceinline__ void tri_inverse_blocked(float *sA, float *sTT, int lda, int w) {
     typedef Op<float> O;
     const int lane = lane_id(), r = lane & 15, kg = lane >> 4;
-    const int b0 = w * 16;
-    // diagonal block: lanes 0..15, lane r solves column r of block w; t[k] = T_ww[k][r]
-    if (lane < 16) {
-        float t[16];
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    // fragments of 16x16 blocks: A operands row r, k = 4 kg ..; B operands column r, k = 4 kg ..
+    auto a_of = [&](int i, int k) { return *reinterpret_cast<const f32x4 *>(&sA[(i * 16 + r) * lda + k * 16 + 4 * kg]); };
+    auto tb_of = [&](int k, int j) { return *reinterpret_cast<const f32x4 *>(&sTT[(j * 16 + r) * lda + k * 16 + 4 * kg]); };
+    auto ta_of = [&](int i, int k) {
+        f32x4 v;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) t[i] = 0.f;
+        for (int s = 0; s < 4; ++s) v[s] = sTT[(k * 16 + 4 * kg + s) * lda + i * 16 + r];
+        return v;
+    };
+    auto put_tt = [&](int i, int j, f32x4 v) { *reinterpret_cast<f32x4 *>(&sTT[(j * 16 + r) * lda + i * 16 + 4 * kg]) = v; };
+    auto put_t = [&](int i, int j, f32x4 v) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            float acc = (i == r) ? 1.f : 0.f;
+        for (int x = 0; x < 4; ++x) sA[(i * 16 + 4 * kg + x) * lda + j * 16 + r] = v[x];
+    };
+    auto keep = [](f32x4 &v) { asm volatile("" : "+v"(v)); }; // (all four elements stay in registers of their own: no read waits for another's)
+    // what the later levels want of A (waves 0..3): f0 A_20 A_10 A_21 A_32, f1 A_30 A_20 A_31 A_21, f2 A_21 A_21, f3 A_31
+    f32x4 f0 = a_of((0xE6 >> (2 * w)) & 3, (0x90 >> (2 * w)) & 3), f1 = a_of((0xBB >> (2 * w)) & 3, w >> 1), f2 = zero, f3 = zero;
+    if (w < 2) f2 = a_of(2, 1);
+    if (w == 0) f3 = a_of(3, 1);
+    // block w: lane r has column r % 8 of its half r / 8 (every lane group the same)
+    const f32x4 aw = a_of(w, w);
+    f32x4 tii;
+    {
+        const int h = r >> 3, c = r & 7;
+        const float *blk = &sA[(w * 16 + h * 8) * lda + w * 16 + h * 8];
+        f32x4 lo[8], hi[8];
 #pragma unroll
-            for (int k4 = 0; k4 < (i + 3) / 4; ++k4) {
-                const f32x4 av = *reinterpret_cast<const f32x4 *>(&sA[(b0 + i) * lda + b0 + 4 * k4]);
-                acc -= av[0] * t[4 * k4 + 0];
-                acc -= av[1] * t[4 * k4 + 1];
-                acc -= av[2] * t[4 * k4 + 2];
-                acc -= av[3] * t[4 * k4 + 3];
-            }
-            t[i] = acc;
+        for (int i = 1; i < 8; ++i) {
+            lo[i] = *reinterpret_cast<const f32x4 *>(blk + i * lda);
+            if (i > 4) hi[i] = *reinterpret_cast<const f32x4 *>(blk + i * lda + 4);
         }
-        // T^T storage: sTT[col * lda + row]
 #pragma unroll
-        for (int i4 = 0; i4 < 4; ++i4)
-            *reinterpret_cast<f32x4 *>(&sTT[(b0 + r) * lda + b0 + 4 * i4]) =
-                f32x4{t[4 * i4], t[4 * i4 + 1], t[4 * i4 + 2], t[4 * i4 + 3]};
+        for (int i = 1; i < 8; ++i) {
+            keep(lo[i]);
+            if (i > 4) keep(hi[i]);
+        }
+        float t[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) t[i] = i == c ? 1.f : 0.f;
+#pragma unroll
+        for (int k = 0; k < 7; ++k)
+#pragma unroll
+            for (int i = k + 1; i < 8; ++i) t[i] -= (k < 4 ? lo[i][k & 3] : hi[i][k & 3]) * t[k];
+        const bool mine = (kg >> 1) == h, up = kg & 1;
+        f32x4 tb;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) tb[s] = mine ? (up ? t[4 + s] : t[s]) : 0.f;
+        put_tt(w, w, tb);
+        const f32x4 x = O::mma(r >= 8 && kg < 2 ? aw : zero, tb, zero);
+        tb -= O::mma(ta_of(w, w), x, zero);
+        put_tt(w, w, tb);
+        put_t(w, w, tb); // (in the place of block w of A, which nobody else reads)
+        tii = ta_of(w, w);
     }
     __syncthreads();
-    // own diagonal block as A fragments: row r, k = 4*kg + s  ->  sTT[(b0 + k) * lda + b0 + r]
-    f32x4 tii;
-#pragma unroll
-    for (int s = 0; s < 4; ++s) tii[s] = sTT[(b0 + 4 * kg + s) * lda + b0 + r];
-    // write the diagonal block of T row-major (replacing A_ww, which is no longer needed)
-#pragma unroll
-    for (int s = 0; s < 4; ++s) sA[(b0 + r) * lda + b0 + 4 * kg + s] = tii[s];
-
-    for (int dlt = 1; dlt < 4; ++dlt) {
-        const int jb = w - dlt; // block column handled at this level
-        if (jb >= 0) {
-            f32x4 x = {0.f, 0.f, 0.f, 0.f};
-            for (int kb = jb; kb < w; ++kb) {
-                // A_{w,kb} (row-major, k contiguous) times T_{kb,jb} (from sTT: column-major, k contiguous)
-                const f32x4 fa = *reinterpret_cast<const f32x4 *>(&sA[(b0 + r) * lda + kb * 16 + 4 * kg]);
-                const f32x4 fb = *reinterpret_cast<const f32x4 *>(&sTT[(jb * 16 + r) * lda + kb * 16 + 4 * kg]);
-                x = O::mma(fa, fb, x);
-            }
-            f32x4 t = {0.f, 0.f, 0.f, 0.f};
-            t = O::mma(tii, x, t); // x is, lane for lane, the B fragment (k = 4*kg + s, n = r)
-            // t[xx] = -T_{w,jb}[row 4*kg + xx][col r]
-#pragma unroll
-            for (int xx = 0; xx < 4; ++xx) {
-                sTT[(jb * 16 + r) * lda + b0 + 4 * kg + xx] = -t[xx];
-            }
+    // 16 -> 32: T_10 (wave 1) and T_32 (wave 3); and what the next level's inner products need of the diagonal blocks
+    f32x4 y0, y1 = zero;
+    {
+        const int k = (0x90 >> (2 * w)) & 3; // 0 0 1 2
+        const f32x4 tk = tb_of(k, k), t1 = w == 3 ? tb_of(1, 1) : tk;
+        const f32x4 x = O::mma(f0, tk, zero); // A_20 T_00, A_10 T_00, A_21 T_11, A_32 T_22
+        y1 = O::mma(f1, t1, zero);            // A_30 T_00, A_20 T_00, A_31 T_11, A_21 T_11
+        y0 = x;
+        if (w & 1) {
+            const f32x4 t = -O::mma(tii, x, zero);
+            put_tt(w, w - 1, t);
+            put_t(w, w - 1, t); // (nobody else reads this block of A any more)
+            y0 = y1;
         }
-        __syncthreads();
     }
-    // T_{w,jb} row-major into sA for the off-diagonal blocks of this block row
-    for (int jb = 0; jb < w; ++jb) {
-#pragma unroll
-        for (int s = 0; s < 4; ++s) sA[(b0 + 4 * kg + s) * lda + jb * 16 + r] = sTT[(jb * 16 + r) * lda + b0 + 4 * kg + s];
+    __syncthreads();
+    // 32 -> 64: wave 0 T_30, wave 1 T_20, wave 2 T_31, wave 3 T_21
+    f32x4 t;
+    {
+        const int i = w & 1 ? 2 : 3;
+        const f32x4 ti2 = ta_of(i, 2), t33 = w & 1 ? zero : ta_of(3, 3), t10 = w < 2 ? tb_of(1, 0) : zero;
+        if (w < 2) y0 = O::mma(f2, t10, y0);
+        if (w == 0) y1 = O::mma(f3, t10, y1);
+        t = O::mma(ti2, y0, zero);
+        if (!(w & 1)) t = O::mma(t33, y1, t);
+        put_t(i, w >> 1, -t); // (every block of A has been read)
     }
 }
 

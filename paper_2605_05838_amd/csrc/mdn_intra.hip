@@ -16,6 +16,10 @@
 // uses Y^T dV~ = K^T (a . T^T dV~).  That trades three 64 x d products and their 1.3 KB per token of HBM
 // round trips for one 64 x 64 x dv product inside the scan.
 //
+// What bounds it: up to a workgroup per CU the chain of one chunk (5.1 us, of which 1.8 until the gates and tiles have arrived; 13 chunks of
+// 16 heads of 128, 7.1 -> 5.6 us for the launch); with more, instruction issue and HBM together (8 x 2 048 tokens of 8 heads 30.8 ->
+// 25.5 us, 107 MB: 4.2 TB/s where a large copy reaches 4.8).
+//
 // One workgroup (4 waves) per (chunk, batch*head).  16-bit storage: T, Bm and the coefficients, row by row, for both scans.
 // 32-bit storage: forward mode writes T, Bm and K^T; backward mode the transposed operands of the reverse scan (Bm^T, T^T, K^T,
 // Q^T); a training forward writes both sets at once, so that the backward need not recompute them; all of them in the blocked
@@ -29,8 +33,9 @@ namespace mdn {
 
 namespace {
 
-constexpr int LDA = 68; // row stride (floats) of the fp32 A / T matrix in LDS
-constexpr int LDG = 65; // row stride (floats) of Gamma in LDS
+// Row strides (floats) of the fp32 A / T matrix and of Gamma in LDS: 16-byte reads of 16 rows take 4.4 clocks of the LDS with 288-byte
+// rows, 8 with 272.
+constexpr int LDA = 72, LDG = 72;
 
 // LDS [R][ld] (first 64 columns) -> global, kblk layout of an [R][64] operand.  Consecutive lanes write
 // consecutive 16-byte pieces of the destination (the pieces of one row's contraction step, then the next
@@ -49,16 +54,17 @@ __device__ __forceinline__ void store_tile_64cols(T *dst, const T *src, int ld, 
 // reverse pass's operands instead of recomputing them)
 // WHOLE: see whole_chunks.
 template <typename T, int DK, int DV, int MODE, bool WHOLE>
-__global__ __launch_bounds__(kThreads) void intra_kernel(Dims d, IntraArgs a) {
+__global__ __launch_bounds__(kThreads, sizeof(T) == 2 ? 3 : 1) void intra_kernel(Dims d, IntraArgs a) {
     constexpr bool FWD = MODE != 1, BWD = MODE != 0, HALF = sizeof(T) == 2;
     static_assert(!HALF || MODE == 0, "16-bit storage: one set of operands");
     typedef Op<T> O;
     constexpr int E = O::EPL;
-    constexpr int LDN = DK + O::PAD; // natural tiles
+    constexpr int LDN = HALF ? DK : DK + O::PAD; // natural tiles (16-bit storage: pieces permuted, see token_tile_row_frag)
     constexpr int LDT = 64 + O::PAD; // transposed tiles (32-bit storage)
     constexpr int DX = BWD ? DK : 0; // second transposed tile: Q^T (reverse-pass operands only)
     constexpr int REG_NAT = 2 * 64 * LDN, REG_TR = HALF ? 0 : (DK + DX) * LDT;
-    constexpr int REGION = REG_NAT > REG_TR ? REG_NAT : REG_TR;
+    constexpr int REG_A = 64 * LDA * 4 / (int)sizeof(T), REG_KQ = REG_NAT > REG_TR ? REG_NAT : REG_TR;
+    constexpr int REGION = REG_KQ > REG_A ? REG_KQ : REG_A;
     constexpr int NVK = 64 * DK / E / kThreads, NVX = BWD ? NVK : 1; // 16-byte vectors per thread
 
     __shared__ __align__(16) T sR[REGION];
@@ -66,7 +72,6 @@ __global__ __launch_bounds__(kThreads) void intra_kernel(Dims d, IntraArgs a) {
     __shared__ __align__(16) float sG[64 * LDA];
     // A, then T: in the space of the K, Q tiles, once every wave is done with those (70 -> 53 KB of LDS for 16-bit
     // storage at d = 128: three workgroups per CU instead of two)
-    static_assert(sizeof(T) * REGION >= sizeof(float) * 64 * LDA, "A does not fit the tile region");
     float *sA = reinterpret_cast<float *>(sR);
     float *sTT = sG;
     __shared__ __align__(16) float s_al[64], s_be[64], s_et[64], s_a[64], s_b[64];
@@ -160,53 +165,82 @@ __global__ __launch_bounds__(kThreads) void intra_kernel(Dims d, IntraArgs a) {
         constexpr int CPR = DK / E;
 #pragma unroll
         for (int u = 0; u < NVK; ++u) {
-            const int c = tid + u * kThreads, row = c / CPR, cc = c % CPR;
+            const int c = tid + u * kThreads, row = c / CPR, cc = HALF ? (c % CPR) ^ (row & (CPR < 16 ? CPR - 1 : 15)) : c % CPR;
             *reinterpret_cast<typename O::Frag *>(sK + row * LDN + cc * E) = rk[u];
             *reinterpret_cast<typename O::Frag *>(sQ + row * LDN + cc * E) = rq[u];
         }
     }
     __syncthreads();
 
-    // ---- masked intra-chunk products: wave w owns rows i0..i0+15.
-    //      The Q K^T product is formed in the orientation whose accumulator lanes hold 4 consecutive
-    //      entries along the contraction index of the consumer (j for Bm, i for Bm^T).
+    // ---- masked intra-chunk products, 16 x 16 tiles (rows i of tile nt, columns j of tile jt).  The ten on or below the diagonal
+    //      are formed, three by a wave, without branches; the six above it are zeroed, two by a wave (some twice):
+    //        wave 0: (1,0) (2,0) (3,0), zeros (0,1) (0,2)    wave 2: (2,2) (3,2) (0,0), zeros (1,3) (2,3)
+    //        wave 1: (1,1) (2,1) (3,1), zeros (0,3) (1,2)    wave 3: (3,3) three times, zeros (1,3) (2,3)
+    //      The products are formed in the orientation whose accumulator lanes hold 4 consecutive entries along the contraction
+    //      index of the consumer (j for Bm and A, i for Bm^T).  What a masked value needs of Gamma is read by every lane: inside the
+    //      selection, each of 32 reads stood in a branch of its own (clocks of a chunk with a CU to itself, this and A's mask: 3 200 +
+    //      1 900, now 2 100 + 1 000).
     const int r = lane & 15, kq = lane >> 4, i0 = w * 16;
+    const int wu = __builtin_amdgcn_readfirstlane(w);
+    auto row_frag = [&](const T *tile, int row, int st) -> typename O::Frag {
+        if constexpr (HALF) return token_tile_row_frag<DK>(tile, row, st, kq);
+        else return O::load(tile + row * LDN + st * O::KSTEP + kq * E);
+    };
+    constexpr int KS = DK / O::KSTEP;
+    auto pick = [&](int table, int u) { return (table >> (8 * u + 2 * wu)) & 3; };
+    auto nt_of = [&](int u) { return pick(0xCFFAE5, u); }; // 1 1 2 3 | 2 2 3 3 | 3 3 0 3
+    auto jt_of = [&](int u) { return pick(0xC4E4E4, u); }; // 0 1 2 3 | 0 1 2 3 | 0 1 0 3
+    auto nz_of = [&](int u) { return pick(0xA450, u); };   // 0 0 1 1 | 0 1 2 2
+    auto jz_of = [&](int u) { return pick(0xFAFD, u); };   // 1 3 3 3 | 2 2 3 3
     {
-        f32x4 kk[4], qk[4];
+        f32x4 kk[3], qk[3]; // element x of product u: k_i . k_j, q_i . k_j with i = nt*16 + r, j = jt*16 + kq*4 + x
         zero_acc(kk);
         zero_acc(qk);
-        mma_rows<T, 4, DK>(kk, sK + i0 * LDN, LDN, sK, LDN);
+#pragma unroll
+        for (int st = 0; st < KS; ++st)
+#pragma unroll
+            for (int u = 0; u < 3; ++u) {
+                const typename O::Frag fa = row_frag(sK, jt_of(u) * 16 + r, st);
+                kk[u] = O::mma(fa, row_frag(sK, nt_of(u) * 16 + r, st), kk[u]);
+                if (FWD) qk[u] = O::mma(fa, row_frag(sQ, nt_of(u) * 16 + r, st), qk[u]);
+            }
         if (BWD) {
-            // qk[nt][x] = q_i . k_j, i = i0 + kq*4 + x, j = nt*16 + r  ->  Bm^T row j, k = i
-            mma_rows<T, 4, DK>(qk, sQ + i0 * LDN, LDN, sK, LDN);
+            // qt[nt][x] = q_i . k_j, i = i0 + kq*4 + x, j = nt*16 + r  ->  Bm^T row j, k = i
+            f32x4 qt[4];
+            zero_acc(qt);
+            mma_rows<T, 4, DK>(qt, sQ + i0 * LDN, LDN, sK, LDN);
             T *out = static_cast<T *>(a.BmT) + blk * 4096;
 #pragma unroll
             for (int nt = 0; nt < 4; ++nt) {
                 const int j = nt * 16 + r;
+                const float et = s_et[j];
                 f32x4 v;
 #pragma unroll
                 for (int x = 0; x < 4; ++x) {
                     const int i = i0 + kq * 4 + x;
-                    v[x] = (j <= i) ? d.scale * s_et[j] * sG[i * LDG + j] * qk[nt][x] : 0.f;
+                    const float full = d.scale * et * sG[i * LDG + j] * qt[nt][x];
+                    v[x] = (j <= i) ? full : 0.f;
                 }
                 store4(out + kblk<T>(64, j, i0 + kq * 4), v);
             }
         }
         if (FWD) {
-            // qk[nt][x] = k_j . q_i, j = i0 + kq*4 + x, i = nt*16 + r  ->  Bm row i, k = j
-            zero_acc(qk);
-            mma_rows<T, 4, DK>(qk, sK + i0 * LDN, LDN, sQ, LDN);
-            T *out = static_cast<T *>(a.Bm) + blk * 4096;
+            T *out = static_cast<T *>(a.Bm) + blk * 4096; // Bm row i, k = j
+            auto put = [&](int i, int j0, f32x4 v) { store4(at32(out, HALF ? (unsigned)(i * 64 + j0) : (unsigned)kblk<T>(64, i, j0)), v); };
 #pragma unroll
-            for (int nt = 0; nt < 4; ++nt) {
-                const int i = nt * 16 + r, j0 = i0 + kq * 4;
-                const float *gr = &sG[i * LDG + j0];
-                const f32x4 et = *reinterpret_cast<const f32x4 *>(&s_et[j0]);
+            for (int u = 0; u < 3; ++u) {
+                const int i = nt_of(u) * 16 + r, j0 = jt_of(u) * 16 + kq * 4;
+                const f32x4 g = *reinterpret_cast<const f32x4 *>(&sG[i * LDG + j0]), et = *reinterpret_cast<const f32x4 *>(&s_et[j0]);
                 f32x4 v;
 #pragma unroll
-                for (int x = 0; x < 4; ++x) v[x] = (j0 + x <= i) ? d.scale * et[x] * gr[x] * qk[nt][x] : 0.f;
-                store4(out + (HALF ? (size_t)(i * 64 + i0 + kq * 4) : kblk<T>(64, i, i0 + kq * 4)), v);
+                for (int x = 0; x < 4; ++x) {
+                    const float full = d.scale * et[x] * g[x] * qk[u][x];
+                    v[x] = (j0 + x <= i) ? full : 0.f;
+                }
+                put(i, j0, v);
             }
+#pragma unroll
+            for (int u = 0; u < 2; ++u) put(nz_of(u) * 16 + r, jz_of(u) * 16 + kq * 4, f32x4{0.f, 0.f, 0.f, 0.f});
         }
         if constexpr (!HALF) {
             // ---- 32-bit storage: the transposed tiles take the space of the K, Q tiles (dst[d][row] = src[row][d]),
@@ -231,27 +265,28 @@ __global__ __launch_bounds__(kThreads) void intra_kernel(Dims d, IntraArgs a) {
             if (BWD) store_tile_64cols<T>(static_cast<T *>(a.QT) + blk * (DK * 64), sXT, LDT, DK, tid);
         }
         __syncthreads(); // every wave is done with the tiles: A takes their place
-        // K K^T is symmetric: element x of tile nt is read as k_i . k_j with i = nt*16 + r (row of A) and
-        // j = i0 + kq*4 + x, so that a lane holds 4 consecutive j of one row: eta and the row of A are one 16-byte
-        // LDS access each
+        // (K K^T is symmetric: k_i . k_j whichever of them was the row of the product)
 #pragma unroll
-        for (int nt = 0; nt < 4; ++nt) {
-            const int i = nt * 16 + r, j0 = i0 + kq * 4;
-            // (Gamma's rows have an odd stride, for the column accesses of the reverse-pass product above: its four
-            //  values are read one by one)
-            const float *gr = &sG[(i > 0 ? i - 1 : 0) * LDG + j0];
-            const f32x4 et = *reinterpret_cast<const f32x4 *>(&s_et[j0]);
+        for (int u = 0; u < 3; ++u) {
+            const int i = nt_of(u) * 16 + r, j0 = jt_of(u) * 16 + kq * 4;
+            const f32x4 g = *reinterpret_cast<const f32x4 *>(&sG[(i > 0 ? i - 1 : 0) * LDG + j0]), et = *reinterpret_cast<const f32x4 *>(&s_et[j0]);
             const float al_i = s_al[i];
             f32x4 v;
 #pragma unroll
-            for (int x = 0; x < 4; ++x) v[x] = (j0 + x < i) ? al_i * et[x] * gr[x] * kk[nt][x] : 0.f;
+            for (int x = 0; x < 4; ++x) {
+                const float full = al_i * et[x] * g[x] * kk[u][x];
+                v[x] = (j0 + x < i) ? full : 0.f;
+            }
             *reinterpret_cast<f32x4 *>(&sA[i * LDA + j0]) = v;
         }
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+            *reinterpret_cast<f32x4 *>(&sA[(nz_of(u) * 16 + r) * LDA + jz_of(u) * 16 + kq * 4]) = f32x4{0.f, 0.f, 0.f, 0.f};
     }
     __syncthreads();
 
     // ---- T = (I + A)^{-1} by 16x16 blocks, wave w = block row w
-    tri_inverse_blocked(sA, sTT, LDA, w);
+    tri_inverse_blocked(sA, sTT, LDA, wu);
     __syncthreads();
 
     if (BWD) {
