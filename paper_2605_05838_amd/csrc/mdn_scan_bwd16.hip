@@ -25,7 +25,7 @@ __global__ __launch_bounds__(kScanThreads) void scan_pair16_kernel(Dims d, ScanB
     __shared__ __align__(16) char lds[sizeof(LB) > sizeof(LF) ? sizeof(LB) : sizeof(LF)];
     const int half = gridDim.x / 2, block = blockIdx.x;
     if (block < half) scan_bwd16<DK, DV, DVB, WHOLE, 2>(d, b, block, *reinterpret_cast<LB *>(lds));
-    else scan_fwd16<DK, DV, DVB, true, WHOLE, 2>(d, f, block - half, *reinterpret_cast<LF *>(lds));
+    else scan_fwd16<DK, DV, DVB, true, WHOLE, 2, false>(d, f, block - half, *reinterpret_cast<LF *>(lds));
 }
 
 template <int DK, int DV, int DVB, int AHEAD> hipError_t launch_t(const Dims &d, const ScanBwdArgs &a, hipStream_t s) {

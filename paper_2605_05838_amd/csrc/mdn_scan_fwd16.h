@@ -21,13 +21,17 @@
 namespace mdn {
 
 // AHEAD: how many chunks in front of the chain the loads are, 2 or (two workgroups per CU: see scan_one_per_cu) 1
-template <int DK, int DV, int DVB, bool REBUILD, int AHEAD> struct ScanFwdLds {
+// QTILE: the q rows come as a tile too (two chunks of them; with 32 columns of d = 128 at the cost of the third k tile), else from HBM into
+// the product waves' registers
+template <int DK, int DV, int DVB, bool REBUILD, int AHEAD, bool QTILE = false> struct ScanFwdLds {
     typedef bf16_t T;
     typedef ATile<T, DVB, 2 * DK> TS; // the states' copy, contraction over dk: S | M
     typedef ATile<T, DVB, 64> TV;     // contraction over the chunk's tokens
     // operands: AHEAD chunks, and the chain's own where a tile is read in the last phase
     static constexpr int SLOTS = AHEAD + 1;
-    __align__(16) T rK[SLOTS][64 * DK];
+    static constexpr int KSLOTS = QTILE && DK == 128 && DVB == 32 ? 2 : SLOTS;
+    __align__(16) T rK[KSLOTS][64 * DK];
+    __align__(16) T rQ[QTILE ? 2 : 1][QTILE ? 64 * DK : 8];
     __align__(16) T rT[REBUILD ? 1 : AHEAD][REBUILD ? 8 : 4096];
     __align__(16) T rB[REBUILD ? 1 : AHEAD][REBUILD ? 8 : 4096];
     __align__(16) T rV[SLOTS][64 * DVB];
@@ -42,14 +46,15 @@ template <int DK, int DV, int DVB, bool REBUILD, int AHEAD> struct ScanFwdLds {
 };
 
 // workgroup `block` of ((BH + 7) / 8) * 8 * DV / DVB
-template <int DK, int DV, int DVB, bool REBUILD, bool WHOLE, int AHEAD>
-__device__ __forceinline__ void scan_fwd16(const Dims &d, const ScanFwdArgs &a, int block, ScanFwdLds<DK, DV, DVB, REBUILD, AHEAD> &lds) {
+template <int DK, int DV, int DVB, bool REBUILD, bool WHOLE, int AHEAD, bool QTILE>
+__device__ __forceinline__ void scan_fwd16(const Dims &d, const ScanFwdArgs &a, int block, ScanFwdLds<DK, DV, DVB, REBUILD, AHEAD, QTILE> &lds) {
+    static_assert(!QTILE || (!REBUILD && AHEAD == 2), "");
     typedef bf16_t T;
     typedef Op<T> O;
-    typedef ScanFwdLds<DK, DV, DVB, REBUILD, AHEAD> L;
+    typedef ScanFwdLds<DK, DV, DVB, REBUILD, AHEAD, QTILE> L;
     typedef typename L::TS TS;
     typedef typename L::TV TV;
-    constexpr int MV = DVB / 16, ND = DK / 64, G = DV / DVB, KS = DK / 32, SLOTS = L::SLOTS;
+    constexpr int MV = DVB / 16, ND = DK / 64, G = DV / DVB, KS = DK / 32, SLOTS = L::SLOTS, KSLOTS = L::KSLOTS;
 
     int bh, blkv;
     xcd_map(block, G, bh, blkv);
@@ -111,7 +116,7 @@ __device__ __forceinline__ void scan_fwd16(const Dims &d, const ScanFwdArgs &a, 
         TileLoad<T, DK, true> tk;
         TileLoad<T, DVB, false> tv;
         TileLoad<float, kCoefRows, false> tc;
-        constexpr int NK = tk.COUNT, NV = tv.COUNT + tc.COUNT;
+        constexpr int NK = tk.COUNT, NQ = QTILE ? NK : 0, NV = tv.COUNT + tc.COUNT;
         tm.aim(64, w2, lane, turn, 63);
         tc.aim(kCoefRows, w2, lane, turn, 63);
         tk.aim(rsk, w2, lane, turn, 63);
@@ -125,6 +130,10 @@ __device__ __forceinline__ void scan_fwd16(const Dims &d, const ScanFwdArgs &a, 
         auto request_k = [&](int n, int slot) {
             tk.request(static_cast<const T *>(a.k) + first_token(n) * DK, lds_addr(lds.rK[0]) + slot * (64 * DK * (int)sizeof(T)), w2, turn);
         };
+        auto request_q = [&](int n, int slot) { // (the rows of q lie as those of k)
+            if constexpr (QTILE)
+                tk.request(static_cast<const T *>(a.q) + first_token(n) * DK, lds_addr(lds.rQ[0]) + slot * (64 * DK * (int)sizeof(T)), w2, turn);
+        };
         auto request_v = [&](int n, int slot) { // V (V~) and the coefficients
             tv.request(static_cast<const T *>(REBUILD ? a.vt_saved : a.v) + first_token(n) * DV + dv0,
                        lds_addr(lds.rV[0]) + slot * (64 * DVB * (int)sizeof(T)), w2, turn);
@@ -136,25 +145,41 @@ __device__ __forceinline__ void scan_fwd16(const Dims &d, const ScanFwdArgs &a, 
             if (n >= n1) break;
             aim_at(n);
             request_k(n, ahead);
+            request_q(n, ahead);
             request_v(n, ahead);
         }
         if constexpr (AHEAD == 2) {
-            if (n0 + 1 < n1) wait_vm<NK + NV>();
+            // With a q tile the k tile is requested in the last phase, the longest one, which with three slots is three chunks ahead:
+            // 16 requests, k and q, at the start of a step kept its first barrier waiting (32 768 tokens of 16 heads of 128, forward
+            // 721 us so, 662 now).
+            constexpr int KAHEAD = QTILE ? KSLOTS : 2;
+            if (KAHEAD == 3 && n0 + 2 < n1) {
+                aim_at(n0 + 2);
+                request_k(n0 + 2, 2);
+            }
+            if (KAHEAD == 3 && n0 + 2 < n1) wait_vm<2 * NK + NQ + NV>();
+            else if (n0 + 1 < n1) wait_vm<NK + NQ + NV>();
             else wait_vm<0>();
             __syncthreads();
-            int slot = 2, par = 0;
+            int slot = 2, par = 0, kslot = 0;
             int n = n0;
             for (; n + 2 < n1; ++n) {
                 const int nn = n + 2;
                 aim_at(nn);
-                request_k(nn, slot);
+                if (!QTILE) request_k(nn, slot);
+                request_q(nn, par); // (q of this chunk has been read)
                 if (!REBUILD) __syncthreads(); // A: T of this chunk has been read
                 request_m(a.Tm, nn, lds.rT[0], par);
                 request_v(nn, slot);
-                wait_vm<NK + NM + NV>(); // everything of the next chunk is there
-                __syncthreads(); // B: so has Bm
+                wait_vm<(KAHEAD == 3 || !QTILE ? NK : 0) + NQ + NM + NV>(); // everything of the next chunk is there
+                __syncthreads(); // B: so have Bm and k
                 request_m(a.Bm, nn, lds.rB[0], par);
+                if (QTILE && n + KAHEAD < n1) {
+                    if (KAHEAD == 3) aim_at(n + 3);
+                    request_k(n + KAHEAD, KAHEAD == 3 ? kslot : par);
+                }
                 slot = slot == 2 ? 0 : slot + 1;
+                kslot = kslot == 2 ? 0 : kslot + 1;
                 par ^= 1;
                 __syncthreads(); // C
             }
@@ -197,10 +222,11 @@ __device__ __forceinline__ void scan_fwd16(const Dims &d, const ScanFwdArgs &a, 
     } else {
         // ---------------------------------------------------------------- the chain
         __builtin_amdgcn_s_setprio(3);
-        // the q rows, the only operand without a place in LDS, in registers, requested when those of the chunk before have been used
+        // the q rows: out of their tile with what a step needs first, or, without a place in LDS, from HBM into registers, requested when
+        // those of the chunk before have been used
         struct QRows { O::Frag f[KS]; };
         auto load_q = [&](int n, QRows &q) {
-            if constexpr (!REBUILD) {
+            if constexpr (!REBUILD && !QTILE) {
                 const T *Qg = static_cast<const T *>(a.q) + first_token(n) * DK;
                 const unsigned it = (unsigned)((!WHOLE && n == ragged ? min(i, last) : i) * d.H);
 #pragma unroll
@@ -220,10 +246,15 @@ __device__ __forceinline__ void scan_fwd16(const Dims &d, const ScanFwdArgs &a, 
         f32x4 c0, c1;
         bf16x4 u[MV];
         int slot = 0, par = 0;
+        auto k_tile = [&]() -> const T * { return lds.rK[KSLOTS == SLOTS ? slot : par]; };
         auto first_reads = [&]() {
             if constexpr (!REBUILD) {
 #pragma unroll
-                for (int s = 0; s < KS; ++s) fk[s] = token_tile_row_frag<DK>(lds.rK[slot], i, s, kg);
+                for (int s = 0; s < KS; ++s) fk[s] = token_tile_row_frag<DK>(k_tile(), i, s, kg);
+            }
+            if constexpr (QTILE) {
+#pragma unroll
+                for (int s = 0; s < KS; ++s) q.f[s] = token_tile_row_frag<DK>(lds.rQ[par], i, s, kg);
             }
             c0 = *reinterpret_cast<const f32x4 *>(lds.rC[slot] + i * kCoefRows);
             c1 = *reinterpret_cast<const f32x4 *>(lds.rC[slot] + i * kCoefRows + 4);
@@ -240,7 +271,7 @@ __device__ __forceinline__ void scan_fwd16(const Dims &d, const ScanFwdArgs &a, 
 #pragma unroll
                 for (int s = 0; s < 2; ++s)
 #pragma unroll
-                    for (int nd = 0; nd < ND; ++nd) kt[s][nd] = token_tile_col_frag<DK>(lds.rK[slot], w * ND + nd, s, r, kg);
+                    for (int nd = 0; nd < ND; ++nd) kt[s][nd] = token_tile_col_frag<DK>(k_tile(), w * ND + nd, s, r, kg);
             };
             if constexpr (!REBUILD) {
                 f32x4 x1[MV], x2[MV], os[MV], om[MV], v[MV];

@@ -5,32 +5,40 @@ namespace mdn {
 
 namespace {
 
-template <int DK, int DV, int DVB, bool REBUILD, bool WHOLE, int AHEAD>
+template <int DK, int DV, int DVB, bool REBUILD, bool WHOLE, int AHEAD, bool QTILE>
 __global__ __launch_bounds__(kScanThreads, AHEAD == 1 ? 4 : 2) void scan_fwd16_kernel(Dims d, ScanFwdArgs a, int first) {
-    __shared__ ScanFwdLds<DK, DV, DVB, REBUILD, AHEAD> lds;
-    scan_fwd16<DK, DV, DVB, REBUILD, WHOLE, AHEAD>(d, a, first + blockIdx.x, lds);
+    __shared__ ScanFwdLds<DK, DV, DVB, REBUILD, AHEAD, QTILE> lds;
+    scan_fwd16<DK, DV, DVB, REBUILD, WHOLE, AHEAD, QTILE>(d, a, first + blockIdx.x, lds);
 }
 
-template <int DK, int DV, int DVB, bool REBUILD, bool WHOLE, int AHEAD>
+template <int DK, int DV, int DVB, bool REBUILD, bool WHOLE, int AHEAD, bool QTILE>
 hipError_t launch_w(const Dims &d, const ScanFwdArgs &a, hipStream_t s) {
     static const size_t spread =
-        AHEAD == 1 ? 0 : lds_bytes_for_one_workgroup_per_cu(reinterpret_cast<const void *>(&scan_fwd16_kernel<DK, DV, DVB, REBUILD, WHOLE, AHEAD>));
+        AHEAD == 1 ? 0 : lds_bytes_for_one_workgroup_per_cu(reinterpret_cast<const void *>(&scan_fwd16_kernel<DK, DV, DVB, REBUILD, WHOLE, AHEAD, QTILE>));
     return launch_in_parts(scan_blocks<DV, DVB>(d), [&](int first, dim3 grid) {
-        hipLaunchKernelGGL((scan_fwd16_kernel<DK, DV, DVB, REBUILD, WHOLE, AHEAD>), grid, dim3(kScanThreads), spread, s, d, a, first);
+        hipLaunchKernelGGL((scan_fwd16_kernel<DK, DV, DVB, REBUILD, WHOLE, AHEAD, QTILE>), grid, dim3(kScanThreads), spread, s, d, a, first);
     });
 }
-template <int DK, int DV, int DVB, bool REBUILD, int AHEAD> hipError_t launch_t(const Dims &d, const ScanFwdArgs &a, hipStream_t s) {
-    return whole_chunks(d) ? launch_w<DK, DV, DVB, REBUILD, true, AHEAD>(d, a, s) : launch_w<DK, DV, DVB, REBUILD, false, AHEAD>(d, a, s);
+template <int DK, int DV, int DVB, bool REBUILD, int AHEAD, bool QTILE = false> hipError_t launch_t(const Dims &d, const ScanFwdArgs &a, hipStream_t s) {
+    return whole_chunks(d) ? launch_w<DK, DV, DVB, REBUILD, true, AHEAD, QTILE>(d, a, s) : launch_w<DK, DV, DVB, REBUILD, false, AHEAD, QTILE>(d, a, s);
 }
 // Two workgroups per CU where there are more of them than CUs and the operands of one chunk less make them fit (all but the forward
 // of heads of 128): a workgroup's start and the latencies of its chain then lie beside another one's work.  One / two per CU, forward
 // of heads of 64 in us: 64 x 64 tokens of 16 heads 43.4 / 33.9, 32 x 128 36.1 / 30.8, 32 x 1 024 187 / 182, packed 256 sequences of 30
 // tokens of 16 heads 156 / 107.  One chunk ahead costs a single workgroup up to a tenth of a step, so up to one per CU it is two.
 // (16 columns have a CU for each workgroup: see scan_dvb.)
+// The q rows as a tile brought by the loading waves: no loads, and no waits for them, in the waves of the chain; but 32 KB more of LDS and four
+// more of its reads in a step's last phase.  With 16 columns always.  With 32 only where the kept states' stores hold up every load
+// (d = 128; at d = 64 the chain is the longer part of a step then too).  Forward in us, q in registers / as a tile: 32 768 tokens of 16 heads of
+// 128 761 / 662, with kept states 994 / 927, 777 tokens 24.4 / 24.4; 3 x 1 500 of 8 heads of 64 with kept states 33.4 / 32.9; with 32
+// columns, 4 x 4 096 of 16 heads of 128 with kept states 213 / 200, without 150 / 157, 8 x 2 048 of 8 heads 84 / 87, 4 x 4 096 of
+// 24 heads of 64 100.8 / 105.5.
 template <int DK, int DV, bool REBUILD> hipError_t pick(const Dims &d, const ScanFwdArgs &a, hipStream_t s) {
-    if (scan_dvb(d) == 16) return launch_t<DK, DV, 16, REBUILD, 2>(d, a, s);
+    if (scan_dvb(d) == 16) return launch_t<DK, DV, 16, REBUILD, 2, !REBUILD>(d, a, s);
     if constexpr (2 * sizeof(ScanFwdLds<DK, DV, 32, REBUILD, 1>) <= 160 * 1024)
         if (!scan_one_per_cu(d)) return launch_t<DK, DV, 32, REBUILD, 1>(d, a, s);
+    if constexpr (!REBUILD && DK == 128)
+        if (a.states_saved) return launch_t<DK, DV, 32, REBUILD, 2, true>(d, a, s);
     return launch_t<DK, DV, 32, REBUILD, 2>(d, a, s);
 }
 

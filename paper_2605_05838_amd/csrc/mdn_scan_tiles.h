@@ -1,7 +1,8 @@
 // What the 16-bit scans (forward, reconstruction, reverse) have in common.  A workgroup of eight waves walks the chunks of one
 // (sequence, head) pair for DVB dv columns, one barrier-separated phase after the other, and its waves have three jobs:
-//   waves 0-3  the chain: every product of a step, the states in their accumulators.  They take all operands from LDS (q rows
-//              excepted) and leave all results there, so that nothing on the serial path waits for memory;
+//   waves 0-3  the chain: every product of a step, the states in their accumulators.  They take all operands from LDS (in some
+//              instances of the forward the q rows excepted) and leave all results there, so that nothing on the serial path waits for
+//              memory;
 //   waves 4-5  loads: the operands of chunks further on, HBM -> LDS without registers, into rings of 1 to 3 chunks;
 //   waves 6-7  stores: results of the step before, LDS -> HBM (and at the start, with nothing to store, half of the first loads).
 // Loads and stores are apart because a wave's vector-memory operations are counted in order: a wave that does both waits for the
