@@ -167,8 +167,11 @@ __device__ __forceinline__ void scan_fwd16(const Dims &d, const ScanFwdArgs &a, 
                 const int nn = n + 2;
                 aim_at(nn);
                 if (!QTILE) request_k(nn, slot);
-                request_q(nn, par); // (q of this chunk has been read)
+                // (q of this chunk has been read at the end of the step before, but the first chunk's only behind the first barrier, beside
+                //  this: up to A its tile is not free)
+                if (n > n0) request_q(nn, par);
                 if (!REBUILD) __syncthreads(); // A: T of this chunk has been read
+                if (n == n0) request_q(nn, par);
                 request_m(a.Tm, nn, lds.rT[0], par);
                 request_v(nn, slot);
                 wait_vm<(KAHEAD == 3 || !QTILE ? NK : 0) + NQ + NM + NV>(); // everything of the next chunk is there
