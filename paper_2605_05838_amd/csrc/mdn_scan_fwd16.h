@@ -87,6 +87,7 @@ __device__ __forceinline__ void scan_fwd16(const Dims &d, const ScanFwdArgs &a, 
         if (AHEAD == 2 && n0 + 1 < n1) wait_vm<2 * NM>();
         else wait_vm<0>();
         __syncthreads();
+        if (QTILE) __syncthreads();
         for (int n = n0;; ++n) {
             if (!REBUILD && n == n1) break;
             T *states = static_cast<T *>(a.states_saved) + (sq.blk + n) * (2 * DK * DV); // this chunk's start states
@@ -161,17 +162,15 @@ __device__ __forceinline__ void scan_fwd16(const Dims &d, const ScanFwdArgs &a, 
             else if (n0 + 1 < n1) wait_vm<NK + NQ + NV>();
             else wait_vm<0>();
             __syncthreads();
+            if (QTILE) __syncthreads(); // the first chunk's q has been read
             int slot = 2, par = 0, kslot = 0;
             int n = n0;
             for (; n + 2 < n1; ++n) {
                 const int nn = n + 2;
                 aim_at(nn);
                 if (!QTILE) request_k(nn, slot);
-                // (q of this chunk has been read at the end of the step before, but the first chunk's only behind the first barrier, beside
-                //  this: up to A its tile is not free)
-                if (n > n0) request_q(nn, par);
+                request_q(nn, par); // (q of this chunk has been read)
                 if (!REBUILD) __syncthreads(); // A: T of this chunk has been read
-                if (n == n0) request_q(nn, par);
                 request_m(a.Tm, nn, lds.rT[0], par);
                 request_v(nn, slot);
                 wait_vm<(KAHEAD == 3 || !QTILE ? NK : 0) + NQ + NM + NV>(); // everything of the next chunk is there
@@ -264,6 +263,10 @@ __device__ __forceinline__ void scan_fwd16(const Dims &d, const ScanFwdArgs &a, 
             load_cols_raw<MV>(lds.rV[slot] + i * DVB + kg * (4 * MV), u);
         };
         first_reads();
+        // (the tile of the first chunk's q is requested anew at the start of its step; later ones are read in front of a barrier anyway.
+        //  The first of these requests behind A instead, by a branch in the loading waves: 88.8 instead of 86.2 us for 4 096 tokens of 16 heads
+        //  of 128.)
+        if (QTILE) __syncthreads();
         // (one copy of a step: two or three, for q registers two chunks ahead, took 92.0 instead of 89.2 us for 16 x 512 tokens of 16
         //  heads of 128 and 14.4 instead of 13.9 for 1 x 128)
         for (int n = n0; n < n1; ++n) {
