@@ -22,7 +22,8 @@ namespace mdn {
 
 // AHEAD: how many chunks in front of the chain the loads are, 2 or (two workgroups per CU: see scan_one_per_cu) 1, as far as one set
 // of operands allows
-template <int DK, int DV, int DVB, int AHEAD> struct ScanBwdLds {
+// TOUCH: the operands are brought into the L2 first (LineTouch)
+template <int DK, int DV, int DVB, int AHEAD, bool TOUCH = false> struct ScanBwdLds {
     typedef bf16_t T;
     typedef ATile<T, DVB, 2 * DK> TD; // the adjoints' copy, contraction over dk: dS' | dM'
     typedef ATile<T, DVB, 64> TV;     // contraction over the chunk's tokens
@@ -42,14 +43,15 @@ template <int DK, int DV, int DVB, int AHEAD> struct ScanBwdLds {
     __align__(16) T sR0[TV::SIZE]; // dV^T
     __align__(16) T sRa[TV::SIZE]; // (-a . dV)^T
     __align__(16) T sRb[TV::SIZE]; // (pb . dV)^T
+    __align__(16) unsigned touched[TOUCH ? 128 : 4];
 };
 
 // workgroup `block` of ((BH + 7) / 8) * 8 * DV / DVB
-template <int DK, int DV, int DVB, bool WHOLE, int AHEAD>
-__device__ __forceinline__ void scan_bwd16(const Dims &d, const ScanBwdArgs &a, int block, ScanBwdLds<DK, DV, DVB, AHEAD> &lds) {
+template <int DK, int DV, int DVB, bool WHOLE, int AHEAD, bool TOUCH>
+__device__ __forceinline__ void scan_bwd16(const Dims &d, const ScanBwdArgs &a, int block, ScanBwdLds<DK, DV, DVB, AHEAD, TOUCH> &lds) {
     typedef bf16_t T;
     typedef Op<T> O;
-    typedef ScanBwdLds<DK, DV, DVB, AHEAD> L;
+    typedef ScanBwdLds<DK, DV, DVB, AHEAD, TOUCH> L;
     typedef typename L::TD TD;
     typedef typename L::TV TV;
     constexpr int MV = DVB / 16, ND = DK / 64, G = DV / DVB, KS = DK / 32, KSLOTS = L::KSLOTS;
@@ -82,6 +84,9 @@ __device__ __forceinline__ void scan_bwd16(const Dims &d, const ScanBwdArgs &a, 
         }
         if (AHEAD == 2 && n0 + 1 < n1) wait_vm<2 * tm.COUNT>();
         else wait_vm<0>();
+        [[maybe_unused]] LineTouch<DK, DV, G> touch; // (of what comes before the partial chunk)
+        [[maybe_unused]] int next = n1 - 1 - AHEAD; // the chunk it is at
+        if constexpr (TOUCH) touch.aim(a.k, a.q, a.dO, a.Tm, a.Bm, a.coef, sq, d.H, blkv * 2 + w2, lane, next, -1, 63);
         __syncthreads();
         for (int n = n1 - 1; n >= n0; --n) {
             T *states = static_cast<T *>(a.dstates) + (sq.blk + n) * (2 * DK * DV); // adjoints of this chunk's END states
@@ -91,10 +96,13 @@ __device__ __forceinline__ void scan_bwd16(const Dims &d, const ScanBwdArgs &a, 
             if (AHEAD == 2 && n == n1 - 1) wait_vm<NS / 2>(); // Bm and T of the second chunk are there
             st.template put<NS / 2, NS * 3 / 4>(states, dv0, w2, lane);
             __syncthreads(); // B
+            if constexpr (TOUCH)
+                for (; next >= n0 && next >= n - kTouchAhead; --next) touch.template chunk<-1>(next, lds_addr(lds.touched + w2 * 64));
             store_token_rows<DV, MV, WHOLE>(static_cast<T *>(a.dv) + first_token(n) * DV + dv0, lds.sR0, !WHOLE && n == ragged ? last + 1 : 64, d.H, w2, lane);
             st.template put<NS * 3 / 4, NS>(states, dv0, w2, lane);
             __syncthreads(); // C
         }
+        if constexpr (TOUCH) wait_vm<0>(); // (no transfer outlives the workgroup)
     } else if (wv >= 4) {
         // ---------------------------------------------------------------- loads: two chunks ahead, as the slots become free
         const unsigned rsk = (unsigned)(d.H * DK), rsv = (unsigned)(d.H * DV);

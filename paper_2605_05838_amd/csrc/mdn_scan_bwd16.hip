@@ -6,10 +6,10 @@ namespace mdn {
 
 namespace {
 
-template <int DK, int DV, int DVB, bool WHOLE, int AHEAD>
+template <int DK, int DV, int DVB, bool WHOLE, int AHEAD, bool TOUCH>
 __global__ __launch_bounds__(kScanThreads, AHEAD == 1 ? 4 : 2) void scan_bwd16_kernel(Dims d, ScanBwdArgs a, int first) {
-    __shared__ ScanBwdLds<DK, DV, DVB, AHEAD> lds;
-    scan_bwd16<DK, DV, DVB, WHOLE, AHEAD>(d, a, first + blockIdx.x, lds);
+    __shared__ ScanBwdLds<DK, DV, DVB, AHEAD, TOUCH> lds;
+    scan_bwd16<DK, DV, DVB, WHOLE, AHEAD, TOUCH>(d, a, first + blockIdx.x, lds);
 }
 
 // Both at once: the first half of the workgroups walks the reverse scan, the second half (its steps are shorter) the
@@ -24,21 +24,21 @@ __global__ __launch_bounds__(kScanThreads) void scan_pair16_kernel(Dims d, ScanB
     typedef ScanFwdLds<DK, DV, DVB, true, 2> LF;
     __shared__ __align__(16) char lds[sizeof(LB) > sizeof(LF) ? sizeof(LB) : sizeof(LF)];
     const int half = gridDim.x / 2, block = blockIdx.x;
-    if (block < half) scan_bwd16<DK, DV, DVB, WHOLE, 2>(d, b, block, *reinterpret_cast<LB *>(lds));
-    else scan_fwd16<DK, DV, DVB, true, WHOLE, 2, false>(d, f, block - half, *reinterpret_cast<LF *>(lds));
+    if (block < half) scan_bwd16<DK, DV, DVB, WHOLE, 2, false>(d, b, block, *reinterpret_cast<LB *>(lds));
+    else scan_fwd16<DK, DV, DVB, true, WHOLE, 2, false, false>(d, f, block - half, *reinterpret_cast<LF *>(lds));
 }
 
-template <int DK, int DV, int DVB, int AHEAD> hipError_t launch_t(const Dims &d, const ScanBwdArgs &a, hipStream_t s) {
+template <int DK, int DV, int DVB, int AHEAD, bool TOUCH = false> hipError_t launch_t(const Dims &d, const ScanBwdArgs &a, hipStream_t s) {
     return launch_in_parts(scan_blocks<DV, DVB>(d), [&](int first, dim3 grid) {
         const dim3 block(kScanThreads);
-        if (whole_chunks(d)) hipLaunchKernelGGL((scan_bwd16_kernel<DK, DV, DVB, true, AHEAD>), grid, block, 0, s, d, a, first);
-        else hipLaunchKernelGGL((scan_bwd16_kernel<DK, DV, DVB, false, AHEAD>), grid, block, 0, s, d, a, first);
+        if (whole_chunks(d)) hipLaunchKernelGGL((scan_bwd16_kernel<DK, DV, DVB, true, AHEAD, TOUCH>), grid, block, 0, s, d, a, first);
+        else hipLaunchKernelGGL((scan_bwd16_kernel<DK, DV, DVB, false, AHEAD, TOUCH>), grid, block, 0, s, d, a, first);
     });
 }
 // Two workgroups per CU as in the forward (heads of 64), one / two in us, forward with kept states and backward: 64 x 64 tokens of 16
 // heads 98.8 / 88.3, 32 x 64 55.0 / 49.8, 32 x 128 87.0 / 81.2, 32 x 1 024 604 / 603.
 template <int DK, int DV> hipError_t pick(const Dims &d, const ScanBwdArgs &a, hipStream_t s) {
-    if (scan_dvb(d) == 16) return launch_t<DK, DV, 16, 2>(d, a, s);
+    if (scan_dvb(d) == 16) return touch_pays<DK, DV>(d, true) ? launch_t<DK, DV, 16, 2, true>(d, a, s) : launch_t<DK, DV, 16, 2>(d, a, s);
     if constexpr (2 * sizeof(ScanBwdLds<DK, DV, 32, 1>) <= 160 * 1024)
         if (!scan_one_per_cu(d)) return launch_t<DK, DV, 32, 1>(d, a, s);
     return launch_t<DK, DV, 32, 2>(d, a, s);

@@ -23,7 +23,8 @@ namespace mdn {
 // AHEAD: how many chunks in front of the chain the loads are, 2 or (two workgroups per CU: see scan_one_per_cu) 1
 // QTILE: the q rows come as a tile too (two chunks of them; with 32 columns of d = 128 at the cost of the third k tile), else from HBM into
 // the product waves' registers
-template <int DK, int DV, int DVB, bool REBUILD, int AHEAD, bool QTILE = false> struct ScanFwdLds {
+// TOUCH: the operands are brought into the L2 first (LineTouch)
+template <int DK, int DV, int DVB, bool REBUILD, int AHEAD, bool QTILE = false, bool TOUCH = false> struct ScanFwdLds {
     typedef bf16_t T;
     typedef ATile<T, DVB, 2 * DK> TS; // the states' copy, contraction over dk: S | M
     typedef ATile<T, DVB, 64> TV;     // contraction over the chunk's tokens
@@ -43,15 +44,16 @@ template <int DK, int DV, int DVB, bool REBUILD, int AHEAD, bool QTILE = false> 
     __align__(16) T sVg[TV::SIZE];
     __align__(16) T sVr[TV::SIZE];
     __align__(16) T sO[REBUILD ? 8 : TV::SIZE];
+    __align__(16) unsigned touched[TOUCH ? 128 : 4];
 };
 
 // workgroup `block` of ((BH + 7) / 8) * 8 * DV / DVB
-template <int DK, int DV, int DVB, bool REBUILD, bool WHOLE, int AHEAD, bool QTILE>
-__device__ __forceinline__ void scan_fwd16(const Dims &d, const ScanFwdArgs &a, int block, ScanFwdLds<DK, DV, DVB, REBUILD, AHEAD, QTILE> &lds) {
-    static_assert(!QTILE || (!REBUILD && AHEAD == 2), "");
+template <int DK, int DV, int DVB, bool REBUILD, bool WHOLE, int AHEAD, bool QTILE, bool TOUCH>
+__device__ __forceinline__ void scan_fwd16(const Dims &d, const ScanFwdArgs &a, int block, ScanFwdLds<DK, DV, DVB, REBUILD, AHEAD, QTILE, TOUCH> &lds) {
+    static_assert(!(QTILE || TOUCH) || (!REBUILD && AHEAD == 2), "");
     typedef bf16_t T;
     typedef Op<T> O;
-    typedef ScanFwdLds<DK, DV, DVB, REBUILD, AHEAD, QTILE> L;
+    typedef ScanFwdLds<DK, DV, DVB, REBUILD, AHEAD, QTILE, TOUCH> L;
     typedef typename L::TS TS;
     typedef typename L::TV TV;
     constexpr int MV = DVB / 16, ND = DK / 64, G = DV / DVB, KS = DK / 32, SLOTS = L::SLOTS, KSLOTS = L::KSLOTS;
@@ -86,6 +88,9 @@ __device__ __forceinline__ void scan_fwd16(const Dims &d, const ScanFwdArgs &a, 
         }
         if (AHEAD == 2 && n0 + 1 < n1) wait_vm<2 * NM>();
         else wait_vm<0>();
+        [[maybe_unused]] LineTouch<DK, DV, G> touch;
+        [[maybe_unused]] int next = n0 + AHEAD; // the chunk it is at
+        if constexpr (TOUCH) touch.aim(a.k, a.q, a.v, a.Tm, a.Bm, a.coef, sq, d.H, blkv * 2 + w2, lane, next, ragged, last);
         __syncthreads();
         if (QTILE) __syncthreads();
         for (int n = n0;; ++n) {
@@ -105,12 +110,15 @@ __device__ __forceinline__ void scan_fwd16(const Dims &d, const ScanFwdArgs &a, 
             }
             if (a.states_saved) st.template put<NS / 2, NS * 3 / 4>(states, dv0, w2, lane);
             __syncthreads(); // B
+            if constexpr (TOUCH)
+                for (; next < n1 && next <= n + kTouchAhead; ++next) touch.template chunk<1>(next, lds_addr(lds.touched + w2 * 64));
             if (!REBUILD && a.vt_saved)
                 store_token_rows<DV, MV, WHOLE>(static_cast<T *>(a.vt_saved) + first_token(n) * DV + dv0, lds.sV0, rows_of(n), d.H, w2, lane);
             if (a.states_saved) st.template put<NS * 3 / 4, NS>(states, dv0, w2, lane);
             __syncthreads(); // C
         }
         if (!REBUILD) store_token_rows<DV, MV, WHOLE>(static_cast<T *>(a.o) + first_token(n1 - 1) * DV + dv0, lds.sO, rows_of(n1 - 1), d.H, w2, lane);
+        if constexpr (TOUCH) wait_vm<0>(); // (no transfer outlives the workgroup)
     } else if (wv >= 4) {
         // ---------------------------------------------------------------- loads
         const unsigned rsk = (unsigned)(d.H * DK), rsv = (unsigned)(d.H * DV);

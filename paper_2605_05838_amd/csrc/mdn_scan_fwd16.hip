@@ -5,22 +5,22 @@ namespace mdn {
 
 namespace {
 
-template <int DK, int DV, int DVB, bool REBUILD, bool WHOLE, int AHEAD, bool QTILE>
+template <int DK, int DV, int DVB, bool REBUILD, bool WHOLE, int AHEAD, bool QTILE, bool TOUCH>
 __global__ __launch_bounds__(kScanThreads, AHEAD == 1 ? 4 : 2) void scan_fwd16_kernel(Dims d, ScanFwdArgs a, int first) {
-    __shared__ ScanFwdLds<DK, DV, DVB, REBUILD, AHEAD, QTILE> lds;
-    scan_fwd16<DK, DV, DVB, REBUILD, WHOLE, AHEAD, QTILE>(d, a, first + blockIdx.x, lds);
+    __shared__ ScanFwdLds<DK, DV, DVB, REBUILD, AHEAD, QTILE, TOUCH> lds;
+    scan_fwd16<DK, DV, DVB, REBUILD, WHOLE, AHEAD, QTILE, TOUCH>(d, a, first + blockIdx.x, lds);
 }
 
-template <int DK, int DV, int DVB, bool REBUILD, bool WHOLE, int AHEAD, bool QTILE>
+template <int DK, int DV, int DVB, bool REBUILD, bool WHOLE, int AHEAD, bool QTILE, bool TOUCH>
 hipError_t launch_w(const Dims &d, const ScanFwdArgs &a, hipStream_t s) {
     static const size_t spread =
-        AHEAD == 1 ? 0 : lds_bytes_for_one_workgroup_per_cu(reinterpret_cast<const void *>(&scan_fwd16_kernel<DK, DV, DVB, REBUILD, WHOLE, AHEAD, QTILE>));
+        AHEAD == 1 ? 0 : lds_bytes_for_one_workgroup_per_cu(reinterpret_cast<const void *>(&scan_fwd16_kernel<DK, DV, DVB, REBUILD, WHOLE, AHEAD, QTILE, TOUCH>));
     return launch_in_parts(scan_blocks<DV, DVB>(d), [&](int first, dim3 grid) {
-        hipLaunchKernelGGL((scan_fwd16_kernel<DK, DV, DVB, REBUILD, WHOLE, AHEAD, QTILE>), grid, dim3(kScanThreads), spread, s, d, a, first);
+        hipLaunchKernelGGL((scan_fwd16_kernel<DK, DV, DVB, REBUILD, WHOLE, AHEAD, QTILE, TOUCH>), grid, dim3(kScanThreads), spread, s, d, a, first);
     });
 }
-template <int DK, int DV, int DVB, bool REBUILD, int AHEAD, bool QTILE = false> hipError_t launch_t(const Dims &d, const ScanFwdArgs &a, hipStream_t s) {
-    return whole_chunks(d) ? launch_w<DK, DV, DVB, REBUILD, true, AHEAD, QTILE>(d, a, s) : launch_w<DK, DV, DVB, REBUILD, false, AHEAD, QTILE>(d, a, s);
+template <int DK, int DV, int DVB, bool REBUILD, int AHEAD, bool QTILE = false, bool TOUCH = false> hipError_t launch_t(const Dims &d, const ScanFwdArgs &a, hipStream_t s) {
+    return whole_chunks(d) ? launch_w<DK, DV, DVB, REBUILD, true, AHEAD, QTILE, TOUCH>(d, a, s) : launch_w<DK, DV, DVB, REBUILD, false, AHEAD, QTILE, TOUCH>(d, a, s);
 }
 // Two workgroups per CU where there are more of them than CUs and the operands of one chunk less make them fit (all but the forward
 // of heads of 128): a workgroup's start and the latencies of its chain then lie beside another one's work.  One / two per CU, forward
@@ -34,7 +34,11 @@ template <int DK, int DV, int DVB, bool REBUILD, int AHEAD, bool QTILE = false> 
 // columns, 4 x 4 096 of 16 heads of 128 with kept states 213 / 200, without 150 / 157, 8 x 2 048 of 8 heads 84 / 87, 4 x 4 096 of
 // 24 heads of 64 100.8 / 105.5.
 template <int DK, int DV, bool REBUILD> hipError_t pick(const Dims &d, const ScanFwdArgs &a, hipStream_t s) {
-    if (scan_dvb(d) == 16) return launch_t<DK, DV, 16, REBUILD, 2, !REBUILD>(d, a, s);
+    if (scan_dvb(d) == 16) {
+        if constexpr (!REBUILD)
+            if (touch_pays<DK, DV>(d, a.states_saved)) return launch_t<DK, DV, 16, false, 2, true, true>(d, a, s);
+        return launch_t<DK, DV, 16, REBUILD, 2, !REBUILD>(d, a, s);
+    }
     if constexpr (2 * sizeof(ScanFwdLds<DK, DV, 32, REBUILD, 1>) <= 160 * 1024)
         if (!scan_one_per_cu(d)) return launch_t<DK, DV, 32, REBUILD, 1>(d, a, s);
     if constexpr (!REBUILD && DK == 128)

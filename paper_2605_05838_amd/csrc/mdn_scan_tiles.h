@@ -4,7 +4,8 @@
 //              instances of the forward the q rows excepted) and leave all results there, so that nothing on the serial path waits for
 //              memory;
 //   waves 4-5  loads: the operands of chunks further on, HBM -> LDS without registers, into rings of 1 to 3 chunks;
-//   waves 6-7  stores: results of the step before, LDS -> HBM (and at the start, with nothing to store, half of the first loads).
+//   waves 6-7  stores: results of the step before, LDS -> HBM (and at the start, with nothing to store, half of the first loads; with 16
+//              columns also the operands of later chunks into the L2, see LineTouch).
 // Loads and stores are apart because a wave's vector-memory operations are counted in order: a wave that does both waits for the
 // acknowledgement of its stores whenever it waits for a load behind them.  With loads, stores and products in the same four waves
 // a quarter to a half of a step was spent at the issue of memory instructions and in such waits (the forward scan of 4 x 4 096
@@ -78,6 +79,69 @@ template <typename T, int LEN, bool SWIZZLE> struct TileLoad {
     __device__ __forceinline__ void request(const T *src, unsigned tile, int w2, int turn) const {
 #pragma unroll
         for (int u = 0; u < COUNT; ++u) dma16(src, off[u], tile + piece(u, w2, turn) * 16);
+    }
+};
+
+// The operands of chunks further on than the loads, brought into the L2 by the storing waves: four bytes of every 64, each workgroup of a
+// (sequence, head) pair its share of the lanes.  A CU has only so many lines on their way at a time, so that what the loads bring per step is that
+// over the latency of a line, which with the kept states' stores on the way to HBM grew until the loads were what a step waited for (16
+// columns, d = 128: 3 700 clocks a step with kept states, 3 300 of them in the loading waves, 2 300 without the stores); out of the L2 they keep up.
+// Every 64 bytes: of a line of 128 asked for once only half is fetched.  32 768 tokens of 16 heads of 128 in us, without / every 128 bytes
+// / every 64 / every 32: forward 675 / 662 / 648 / 665, with kept states 924 / 797 / 772 / 803, forward and backward 1 846 / 1 675 / 1 646 / 1 677; three,
+// four and six chunks ahead 1 661, 1 646 and 1 657.
+constexpr int kTouchAhead = 4;
+// Only where a call moves more than twice the 256 MB of the last-level cache, whose latency the loads cover: forward with kept states and
+// backward in us, without / with, 16 heads of 128 with 2 048 tokens 114.2 / 115.8, 8 192 (331 MB) 440 / 449, 16 384 (663 MB) 849 / 832, 4 heads with
+// 131 072 5 550 / 4 938; forward alone, 16 384 (336 MB) 309 / 315, 32 768 (671 MB) 675 / 648.  And not with 32 columns, where every CU is at
+// work and HBM itself is busy: 4 x 4 096 of 16 heads of 128 595 / 604 (every 128 bytes), forward of heads of 64 96 / 115.
+template <int DK, int DV> bool touch_pays(const Dims &d, bool kept) {
+    constexpr size_t operands = 64 * (2 * DK + DV + kCoefRows * 2 + 2 * 64) * 2, rows = 64 * DV * 2, states = 2 * DK * DV * 2;
+    return (size_t)d.nchunks * d.H * (operands + rows + (kept ? states + rows : 0)) > (size_t)512 << 20;
+}
+template <int DK, int DV, int G> struct LineTouch {
+    static constexpr int LINE = 64, RK = DK * 2 / LINE, RV = DV * 2 / LINE;                              // lines of a row
+    static constexpr int K = 64 * RK, V = 64 * RV, M = 4096 * 2 / LINE, C = 64 * kCoefRows * 4 / LINE; // of a tensor's chunk
+    static constexpr int LINES = 2 * K + V + 2 * M + C, N = (LINES + G * 128 - 1) / (G * 128);
+    const char *at[N];
+    ptrdiff_t step[N];
+    int end[N]; // a lane's line is in the chunks before this one
+    // part: this wave's number among those of the pair's workgroups; n: the first chunk touched; rows behind `last` are not in chunk `ragged`
+    __device__ __forceinline__ void aim(const void *k, const void *q, const void *v, const void *Tm, const void *Bm, const float *coef, const ScanSeq &sq, int H,
+                                        int part, int lane, int n, int ragged, int last) {
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            int p = (u * G * 2 + part) * 64 + lane;
+            end[u] = p < LINES ? sq.n1 : 0;
+            if (p < 2 * K + V) { // [tokens, H, D]
+                const void *t = p < K ? k : p < 2 * K ? q : v;
+                const int per_row = p < 2 * K ? RK : RV, bytes = per_row * LINE;
+                p = p < K ? p : p < 2 * K ? p - K : p - 2 * K;
+                const int row = p / per_row;
+                step[u] = (ptrdiff_t)64 * H * bytes;
+                at[u] = static_cast<const char *>(t) + (sq.tok + (size_t)row * H) * bytes + p % per_row * LINE;
+                if (ragged >= 0 && row > last) end[u] = ragged;
+            } else { // chunk blocks
+                p = min(p, LINES - 1) - (2 * K + V);
+                const void *t = p < M ? Tm : p < 2 * M ? Bm : coef;
+                step[u] = (p < 2 * M ? M : C) * LINE;
+                p = p < M ? p : p < 2 * M ? p - M : p - 2 * M;
+                at[u] = static_cast<const char *>(t) + sq.blk * step[u] + p * LINE;
+            }
+            at[u] += n * step[u];
+        }
+    }
+    // chunk n: that of aim(), then the one after (DIR 1) or before it (-1) at every call.  (As LDS transfers, which nothing has to wait
+    // for: dst is 256 bytes that nobody reads.)
+    template <int DIR> __device__ __forceinline__ void chunk(int n, unsigned dst) {
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            if (n < end[u])
+                asm volatile("s_mov_b32 m0, %1\n\ts_nop 4\n\tglobal_load_lds_dword %0, off"
+                             :
+                             : "v"(at[u]), "s"(__builtin_amdgcn_readfirstlane((int)dst))
+                             : "memory", "m0");
+            at[u] += DIR * step[u];
+        }
     }
 };
 
