@@ -13,7 +13,8 @@
 //
 // What bounds it: with every CU busy (256 workgroups) the mixture of loads and stores itself; a program that only makes this
 // kernel's requests takes 155-168 us at 4 x 4 096 tokens of 16 heads of 128.  With fewer workgroups or without kept states, the
-// step's chain of LDS reads, products and barriers.
+// step's chain of LDS reads, products and barriers; with few workgroups, kept states and more data than the caches hold, the loads'
+// latency beside the stores (LineTouch).
 #pragma once
 #include "mdn_scan_tiles.h"
 #include "mdn_kernels.h"
