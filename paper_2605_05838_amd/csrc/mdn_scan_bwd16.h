@@ -96,10 +96,10 @@ __device__ __forceinline__ void scan_bwd16(const Dims &d, const ScanBwdArgs &a, 
             if (AHEAD == 2 && n == n1 - 1) wait_vm<NS / 2>(); // Bm and T of the second chunk are there
             st.template put<NS / 2, NS * 3 / 4>(states, dv0, w2, lane);
             __syncthreads(); // B
-            if constexpr (TOUCH)
-                for (; next >= n0 && next >= n - kTouchAhead; --next) touch.template chunk<-1>(next, lds_addr(lds.touched + w2 * 64));
             store_token_rows<DV, MV, WHOLE>(static_cast<T *>(a.dv) + first_token(n) * DV + dv0, lds.sR0, !WHOLE && n == ragged ? last + 1 : 64, d.H, w2, lane);
             st.template put<NS * 3 / 4, NS>(states, dv0, w2, lane);
+            if constexpr (TOUCH)
+                for (; next >= n0 && next >= n - kTouchAhead; --next) touch.template chunk<-1>(next, lds_addr(lds.touched + w2 * 64));
             __syncthreads(); // C
         }
         if constexpr (TOUCH) wait_vm<0>(); // (no transfer outlives the workgroup)

@@ -111,11 +111,11 @@ __device__ __forceinline__ void scan_fwd16(const Dims &d, const ScanFwdArgs &a, 
             }
             if (a.states_saved) st.template put<NS / 2, NS * 3 / 4>(states, dv0, w2, lane);
             __syncthreads(); // B
-            if constexpr (TOUCH)
-                for (; next < n1 && next <= n + kTouchAhead; ++next) touch.template chunk<1>(next, lds_addr(lds.touched + w2 * 64));
             if (!REBUILD && a.vt_saved)
                 store_token_rows<DV, MV, WHOLE>(static_cast<T *>(a.vt_saved) + first_token(n) * DV + dv0, lds.sV0, rows_of(n), d.H, w2, lane);
             if (a.states_saved) st.template put<NS * 3 / 4, NS>(states, dv0, w2, lane);
+            if constexpr (TOUCH)
+                for (; next < n1 && next <= n + kTouchAhead; ++next) touch.template chunk<1>(next, lds_addr(lds.touched + w2 * 64));
             __syncthreads(); // C
         }
         if (!REBUILD) store_token_rows<DV, MV, WHOLE>(static_cast<T *>(a.o) + first_token(n1 - 1) * DV + dv0, lds.sO, rows_of(n1 - 1), d.H, w2, lane);

@@ -88,11 +88,12 @@ template <typename T, int LEN, bool SWIZZLE> struct TileLoad {
 // columns, d = 128: 3 700 clocks a step with kept states, 3 300 of them in the loading waves, 2 300 without the stores); out of the L2 they keep up.
 // Every 64 bytes: of a line of 128 asked for once only half is fetched.  32 768 tokens of 16 heads of 128 in us, without / every 128 bytes
 // / every 64 / every 32: forward 675 / 662 / 648 / 665, with kept states 924 / 797 / 772 / 803, forward and backward 1 846 / 1 675 / 1 646 / 1 677; three,
-// four and six chunks ahead 1 661, 1 646 and 1 657.
+// four and six chunks ahead 1 661, 1 646 and 1 657.  Those in front of a step's last stores; behind them, as now, with kept states 750, forward
+and backward 1 614 (65 536 tokens of 16 heads of 64 2 466, 2 478 in front of them, 2 838 without); in the phase before 1 622, but 2 767 with heads of 64.
 constexpr int kTouchAhead = 4;
 // Only where a call moves more than twice the 256 MB of the last-level cache, whose latency the loads cover: forward with kept states and
-// backward in us, without / with, 16 heads of 128 with 2 048 tokens 114.2 / 115.8, 8 192 (331 MB) 440 / 449, 16 384 (663 MB) 849 / 832, 4 heads with
-// 131 072 5 550 / 4 938; forward alone, 16 384 (336 MB) 309 / 315, 32 768 (671 MB) 675 / 648.  And not with 32 columns, where every CU is at
+// backward in us, without / with, 16 heads of 128 with 2 048 tokens 114.2 / 115.8, 8 192 (331 MB) 440 / 449, 16 384 (663 MB) 849 / 833, 4 heads with
+// 131 072 5 550 / 4 850; forward alone, 16 384 (336 MB) 309 / 315, 32 768 (671 MB) 675 / 648.  And not with 32 columns, where every CU is at
 // work and HBM itself is busy: 4 x 4 096 of 16 heads of 128 595 / 604 (every 128 bytes), forward of heads of 64 96 / 115.
 template <int DK, int DV> bool touch_pays(const Dims &d, bool kept) {
     constexpr size_t operands = 64 * (2 * DK + DV + kCoefRows * 2 + 2 * 64) * 2, rows = 64 * DV * 2, states = 2 * DK * DV * 2;
