@@ -89,7 +89,7 @@ template <typename T, int LEN, bool SWIZZLE> struct TileLoad {
 // Every 64 bytes: of a line of 128 asked for once only half is fetched.  32 768 tokens of 16 heads of 128 in us, without / every 128 bytes
 // / every 64 / every 32: forward 675 / 662 / 648 / 665, with kept states 924 / 797 / 772 / 803, forward and backward 1 846 / 1 675 / 1 646 / 1 677; three,
 // four and six chunks ahead 1 661, 1 646 and 1 657.  Those in front of a step's last stores; behind them, as now, with kept states 750, forward
-and backward 1 614 (65 536 tokens of 16 heads of 64 2 466, 2 478 in front of them, 2 838 without); in the phase before 1 622, but 2 767 with heads of 64.
+// and backward 1 614 (65 536 tokens of 16 heads of 64 2 466, 2 478 in front of them, 2 838 without); in the phase before 1 622, but 2 767 with heads of 64.
 constexpr int kTouchAhead = 4;
 // Only where a call moves more than twice the 256 MB of the last-level cache, whose latency the loads cover: forward with kept states and
 // backward in us, without / with, 16 heads of 128 with 2 048 tokens 114.2 / 115.8, 8 192 (331 MB) 440 / 449, 16 384 (663 MB) 849 / 833, 4 heads with
