@@ -303,98 +303,68 @@ __device__ __forceinline__ void coef_scan_reverse_part2(int ldg, int w, const Re
 }
 
 // ---- T = (I + A)^{-1}, A strictly lower triangular 64x64 fp32 in LDS (row-major, stride lda, zeros on and above the diagonal).
-//      Called by 4 waves (w = 0..3).  On return (behind a barrier of the caller's) sA holds T (row-major).  sTT is scratch of 64*lda
-//      floats, T^T.  Diagonal blocks of 8 by forward substitution, then by doubling: with T1, T2 the inverses of two neighbouring
-//      diagonal blocks and L the block of A between them, the inverse of both has -T2 L T1 in L's place.
-//      8 -> 16: inside a wave, 16 -> 32 and 32 -> 64 in 16x16 blocks over the waves; fp32 MFMA.  (The accumulator of the inner product is,
-//      lane for lane, the B fragment of the outer one.)  What bounds it is the chain of dependent products and LDS
-//      round trips: 3 600 clocks of a chunk's 12 000 with a CU to itself (13 chunks of 16 heads of 128); with diagonal blocks of 16 by
-//      substitution and one block diagonal of T after the other, each behind a barrier, 4 900 of 15 500.
-__device__ __forceinline__ void tri_inverse_blocked(float *sA, float *sTT, int lda, int w) {
+//      Called by 4 waves (w = 0..3).  On return (behind a barrier of the caller's) sA holds T (row-major).
+//        T_ii = (I + A_ii)^{-1}                              (forward substitution, lane = column, wave i)
+//        T_ij = -T_ii * sum_{k=j..i-1} A_ik T_kj   (i > j)    (16x16 blocks, fp32 MFMA; wave j, one block below the other)
+//      A block of the chain never leaves the registers: the accumulator of either product is, lane for lane, the B fragment of
+//      the next.  What bounds it is that chain of dependent products behind the substitution.  The diagonal blocks are substituted whole: put
+//      together from inverses of 8x8 blocks, 32 of four of them (the launch of 13 chunks of 16 heads of 128 between events 9.77 us so,
+//      9.83 as it is; 4 x 4 096 tokens of 16 heads 50.1 / 50.8), a row that overflows meets zeros in products over all rows of its block, and
+//      the tokens before it lose their finite values.
+__device__ __forceinline__ void tri_inverse_blocked(float *sA, int lda, int w) {
     typedef Op<float> O;
     const int lane = lane_id(), r = lane & 15, kg = lane >> 4;
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-    // fragments of 16x16 blocks: A operands row r, k = 4 kg ..; B operands column r, k = 4 kg ..
+    // 16x16 blocks as A operands: row r, k = 4 kg ..
     auto a_of = [&](int i, int k) { return *reinterpret_cast<const f32x4 *>(&sA[(i * 16 + r) * lda + k * 16 + 4 * kg]); };
-    auto tb_of = [&](int k, int j) { return *reinterpret_cast<const f32x4 *>(&sTT[(j * 16 + r) * lda + k * 16 + 4 * kg]); };
-    auto ta_of = [&](int i, int k) {
-        f32x4 v;
-#pragma unroll
-        for (int s = 0; s < 4; ++s) v[s] = sTT[(k * 16 + 4 * kg + s) * lda + i * 16 + r];
-        return v;
-    };
-    auto put_tt = [&](int i, int j, f32x4 v) { *reinterpret_cast<f32x4 *>(&sTT[(j * 16 + r) * lda + i * 16 + 4 * kg]) = v; };
-    auto put_t = [&](int i, int j, f32x4 v) {
+    auto put = [&](int i, int j, f32x4 v) {
 #pragma unroll
         for (int x = 0; x < 4; ++x) sA[(i * 16 + 4 * kg + x) * lda + j * 16 + r] = v[x];
     };
-    auto keep = [](f32x4 &v) { asm volatile("" : "+v"(v)); }; // (all four elements stay in registers of their own: no read waits for another's)
-    // what the later levels want of A (waves 0..3): f0 A_20 A_10 A_21 A_32, f1 A_30 A_20 A_31 A_21, f2 A_21 A_21, f3 A_31
-    f32x4 f0 = a_of((0xE6 >> (2 * w)) & 3, (0x90 >> (2 * w)) & 3), f1 = a_of((0xBB >> (2 * w)) & 3, w >> 1), f2 = zero, f3 = zero;
-    if (w < 2) f2 = a_of(2, 1);
-    if (w == 0) f3 = a_of(3, 1);
-    // block w: lane r has column r % 8 of its half r / 8 (every lane group the same)
-    const f32x4 aw = a_of(w, w);
-    f32x4 tii;
+    // what the chain wants of A: blocks (i, k), i > k >= w
+    f32x4 a10 = zero, a20 = zero, a30 = zero, a21 = zero, a31 = zero, a32 = zero;
+    if (w == 0) a10 = a_of(1, 0), a20 = a_of(2, 0), a30 = a_of(3, 0);
+    if (w <= 1) a21 = a_of(2, 1), a31 = a_of(3, 1);
+    if (w <= 2) a32 = a_of(3, 2);
+    f32x4 tjj; // T_ww as a B operand: column r, k = 4 kg ..
     {
-        const int h = r >> 3, c = r & 7;
-        const float *blk = &sA[(w * 16 + h * 8) * lda + w * 16 + h * 8];
-        f32x4 lo[8], hi[8];
+        const float *blk = &sA[(w * 16) * lda + w * 16];
+        float t[16];
 #pragma unroll
-        for (int i = 1; i < 8; ++i) {
-            lo[i] = *reinterpret_cast<const f32x4 *>(blk + i * lda);
-            if (i > 4) hi[i] = *reinterpret_cast<const f32x4 *>(blk + i * lda + 4);
+        for (int i = 0; i < 16; ++i) t[i] = i == r ? 1.f : 0.f;
+#pragma unroll
+        for (int k4 = 0; k4 < 4; ++k4) {
+            f32x4 a[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                if (i > 4 * k4) a[i] = *reinterpret_cast<const f32x4 *>(blk + i * lda + 4 * k4);
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    if (i > 4 * k4 + s) t[i] -= a[i][s] * t[4 * k4 + s];
         }
 #pragma unroll
-        for (int i = 1; i < 8; ++i) {
-            keep(lo[i]);
-            if (i > 4) keep(hi[i]);
-        }
-        float t[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) t[i] = i == c ? 1.f : 0.f;
-#pragma unroll
-        for (int k = 0; k < 7; ++k)
-#pragma unroll
-            for (int i = k + 1; i < 8; ++i) t[i] -= (k < 4 ? lo[i][k & 3] : hi[i][k & 3]) * t[k];
-        const bool mine = (kg >> 1) == h, up = kg & 1;
-        f32x4 tb;
-#pragma unroll
-        for (int s = 0; s < 4; ++s) tb[s] = mine ? (up ? t[4 + s] : t[s]) : 0.f;
-        put_tt(w, w, tb);
-        const f32x4 x = O::mma(r >= 8 && kg < 2 ? aw : zero, tb, zero);
-        tb -= O::mma(ta_of(w, w), x, zero);
-        put_tt(w, w, tb);
-        put_t(w, w, tb); // (in the place of block w of A, which nobody else reads)
-        tii = ta_of(w, w);
+        for (int s = 0; s < 4; ++s) tjj[s] = kg & 2 ? (kg & 1 ? t[12 + s] : t[8 + s]) : kg & 1 ? t[4 + s] : t[s];
     }
+    put(w, w, tjj); // (in the place of block w of A, which nobody else reads)
     __syncthreads();
-    // 16 -> 32: T_10 (wave 1) and T_32 (wave 3); and what the next level's inner products need of the diagonal blocks
-    f32x4 y0, y1 = zero;
-    {
-        const int k = (0x90 >> (2 * w)) & 3; // 0 0 1 2
-        const f32x4 tk = tb_of(k, k), t1 = w == 3 ? tb_of(1, 1) : tk;
-        const f32x4 x = O::mma(f0, tk, zero); // A_20 T_00, A_10 T_00, A_21 T_11, A_32 T_22
-        y1 = O::mma(f1, t1, zero);            // A_30 T_00, A_20 T_00, A_31 T_11, A_21 T_11
-        y0 = x;
-        if (w & 1) {
-            const f32x4 t = -O::mma(tii, x, zero);
-            put_tt(w, w - 1, t);
-            put_t(w, w - 1, t); // (nobody else reads this block of A any more)
-            y0 = y1;
-        }
-    }
-    __syncthreads();
-    // 32 -> 64: wave 0 T_30, wave 1 T_20, wave 2 T_31, wave 3 T_21
-    f32x4 t;
-    {
-        const int i = w & 1 ? 2 : 3;
-        const f32x4 ti2 = ta_of(i, 2), t33 = w & 1 ? zero : ta_of(3, 3), t10 = w < 2 ? tb_of(1, 0) : zero;
-        if (w < 2) y0 = O::mma(f2, t10, y0);
-        if (w == 0) y1 = O::mma(f3, t10, y1);
-        t = O::mma(ti2, y0, zero);
-        if (!(w & 1)) t = O::mma(t33, y1, t);
-        put_t(i, w >> 1, -t); // (every block of A has been read)
+    if (w == 0) {
+        const f32x4 t11 = a_of(1, 1), t22 = a_of(2, 2), t33 = a_of(3, 3);
+        const f32x4 t10 = -O::mma(t11, O::mma(a10, tjj, zero), zero);
+        put(1, 0, t10);
+        const f32x4 t20 = -O::mma(t22, O::mma(a21, t10, O::mma(a20, tjj, zero)), zero);
+        put(2, 0, t20);
+        const f32x4 t30 = -O::mma(t33, O::mma(a32, t20, O::mma(a31, t10, O::mma(a30, tjj, zero))), zero);
+        put(3, 0, t30);
+    } else if (w == 1) {
+        const f32x4 t22 = a_of(2, 2), t33 = a_of(3, 3);
+        const f32x4 t21 = -O::mma(t22, O::mma(a21, tjj, zero), zero);
+        put(2, 1, t21);
+        const f32x4 t31 = -O::mma(t33, O::mma(a32, t21, O::mma(a31, tjj, zero)), zero);
+        put(3, 1, t31);
+    } else if (w == 2) {
+        put(3, 2, -O::mma(a_of(3, 3), O::mma(a32, tjj, zero), zero));
     }
 }
 

@@ -17,7 +17,7 @@
 // round trips for one 64 x 64 x dv product inside the scan.
 //
 // What bounds it: up to a workgroup per CU the chain of one chunk (5.1 us, of which 1.8 until the gates and tiles have arrived; 13 chunks of
-// 16 heads of 128, 7.1 -> 5.6 us for the launch); with more, instruction issue and HBM together (8 x 2 048 tokens of 8 heads 30.8 ->
+// 16 heads of 128, 7.1 -> 5.7 us for the launch); with more, instruction issue and HBM together (8 x 2 048 tokens of 8 heads 30.8 ->
 // 25.5 us, 107 MB: 4.2 TB/s where a large copy reaches 4.8).
 //
 // One workgroup (4 waves) per (chunk, batch*head).  16-bit storage: T, Bm and the coefficients, row by row, for both scans.
@@ -68,12 +68,11 @@ __global__ __launch_bounds__(kThreads, sizeof(T) == 2 ? 3 : 1) void intra_kernel
     constexpr int NVK = 64 * DK / E / kThreads, NVX = BWD ? NVK : 1; // 16-byte vectors per thread
 
     __shared__ __align__(16) T sR[REGION];
-    // Gamma (row stride LDG); later scratch of the block inverse
-    __shared__ __align__(16) float sG[64 * LDA];
+    // Gamma (row stride LDG)
+    __shared__ __align__(16) float sG[64 * LDG];
     // A, then T: in the space of the K, Q tiles, once every wave is done with those (70 -> 53 KB of LDS for 16-bit
     // storage at d = 128: three workgroups per CU instead of two)
     float *sA = reinterpret_cast<float *>(sR);
-    float *sTT = sG;
     __shared__ __align__(16) float s_al[64], s_be[64], s_et[64], s_a[64], s_b[64];
 
     T *sK = sR, *sQ = sR + 64 * LDN;      // phase A
@@ -285,8 +284,8 @@ __global__ __launch_bounds__(kThreads, sizeof(T) == 2 ? 3 : 1) void intra_kernel
     }
     __syncthreads();
 
-    // ---- T = (I + A)^{-1} by 16x16 blocks, wave w = block row w
-    tri_inverse_blocked(sA, sTT, LDA, wu);
+    // ---- T = (I + A)^{-1}
+    tri_inverse_blocked(sA, LDA, wu);
     __syncthreads();
 
     if (BWD) {

@@ -1,7 +1,8 @@
-"""The chunk-local operands where every block of A = (P K~^T) .* Gamma^- counts: keys with a common part, so that no product of two
+"""The chunk-local operands where a token's products overflow, and where every block of A = (P K~^T) .* Gamma^- counts: keys with a common part, so that no product of two
 of them is small, slow gates, and lengths that end inside each of the 16-token blocks the triangular inverse is built from."""
 import numpy as np
 import pytest
+import torch
 
 from gpu_util import host, rel_err, rms_rel_err, to_dev
 from oracle import mdn_oracle as orc
@@ -32,3 +33,22 @@ def test_correlated_keys(dtype, d, T):
     pairs = [(n, f[n], rf[n]) for n in ("o", "S", "M")] + [(n, g[n], rb[n]) for n in ("dq", "dk", "dv", "dbeta", "dalpha", "dmu")]
     errs = {n: max(rel_err(host(y), ref), rms_rel_err(host(y), ref)) for n, y, ref in pairs}
     assert max(errs.values()) <= TOL[dtype], errs
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d,t", [(128, 3), (128, 12), (64, 20), (64, 27), (128, 40), (64, 63)])
+def test_a_token_that_overflows_leaves_the_tokens_before_it_alone(dtype, d, t):
+    """A key of 1e25 in every element: finite, and so are its products with ordinary keys, but not the later rows of T.  What the tokens
+    before it give, V~ and dq, is that of a call without it, bit for bit."""
+    w = synth.custom(B=1, T=64, H=2, dk=d, dv=d, dtype=dtype, seed=t, backward=True)
+    x = to_dev(w)
+
+    def run():
+        a = (x["q"], x["k"], x["v"], x["beta"], x["alpha"], x["mu"])
+        f = binding.mdn_chunk_fwd(*a, scale=w.scale, save_vt=True)
+        return f["vt"][:, :t], binding.mdn_chunk_bwd(*a, f["vt"], x["dO"], scale=w.scale)["dq"][:, :t]
+
+    plain = [y.clone() for y in run()]
+    x["k"][0, t] = 1e25
+    for n, y, ref in zip(("vt", "dq"), run(), plain):
+        assert torch.isfinite(ref).all() and torch.equal(y, ref), n
