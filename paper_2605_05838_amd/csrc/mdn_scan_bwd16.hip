@@ -38,7 +38,8 @@ template <int DK, int DV, int DVB, int AHEAD, bool TOUCH = false> hipError_t lau
 // Two workgroups per CU as in the forward (heads of 64), one / two in us, forward with kept states and backward: 64 x 64 tokens of 16
 // heads 98.8 / 88.3, 32 x 64 55.0 / 49.8, 32 x 128 87.0 / 81.2, 32 x 1 024 604 / 603.
 template <int DK, int DV> hipError_t pick(const Dims &d, const ScanBwdArgs &a, hipStream_t s) {
-    if (scan_dvb(d) == 16) return touch_pays<DK, DV>(d, true) ? launch_t<DK, DV, 16, 2, true>(d, a, s) : launch_t<DK, DV, 16, 2>(d, a, s);
+    if (scan_dvb(d) == 16)
+        return touch_pays(call_bytes(d, false, true), true) ? launch_t<DK, DV, 16, 2, true>(d, a, s) : launch_t<DK, DV, 16, 2>(d, a, s);
     if constexpr (2 * sizeof(ScanBwdLds<DK, DV, 32, 1>) <= 160 * 1024)
         if (!scan_one_per_cu(d)) return launch_t<DK, DV, 32, 1>(d, a, s);
     return launch_t<DK, DV, 32, 2>(d, a, s);

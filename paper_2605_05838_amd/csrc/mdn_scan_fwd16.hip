@@ -36,7 +36,7 @@ template <int DK, int DV, int DVB, bool REBUILD, int AHEAD, bool QTILE = false, 
 template <int DK, int DV, bool REBUILD> hipError_t pick(const Dims &d, const ScanFwdArgs &a, hipStream_t s) {
     if (scan_dvb(d) == 16) {
         if constexpr (!REBUILD)
-            if (touch_pays<DK, DV>(d, a.states_saved)) return launch_t<DK, DV, 16, false, 2, true, true>(d, a, s);
+            if (touch_pays(call_bytes(d, a.vt_saved, a.states_saved), false)) return launch_t<DK, DV, 16, false, 2, true, true>(d, a, s);
         return launch_t<DK, DV, 16, REBUILD, 2, !REBUILD>(d, a, s);
     }
     if constexpr (2 * sizeof(ScanFwdLds<DK, DV, 32, REBUILD, 1>) <= 160 * 1024)

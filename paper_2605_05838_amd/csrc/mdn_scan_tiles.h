@@ -13,6 +13,7 @@
 #pragma once
 #include "mdn_device.h"
 #include "mdn_kernels.h"
+#include "mdn_scan_rules.h"
 #include "mdn_seq.h"
 
 namespace mdn {
@@ -32,6 +33,8 @@ template <typename F> hipError_t launch_in_parts(int blocks, F &&launch) {
     return hipSuccess;
 }
 template <int DV, int DVB> int scan_blocks(const Dims &d) { return (d.BH + 7) / 8 * 8 * (DV / DVB); }
+// see scan_bytes
+inline size_t call_bytes(const Dims &d, bool vt, bool states) { return scan_bytes((size_t)d.nchunks * d.H, d.dk, vt, states); }
 
 // LDS address of a __shared__ object, as M0 takes it
 __device__ __forceinline__ unsigned lds_addr(const void *p) {
@@ -91,14 +94,7 @@ template <typename T, int LEN, bool SWIZZLE> struct TileLoad {
 // four and six chunks ahead 1 661, 1 646 and 1 657.  Those in front of a step's last stores; behind them, as now, with kept states 750, forward
 // and backward 1 614 (65 536 tokens of 16 heads of 64 2 466, 2 478 in front of them, 2 838 without); in the phase before 1 622, but 2 767 with heads of 64.
 constexpr int kTouchAhead = 4;
-// Only where a call moves more than twice the 256 MB of the last-level cache, whose latency the loads cover: forward with kept states and
-// backward in us, without / with, 16 heads of 128 with 2 048 tokens 114.2 / 115.8, 8 192 (331 MB) 440 / 449, 16 384 (663 MB) 849 / 833, 4 heads with
-// 131 072 5 550 / 4 850; forward alone, 16 384 (336 MB) 309 / 315, 32 768 (671 MB) 675 / 648.  And not with 32 columns, where every CU is at
-// work and HBM itself is busy: 4 x 4 096 of 16 heads of 128 595 / 604 (every 128 bytes), forward of heads of 64 96 / 115.
-template <int DK, int DV> bool touch_pays(const Dims &d, bool kept) {
-    constexpr size_t operands = 64 * (2 * DK + DV + kCoefRows * 2 + 2 * 64) * 2, rows = 64 * DV * 2, states = 2 * DK * DV * 2;
-    return (size_t)d.nchunks * d.H * (operands + rows + (kept ? states + rows : 0)) > (size_t)512 << 20;
-}
+// Where it is used: see touch_pays.
 template <int DK, int DV, int G> struct LineTouch {
     static constexpr int LINE = 64, RK = DK * 2 / LINE, RV = DV * 2 / LINE;                              // lines of a row
     static constexpr int K = 64 * RK, V = 64 * RV, M = 4096 * 2 / LINE, C = 64 * kCoefRows * 4 / LINE; // of a tensor's chunk
