@@ -27,22 +27,21 @@ template <int DK, int DV, int DVB, bool REBUILD, int AHEAD, bool QTILE = false, 
 // of heads of 64 in us: 64 x 64 tokens of 16 heads 43.4 / 33.9, 32 x 128 36.1 / 30.8, 32 x 1 024 187 / 182, packed 256 sequences of 30
 // tokens of 16 heads 156 / 107.  One chunk ahead costs a single workgroup up to a tenth of a step, so up to one per CU it is two.
 // (16 columns have a CU for each workgroup: see scan_dvb.)
-// The q rows as a tile brought by the loading waves: no loads, and no waits for them, in the waves of the chain; but 32 KB more of LDS and four
-// more of its reads in a step's last phase.  With 16 columns always.  With 32 only where the kept states' stores hold up every load
-// (d = 128; at d = 64 the chain is the longer part of a step then too).  Forward in us, q in registers / as a tile: 32 768 tokens of 16 heads of
-// 128 761 / 662, with kept states 994 / 927, 777 tokens 24.4 / 24.4; 3 x 1 500 of 8 heads of 64 with kept states 33.4 / 32.9; with 32
-// columns, 4 x 4 096 of 16 heads of 128 with kept states 213 / 200, without 150 / 157, 8 x 2 048 of 8 heads 84 / 87, 4 x 4 096 of
-// 24 heads of 64 100.8 / 105.5.
 template <int DK, int DV, bool REBUILD> hipError_t pick(const Dims &d, const ScanFwdArgs &a, hipStream_t s) {
-    if (scan_dvb(d) == 16) {
-        if constexpr (!REBUILD)
-            if (touch_pays(call_bytes(d, a.vt_saved, a.states_saved), false)) return launch_t<DK, DV, 16, false, 2, true, true>(d, a, s);
-        return launch_t<DK, DV, 16, REBUILD, 2, !REBUILD>(d, a, s);
+    const int columns = scan_dvb(d);
+    [[maybe_unused]] const size_t chunks = ((size_t)d.nchunks * d.H + d.BH - 1) / d.BH, bytes = call_bytes(d, a.vt_saved, a.states_saved);
+    [[maybe_unused]] const bool q_tile = q_tile_pays(columns, DK, d.BH, chunks, bytes, a.vt_saved, a.states_saved);
+    if (columns == 16) {
+        if constexpr (!REBUILD) {
+            if (touch_pays(bytes, false)) return launch_t<DK, DV, 16, false, 2, true, true>(d, a, s);
+            if (q_tile) return launch_t<DK, DV, 16, false, 2, true>(d, a, s);
+        }
+        return launch_t<DK, DV, 16, REBUILD, 2>(d, a, s);
     }
     if constexpr (2 * sizeof(ScanFwdLds<DK, DV, 32, REBUILD, 1>) <= 160 * 1024)
         if (!scan_one_per_cu(d)) return launch_t<DK, DV, 32, REBUILD, 1>(d, a, s);
     if constexpr (!REBUILD && DK == 128)
-        if (a.states_saved) return launch_t<DK, DV, 32, REBUILD, 2, true>(d, a, s);
+        if (q_tile) return launch_t<DK, DV, 32, REBUILD, 2, true>(d, a, s);
     return launch_t<DK, DV, 32, REBUILD, 2>(d, a, s);
 }
 

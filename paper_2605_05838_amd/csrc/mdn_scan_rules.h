@@ -25,4 +25,23 @@ constexpr size_t scan_bytes(size_t blocks, int d, bool vt, bool states) {
 // another pass over all of it (32 768 tokens of 16 heads of 128, a reverse scan in eight segments of 153 MB: the 1 663 / 1 608 above).
 constexpr bool touch_pays(size_t bytes, bool reverse) { return bytes > (reverse ? 9 : 10) * kLastLevelCache / 5; }
 
+// Whether a forward scan takes the q rows as a tile brought by the loading waves: no loads, and no waits for them, in the waves of the
+// chain; but 32 KB more of LDS and four more of its reads in a step's last phase.  `chunks`: of a sequence, on average.  Forward in us, q in
+// registers / as a tile.
+// 32 columns: where the kept states' stores hold up every load (d = 128; at d = 64 the chain is the longer part of a step then too).  The launch
+// between those of a training step, 16 heads of 128: 4 x 1 500 tokens 64.8 / 62.9, 4 x 2 048 82.6 / 79.3, 4 x 2 500 105.4 / 98.7, of a whole layer's 4 x 2 048
+// 65.8 / 64.0; calls of nothing but the forward, 4 x 2 048 83.2 / 83.9, 4 x 3 072 120 / 123, 8 x 2 048 213 / 205.  Without kept states 4 x 4 096 150 / 157,
+// 8 x 2 048 of 8 heads 84 / 87, 4 x 4 096 of 24 heads of 64 100.8 / 105.5.
+// 16 columns: where states are kept (16 heads of 128, 4 096 tokens 86.8 / 85.0; 4 heads 82.2 / 77.5) and where the start counts (up to 8 chunks: 64 tokens of
+// 16 heads of 128 11.0 / 10.7, 512 19.2 / 19.1, 600 of 8 heads 20.7 / 20.8).  Else, with inputs out of HBM, heads of 128 where the caches don't hold what
+// is moved, with V~ a little earlier (16 heads, 16 384 tokens (344 MB) 334 / 320, 22 000 508 / 452, 30 000 of 8 heads (315 MB) 548 / 546; V~ kept, 30 000 of 6
+// (282 MB) 603 / 550); below it what the tile's reads add to the chain is more (777 25.2 / 25.9, 4 096 of 8 heads 78.8 / 81.3, 6 000 122 / 128, 30 000 of 4 502 /
+// 536, V~ kept 510 / 533).  Heads of 64 except where a few pairs' loads have the memory to themselves (16 heads, 8 192 tokens 133 / 131, 22 000 395 / 367;
+// 4 heads, 4 096 56.4 / 57.3, 30 000 386 / 370; 2 heads 53.5 / 56.1, 342 / 360, but V~ kept 53.9 / 54.5, 359 / 358).
+constexpr bool q_tile_pays(int columns, int d, size_t pairs, size_t chunks, size_t bytes, bool vt, bool states) {
+    if (columns == 32) return d == 128 && states;
+    if (states || chunks <= 8) return true;
+    return d == 64 ? vt || pairs >= 4 : bytes > (vt ? 4 : 5) * kLastLevelCache / 4;
+}
+
 } // namespace mdn
