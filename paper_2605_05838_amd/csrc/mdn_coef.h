@@ -97,29 +97,9 @@ __device__ __forceinline__ void scan_affine_rev(float &c, float &d, int lane = l
     }
 }
 
-// ---- column scans of the 64x64 coefficient matrices; one wave, lane j owns column j and also HOLDS
-//      the gates of token j (al, be, mu); the gates of row i reach all lanes through v_readlane.
-//      sG[i*ldg + j] = Gamma_ij (0 above the diagonal).  The final values (row 63) are returned.
-//      If WANT_RHO: sRho[i*ldg + j] = Rho_ij as well.
-template <bool WANT_RHO>
-__device__ __forceinline__ void coef_column_scan(float al, float be, float mu, float *sG, float *sRho, int ldg,
-                                                 float &gC, float &rC) {
-    const int j = lane_id();
-    float g = 0.f, rho = 0.f;
-#pragma unroll
-    for (int i = 0; i < 64; ++i) {
-        const float a_i = lane_bcast(al, i), b_i = lane_bcast(be, i), m_i = lane_bcast(mu, i);
-        rho = (i == j) ? 1.f : rho * m_i;
-        g = a_i * g + b_i * rho;
-        sG[i * ldg + j] = g;
-        if (WANT_RHO) sRho[i * ldg + j] = rho;
-    }
-    gC = g;
-    rC = rho;
-}
-
-// ---- the same column scans split over 4 waves: wave w (0..3) produces rows 16w .. 16w+15 of Gamma
-//      (and Rho) for all 64 columns, lane j = column j, every wave holding the gates of token `lane`.
+// ---- column scans of the 64x64 coefficient matrices, by 4 waves: wave w (0..3) produces rows 16w .. 16w+15 of Gamma
+//      (sG[i*ldg + j] = Gamma_ij, 0 above the diagonal; with WANT_RHO sRho likewise) for all 64 columns, lane j = column j, every wave
+//      holding the gates of token `lane`; the gates of row i reach all lanes through v_readlane.
 //      The state (g, rho) of column j moves from row i-1 to row i by the triangular map
 //        T_i = [alpha_i, beta_i mu_i; 0, mu_i],   starting from (beta_j, 1) in row j.
 //      A wave gets the state its columns have in row 16w-1 without walking there: products of the T_i
@@ -173,43 +153,10 @@ __device__ __forceinline__ void coef_column_scan_blocked(float al, float be, flo
     rC = rho;
 }
 
-// ---- reverse of the column scans (adjoint): lane j owns column j.  With D_ij the direct adjoint of
-//      Gamma_ij (sD1[i][j] + sD2[i+1][j], plus dgc_j in row 63) and drc_j the direct adjoint of Rho_63,j:
+// ---- reverse of the column scans (adjoint).  With D_ij the direct adjoint of Gamma_ij (sD1[i][j] + sD2[i+1][j], plus dgc_j in
+//      row 63) and drc_j the direct adjoint of Rho_63,j:
 //        G_ij = D_ij + alpha_{i+1} G_{i+1,j}            R_ij = [i = 63] drc_j + beta_i G_ij + mu_{i+1} R_{i+1,j}
-//      for i = 63 .. j.  Writes sGa[i][j] = G_ij, sRa[i][j] = R_ij (zero for i < j).
-__device__ __forceinline__ void coef_column_scan_reverse(float al, float be, float mu, const float *sD1,
-                                                         const float *sD2, float dgc, float drc, float *sGa,
-                                                         float *sRa, int ldg) {
-    const int j = lane_id();
-    float cg = 0.f, cr = 0.f; // alpha_{i+1} G_{i+1,j}, mu_{i+1} R_{i+1,j}
-    // 16 rows at a time: all direct adjoints of the block are read before its dependent chain starts
-    // (every entry of sD1 / sD2 is defined, zero above the diagonal), so no LDS wait sits on the chain
-#pragma unroll
-    for (int i0 = 48; i0 >= 0; i0 -= 16) {
-        float dir[16];
-#pragma unroll
-        for (int u = 0; u < 16; ++u) dir[u] = sD1[(i0 + u) * ldg + j] + sD2[(i0 + u + 1) * ldg + j];
-#pragma unroll
-        for (int u = 15; u >= 0; --u) {
-            const int i = i0 + u;
-            const float a_i = lane_bcast(al, i), b_i = lane_bcast(be, i), m_i = lane_bcast(mu, i);
-            float G = dir[u] + cg, R = cr;
-            if (i == 63) {
-                G += dgc;
-                R += drc;
-            }
-            R += b_i * G;
-            G = (i >= j) ? G : 0.f;
-            R = (i >= j) ? R : 0.f;
-            sGa[i * ldg + j] = G;
-            sRa[i * ldg + j] = R;
-            cg = a_i * G;
-            cr = m_i * R;
-        }
-    }
-}
-
-// ---- the reverse column scans split over 4 waves: wave w (0..3) owns rows 16w .. 16w+15, lane j = column j.
+//      for i = 63 .. j, zero for i < j.  By 4 waves: wave w (0..3) owns rows 16w .. 16w+15, lane j = column j.
 //      Part 1 walks the wave's rows upwards with nothing coming in from the rows below (16 dependent
 //      steps).  With the three coefficients with which an incoming pair (Gin, Rin) = (G, R) of the row below
 //      the segment enters each row,

@@ -70,10 +70,10 @@ __global__ __launch_bounds__(kThreads, sizeof(T) == 2 ? 3 : 1) void intra_kernel
     __shared__ __align__(16) T sR[REGION];
     // Gamma (row stride LDG)
     __shared__ __align__(16) float sG[64 * LDG];
-    // A, then T: in the space of the K, Q tiles, once every wave is done with those (70 -> 53 KB of LDS for 16-bit
+    // A, then T: in the space of the K, Q tiles, once every wave is done with those (70 -> 52 KB of LDS for 16-bit
     // storage at d = 128: three workgroups per CU instead of two)
     float *sA = reinterpret_cast<float *>(sR);
-    __shared__ __align__(16) float s_al[64], s_be[64], s_et[64], s_a[64], s_b[64];
+    __shared__ __align__(16) float s_al[64], s_et[64];
 
     T *sK = sR, *sQ = sR + 64 * LDN;      // phase A
     T *sKT = sR, *sXT = sR + DK * LDT;    // phase B (aliases phase A)
@@ -143,10 +143,7 @@ __global__ __launch_bounds__(kThreads, sizeof(T) == 2 ? 3 : 1) void intra_kernel
             float c = al, pb = be * pm;
             scan_affine_fwd(c, pb); // b_i = alpha_i b_{i-1} + beta_i m_i
             s_al[lane] = al;
-            s_be[lane] = be;
             s_et[lane] = et;
-            s_a[lane] = pa;
-            s_b[lane] = pb;
             // alpha_i b_{i-1} (b_{-1} = 0), and the chunk-end values a_C, b_C, m_C into every row
             const f32x4 c0 = {pa, pb, al * wave_up1(pb, 0.f, lane), lane_value(pa, 63)};
             *reinterpret_cast<f32x4 *>(coef + lane * kCoefRows + COEF_A) = c0;
