@@ -176,17 +176,17 @@ bool few_scan_workgroups(const Dims &d) { return 2 * scan_workgroups(d) <= num_c
 // reverse scan's launch if the call is not split, and on the second stream if it is: then the gradient launches wait for all of it, and
 // less of them is hidden: two segments from 2 400 blocks on, another one per 2 048.  Backward in us, unsplit / 2 / 4 / 8 segments,
 // d = 128, states kept; reconstructed; reconstructed, with adjoints of the final states:
-//   blocks  1 024 (16 heads, T =  4 096):   126 /   142 /   147 /   184;    155 /   165 /   178 /   218;    227 /   241 /   257 /   312
-//   blocks  2 048 (16 heads, T =  8 192):   299 /   279 /   277 /   299;    320 /   336 /   347 /   379;    476 /   477 /   488 /   512
-//                 ( 4 heads, T = 32 768):   699 /   715 /   719 /   750;    700 /   697 /   707 /   732;    948 /   918 /   913 /   944
-//   blocks  2 504 ( 8 heads, T = 20 032):   542 /   518 /   521 /   548;    518 /   520 /   537 /   556;    771 /   716 /   717 /   754
-//   blocks  4 096 (16 heads, T = 16 384):   607 /   541 /   508 /   519;    681 /   641 /   657 /   691;  1 000 /   920 /   936 /   957
-//   blocks  8 192 (16 heads, T = 32 768): 1 173 / 1 031 /   967 /   944;  1 418 / 1 261 / 1 271 / 1 298;  2 015 / 1 814 / 1 817 / 1 806
-// and 421 / 381 / 367 / 400; 418 / 402 / 413 / 444; 535 / 496 / 503 / 532 for 4 096 blocks of d = 64.  (With the reconstruction in
+//   blocks  1 024 (16 heads, T =  4 096):   132 /   142 /   145 /   181;    146 /   164 /   174 /   223;    224 /   240 /   255 /   311
+//   blocks  2 048 (16 heads, T =  8 192):   303 /   284 /   280 /   304;    310 /   333 /   337 /   371;    476 /   477 /   487 /   507
+//                 ( 4 heads, T = 32 768):   702 /   719 /   724 /   758;    698 /   692 /   707 /   733;    951 /   916 /   910 /   945
+//   blocks  2 504 ( 8 heads, T = 20 032):   546 /   521 /   523 /   554;    517 /   516 /   533 /   557;    766 /   714 /   712 /   752
+//   blocks  4 096 (16 heads, T = 16 384):   526 /   486 /   470 /   473;    662 /   628 /   622 /   668;    981 /   885 /   873 /   912
+//   blocks  8 192 (16 heads, T = 32 768): 1 085 /   947 /   889 /   858;  1 428 / 1 220 / 1 193 / 1 244;  2 012 / 1 744 / 1 706 / 1 721
+// and 421 / 385 / 369 / 410; 413 / 398 / 405 / 438; 534 / 504 / 509 / 530 for 4 096 blocks of d = 64.  (With the reconstruction in
 // front of the segments 4 096 blocks of d = 128 took 752 in 4.)  32-bit storage takes four times as long per block (512 blocks, 8
-// heads, states kept: 445 / 417 / 432 / 555; 2 048 of d = 64, 4 heads: 1 721 / 1 645 / 1 612 / 1 621; reconstructed 582 / 464 / 479 /
-// 646 and 2 314 / 1 707 / 1 672 / 1 689); segments of fewer than 32 chunks are all start and drain.  Forward: 168 / 192 / 195 / 229 for
-// the second row, 834 / 861 / 842 / 844 for the last.
+// heads, states kept: 445 / 417 / 433 / 557; 2 048 of d = 64, 4 heads: 1 721 / 1 643 / 1 608 / 1 614; reconstructed 580 / 455 / 472 /
+// 644 and 2 296 / 1 697 / 1 662 / 1 682); segments of fewer than 32 chunks are all start and drain.  Forward: 161 / 188 / 194 / 219 for
+// the second row, 754 / 781 / 766 / 782 for the last.
 long long backward_segments(const Dims &d, bool rebuild) {
     const long long grad = (long long)d.N * d.BH * d.dk * (d.dtype == MDN_DTYPE_F32 ? 4 : 1); // its time, in 1/128 blocks
     const long long k = rebuild && !wide(d) ? (grad / 128 + 1696) / 2048 : grad / (128 * 1024);
@@ -621,9 +621,9 @@ Dims one_sequence(const Dims &d, const int32_t *cu, int i) {
 // a step of their longest or ~0.06 us a chunk block, whichever is more.  (In the unit of a hidden chunk block: 1 000, 88, 3/2.)
 // (The line is drawn for gradient launches that are hidden whole.  Behind a reconstruction on the second stream less of them is, 10 to
 // 30 us per 1 024 blocks, but on either side of it the two orders are within a tenth.)
-// Backward in us, together / alone, 16 heads of 128: 29 500 tokens and 16 of 205 1 414 / 1 350; 31 130 and 1 638 1 428 / 1 319; 60 000 and
-// 16 of 300 2 748 / 2 501; 8 heads 884 / 863, 880 / 904, 1 860 / 1 749; 16 heads of 64 925 / 878, 943 / 905, 1 835 / 1 722; near the
-// line 100, 20 037 and 63 tokens of 8 heads of 128 530 / 589.  Not taken: 16 384 and 32 of 512; 24 576 and 8 192.
+// Backward in us, together / alone, 16 heads of 128: 29 500 tokens and 16 of 205 1 370 / 1 248; 31 130 and 1 638 1 374 / 1 248; 60 000 and
+// 16 of 300 2 645 / 2 354; 8 heads 851 / 832, 871 / 842, 1 825 / 1 603; 16 heads of 64 898 / 814, 926 / 830, 1 798 / 1 580; near the
+// line 100, 20 037 and 63 tokens of 8 heads of 128 524 / 577.  Not taken: 16 384 and 32 of 512, 8 heads 642 / 655; 24 576 and 8 192, 16 heads 1 255 / 1 232.
 int long_sequence(const Dims &d, const int32_t *cu, int32_t n_seq) {
     int a = 0;
     for (int i = 1; i < n_seq; ++i)
