@@ -26,8 +26,8 @@ constexpr size_t scan_bytes(size_t blocks, int d, bool vt, bool states) {
 constexpr bool touch_pays(size_t bytes, bool reverse) { return bytes > (reverse ? 9 : 10) * kLastLevelCache / 5; }
 
 // Whether a forward scan takes the q rows as a tile brought by the loading waves: no loads, and no waits for them, in the waves of the
-// chain; but 32 KB more of LDS and four more of its reads in a step's last phase.  `chunks`: of a sequence, on average.  Forward in us, q in
-// registers / as a tile.
+// chain; but 16 (d = 64) or 32 KB more of LDS and four more of its reads in a step's last phase.  `pairs`: (sequence, head) pairs; `chunks`:
+// of a sequence, on average.  Forward in us, q in registers / as a tile.
 // 32 columns: where the kept states' stores hold up every load (d = 128; at d = 64 the chain is the longer part of a step then too).  The launch
 // between those of a training step, 16 heads of 128: 4 x 1 500 tokens 64.8 / 62.9, 4 x 2 048 82.6 / 79.3, 4 x 2 500 105.4 / 98.7, of a whole layer's 4 x 2 048
 // 65.8 / 64.0; calls of nothing but the forward, 4 x 2 048 83.2 / 83.9, 4 x 3 072 120 / 123, 8 x 2 048 213 / 205.  Without kept states 4 x 4 096 150 / 157,
